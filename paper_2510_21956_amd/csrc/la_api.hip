@@ -18,23 +18,27 @@ static size_t round_up(size_t x, size_t m) { return (x + m - 1) / m * m; }
 
 static bool supported_d(int D) { return D == 16 || D == 32 || D == 64 || D == 128 || D == 256; }
 
-// Segment length.  The masked apply kernels keep one (D = 128), two (fp32, D = 64) or four
-// (D = 32) workgroups resident per compute unit (the unmasked ones, which hold no tiles of K
-// and V, four), and a workgroup walks its segment serially, so the launch is balanced when
-// slices x segments is about 256 x that residency: every compute unit then gets the
-// same number of equally long segments in a single round.
-// Segments are also kept long enough that the D x D state a segment hands over stays
-// small next to the rows it covers (a sixth of their bytes at the shortest: short
-// sequences in few slices would otherwise leave most of the chip idle).  la_debug_override can force a length (rounded up to 64).
+// Segment length.  A workgroup walks its segment serially, so a launch is balanced when slices
+// x segments is about 256 x the workgroups that a compute unit holds at once: every compute
+// unit then gets the same number of equally long segments in a single round.  The sweeps of
+// the backward pass set that number (registers and LDS): one at D = 128 and two at D = 64
+// (measured at D = 64, bf16, 36 slices of 5003 rows: 159 us a step for one, 117 for two, 127
+// for three; fp32, 64 slices of 4096: 377, 305, 361), four at D = 32.  Without the mask the
+// ascending sweep, which holds two states, sets it: two (fp32) or three (bf16) at D = 64, one
+// at D = 128 (fp32, 32 slices of 8192 rows: 417 us a step, 445 for two, 488 for four).
+// Segments are also kept long enough that the D x D state a segment hands over stays small
+// next to the rows it covers (a sixth of their bytes at the shortest: short sequences in few
+// slices would otherwise leave most of the chip idle).  la_debug_override can force a length
+// (rounded up to 64).
 Plan make_plan(int B, int H, int N, int D, la_dtype dt, int causal, int is_backward)
 {
     Plan p;
     const long BH = (long)B * H;
     const int min_len = (D >= 128) ? 192 : 128;
-    const long resident = D == 256                      ? 1
-                          : (!causal || D <= 32)        ? 4
-                          : (dt == LA_F32 && D <= 64) ? 2
-                                                        : 1;
+    const long resident = D == 256 ? 1
+                          : D <= 32 ? 4
+                          : D == 64 ? (!causal && dt == LA_BF16 ? 3 : 2)
+                                    : 1;
     const long target = 256 * resident;
     long want = (target + BH / 2) / BH;  // nearest number of segments per slice
     long max_by_len = N / min_len;
@@ -63,7 +67,7 @@ Plan make_plan(int B, int H, int N, int D, la_dtype dt, int causal, int is_backw
         }
     }
     const size_t DD = (size_t)D * D;
-    p.slot_floats = round_up(is_backward ? 3 * DD + 3 * D : DD + 2 * D, 64);
+    p.slot_floats = round_up(is_backward ? 2 * DD + 4 * D : DD + 2 * D, 64);
     const size_t slots = (size_t)BH * p.nseg * p.slot_floats;
     p.delta_offset_floats = round_up(slots, 64);
     p.total_bytes = is_backward ? (p.delta_offset_floats + round_up((size_t)BH * N, 64)) * 4

@@ -37,7 +37,7 @@ __device__ __forceinline__ void store_elem(bf16_t *p, size_t i, float x) { p[i] 
 // may be shorter).  Each (slice, segment) owns one state slot in the
 // workspace.  A forward slot is [S (D*D) | z (D) | p (D)]; a backward slot is
 // [S (D*D) | z (D) | R (D*D) | u (D) | w (D)] (the matrix-core path stores S
-// transposed and appends R transposed), both padded to `slot_floats`.
+// transposed), both padded to `slot_floats`.
 // S = sum k v^T, z = sum k, p = sum v are the running sums of Eq. xy (without
 // the factors a, b); R = sum q OmegaHat^T, u = sum delta q, w = sum OmegaHat
 // are those of Eq. endd.  The backward workspace also holds delta_i =
@@ -130,7 +130,7 @@ struct Tracer {
 void launch_scan_slots(float *ws, int BH, int nseg, size_t slot_floats, int off, int len, int mode,
                        int lo, int hi, hipStream_t st);
 
-// Matrix-core path (la_fast.hip): D = 64 and D = 128, fp32 and bf16, both passes.
+// Matrix-core path (la_fast.hip): D = 32, 64 and 128, fp32 and bf16, both passes.
 bool fast_supported(const Problem &pr, int is_backward);
 // `saved` (may be null) is the forward-to-backward hand-over buffer described in Plan.
 la_status fast_backward(const Problem &pr, const Plan &pl, const void *Q, const void *K,
@@ -140,6 +140,23 @@ la_status fast_backward(const Problem &pr, const Plan &pl, const void *Q, const 
 la_status fast_forward(const Problem &pr, const Plan &pl, const void *Q, const void *K,
                        const void *V, void *O, float *G, float *ws, float *saved, hipStream_t st,
                        Tracer &tc);
+
+// Matrix-core kernels (la_split.hip): D = 32, 64, 128 (ld == D), or 128 columns of rows
+// ld = 256 wide, one of several launches that build the results up (without normalisation):
+// xflags, Gin, Fraw and BlockPass as in split_forward / split_backward.  dK == nullptr: dQ only.
+struct BlockPass {
+    int xflags = 0;
+    float *Pq = nullptr, *Pk = nullptr, *Pv = nullptr;
+};
+la_status planes_forward(const Problem &pr, const Plan &pl, int ld, const void *Q, const void *K,
+                         const void *V, void *O, float *G, float *ws, float *saved, hipStream_t st,
+                         Tracer &tc, int xflags = 0, const float *Gin = nullptr, float *Fraw = nullptr);
+la_status planes_backward(const Problem &pr, const Plan &pl, int ld, const void *Q, const void *K,
+                          const void *V, const void *O, const float *G, const void *dO, void *dQ,
+                          void *dK, void *dV, float *ws, const float *saved, hipStream_t st,
+                          Tracer &tc, const BlockPass &bp = BlockPass());
+la_status planes_totals(const Problem &pr, const Plan &pl, int ld, const void *K, const void *V,
+                        float *ws, hipStream_t st);
 
 // The ascending sweep of the backward pass alone: dQ for the coefficients in pr (matrix-core path).
 la_status fast_backward_dq(const Problem &pr, const Plan &pl, const void *Q, const void *K,

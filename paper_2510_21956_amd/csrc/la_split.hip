@@ -1,0 +1,1077 @@
+// Matrix-core kernels for gfx950: the chunk algebra of the three phases (per-segment sums, scan,
+// apply) with every contraction on the bf16 matrix pipe, on tiles of one to three bf16 planes
+// (la_planes.h).
+//   fp32 tensors take three planes everywhere, which is fp32 arithmetic;
+//   bf16 tensors are tiles of one plane as they stand; intermediates (weight blocks, running
+//     states, the 1/g scaling) take two planes in the first rows of a sequence and one beyond
+//     (lo_rows_of);
+//   bf16 tensors whose Q, K rows are normalised on the way stay one-plane tiles of the raw rows:
+//     the factors 1/|q|, 1/|k| go to the weight blocks, to the outputs and to the wave's own
+//     operand of the running sums' updates, which are fp32 in three planes here.
+//
+// A workgroup of D/16 waves handles one (slice, segment) in chunks of 32 rows; wave w owns
+// columns [16w, 16w+16) of the D x D running state, which stays in its accumulators for the
+// whole segment.  Output blocks are computed transposed (accumulator rows = output columns): a
+// lane then holds four columns of a row, which an exchange between lanes turns into whole
+// runs of a row (store_block).  The backward sweeps of fp32, which have no registers to spare,
+// compute them the other way round, store single floats and need no exchange (SWAP).
+//
+// The descending sums weight row i by 1/g_i.  With split rows of Q (QT) the kernels stage
+// q_i / g_i instead of q_i, and everything follows from that one tile:
+//   R = sum (q/g) dO^T,   dK_n = b (sum_i Cm'_in (q_i/g_i) + ...),  Cm'_in = dO_i . v_n - dprime_i,
+//   dV_n = sum_i (a/g_i + b (q_i/g_i) . k_n) dO_i + ...,   u = sum dprime (q/g),  w = sum dO / g,
+// so no scaled copy of dO is kept next to dO itself.  With one-plane tiles, which must stay
+// exact, the weight blocks carry the 1/g, and the wave's own 32 x 16 operand of R's update is
+// scaled in registers.
+#include "la_planes.h"
+
+namespace la {
+namespace {
+
+enum { P32, N32, P16, N16 };  // fp32, fp32 normalised, bf16, bf16 normalised
+// Planes of Q and K (LQ), of V and dO (LV), of intermediates (LX).
+template <int MODE>
+struct Mode {
+    typedef typename std::conditional<MODE == P32 || MODE == N32, float, __bf16>::type TIO;
+    static constexpr bool NORM = MODE == N32 || MODE == N16;
+    static constexpr int LQ = sizeof(TIO) == 4 ? 3 : 1, LV = LQ, LX = MODE == P16 ? 2 : 3;
+    static constexpr bool QT = sizeof(TIO) == 4, SWAP = QT;
+    // bf16 rows are normalised through factors 1/|q|, 1/|k| on what is fp32 anyway (RN)
+    static constexpr bool RN = MODE == N16;
+    // Chunks requested ahead.  A CU keeps 5 TB/s / 256 busy with some 40 KB in flight; a chunk of
+    // the four tensors of the descending sweep is 64 KB in fp32 but 32 KB in bf16 (D = 128).
+    static constexpr int DEPTH = sizeof(TIO) == 2 ? 2 : 1;
+};
+
+// A wave's 16 entries of a vector sum (z, p, u, w) in the layout of its output blocks: one
+// column a lane (SWAP), or the columns 4g .. 4g+3 of the lane group.
+template <bool SWAP>
+struct Sum {
+    typename std::conditional<SWAP, float, f4v>::type v;
+    __device__ __forceinline__ Sum()
+    {
+        if constexpr (SWAP) v = 0.f;
+        else v = f4v{0.f, 0.f, 0.f, 0.f};
+    }
+    __device__ __forceinline__ void load(const float *p, int w, int c, int g)
+    {
+        if constexpr (SWAP) v = p[w * 16 + c];
+        else v = *reinterpret_cast<const f4v *>(p + w * 16 + 4 * g);
+    }
+    __device__ __forceinline__ void store(float *p, int w, int c, int g) const
+    {
+        if constexpr (SWAP) {
+            if (g == 0) p[w * 16 + c] = v;
+        } else {
+            if (c == 0) *reinterpret_cast<f4v *>(p + w * 16 + 4 * g) = v;
+        }
+    }
+    // += sum over the chunk rows of f's columns, weighted by the factor planes in wgt
+    template <int LF, int LW>
+    __device__ __forceinline__ void add(const bf8v (&f)[LF], const bf8v (&wgt)[LW])
+    {
+        if constexpr (SWAP) v += step_product<LW, LF>(wgt, f)[0];
+        else v += step_product<LF, LW>(f, wgt);
+    }
+};
+// Per-row factors of the chunk for output block m: the lane's four rows (SWAP) or its one row.
+template <bool SWAP>
+__device__ __forceinline__ auto row_factor(const float *x, int m, int c, int g)
+{
+    if constexpr (SWAP) return *reinterpret_cast<const f4v *>(x + m * 16 + 4 * g);
+    else return x[m * 16 + c];
+}
+// own columns (x) of the weight block (p) or the other way round
+template <bool SWAP, int LA, int LB>
+__device__ __forceinline__ f4v own_product(const bf8v (&own)[LA], const bf8v (&p)[LB])
+{
+    if constexpr (SWAP) return step_product<LB, LA>(p, own);
+    else return step_product<LA, LB>(own, p);
+}
+// One 16-row block of a gradient; LD != D builds it up over two launches (store_grad_block).
+template <bool SWAP, int D, int LD, typename TIO>
+__device__ __forceinline__ void store_grad(TIO *out, float *part, bool add, int w, int rows_valid, int l,
+                                           f4v x)
+{
+    if constexpr (SWAP)
+        store_cols_block(out, LD, w * 16, rows_valid, l % 16, l / 16, x, LD != D && add);
+    else
+        store_grad_block<TIO, D, LD>(out, part, add, w * 16, rows_valid, l, x[0], x[1], x[2], x[3]);
+}
+// Backward of the row normalisation on the two output blocks; xhat = scale * the tile's rows.
+template <bool SWAP, bool OP, int D, int LQ>
+__device__ __forceinline__ void project_chunk(f4v (&x)[2], const __bf16 *tile, const Lanes<D, (D >= 128)> &ln,
+                                              const float *scale, float *dots, const float *inv, int w,
+                                              int c, int g)
+{
+    if constexpr (SWAP) {
+        bf8v f[LQ];
+        f4v xh[2];
+        if constexpr (OP) load_cols_op<D, LQ>(f, tile, ln.local(ln.ocol), w);
+        else load_cols<D, LQ>(f, tile, ln.local(ln.col), w);
+        frag_values<LQ>(xh, f);
+        if (scale) {
+#pragma unroll
+            for (int m = 0; m < 2; ++m) xh[m] *= *reinterpret_cast<const f4v *>(scale + m * 16 + 4 * g);
+        }
+        project_cols<D / 16>(x, xh, dots, inv, w, c, g);
+    } else {
+        float y[2][4], xh[2][4];
+#pragma unroll
+        for (int m = 0; m < 2; ++m) {
+            const int r = m * 16 + c;
+            quad_values<D, LQ>(xh[m], tile + (OP ? Tile<D>::op_quad(r, 4 * w + g) : Tile<D>::nat_quad(r, 4 * w + g)));
+            const float sc = scale ? scale[r] : 1.f;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                xh[m][e] *= sc;
+                y[m][e] = x[m][e];
+            }
+        }
+        project_blocks<D / 16, CR, 2>(y, xh, dots, inv, w, c, g);
+#pragma unroll
+        for (int m = 0; m < 2; ++m)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) x[m][e] = y[m][e];
+    }
+}
+// The wave's own column fragment f (one plane) times the row factors in r1 and, if given, r2,
+// split again.
+template <int L>
+__device__ __forceinline__ void scale_frag(bf8v (&o)[L], const bf8v (&f)[1], const float *r1, int g,
+                                           const float *r2 = nullptr)
+{
+    f4v x[2];
+    frag_values<1>(x, f);
+#pragma unroll
+    for (int m = 0; m < 2; ++m) {
+        x[m] *= *reinterpret_cast<const f4v *>(r1 + 16 * m + 4 * g);
+        if (r2) x[m] *= *reinterpret_cast<const f4v *>(r2 + 16 * m + 4 * g);
+    }
+    split_frag<L>(x[0], x[1], o);
+}
+// A per-row factor array (32 floats) as an operand: three planes.
+__device__ __forceinline__ void factor_frag(bf8v (&o)[3], const float *r, int g)
+{
+    split_frag<3>(*reinterpret_cast<const f4v *>(r + 4 * g),
+                  *reinterpret_cast<const f4v *>(r + 16 + 4 * g), o);
+}
+
+// ---------------------------------------------------------------------------
+// Phase 1: per-segment S = sum k v^T, z = sum k, p = sum v (Eq. xy without the factors), to
+// slot `seg + slot_shift` as [S | z | p], or [S^T | z] (TRANSPOSED) for the backward pass.
+// ---------------------------------------------------------------------------
+template <bool NORM, bool OP, int L, typename CH>
+__device__ __forceinline__ void stage(const CH &ch, __bf16 *tile, float *inv_out = nullptr,
+                                      const float *scale = nullptr)
+{
+    if constexpr (L == 1) {  // bf16 as it stands; NORM: 1 / |row| to inv_out
+        if constexpr (NORM) {
+            f4v x[2] = {ch.value(0), ch.value(1)};
+            normalise_quads<CH>(x, inv_out);
+        }
+        ch.template store<OP, L>(tile);
+    } else {
+        f4v x[2] = {ch.value(0), ch.value(1)};
+        if constexpr (NORM) normalise_quads<CH>(x, inv_out);
+        if (scale) {
+#pragma unroll
+            for (int k = 0; k < 2; ++k) x[k] *= scale[CH::row(k)];
+        }
+        CH::template store_values<OP, L>(tile, x);
+    }
+}
+
+template <int MODE, int D, bool TRANSPOSED, int LD>
+__global__ __launch_bounds__(4 * D, 2) void ks_kv_state(
+    const typename Mode<MODE>::TIO *__restrict__ K, const typename Mode<MODE>::TIO *__restrict__ V, float *__restrict__ ws, int N, int nseg,
+    int nseg_run, SegMap sm, size_t slot_floats, int slot_shift)
+{
+    typedef Mode<MODE> MD;
+    typedef typename MD::TIO TIO;
+    constexpr int LQ = MD::LQ, LV = MD::LV, NRB = D / 16, PL = Tile<D>::PLANE;
+    typedef Chunk<TIO, D, LD> CH;
+    __shared__ __align__(16) __bf16 lds[(LQ + LV) * PL];
+    __shared__ __align__(16) float ik[MD::RN ? CR : 4];  // 1 / |k|
+    __bf16 *Kt = lds, *Vt = lds + LQ * PL;
+    const int bh = blockIdx.x / nseg_run, seg = blockIdx.x % nseg_run;
+    const TIO *Kp = K + (size_t)bh * N * LD, *Vp = V + (size_t)bh * N * LD;
+    const long row0 = seg_row(sm, seg, nseg, N), row1 = seg_row(sm, seg + 1, nseg, N);
+    const int t = threadIdx.x, l = t % 64, c = l % 16, g = l / 16;
+    const int w = __builtin_amdgcn_readfirstlane(t / 64);
+    const Lanes<D> ln(c, g);
+    const bf8v one[1] = {ones_frag()};
+
+    Blk st[NRB];
+#pragma unroll
+    for (int rb = 0; rb < NRB; ++rb) st[rb].zero();
+    f4v zacc = {0.f, 0.f, 0.f, 0.f}, pacc = zacc;  // z, p [16w + 4g + e]
+    struct Set {
+        CH k, v;
+    } sets[MD::DEPTH];
+    const long c_last = row0 + (row1 - row0 - 1) / CR * CR;
+#pragma unroll
+    for (int i = 0; i < MD::DEPTH; ++i) {
+        sets[i].k.load(Kp, min(row0 + i * CR, c_last), N);
+        sets[i].v.load(Vp, min(row0 + i * CR, c_last), N);
+    }
+    auto chunk = [&](long c0, Set &cur) __attribute__((always_inline)) {
+        __syncthreads();
+        stage<MD::NORM, false, LQ>(cur.k, Kt, MD::RN ? ik : nullptr);
+        cur.v.template store<false, LV>(Vt);
+        __syncthreads();
+        const long cn = min(c0 + MD::DEPTH * CR, c_last);
+        cur.k.load(Kp, cn, N);
+        cur.v.load(Vp, cn, N);
+        bf8v kf[LQ];
+        load_cols<D, LQ>(kf, Kt, ln.local(ln.col), w);
+        if constexpr (MD::RN) {
+            bf8v fk[3];
+            factor_frag(fk, ik, g);
+            zacc += step_product<LQ, 3>(kf, fk);
+        } else {
+            zacc += step_product<LQ, 1>(kf, one);
+        }
+        if constexpr (TRANSPOSED) {
+            if constexpr (MD::RN) {
+                bf8v kh[3];
+                scale_frag<3>(kh, kf, ik, g);
+                rank_update<D, LV, 3>(st, Vt, kh, ln);
+            } else {
+                rank_update<D, LV, LQ>(st, Vt, kf, ln);
+            }
+        } else {
+            bf8v vf[LV];
+            load_cols<D, LV>(vf, Vt, ln.local(ln.col), w);
+            pacc += step_product<LV, 1>(vf, one);
+            if constexpr (MD::RN) {
+                bf8v vh[3];
+                scale_frag<3>(vh, vf, ik, g);
+                rank_update<D, LQ, 3>(st, Kt, vh, ln);
+            } else {
+                rank_update<D, LQ, LV>(st, Kt, vf, ln);
+            }
+        }
+    };
+    for (long c0 = row0; c0 < row1; c0 += MD::DEPTH * CR) {
+        chunk(c0, sets[0]);
+        if (MD::DEPTH == 2 && c0 + CR < row1) chunk(c0 + CR, sets[MD::DEPTH - 1]);
+    }
+    float *slot = ws + ((size_t)bh * nseg + seg + slot_shift) * slot_floats;
+#pragma unroll
+    for (int rb = 0; rb < NRB; ++rb)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) slot[(rb * 16 + 4 * g + i) * D + w * 16 + c] = st[rb].get(i);
+    if (c == 0) {
+        *reinterpret_cast<f4v *>(slot + D * D + w * 16 + 4 * g) = zacc;
+        if constexpr (!TRANSPOSED) *reinterpret_cast<f4v *>(slot + D * D + D + w * 16 + 4 * g) = pacc;
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Phase 3 (forward): Eq. fglast / div chunk by chunk.
+//   f = tril(a + b Q_c K_c^T) V_c + a 1 p^T + b Q_c S ;  g = rowsum(tril) + a n + b Q_c z
+//   then S += K_c^T V_c, z += sum k, p += sum v
+// LD != D: the call works on D columns of rows LD wide and is one of several launches that
+// build O up: xflags & XF_RAW leaves the numerator undivided in O and the launch's share of g
+// in G; xflags & XF_ACC adds the numerator that O holds and the share of g in Gin first.  bf16
+// tensors keep the undivided numerator in Fraw instead (fp32, B*H*N rows of D): O is rounded once.
+// ---------------------------------------------------------------------------
+template <int MODE, int D, bool CAUSAL, int LD>
+__global__ __launch_bounds__(4 * D, 2) void ks_fwd_apply(
+    const typename Mode<MODE>::TIO *__restrict__ Q, const typename Mode<MODE>::TIO *__restrict__ K,
+    const typename Mode<MODE>::TIO *__restrict__ V, typename Mode<MODE>::TIO *__restrict__ O, float *__restrict__ G, const float *__restrict__ ws,
+    float *__restrict__ saved, int N, int nseg, SegMap sm, size_t slot_floats, size_t saved_floats,
+    float a, float b, int xflags, const float *__restrict__ Gin, float *__restrict__ Fraw)
+{
+    typedef Mode<MODE> MD;
+    typedef typename MD::TIO TIO;
+    constexpr int LQ = MD::LQ, LV = MD::LV, LX = MD::LX;
+    constexpr bool RAW32 = LD != D && sizeof(TIO) == 2;
+    constexpr int NW = D / 16, NRB = D / 16, PL = Tile<D>::PLANE, WPL = Tile<32>::PLANE;
+    constexpr int TS = CAUSAL ? 1 : 0;
+    typedef Chunk<TIO, D, LD> CH;
+    __shared__ __align__(16) __bf16 lds[(1 + TS) * LQ * PL + TS * (LV * PL + LX * WPL)];
+    __shared__ __align__(16) float zs[D], qzs[CR], psum[2][CR], ginv[NW][CR];
+    __shared__ __align__(16) float iq[MD::RN ? CR : 4], ik[MD::RN ? CR : 4];  // 1 / |q|, 1 / |k|
+    __bf16 *Qt = lds;  // operand-ordered; K and V natural
+    __bf16 *Kt = Qt + LQ * PL, *Vt = Kt + TS * LQ * PL, *Pt = Vt + TS * LV * PL;
+
+    const int bh = blockIdx.x / nseg, seg = blockIdx.x % nseg;
+    const size_t base = (size_t)bh * N * LD;
+    const TIO *Qp = Q + base, *Kp = K + base, *Vp = V + base;
+    TIO *Op = O + base;
+    float *Gp = G + (size_t)bh * N;
+    const long row0 = seg_row(sm, seg, nseg, N), row1 = seg_row(sm, seg + 1, nseg, N);
+    const int t = threadIdx.x, l = t % 64, c = l % 16, g = l / 16;
+    const int w = __builtin_amdgcn_readfirstlane(t / 64);
+    const Lanes<D> ln(c, g);
+    const Lanes<32> lw(c, g);
+    const bf8v one[1] = {ones_frag()};
+
+    // initial state from the scanned slot: S[r][j], j = 16w + c
+    const bool zero_init = CAUSAL && seg == 0;
+    const float *slot = ws + ((size_t)bh * nseg + (CAUSAL ? seg : 0)) * slot_floats;
+    Blk st[NRB];
+#pragma unroll
+    for (int rb = 0; rb < NRB; ++rb) st[rb].zero();
+    f4v pacc = {0.f, 0.f, 0.f, 0.f}, zacc = pacc;  // p, z [16w + 4g + e]
+    if (!zero_init) {
+#pragma unroll
+        for (int rb = 0; rb < NRB; ++rb)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) st[rb].set(i, slot[(rb * 16 + 4 * g + i) * D + w * 16 + c]);
+        pacc = *reinterpret_cast<const f4v *>(slot + D * D + D + w * 16 + 4 * g);
+        zacc = *reinterpret_cast<const f4v *>(slot + D * D + w * 16 + 4 * g);
+    }
+    if (c == 0) *reinterpret_cast<f4v *>(zs + w * 16 + 4 * g) = zacc;
+    // the block above the diagonal stays zero
+    if constexpr (CAUSAL) {
+        if (t < 64) store_weights<LX>(Pt, c, 1, g, f4v{0.f, 0.f, 0.f, 0.f});
+    }
+    // Hand-over to the backward pass: entry s = [S^T | z] over all rows before segment s (with
+    // the mask); entry 0 the sums over the whole sequence (without).
+    if (!CAUSAL && saved && seg == 0) {
+        float *dst = saved + (size_t)bh * nseg * saved_floats;
+#pragma unroll
+        for (int rb = 0; rb < NRB; ++rb)
+            *reinterpret_cast<f4v *>(dst + (w * 16 + c) * D + rb * 16 + 4 * g) = st[rb].v;
+        if (c == 0) *reinterpret_cast<f4v *>(dst + D * D + w * 16 + 4 * g) = zacc;
+    }
+
+    struct Set {
+        CH q, k, v;
+    } sets[MD::DEPTH];
+    const long c_last = row0 + (row1 - row0 - 1) / CR * CR;
+#pragma unroll
+    for (int i = 0; i < MD::DEPTH; ++i) {
+        const long ci = min(row0 + i * CR, c_last);
+        sets[i].q.load(Qp, ci, N);
+        if constexpr (CAUSAL) {
+            sets[i].k.load(Kp, ci, N);
+            sets[i].v.load(Vp, ci, N);
+        }
+    }
+    auto chunk = [&](long c0, Set &cur) __attribute__((always_inline)) {
+        const bool lo_on = c0 < sm.lo_rows;  // second plane of the intermediates: early rows
+        __syncthreads();  // every wave is done with the previous chunk's tiles; zs is written
+        {
+            f4v x[2] = {cur.q.value(0), cur.q.value(1)};
+            if constexpr (MD::NORM) normalise_quads<CH>(x, MD::RN ? iq : nullptr);
+            float s[2];
+#pragma unroll
+            for (int k = 0; k < 2; ++k)
+                s[k] = dot4(x[k], *reinterpret_cast<const f4v *>(zs + 4 * CH::quad(k)));
+            CH::row_totals(s);
+            if (CH::leader()) {
+#pragma unroll
+                for (int k = 0; k < 2; ++k) qzs[CH::row(k)] = s[k];
+            }
+            if constexpr (LQ == 1) cur.q.template store<true, 1>(Qt);
+            else CH::template store_values<true, LQ>(Qt, x);
+        }
+        if constexpr (CAUSAL) {
+            stage<MD::NORM, false, LQ>(cur.k, Kt, MD::RN ? ik : nullptr);
+            cur.v.template store<false, LV>(Vt);
+        }
+        __syncthreads();
+        const long cn = min(c0 + MD::DEPTH * CR, c_last);
+        cur.q.load(Qp, cn, N);
+
+        // ---- phase A: weight blocks P = tril(a + b Q K^T), rows n, columns i ----
+        if constexpr (CAUSAL) {
+#pragma unroll 1
+            for (int pidx = w; pidx < 3; pidx += NW) {
+                const int ib = pidx ? 1 : 0, nb = pidx == 2 ? 1 : 0;
+                f4v pa = block_product<D, LQ, LQ>(Kt, nb, Qt, ib, ln);
+                if constexpr (MD::RN)
+                    pa *= iq[ib * 16 + c] * *reinterpret_cast<const f4v *>(ik + nb * 16 + 4 * g);
+                const int last = nb == ib ? c : 15;  // last row n at or before row i
+                f4v x;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) x[e] = 4 * g + e > last ? 0.f : a + b * pa[e];
+                with_planes<LX>(lo_on, [&](auto n) { store_weights<n.value>(Pt, ib * 16 + c, nb, g, x); });
+                const float rs = reduce_lane_groups((x[0] + x[1]) + (x[2] + x[3]));
+                if (g == 0) psum[nb][ib * 16 + c] = rs;
+            }
+            cur.k.load(Kp, cn, N);
+        }
+        // The product with the state needs nothing of phase A.
+        f4v fh[2], fl[2];  // rows j = 16w + 4g + e, columns i
+#pragma unroll
+        for (int m = 0; m < 2; ++m) fh[m] = fl[m] = f4v{0.f, 0.f, 0.f, 0.f};
+        with_planes<LX>(lo_on, [&](auto n) { state_product<D, n.value, LQ, false>(fh, fl, st, Qt, ln); });
+        bf8v vf[LV];
+        if constexpr (CAUSAL) {
+            load_cols<D, LV>(vf, Vt, ln.local(ln.col), w);
+            cur.v.load(Vp, cn, N);
+        }
+        __syncthreads();
+
+        // ---- phase B: denominators; V^T P^T on top, divide, store ----
+        if (l < CR) {
+            float ps = 0.f;
+            if constexpr (CAUSAL) ps = psum[0][l] + (l >= 16 ? psum[1][l] : 0.f);
+            float gv = b * qzs[l] + a * (CAUSAL ? (float)c0 : (float)N) + ps;
+            const bool valid = l < (int)(row1 - c0);
+            if constexpr (LD != D) {
+                if ((xflags & XF_ACC) && valid) gv += (Gin + (size_t)bh * N + c0)[l];
+                ginv[w][l] = (xflags & XF_RAW) ? 1.f : 1.f / gv;
+            } else {
+                ginv[w][l] = 1.f / gv;
+            }
+            if (w == 0 && G && valid) (Gp + c0)[l] = gv;
+        }
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int m = 0; m < 2; ++m) {
+            f4v f = (MD::RN ? b * iq[m * 16 + c] : b) * (fh[m] + fl[m]);
+            if constexpr (CAUSAL) {
+                with_planes<LX>(lo_on, [&](auto n) {
+                    bf8v pf[n.value];
+                    load_rows<32, n.value>(pf, Pt, lw.row, m, 0);
+                    f += step_product<LV, n.value>(vf, pf);
+                });
+            }
+            const f4v y = (f + a * pacc) * ginv[w][m * 16 + c];
+            const int nrows = (int)(row1 - c0) - m * 16;
+            float *fr = RAW32 ? Fraw + ((size_t)bh * N + c0 + m * 16) * D : nullptr;
+            if (RAW32 && (xflags & XF_RAW))
+                store_block<float>(fr, D, w * 16, nrows, l, y[0], y[1], y[2], y[3]);
+            else
+                store_block<TIO>(Op + (size_t)(c0 + m * 16) * LD, LD, w * 16, nrows, l, y[0], y[1], y[2],
+                                 y[3], (LD != D && (xflags & XF_ACC)) ? 2 : 0, &ginv[w][m * 16], fr, D);
+        }
+        if constexpr (CAUSAL) {
+            pacc += step_product<LV, 1>(vf, one);
+            bf8v kf[LQ];
+            load_cols<D, LQ>(kf, Kt, ln.local(ln.col), w);
+            if constexpr (MD::RN) {
+                bf8v fk[3], vh[3];
+                factor_frag(fk, ik, g);
+                zacc += step_product<LQ, 3>(kf, fk);
+                scale_frag<3>(vh, vf, ik, g);
+                rank_update<D, LQ, 3>(st, Kt, vh, ln);
+            } else {
+                zacc += step_product<LQ, 1>(kf, one);
+                rank_update<D, LQ, LV>(st, Kt, vf, ln);
+            }
+            // zs was read while this chunk was staged; it is read again behind the barrier at
+            // the top of the next one
+            if (c == 0) *reinterpret_cast<f4v *>(zs + w * 16 + 4 * g) = zacc;
+        }
+    };
+    for (long c0 = row0; c0 < row1; c0 += MD::DEPTH * CR) {
+        chunk(c0, sets[0]);
+        if (MD::DEPTH == 2 && c0 + CR < row1) chunk(c0 + CR, sets[MD::DEPTH - 1]);
+    }
+    if (CAUSAL && saved && seg + 1 < nseg) {
+        float *dst = saved + ((size_t)bh * nseg + seg + 1) * saved_floats;
+#pragma unroll
+        for (int rb = 0; rb < NRB; ++rb)
+            *reinterpret_cast<f4v *>(dst + (w * 16 + c) * D + rb * 16 + 4 * g) = st[rb].v;
+        if (c == 0) *reinterpret_cast<f4v *>(dst + D * D + w * 16 + 4 * g) = zacc;
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Backward, ascending sweep: dQ (Eq. back1), dprime, and the segment's reverse sums.
+//   Cm'_in = dO_i . v_n - dprime_i,  dprime_i = o_i . dO_i
+//   dQ_c = diag(b / g) (tril(Cm') K_c + dO_c S^T - dprime z^T);  then S += K_c^T V_c, z += sum k
+//   R += (Q/g)_c^T dO_c,  u += sum dprime (q/g),  w += sum dO / g
+// The state is held transposed (rows j, columns r): the product contracts over j.
+// LD != D: xflags & 1 marks the second of the two launches that build dQ up.
+// ---------------------------------------------------------------------------
+template <int MODE, int D, bool CAUSAL, int LD>
+__global__ __launch_bounds__(4 * D, 2) void ks_bwd_dq(
+    const typename Mode<MODE>::TIO *__restrict__ Q, const typename Mode<MODE>::TIO *__restrict__ K,
+    const typename Mode<MODE>::TIO *__restrict__ V, const typename Mode<MODE>::TIO *__restrict__ O,
+    const float *__restrict__ G, const typename Mode<MODE>::TIO *__restrict__ dO,
+    typename Mode<MODE>::TIO *__restrict__ dQ, float *ws, const float *sinit, size_t sinit_floats,
+    float *__restrict__ dprime, int N, int nseg, SegMap sm, size_t slot_floats, float b, int xflags,
+    float *__restrict__ Pq)
+{
+    typedef Mode<MODE> MD;
+    typedef typename MD::TIO TIO;
+    constexpr int LQ = MD::LQ, LV = MD::LV, LX = MD::LX;
+    constexpr bool SWAP = MD::SWAP, QT = MD::QT, PROJ = MD::NORM;
+    constexpr int NW = D / 16, NRB = D / 16, PL = Tile<D>::PLANE, WPL = Tile<32>::PLANE;
+    constexpr int TS = CAUSAL ? 1 : 0;
+    typedef Chunk<TIO, D, LD> CH;
+    typedef BwdSlot<D> SL;
+    __shared__ __align__(16) __bf16 lds[LV * PL + LQ * PL + TS * (LV * PL + LQ * PL + LX * WPL)];
+    __shared__ __align__(16) __bf16 frs[2][3 * CR], fdl[3 * CR];  // 1/g, dprime as operands
+    __shared__ __align__(16) float rsb[2][CR], gb[2][CR], dl[CR];
+    __shared__ __align__(16) float qinv[PROJ ? CR : 4], dots[PROJ ? NW * CR : 4];  // 1 / |q|
+    __shared__ __align__(16) float ik[MD::RN ? CR : 4];                            // 1 / |k|
+    __bf16 *dOt = lds;  // operand-ordered; the others natural
+    __bf16 *Qt = dOt + LV * PL, *Vt = Qt + LQ * PL, *Kt = Vt + TS * LV * PL, *Ct = Kt + TS * LQ * PL;
+
+    const int bh = blockIdx.x / nseg, seg = blockIdx.x % nseg;
+    const size_t base = (size_t)bh * N * LD;
+    const TIO *Qp = Q + base, *Kp = K + base, *Vp = V + base, *Op = O + base, *dOp = dO + base;
+    TIO *dQp = dQ + base;
+    const float *Gp = G + (size_t)bh * N;
+    float *dp = dprime + (size_t)bh * N;
+    const long row0 = seg_row(sm, seg, nseg, N), row1 = seg_row(sm, seg + 1, nseg, N);
+    const int t = threadIdx.x, l = t % 64, c = l % 16, g = l / 16;
+    const int w = __builtin_amdgcn_readfirstlane(t / 64);
+    const Lanes<D, (D >= 128)> ln(c, g);
+    const Lanes<32> lw(c, g);
+    const bf8v one[1] = {ones_frag()};
+    const bool need_R = CAUSAL ? (seg > 0) : true;  // segment 0's sums start no one
+    const bool need_Q = need_R || PROJ;
+
+    const bool zero_init = CAUSAL && seg == 0;
+    const float *slot = sinit + ((size_t)bh * nseg + (CAUSAL ? seg : 0)) * sinit_floats;
+    Blk st[NRB], accR[NRB];  // S^T: rows j, columns r = 16w + c;  R: rows r, columns j
+#pragma unroll
+    for (int jb = 0; jb < NRB; ++jb) {
+        accR[jb].zero();
+        st[jb].zero();
+    }
+    Sum<SWAP> zacc, uacc, wacc;  // z, u, w
+    if (!zero_init) {
+#pragma unroll
+        for (int jb = 0; jb < NRB; ++jb)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                st[jb].set(i, slot[SL::ST + (jb * 16 + 4 * g + i) * D + w * 16 + c]);
+        zacc.load(slot + SL::Z, w, c, g);
+    }
+    if constexpr (CAUSAL) {
+        if (t < 64) store_weights<LX>(Ct, c, 1, g, f4v{0.f, 0.f, 0.f, 0.f});
+    }
+
+    struct Set {
+        CH d, o, k, v, q;
+        float g;  // g of row t % 32
+    } sets[MD::DEPTH];
+    const long c_last = row0 + (row1 - row0 - 1) / CR * CR;
+    // 1/g of the chunk starting at c0, whose g is gn, into buffer `par`
+    auto post_factors = [&](long c0, float gn, int par) {
+        if (t < CR) {
+            const bool ok = t < (int)(row1 - c0);
+            const float r = ok ? __builtin_amdgcn_rcpf(gn) : 0.f;
+            rsb[par][t] = r;
+            gb[par][t] = ok ? gn : 0.f;
+            store_factor<3>(frs[par], t, r);
+        }
+    };
+#pragma unroll
+    for (int i = 0; i < MD::DEPTH; ++i) {
+        const long ci = min(row0 + i * CR, c_last);
+        sets[i].g = load_row_float(Gp, ci, N, t % CR);
+        sets[i].d.load(dOp, ci, N);
+        sets[i].o.load(Op, ci, N);
+        if constexpr (CAUSAL) {
+            sets[i].v.load(Vp, ci, N);
+            sets[i].k.load(Kp, ci, N);
+        }
+        sets[i].q.load(Qp, ci, N);
+    }
+    post_factors(row0, sets[0].g, 0);
+    // nxt: the set that holds the chunk after this one
+    auto chunk = [&](long c0, Set &cur, Set &nxt, int par) __attribute__((always_inline)) {
+        __syncthreads();
+        const float *rs = rsb[par];
+        const bool lo_on = c0 < sm.lo_rows;  // second plane of the intermediates: early rows
+        if (need_Q) stage<MD::NORM, false, LQ>(cur.q, Qt, PROJ ? qinv : nullptr, QT ? rs : nullptr);
+        {
+            float s[2] = {dot4(cur.d.value(0), cur.o.value(0)), dot4(cur.d.value(1), cur.o.value(1))};
+            CH::row_totals(s);
+            if (CH::leader()) {
+#pragma unroll
+                for (int k = 0; k < CH::NLD; ++k) {
+                    const int r = CH::row(k);
+                    dl[r] = s[k];
+                    // the row's weight in u: the staged rows are q/g (QT), or q (times 1/|q|;
+                    // this lane wrote that factor)
+                    float wu = QT ? s[k] : s[k] * rs[r];
+                    if constexpr (MD::RN) wu *= qinv[r];
+                    store_factor<3>(fdl, r, wu);
+                    if (r < (int)(row1 - c0)) (dp + c0)[r] = s[k];
+                }
+            }
+            cur.d.template store<true, LV>(dOt);
+        }
+        if constexpr (CAUSAL) {
+            cur.v.template store<false, LV>(Vt);
+            stage<MD::NORM, false, LQ>(cur.k, Kt, MD::RN ? ik : nullptr);
+        }
+        __syncthreads();
+        const long cn = min(c0 + MD::DEPTH * CR, c_last);
+        cur.g = load_row_float(Gp, cn, N, t % CR);
+        cur.d.load(dOp, cn, N);
+        cur.o.load(Op, cn, N);
+        if constexpr (!CAUSAL) cur.q.load(Qp, cn, N);
+
+        // ---- phase A: weight blocks Cm' (rows n, columns i) ----
+        if constexpr (CAUSAL) {
+#pragma unroll 1
+            for (int pidx = w; pidx < 3; pidx += NW) {
+                const int ib = pidx ? 1 : 0, nb = pidx == 2 ? 1 : 0;
+                const f4v pa = block_product<D, LV, LV>(Vt, nb, dOt, ib, ln);
+                const float di = dl[ib * 16 + c];
+                const int last = nb == ib ? c : 15;  // last row n at or before row i
+                f4v x;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) x[e] = 4 * g + e > last ? 0.f : pa[e] - di;
+                if constexpr (MD::RN) x *= *reinterpret_cast<const f4v *>(ik + nb * 16 + 4 * g);
+                with_planes<LX>(lo_on, [&](auto n) { store_weights<n.value>(Ct, ib * 16 + c, nb, g, x); });
+            }
+            cur.v.load(Vp, cn, N);
+        }
+        f4v fh[2], fl[2];  // rows i, columns r (SWAP), or rows r, columns i
+#pragma unroll
+        for (int m = 0; m < 2; ++m) fh[m] = fl[m] = f4v{0.f, 0.f, 0.f, 0.f};
+        with_planes<LX>(lo_on, [&](auto n) { state_product<D, n.value, LV, SWAP>(fh, fl, st, dOt, ln); });
+        bf8v kf[LQ];
+        if constexpr (CAUSAL) {
+            load_cols<D, LQ>(kf, Kt, ln.local(ln.col), w);
+            cur.k.load(Kp, cn, N);
+            __syncthreads();
+        }
+
+        // ---- phase B: K^T Cm'^T on top, scale, store ----
+        f4v x[2];
+#pragma unroll
+        for (int m = 0; m < 2; ++m) {
+            f4v f = fh[m] + fl[m];
+            if constexpr (CAUSAL) {
+                with_planes<LX>(lo_on, [&](auto n) {
+                    bf8v pf[n.value];
+                    load_rows<32, n.value>(pf, Ct, lw.row, m, 0);
+                    f += own_product<SWAP, LQ, n.value>(kf, pf);
+                });
+            }
+            x[m] = (b * row_factor<SWAP>(rs, m, c, g)) * (f - zacc.v * row_factor<SWAP>(dl, m, c, g));
+        }
+        if constexpr (PROJ)  // qhat = g (q/g), or q / |q|
+            project_chunk<SWAP, false, D, LQ>(x, Qt, ln, QT ? gb[par] : qinv, dots, qinv, w, c, g);
+#pragma unroll
+        for (int m = 0; m < 2; ++m)
+            store_grad<SWAP, D, LD>(dQp + (size_t)(c0 + m * 16) * LD,
+                                    Pq + ((size_t)bh * N + c0 + m * 16) * D, xflags & 1, w,
+                                    (int)(row1 - c0) - m * 16, l, x[m]);
+        if constexpr (CAUSAL) {
+            cur.q.load(Qp, cn, N);
+            if constexpr (MD::RN) {
+                bf8v fk[3], kh[3];
+                factor_frag(fk, ik, g);
+                zacc.add(kf, fk);
+                scale_frag<3>(kh, kf, ik, g);
+                rank_update<D, LV, 3>(st, Vt, kh, ln);
+            } else {
+                zacc.add(kf, one);
+                rank_update<D, LV, LQ>(st, Vt, kf, ln);
+            }
+        }
+        if (need_R) {
+            bf8v df[LV], qf[LQ], fr[3], fd[3];
+            load_cols_op<D, LV>(df, dOt, ln.local(ln.ocol), w);
+            load_cols<D, LQ>(qf, Qt, ln.local(ln.col), w);
+            load_factor<3>(fr, frs[par], g);
+            load_factor<3>(fd, fdl, g);
+            wacc.add(df, fr);
+            uacc.add(qf, fd);
+            if constexpr (QT) {
+                rank_update<D, LQ, LV>(accR, Qt, df, ln);
+            } else {
+                with_planes<LX>(lo_on, [&](auto n) {
+                    bf8v oh[n.value];
+                    scale_frag<n.value>(oh, df, rs, g, MD::RN ? qinv : nullptr);
+                    rank_update<D, LQ, n.value>(accR, Qt, oh, ln);
+                });
+            }
+        }
+        post_factors(min(c0 + CR, row1), nxt.g, par ^ 1);
+    };
+    if constexpr (MD::DEPTH == 2) {
+        for (long c0 = row0; c0 < row1; c0 += 2 * CR) {
+            chunk(c0, sets[0], sets[MD::DEPTH - 1], 0);
+            if (c0 + CR < row1) chunk(c0 + CR, sets[MD::DEPTH - 1], sets[0], 1);
+        }
+    } else {
+        int par = 0;
+        for (long c0 = row0; c0 < row1; c0 += CR, par ^= 1) chunk(c0, sets[0], sets[0], par);
+    }
+    if (need_R) {
+        float *out = ws + ((size_t)bh * nseg + seg - (CAUSAL ? 1 : 0)) * slot_floats;
+#pragma unroll
+        for (int rb = 0; rb < NRB; ++rb)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) out[SL::R + (rb * 16 + 4 * g + i) * D + w * 16 + c] = accR[rb].get(i);
+        wacc.store(out + SL::W, w, c, g);
+        uacc.store(out + SL::U, w, c, g);
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Backward, descending sweep: dK and dV (Eq. back1 / back2).
+//   dK_c = b (tril(Cm')^T (Q/g)_c + V_c R^T - 1 u^T),   Cm'_in = dO_i . v_n - dprime_i
+//   dV_c = tril(W)^T dO_c + a 1 w^T + b K_c R,          W_in = a / g_i + b (q_i/g_i) . k_n
+//   then R += (Q/g)_c^T dO_c, u += sum dprime (q/g), w += sum dO / g.
+// R is held twice: rows r x columns j for dV, rows j x columns r for dK.
+// LD != D: xflags & 2 (dK), & 4 (dV) mark the second of the two launches that build them up.
+// ---------------------------------------------------------------------------
+template <int MODE, int D, bool CAUSAL, int LD>
+__global__ __launch_bounds__(4 * D, 2) void ks_bwd_dkv(
+    const typename Mode<MODE>::TIO *__restrict__ Q, const typename Mode<MODE>::TIO *__restrict__ K,
+    const typename Mode<MODE>::TIO *__restrict__ V, const float *__restrict__ G,
+    const typename Mode<MODE>::TIO *__restrict__ dO, typename Mode<MODE>::TIO *__restrict__ dK,
+    typename Mode<MODE>::TIO *__restrict__ dV, const float *__restrict__ ws, const float *__restrict__ dprime, int N,
+    int nseg, SegMap sm, size_t slot_floats, float a, float b, int xflags,
+    float *__restrict__ Pk, float *__restrict__ Pv)
+{
+    typedef Mode<MODE> MD;
+    typedef typename MD::TIO TIO;
+    constexpr int LQ = MD::LQ, LV = MD::LV, LX = MD::LX;
+    constexpr bool SWAP = MD::SWAP, QT = MD::QT, PROJ = MD::NORM;
+    constexpr int NW = D / 16, NRB = D / 16, PL = Tile<D>::PLANE, WPL = Tile<32>::PLANE;
+    constexpr int TS = CAUSAL ? 1 : 0;
+    typedef Chunk<TIO, D, LD> CH;
+    typedef BwdSlot<D> SL;
+    __shared__ __align__(16) __bf16 lds[LQ * PL + LV * PL + TS * (LQ * PL + LV * PL + 2 * LX * WPL)];
+    __shared__ __align__(16) __bf16 frs[2][3 * CR], fdl[2][3 * CR];  // 1/g, dprime as operands
+    __shared__ __align__(16) float rsb[2][CR], dlb[2][CR];
+    __shared__ __align__(16) float kinv[PROJ ? CR : 4], dots[PROJ ? NW * CR : 4];  // 1 / |k|
+    __shared__ __align__(16) float iq[MD::RN ? CR : 4];                            // 1 / |q|
+    __bf16 *Kt = lds, *Vt = Kt + LQ * PL;  // operand-ordered; Q/g and dO natural
+    __bf16 *Qt = Vt + LV * PL, *dOt = Qt + TS * LQ * PL, *Ct = dOt + TS * LV * PL,
+           *Wt = Ct + TS * LX * WPL;
+
+    const int bh = blockIdx.x / nseg, seg = blockIdx.x % nseg;
+    const size_t base = (size_t)bh * N * LD;
+    const TIO *Qp = Q + base, *Kp = K + base, *Vp = V + base, *dOp = dO + base;
+    TIO *dKp = dK + base, *dVp = dV + base;
+    const float *Gp = G + (size_t)bh * N, *dp = dprime + (size_t)bh * N;
+    const long row0 = seg_row(sm, seg, nseg, N), row1 = seg_row(sm, seg + 1, nseg, N);
+    const int t = threadIdx.x, l = t % 64, c = l % 16, g = l / 16;
+    const int w = __builtin_amdgcn_readfirstlane(t / 64);
+    const Lanes<D, (D >= 128)> ln(c, g);
+    const Lanes<32> lw(c, g);
+
+    const bool zero_init = CAUSAL && seg == nseg - 1;
+    const float *slot = ws + ((size_t)bh * nseg + (CAUSAL ? seg : 0)) * slot_floats;
+    Blk Ra[NRB], Rb[NRB];  // R: rows r, columns j = 16w + c;  R^T: rows j, columns r = 16w + c
+#pragma unroll
+    for (int rb = 0; rb < NRB; ++rb) {
+        Ra[rb].zero();
+        Rb[rb].zero();
+    }
+    Sum<SWAP> uacc, wacc;  // u, w
+    if (!zero_init) {
+#pragma unroll
+        for (int rb = 0; rb < NRB; ++rb) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                Ra[rb].set(i, slot[SL::R + (rb * 16 + 4 * g + i) * D + w * 16 + c]);
+            Rb[rb].v = *reinterpret_cast<const f4v *>(slot + SL::R + (w * 16 + c) * D + rb * 16 + 4 * g);
+        }
+        uacc.load(slot + SL::U, w, c, g);
+        wacc.load(slot + SL::W, w, c, g);
+    }
+    if constexpr (CAUSAL) {
+        if (t < 64) {
+            store_weights<LX>(Ct, 16 + c, 0, g, f4v{0.f, 0.f, 0.f, 0.f});
+            store_weights<LX>(Wt, 16 + c, 0, g, f4v{0.f, 0.f, 0.f, 0.f});
+        }
+    }
+
+    const long nchunks = (row1 - row0 + CR - 1) / CR;
+    struct Set {
+        CH k, v, q, d;
+        float g, dp;  // g, dprime of row t % 32
+    } sets[MD::DEPTH];
+    auto post_factors = [&](long c0, const Set &x, int par) {
+        if (CAUSAL && t < CR) {
+            const bool ok = t < (int)(row1 - c0);
+            const float r = ok ? __builtin_amdgcn_rcpf(x.g) : 0.f, d = ok ? x.dp : 0.f;
+            rsb[par][t] = r;
+            dlb[par][t] = d;
+            store_factor<3>(frs[par], t, r);
+            store_factor<3>(fdl[par], t, QT ? d : d * r);
+        }
+    };
+#pragma unroll
+    for (int i = 0; i < MD::DEPTH; ++i) {
+        const long cl = row0 + max(nchunks - 1 - i, 0L) * CR;
+        sets[i].k.load(Kp, cl, N);
+        sets[i].v.load(Vp, cl, N);
+        if constexpr (CAUSAL) {
+            sets[i].g = load_row_float(Gp, cl, N, t % CR);
+            sets[i].dp = load_row_float(dp, cl, N, t % CR);
+            sets[i].q.load(Qp, cl, N);
+            sets[i].d.load(dOp, cl, N);
+        }
+    }
+    post_factors(row0 + (nchunks - 1) * CR, sets[0], 0);
+    // nxt: the set that holds the chunk after this one
+    auto chunk = [&](long ci, Set &cur, Set &nxt, int par) __attribute__((always_inline)) {
+        const long c0 = row0 + ci * CR;
+        const float *rs = rsb[par], *dl = dlb[par];
+        const bool lo_on = c0 < sm.lo_rows;  // second plane of the intermediates: early rows
+        __syncthreads();
+        stage<MD::NORM, true, LQ>(cur.k, Kt, PROJ ? kinv : nullptr);
+        cur.v.template store<true, LV>(Vt);
+        if constexpr (CAUSAL) {
+            stage<MD::NORM, false, LQ>(cur.q, Qt, MD::RN ? iq : nullptr, QT ? rs : nullptr);
+            if constexpr (MD::RN) {  // the weights in u take the factor this lane just wrote
+                const int r = CH::row(0);
+                if (CH::leader()) store_factor<3>(fdl[par], r, dl[r] * rs[r] * iq[r]);
+            }
+            cur.d.template store<false, LV>(dOt);
+        }
+        __syncthreads();
+        const long cn = row0 + max(ci - MD::DEPTH, 0L) * CR;
+        cur.k.load(Kp, cn, N);
+        cur.v.load(Vp, cn, N);
+        if constexpr (CAUSAL) {
+            cur.g = load_row_float(Gp, cn, N, t % CR);
+            cur.dp = load_row_float(dp, cn, N, t % CR);
+            // ---- phase A: weight blocks Cm' and W (rows i, columns n) ----
+#pragma unroll 1
+            for (int pidx = w; pidx < 6; pidx += NW) {
+                const int q = pidx >= 3 ? pidx - 3 : pidx, ib = q ? 1 : 0, nb = q == 2 ? 1 : 0;
+                f4v x;
+                if (pidx < 3) {
+                    const f4v pc = block_product<D, LV, LV>(dOt, ib, Vt, nb, ln);
+                    x = pc - *reinterpret_cast<const f4v *>(dl + ib * 16 + 4 * g);
+                    if constexpr (!QT) x *= *reinterpret_cast<const f4v *>(rs + ib * 16 + 4 * g);
+                    if constexpr (MD::RN) x *= *reinterpret_cast<const f4v *>(iq + ib * 16 + 4 * g);
+                } else {
+                    f4v pw = block_product<D, LQ, LQ>(Qt, ib, Kt, nb, ln);
+                    if constexpr (MD::RN)
+                        pw *= kinv[nb * 16 + c] * *reinterpret_cast<const f4v *>(iq + ib * 16 + 4 * g);
+                    const f4v r4 = *reinterpret_cast<const f4v *>(rs + ib * 16 + 4 * g);
+                    if constexpr (QT) x = a * r4 + b * pw;
+                    else x = (a + b * pw) * r4;
+                }
+                const int first = nb == ib ? c : 0;  // first row i that sees column n
+#pragma unroll
+                for (int e = 0; e < 4; ++e) x[e] = 4 * g + e < first ? 0.f : x[e];
+                with_planes<LX>(lo_on, [&](auto n) {
+                    store_weights<n.value>(pidx < 3 ? Ct : Wt, nb * 16 + c, ib, g, x);
+                });
+            }
+        }
+        f4v kh[2], kl[2];  // rows n, columns r (SWAP), or rows r, columns n
+#pragma unroll
+        for (int m = 0; m < 2; ++m) kh[m] = kl[m] = f4v{0.f, 0.f, 0.f, 0.f};
+        with_planes<LX>(lo_on, [&](auto n) { state_product<D, n.value, LV, SWAP>(kh, kl, Rb, Vt, ln); });
+        if constexpr (CAUSAL) {
+            cur.q.load(Qp, cn, N);
+            __syncthreads();
+        }
+
+        // ---- phase B ----
+        bf8v qf[LQ], df[LV];
+        if constexpr (CAUSAL) load_cols<D, LQ>(qf, Qt, ln.local(ln.col), w);
+        f4v x[2];
+#pragma unroll
+        for (int m = 0; m < 2; ++m) {
+            f4v f = kh[m] + kl[m];
+            if constexpr (CAUSAL) {
+                with_planes<LX>(lo_on, [&](auto n) {
+                    bf8v pf[n.value];
+                    load_rows<32, n.value>(pf, Ct, lw.row, m, 0);
+                    f += own_product<SWAP, LQ, n.value>(qf, pf);
+                });
+            }
+            x[m] = b * (f - uacc.v);
+        }
+        if constexpr (PROJ)
+            project_chunk<SWAP, true, D, LQ>(x, Kt, ln, QT ? nullptr : kinv, dots, kinv, w, c, g);
+#pragma unroll
+        for (int m = 0; m < 2; ++m)
+            store_grad<SWAP, D, LD>(dKp + (size_t)(c0 + m * 16) * LD,
+                                    Pk + ((size_t)bh * N + c0 + m * 16) * D, xflags & 2, w,
+                                    (int)(row1 - c0) - m * 16, l, x[m]);
+        if constexpr (CAUSAL) cur.d.load(dOp, cn, N);
+        f4v vh[2], vl[2];  // rows n, columns j (SWAP), or rows j, columns n
+#pragma unroll
+        for (int m = 0; m < 2; ++m) vh[m] = vl[m] = f4v{0.f, 0.f, 0.f, 0.f};
+        with_planes<LX>(lo_on, [&](auto n) { state_product<D, n.value, LQ, SWAP>(vh, vl, Ra, Kt, ln); });
+        if constexpr (CAUSAL) load_cols<D, LV>(df, dOt, ln.local(ln.col), w);
+#pragma unroll
+        for (int m = 0; m < 2; ++m) {
+            f4v f = a * wacc.v + (MD::RN ? b * kinv[m * 16 + c] : b) * (vh[m] + vl[m]);
+            if constexpr (CAUSAL) {
+                with_planes<LX>(lo_on, [&](auto n) {
+                    bf8v pf[n.value];
+                    load_rows<32, n.value>(pf, Wt, lw.row, m, 0);
+                    f += own_product<SWAP, LV, n.value>(df, pf);
+                });
+            }
+            store_grad<SWAP, D, LD>(dVp + (size_t)(c0 + m * 16) * LD,
+                                    Pv + ((size_t)bh * N + c0 + m * 16) * D, xflags & 4, w,
+                                    (int)(row1 - c0) - m * 16, l, f);
+        }
+        if constexpr (CAUSAL) {
+            bf8v fr[3], fd[3];
+            load_factor<3>(fr, frs[par], g);
+            load_factor<3>(fd, fdl[par], g);
+            wacc.add(df, fr);
+            uacc.add(qf, fd);
+            if constexpr (QT) {
+                rank_update<D, LQ, LV>(Ra, Qt, df, ln);
+                rank_update<D, LV, LQ>(Rb, dOt, qf, ln);
+            } else {
+                with_planes<LX>(lo_on, [&](auto n) {
+                    bf8v oh[n.value], qg[n.value];
+                    scale_frag<n.value>(oh, df, rs, g, MD::RN ? iq : nullptr);
+                    scale_frag<n.value>(qg, qf, rs, g, MD::RN ? iq : nullptr);
+                    rank_update<D, LQ, n.value>(Ra, Qt, oh, ln);
+                    rank_update<D, LV, n.value>(Rb, dOt, qg, ln);
+                });
+            }
+            post_factors(row0 + max(ci - 1, 0L) * CR, nxt, par ^ 1);
+        }
+    };
+    if constexpr (MD::DEPTH == 2) {
+        for (long ci = nchunks - 1; ci >= 0; ci -= 2) {
+            chunk(ci, sets[0], sets[MD::DEPTH - 1], 0);
+            if (ci > 0) chunk(ci - 1, sets[MD::DEPTH - 1], sets[0], 1);
+        }
+    } else {
+        int par = 0;
+        for (long ci = nchunks - 1; ci >= 0; --ci, par ^= 1) chunk(ci, sets[0], sets[0], par);
+    }
+}
+
+template <int MODE, int D, int LD>
+la_status run_forward(const Problem &pr, const Plan &pl, const void *Qv, const void *Kv,
+                      const void *Vv, void *Ov, float *G, float *ws, float *saved, hipStream_t st,
+                      Tracer &tc, int xflags, const float *Gin, float *Fraw)
+{
+    typedef typename Mode<MODE>::TIO TIO;
+    const TIO *Q = (const TIO *)Qv, *K = (const TIO *)Kv, *V = (const TIO *)Vv;
+    TIO *O = (TIO *)Ov;
+    const int nseg = pl.nseg, nrun = pr.causal ? nseg - 1 : nseg;
+    const dim3 block(4 * D);
+    if (nrun > 0) {
+        ks_kv_state<MODE, D, false, LD><<<dim3(pr.BH * nrun), block, 0, st>>>(
+            K, V, ws, pr.N, nseg, nrun, pl.map, pl.slot_floats, pr.causal ? 1 : 0);
+        tc.mark("fwd_state");
+        launch_scan_slots(ws, pr.BH, nseg, pl.slot_floats, 0, D * D + 2 * D, pr.causal ? 0 : 2,
+                          pr.causal ? 1 : 0, nseg - 1, st);
+        tc.mark("scan_slots");
+    }
+    auto *kernel = pr.causal ? ks_fwd_apply<MODE, D, true, LD> : ks_fwd_apply<MODE, D, false, LD>;
+    kernel<<<dim3(pr.BH * nseg), block, 0, st>>>(Q, K, V, O, G, ws, saved, pr.N, nseg, pl.map,
+                                                 pl.slot_floats, pl.saved_floats, pr.a, pr.b, xflags,
+                                                 Gin, Fraw);
+    tc.mark("fwd_apply");
+    return launch_status();
+}
+
+// dK == nullptr: the ascending sweep alone (dQ and the per-row o . dO).
+template <int MODE, int D, int LD>
+la_status run_backward(const Problem &pr, const Plan &pl, const void *Qv, const void *Kv,
+                       const void *Vv, const void *Ov, const float *G, const void *dOv, void *dQv,
+                       void *dKv, void *dVv, float *ws, const float *saved, hipStream_t st,
+                       Tracer &tc, const BlockPass &bp)
+{
+    typedef typename Mode<MODE>::TIO TIO;
+    typedef BwdSlot<D> SL;
+    const TIO *Q = (const TIO *)Qv, *K = (const TIO *)Kv, *V = (const TIO *)Vv,
+              *O = (const TIO *)Ov, *dO = (const TIO *)dOv;
+    TIO *dQ = (TIO *)dQv, *dK = (TIO *)dKv, *dV = (TIO *)dVv;
+    const int nseg = pl.nseg, nrun = pr.causal ? nseg - 1 : nseg;
+    float *dprime = ws + pl.delta_offset_floats;
+    const dim3 grid(pr.BH * nseg), block(4 * D);
+    // forward-running sums before every segment: handed over by the forward pass, or
+    // per-segment sums (none needed from a masked pass's last segment) and a scan here
+    if (!saved && nrun > 0) {
+        ks_kv_state<MODE, D, true, LD><<<dim3(pr.BH * nrun), block, 0, st>>>(
+            K, V, ws, pr.N, nseg, nrun, pl.map, pl.slot_floats, pr.causal ? 1 : 0);
+        tc.mark("bwd_state");
+        launch_scan_slots(ws, pr.BH, nseg, pl.slot_floats, SL::ST, SL::R - SL::ST, pr.causal ? 0 : 2,
+                          pr.causal ? 1 : 0, nseg - 1, st);
+        tc.mark("scan_slots");
+    }
+    const float *sinit = saved ? saved : ws;
+    const size_t sinit_floats = saved ? pl.saved_floats : pl.slot_floats;
+    auto *dq = pr.causal ? ks_bwd_dq<MODE, D, true, LD> : ks_bwd_dq<MODE, D, false, LD>;
+    dq<<<grid, block, 0, st>>>(Q, K, V, O, G, dO, dQ, ws, sinit, sinit_floats, dprime, pr.N, nseg,
+                               pl.map, pl.slot_floats, pr.b, bp.xflags, bp.Pq);
+    tc.mark("bwd_dq");
+    if (!dK) return launch_status();
+    // reverse-running sums left by the ascending sweep
+    if (!pr.causal || nseg > 1) {
+        launch_scan_slots(ws, pr.BH, nseg, pl.slot_floats, SL::R, SL::END - SL::R, pr.causal ? 1 : 2, 0,
+                          pr.causal ? nseg - 2 : nseg - 1, st);
+        tc.mark("scan_slots_rev");
+    }
+    auto *dkv = pr.causal ? ks_bwd_dkv<MODE, D, true, LD> : ks_bwd_dkv<MODE, D, false, LD>;
+    dkv<<<grid, block, 0, st>>>(Q, K, V, G, dO, dK, dV, ws, dprime, pr.N, nseg, pl.map, pl.slot_floats,
+                                pr.a, pr.b, bp.xflags, bp.Pk, bp.Pv);
+    tc.mark("bwd_dkv");
+    return launch_status();
+}
+
+template <int MODE, int D, int LD>
+la_status run_totals(const Problem &pr, const Plan &pl, const void *K, const void *V, float *ws,
+                     hipStream_t st)
+{
+    typedef typename Mode<MODE>::TIO TIO;
+    ks_kv_state<MODE, D, false, LD><<<dim3(pr.BH * pl.nseg), dim3(4 * D), 0, st>>>(
+        (const TIO *)K, (const TIO *)V, ws, pr.N, pl.nseg, pl.nseg, pl.map, pl.slot_floats, 0);
+    launch_scan_slots(ws, pr.BH, pl.nseg, pl.slot_floats, 0, D * D + 2 * D, 2, 0, pl.nseg - 1, st);
+    return launch_status();
+}
+
+int mode_of(const Problem &pr)
+{
+    return pr.dt == LA_F32 ? (pr.norm_qk ? N32 : P32) : (pr.norm_qk ? N16 : P16);
+}
+
+}  // namespace
+
+#define LA_BY_MODE(CALL)                                   \
+    switch (mode_of(pr) * 1024 + pr.D + (ld == 256)) {     \
+        case P32 * 1024 + 32: return CALL(P32, 32, 32);    \
+        case P32 * 1024 + 64: return CALL(P32, 64, 64);    \
+        case P32 * 1024 + 128: return CALL(P32, 128, 128); \
+        case P32 * 1024 + 129: return CALL(P32, 128, 256); \
+        case N32 * 1024 + 32: return CALL(N32, 32, 32);    \
+        case N32 * 1024 + 64: return CALL(N32, 64, 64);    \
+        case N32 * 1024 + 128: return CALL(N32, 128, 128); \
+        case P16 * 1024 + 32: return CALL(P16, 32, 32);    \
+        case P16 * 1024 + 64: return CALL(P16, 64, 64);    \
+        case P16 * 1024 + 128: return CALL(P16, 128, 128); \
+        case P16 * 1024 + 129: return CALL(P16, 128, 256); \
+        case N16 * 1024 + 32: return CALL(N16, 32, 32);    \
+        case N16 * 1024 + 64: return CALL(N16, 64, 64);    \
+        case N16 * 1024 + 128: return CALL(N16, 128, 128); \
+    }                                                      \
+    return LA_ERR_UNSUPPORTED
+
+la_status planes_forward(const Problem &pr, const Plan &pl, int ld, const void *Q, const void *K,
+                         const void *V, void *O, float *G, float *ws, float *saved, hipStream_t st,
+                         Tracer &tc, int xflags, const float *Gin, float *Fraw)
+{
+#define LA_FORWARD(M, D, LD) \
+    (run_forward<M, D, LD>(pr, pl, Q, K, V, O, G, ws, saved, st, tc, xflags, Gin, Fraw))
+    LA_BY_MODE(LA_FORWARD);
+}
+
+la_status planes_backward(const Problem &pr, const Plan &pl, int ld, const void *Q, const void *K,
+                          const void *V, const void *O, const float *G, const void *dO, void *dQ,
+                          void *dK, void *dV, float *ws, const float *saved, hipStream_t st,
+                          Tracer &tc, const BlockPass &bp)
+{
+#define LA_BACKWARD(M, D, LD) \
+    (run_backward<M, D, LD>(pr, pl, Q, K, V, O, G, dO, dQ, dK, dV, ws, saved, st, tc, bp))
+    LA_BY_MODE(LA_BACKWARD);
+}
+
+la_status planes_totals(const Problem &pr, const Plan &pl, int ld, const void *K, const void *V,
+                        float *ws, hipStream_t st)
+{
+#define LA_TOTALS(M, D, LD) (run_totals<M, D, LD>(pr, pl, K, V, ws, st))
+    LA_BY_MODE(LA_TOTALS);
+}
+
+}  // namespace la

@@ -1,5 +1,5 @@
 // Head size 256: token-serial kernels with the D x D running state in registers.  The
-// library runs D = 256 on the matrix-core kernels (la_fast.hip); these are what
+// library runs D = 256 on the matrix-core kernels (la_split.hip); these are what
 // la_debug_override(.., 1) switches to, as it does to the plain-ALU kernels at the other
 // head sizes; the parity tests run them under that setting.
 //
