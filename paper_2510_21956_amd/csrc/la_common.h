@@ -172,9 +172,8 @@ la_status reduce_dot(const void *X, const void *Y, size_t n, la_dtype dt, float 
 // for every one of `rows` rows of D elements, xhat = x / ||x||.
 la_status project_rows(const void *X, void *dX, size_t rows, int D, la_dtype dt, hipStream_t st);
 
-// Sums over the whole sequence, S = sum k v^T, z = sum k, p = sum v, left in slot 0 of every
-// slice as [S | z | p] (forward plan without the mask): phases 1 and 2 of the unmasked
-// forward pass on their own.
+// Per-segment sums over the whole sequence, S = sum k v^T, z = sum k, p = sum v, in the slots of
+// every slice as [S | z | p] (forward plan without the mask); state_from_totals adds the slots up.
 la_status fast_kv_totals(const Problem &pr, const Plan &pl, const void *K, const void *V,
                          float *ws, hipStream_t st);
 la_status generic_kv_totals(const Problem &pr, const Plan &pl, const void *K, const void *V,

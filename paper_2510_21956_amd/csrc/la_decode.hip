@@ -6,9 +6,10 @@
 // sums, then read out, o_t = (a p + b S^T q_t) / g_t, g_t = a count + b q_t . z (Eq. fglast, div).
 //
 // One workgroup per slice keeps the whole state in registers for the T rows of the call (no
-// other workgroup touches that slice's state, so updating it in place is race-free): thread
-// t owns column j = t % D of the rows r = t / D + RG i.  The step is bound by reading and
-// writing the state once per call: 8 D^2 bytes per slice.
+// other workgroup touches that slice's state, so updating it in place is race-free).  The step
+// is bound by reading and writing the state once per call, 8 D^2 bytes per slice, and with one
+// row by the latency of doing so: as many lanes as the state has 16-byte units (up to 1024
+// threads), each with a few of them, have the whole state in flight at once.
 #include "la_common.h"
 
 namespace la {
@@ -16,9 +17,11 @@ namespace {
 
 template <int D>
 struct DC {
-    static constexpr int NT = D <= 128 ? 256 : 1024;  // threads per workgroup
-    static constexpr int RG = NT / D;                 // row groups: threads that share a column
-    static constexpr int RPT = D / RG;                // state rows per thread
+    static constexpr int LR = D / 4;                                  // lanes that share a row
+    static constexpr int NT = D * D / 16 < 64 ? 64 : (D * D / 16 > 1024 ? 1024 : D * D / 16);
+    static constexpr int RG = NT / LR;                                // row groups
+    static constexpr int RPT = D / RG;                                // consecutive rows per thread
+    static constexpr int NW = NT / 64;
 };
 
 __device__ __forceinline__ float wave_sum(float x)
@@ -28,6 +31,18 @@ __device__ __forceinline__ float wave_sum(float x)
     return x;
 }
 
+typedef float f4 __attribute__((ext_vector_type(4)));
+typedef unsigned int u2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ f4 load4(const float *p) { return *reinterpret_cast<const f4 *>(p); }
+__device__ __forceinline__ f4 load4(const bf16_t *p)
+{
+    const u2 u = *reinterpret_cast<const u2 *>(p);
+    return f4{__uint_as_float(u[0] << 16), __uint_as_float(u[0] & 0xffff0000u),
+              __uint_as_float(u[1] << 16), __uint_as_float(u[1] & 0xffff0000u)};
+}
+
+// Thread t holds columns 4 (t % LR) .. + 3 of rows RPT (t / LR) .. + RPT - 1 of S; thread t < D
+// also holds z[t] and p[t].
 template <typename T, int D>
 __global__ __launch_bounds__((DC<D>::NT)) void k_decode(const T *__restrict__ Q,
                                                        const T *__restrict__ K,
@@ -36,71 +51,105 @@ __global__ __launch_bounds__((DC<D>::NT)) void k_decode(const T *__restrict__ Q,
                                                        float *__restrict__ state, int Tn,
                                                        size_t state_floats, float a, float b)
 {
-    constexpr int NT = DC<D>::NT, RG = DC<D>::RG, RPT = DC<D>::RPT;
-    __shared__ float qs[D], ks[D], vs[D], zs[D], part[RG][D], red[NT / 64], gsh;
-    const int bh = blockIdx.x, t = threadIdx.x, j = t % D, rg = t / D;
+    constexpr int LR = DC<D>::LR, RPT = DC<D>::RPT, NW = DC<D>::NW, NT = DC<D>::NT;
+    constexpr int NO = (D + NT - 1) / NT;  // output columns per thread of the final sums
+    // two buffers: a row's sums are read while the next row's are written
+    __shared__ __align__(16) float part[2][NW][D];
+    __shared__ float partz[2][NW];
+    const int bh = blockIdx.x, t = threadIdx.x, w = t / 64, j = 4 * (t % LR), r0 = RPT * (t / LR);
     float *st = state + (size_t)bh * state_floats;
-    float S[RPT];
+    f4 S[RPT];
+    float z[NO], p[NO];
 #pragma unroll
-    for (int i = 0; i < RPT; ++i) S[i] = st[(size_t)(rg + RG * i) * D + j];
-    if (t < D) zs[t] = st[D * D + t];
-    float pj = st[D * D + D + j];  // every row group keeps its own copy of p[j]
+    for (int i = 0; i < RPT; ++i) S[i] = load4(st + (size_t)(r0 + i) * D + j);
+#pragma unroll
+    for (int m = 0; m < NO; ++m) {
+        const int col = t + m * NT;
+        z[m] = col < D ? st[D * D + col] : 0.f;
+        p[m] = col < D ? st[D * D + D + col] : 0.f;
+    }
     float cnt = st[D * D + 2 * D];
     const size_t base = (size_t)bh * Tn * D;
     for (int tok = 0; tok < Tn; ++tok) {
-        __syncthreads();  // the previous row's reads of qs, ks, vs, part are done
-        if (t < D) {
-            const size_t e = base + (size_t)tok * D + t;
-            qs[t] = load_elem(Q, e);
-            const float kt = load_elem(K, e);
-            ks[t] = kt;
-            vs[t] = load_elem(V, e);
-            zs[t] += kt;  // the new row enters the sums before it is read out
+        const T *q = Q + base + (size_t)tok * D, *k = K + base + (size_t)tok * D,
+                *v = V + base + (size_t)tok * D;
+        const int buf = tok & 1;
+        const f4 v4 = load4(v + j);
+        f4 f = {0.f, 0.f, 0.f, 0.f};
+        float qz = 0.f;
+#pragma unroll
+        for (int i = 0; i < RPT; ++i) {  // the new row enters the sums before it is read out
+            const float ki = load_elem(k, r0 + i), qi = load_elem(q, r0 + i);
+            S[i] += ki * v4;
+            f += qi * S[i];
+            // D = 256: 64 registers of state, so the loads of q and k stay a few rows ahead
+            if (RPT > 8 && i % 4 == 3) __builtin_amdgcn_sched_barrier(0);
         }
+#pragma unroll
+        for (int m = 0; m < NO; ++m) {
+            const int col = t + m * NT;
+            if (col < D) {
+                z[m] += load_elem(k, col);
+                p[m] += load_elem(v, col);
+                qz += load_elem(q, col) * z[m];
+            }
+        }
+        qz = wave_sum(qz);
+#pragma unroll
+        for (int m = LR; m < 64; m <<= 1) {  // the row groups of this wave
+#pragma unroll
+            for (int e = 0; e < 4; ++e) f[e] += __shfl_xor(f[e], m);
+        }
+        if (t % 64 < LR) *reinterpret_cast<f4 *>(&part[buf][w][j]) = f;
+        if (t % 64 == 0) partz[buf][w] = qz;
         cnt += 1.f;
         __syncthreads();
-        // g = a count + b q . z
-        float s = 0.f;
-        for (int m = t; m < D; m += NT) s += qs[m] * zs[m];
-        s = wave_sum(s);
-        if (t % 64 == 0) red[t / 64] = s;
-        const float vj = vs[j];
-        pj += vj;
-        float f = 0.f;
 #pragma unroll
-        for (int i = 0; i < RPT; ++i) {
-            const int r = rg + RG * i;
-            S[i] += ks[r] * vj;
-            f += S[i] * qs[r];
-        }
-        part[rg][j] = f;
-        __syncthreads();
-        if (t == 0) {
-            float qz = 0.f;
-            for (int wv = 0; wv < NT / 64; ++wv) qz += red[wv];
-            gsh = a * cnt + b * qz;
-        }
-        __syncthreads();
-        if (t < D) {
-            float lin = 0.f;
+        for (int m = 0; m < NO; ++m) {
+            const int col = t + m * NT;
+            if (col < D) {
+                float lin = 0.f, qs = 0.f;
 #pragma unroll
-            for (int r = 0; r < RG; ++r) lin += part[r][t];
-            const float gv = gsh;
-            store_elem(O, base + (size_t)tok * D + t, (a * pj + b * lin) / gv);
-            if (t == 0 && G) G[(size_t)bh * Tn + tok] = gv;
+                for (int x = 0; x < NW; ++x) {
+                    lin += part[buf][x][col];
+                    qs += partz[buf][x];
+                }
+                const float gv = a * cnt + b * qs;  // g = a count + b q . z
+                store_elem(O, base + (size_t)tok * D + col, (a * p[m] + b * lin) / gv);
+                if (col == 0 && G) G[(size_t)bh * Tn + tok] = gv;
+            }
         }
     }
 #pragma unroll
-    for (int i = 0; i < RPT; ++i) st[(size_t)(rg + RG * i) * D + j] = S[i];
-    __syncthreads();
-    if (t < D) {
-        st[D * D + t] = zs[t];
-        st[D * D + D + t] = pj;  // t < D is row group 0, column t
+    for (int i = 0; i < RPT; ++i) *reinterpret_cast<f4 *>(st + (size_t)(r0 + i) * D + j) = S[i];
+#pragma unroll
+    for (int m = 0; m < NO; ++m) {
+        const int col = t + m * NT;
+        if (col < D) {
+            st[D * D + col] = z[m];
+            st[D * D + D + col] = p[m];
+        }
     }
+    __syncthreads();  // every thread has read the count
     if (t == 0) st[D * D + 2 * D] = cnt;
 }
 
-// state (+)= [S | z | p] totals left in slot 0 of every slice by the forward sums, count (+)= N
+// Sum of element e over the slots of a slice, in ascending order; eight loads in flight.
+__device__ __forceinline__ float sum_slots(const float *src, int e, int nseg, size_t slot_floats)
+{
+    float run = 0.f;
+    for (int s0 = 0; s0 < nseg; s0 += 8) {
+        float x[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) x[i] = s0 + i < nseg ? src[(size_t)(s0 + i) * slot_floats + e] : 0.f;
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+            if (s0 + i < nseg) run = s0 + i == 0 ? x[i] : run + x[i];
+    }
+    return run;
+}
+
+// state (+)= the sums of [S | z | p] over the slots of every slice, count (+)= N
 template <int DUMMY>
 __global__ __launch_bounds__(256) void k_state_from_totals(const float *__restrict__ ws,
                                                            float *__restrict__ state, int D,
@@ -112,12 +161,12 @@ __global__ __launch_bounds__(256) void k_state_from_totals(const float *__restri
     const float *src = ws + (size_t)bh * nseg * slot_floats;
     float *dst = state + (size_t)bh * state_floats;
     for (int e = blockIdx.y * 256 + threadIdx.x; e <= len; e += gridDim.y * 256) {
-        const float x = e < len ? src[e] : (float)N;
+        const float x = e < len ? sum_slots(src, e, nseg, slot_floats) : (float)N;
         dst[e] = accumulate ? dst[e] + x : x;
     }
 }
 
-// The same for D = 256 from the totals of the block problem (k block i, v block j) at D = 128:
+// The same for D = 256 from the slots of the block problem (k block i, v block j) at D = 128:
 // S block (i, j); z block i (taken when j = 0); p block j (when i = 0); the count once.
 __global__ __launch_bounds__(256) void k_state_block_from_totals(const float *__restrict__ ws,
                                                                  float *__restrict__ state,
@@ -133,15 +182,15 @@ __global__ __launch_bounds__(256) void k_state_block_from_totals(const float *__
         float x;
         int to;
         if (e < H * H) {
-            x = src[e];
+            x = sum_slots(src, e, nseg, slot_floats);
             to = (bi * H + e / H) * D + bj * H + e % H;
         } else if (e < H * H + H) {
             if (bj != 0) continue;
-            x = src[e];
+            x = sum_slots(src, e, nseg, slot_floats);
             to = D * D + bi * H + (e - H * H);
         } else if (e < len) {
             if (bi != 0) continue;
-            x = src[e];
+            x = sum_slots(src, e, nseg, slot_floats);
             to = D * D + D + bj * H + (e - H * H - H);
         } else {
             if (bi != 0 || bj != 0) continue;

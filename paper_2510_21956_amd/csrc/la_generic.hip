@@ -629,8 +629,6 @@ la_status totals_by_d(const Problem &pr, const Plan &pl, const void *Kv, const v
         case 128: k_fwd_state<T, 128><<<grid, block, 0, st>>>(k, v, ws, pr.N, pl.nseg, pl.nseg, pl.seg_len, pl.slot_floats, 0, pr.norm_qk); break;
         default: return LA_ERR_UNSUPPORTED;
     }
-    launch_scan_slots(ws, pr.BH, pl.nseg, pl.slot_floats, 0, pr.D * pr.D + 2 * pr.D, 2, 0,
-                      pl.nseg - 1, st);
     return launch_status();
 }
 }  // namespace

@@ -1018,7 +1018,6 @@ la_status run_totals(const Problem &pr, const Plan &pl, const void *K, const voi
     typedef typename Mode<MODE>::TIO TIO;
     ks_kv_state<MODE, D, false, LD><<<dim3(pr.BH * pl.nseg), dim3(4 * D), 0, st>>>(
         (const TIO *)K, (const TIO *)V, ws, pr.N, pl.nseg, pl.nseg, pl.map, pl.slot_floats, 0);
-    launch_scan_slots(ws, pr.BH, pl.nseg, pl.slot_floats, 0, D * D + 2 * D, 2, 0, pl.nseg - 1, st);
     return launch_status();
 }
 
