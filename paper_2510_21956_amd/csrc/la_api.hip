@@ -66,8 +66,9 @@ Plan make_plan(int B, int H, int N, int D, la_dtype dt, int causal, int is_backw
             if (seg_row(p.map, p.nseg - 1, p.nseg, N) >= N) p.map.cost_seg = 0;
         }
     }
-    const size_t DD = (size_t)D * D;
-    p.slot_floats = round_up(is_backward ? 2 * DD + 4 * D : DD + 2 * D, 64);
+    // D = 16 runs on the tiles of D = 32
+    const size_t SD = D == 16 ? 32 : D, DD = SD * SD;
+    p.slot_floats = round_up(is_backward ? 2 * DD + 4 * SD : DD + 2 * SD, 64);
     const size_t slots = (size_t)BH * p.nseg * p.slot_floats;
     p.delta_offset_floats = round_up(slots, 64);
     p.total_bytes = is_backward ? (p.delta_offset_floats + round_up((size_t)BH * N, 64)) * 4
@@ -146,6 +147,12 @@ static bool any_alias(const Range *ins, int nin, const Range *outs, int nout)
             if (overlap(outs[i], outs[j])) return true;
     }
     return false;
+}
+
+// D = 16 on the tiles of D = 32: the forward and backward passes (no hand-over buffer).
+static bool use_padded(const Problem &pr)
+{
+    return pr.D == 16 && !g_force_generic.load(std::memory_order_relaxed);
 }
 
 // la_debug_override can force the plain-ALU kernels (for A/B comparison and debugging).
@@ -279,7 +286,7 @@ static la_status forward_impl(const void *Q, const void *K, const void *V, void 
     }
     if (hipPeekAtLastError() != hipSuccess) return LA_ERR_LAUNCH;  // left pending, nothing enqueued
     la::Tracer tc(trace, (hipStream_t)hip_stream);
-    if (fast)
+    if (fast || la::use_padded(pr))
         return la::fast_forward(pr, pl, Q, K, V, O, G, (float *)workspace, sv,
                                 (hipStream_t)hip_stream, tc);
     if (D == 256)
@@ -341,7 +348,7 @@ static la_status backward_impl(const void *Q, const void *K, const void *V, cons
         char *wsb = (char *)workspace;
         void *o2 = wsb + rc.o_off;
         float *g2 = (float *)(wsb + rc.g_off);
-        const bool ffast = la::use_fast(pr, 0);
+        const bool ffast = la::use_fast(pr, 0) || la::use_padded(pr);
         s = ffast ? la::fast_forward(pr, pf, Q, K, V, o2, g2, (float *)(wsb + rc.fwd_ws_off),
                                      nullptr, st, tc)
             : D == 256
@@ -353,7 +360,8 @@ static la_status backward_impl(const void *Q, const void *K, const void *V, cons
         if (!O) O = o2;
         if (!G) G = g2;
     }
-    s = fast ? la::fast_backward(pr, pl, Q, K, V, O, G, dO, dQ, dK, dV, (float *)workspace, sv, st,
+    const bool planes = fast || la::use_padded(pr);
+    s = planes ? la::fast_backward(pr, pl, Q, K, V, O, G, dO, dQ, dK, dV, (float *)workspace, sv, st,
                                  tc)
         : D == 256
             ? la::backward_256(pr, pl, B, H, Q, K, V, O, G, dO, dQ, dK, dV, (float *)workspace, st,
@@ -362,7 +370,7 @@ static la_status backward_impl(const void *Q, const void *K, const void *V, cons
                                    tc);
     // the matrix-core kernels take dQ, dK through the backward of the normalisation before
     // they store them
-    if (s != LA_OK || !norm_qk || fast) return s;
+    if (s != LA_OK || !norm_qk || planes) return s;
     // the plain-ALU kernels left the gradients for the normalised rows: the same, in place
     s = la::project_rows(Q, dQ, T, D, dt, st);
     if (s != LA_OK) return s;

@@ -131,7 +131,7 @@ __device__ __forceinline__ void store_block(T *base, int ld, int col0, int rows_
     }
 }
 
-// One 16-row block of a gradient.  With LD != D (a block of D columns of rows LD wide) the
+// One 16-row block of a gradient.  With LD > D (a block of D columns of rows LD wide) the
 // gradient is the sum of two launches: fp32 tensors add in place (`add` in the second launch);
 // bf16 tensors keep the first launch's share in `part` (fp32, rows of D: early rows of a masked
 // pass are small differences of large shares) and the second launch adds it and rounds once.
@@ -140,7 +140,7 @@ __device__ __forceinline__ void store_grad_block(TIO *out, float *part, bool add
                                                  int rows_valid, int l, float x0, float x1,
                                                  float x2, float x3)
 {
-    if constexpr (LD == D)
+    if constexpr (LD <= D)
         store_block<TIO>(out, LD, col0, rows_valid, l, x0, x1, x2, x3);
     else if constexpr (sizeof(TIO) == 4)
         store_block<TIO>(out, LD, col0, rows_valid, l, x0, x1, x2, x3, add ? 1 : 0);

@@ -259,6 +259,7 @@ struct Chunk {
     static constexpr bool F32 = sizeof(TIO) == 4;
     static constexpr int PER_ROW = F32 ? D / 4 : D / 8;  // lanes that share a row
     static constexpr int NLD = F32 ? 2 : 1;              // 16-byte loads per thread
+    static constexpr int COLS = LD < D ? LD : D;         // columns there are; the others read as zeros
     u4v raw[NLD];
 
     static __device__ __forceinline__ int row(int k)
@@ -280,9 +281,10 @@ struct Chunk {
     {
         const long rows = (N - c0 < CR) ? N - c0 : CR;
         const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
-            const_cast<TIO *>(X + (size_t)c0 * LD), 0, (int)(((rows - 1) * LD + D) * sizeof(TIO)),
+            const_cast<TIO *>(X + (size_t)c0 * LD), 0, (int)(((rows - 1) * LD + COLS) * sizeof(TIO)),
             kBufferFlags);
-        const int off = (row(0) * LD + 4 * quad(0)) * (int)sizeof(TIO);
+        int off = (row(0) * LD + 4 * quad(0)) * (int)sizeof(TIO);
+        if (LD < D && 4 * quad(0) >= COLS) off = 1 << 30;  // out of range
 #pragma unroll
         for (int k = 0; k < NLD; ++k)
             raw[k] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, off + k * 16 * LD * (int)sizeof(TIO),

@@ -9,6 +9,8 @@
 //     the factors 1/|q|, 1/|k| go to the weight blocks, to the outputs and to the wave's own
 //     operand of the running sums' updates, which are fp32 in three planes here.
 //
+// Head size 16 runs on the kernels of D = 32 with columns 16 .. 31 zero (LD < D).
+//
 // A workgroup of D/16 waves handles one (slice, segment) in chunks of 32 rows; wave w owns
 // columns [16w, 16w+16) of the D x D running state, which stays in its accumulators for the
 // whole segment.  Output blocks are computed transposed (accumulator rows = output columns): a
@@ -88,13 +90,14 @@ __device__ __forceinline__ f4v own_product(const bf8v (&own)[LA], const bf8v (&p
     if constexpr (SWAP) return step_product<LB, LA>(p, own);
     else return step_product<LA, LB>(own, p);
 }
-// One 16-row block of a gradient; LD != D builds it up over two launches (store_grad_block).
+// One 16-row block of a gradient; LD > D builds it up over two launches (store_grad_block).
 template <bool SWAP, int D, int LD, typename TIO>
 __device__ __forceinline__ void store_grad(TIO *out, float *part, bool add, int w, int rows_valid, int l,
                                            f4v x)
 {
+    if (LD < D && w * 16 >= LD) return;  // columns that are not there
     if constexpr (SWAP)
-        store_cols_block(out, LD, w * 16, rows_valid, l % 16, l / 16, x, LD != D && add);
+        store_cols_block(out, LD, w * 16, rows_valid, l % 16, l / 16, x, LD > D && add);
     else
         store_grad_block<TIO, D, LD>(out, part, add, w * 16, rows_valid, l, x[0], x[1], x[2], x[3]);
 }
@@ -272,7 +275,7 @@ __global__ __launch_bounds__(4 * D, 2) void ks_kv_state(
 // Phase 3 (forward): Eq. fglast / div chunk by chunk.
 //   f = tril(a + b Q_c K_c^T) V_c + a 1 p^T + b Q_c S ;  g = rowsum(tril) + a n + b Q_c z
 //   then S += K_c^T V_c, z += sum k, p += sum v
-// LD != D: the call works on D columns of rows LD wide and is one of several launches that
+// LD > D: the call works on D columns of rows LD wide and is one of several launches that
 // build O up: xflags & XF_RAW leaves the numerator undivided in O and the launch's share of g
 // in G; xflags & XF_ACC adds the numerator that O holds and the share of g in Gin first.  bf16
 // tensors keep the undivided numerator in Fraw instead (fp32, B*H*N rows of D): O is rounded once.
@@ -287,7 +290,7 @@ __global__ __launch_bounds__(4 * D, 2) void ks_fwd_apply(
     typedef Mode<MODE> MD;
     typedef typename MD::TIO TIO;
     constexpr int LQ = MD::LQ, LV = MD::LV, LX = MD::LX;
-    constexpr bool RAW32 = LD != D && sizeof(TIO) == 2;
+    constexpr bool RAW32 = LD > D && sizeof(TIO) == 2;
     constexpr int NW = D / 16, NRB = D / 16, PL = Tile<D>::PLANE, WPL = Tile<32>::PLANE;
     constexpr int TS = CAUSAL ? 1 : 0;
     typedef Chunk<TIO, D, LD> CH;
@@ -414,7 +417,7 @@ __global__ __launch_bounds__(4 * D, 2) void ks_fwd_apply(
             if constexpr (CAUSAL) ps = psum[0][l] + (l >= 16 ? psum[1][l] : 0.f);
             float gv = b * qzs[l] + a * (CAUSAL ? (float)c0 : (float)N) + ps;
             const bool valid = l < (int)(row1 - c0);
-            if constexpr (LD != D) {
+            if constexpr (LD > D) {
                 if ((xflags & XF_ACC) && valid) gv += (Gin + (size_t)bh * N + c0)[l];
                 ginv[w][l] = (xflags & XF_RAW) ? 1.f : 1.f / gv;
             } else {
@@ -434,13 +437,14 @@ __global__ __launch_bounds__(4 * D, 2) void ks_fwd_apply(
                 });
             }
             const f4v y = (f + a * pacc) * ginv[w][m * 16 + c];
+            if (LD < D && w * 16 >= LD) break;  // columns that are not there
             const int nrows = (int)(row1 - c0) - m * 16;
             float *fr = RAW32 ? Fraw + ((size_t)bh * N + c0 + m * 16) * D : nullptr;
             if (RAW32 && (xflags & XF_RAW))
                 store_block<float>(fr, D, w * 16, nrows, l, y[0], y[1], y[2], y[3]);
             else
                 store_block<TIO>(Op + (size_t)(c0 + m * 16) * LD, LD, w * 16, nrows, l, y[0], y[1], y[2],
-                                 y[3], (LD != D && (xflags & XF_ACC)) ? 2 : 0, &ginv[w][m * 16], fr, D);
+                                 y[3], (LD > D && (xflags & XF_ACC)) ? 2 : 0, &ginv[w][m * 16], fr, D);
         }
         if constexpr (CAUSAL) {
             pacc += step_product<LV, 1>(vf, one);
@@ -480,7 +484,7 @@ __global__ __launch_bounds__(4 * D, 2) void ks_fwd_apply(
 //   dQ_c = diag(b / g) (tril(Cm') K_c + dO_c S^T - dprime z^T);  then S += K_c^T V_c, z += sum k
 //   R += (Q/g)_c^T dO_c,  u += sum dprime (q/g),  w += sum dO / g
 // The state is held transposed (rows j, columns r): the product contracts over j.
-// LD != D: xflags & 1 marks the second of the two launches that build dQ up.
+// LD > D: xflags & 1 marks the second of the two launches that build dQ up.
 // ---------------------------------------------------------------------------
 template <int MODE, int D, bool CAUSAL, int LD>
 __global__ __launch_bounds__(4 * D, 2) void ks_bwd_dq(
@@ -713,7 +717,7 @@ __global__ __launch_bounds__(4 * D, 2) void ks_bwd_dq(
 //   dV_c = tril(W)^T dO_c + a 1 w^T + b K_c R,          W_in = a / g_i + b (q_i/g_i) . k_n
 //   then R += (Q/g)_c^T dO_c, u += sum dprime (q/g), w += sum dO / g.
 // R is held twice: rows r x columns j for dV, rows j x columns r for dK.
-// LD != D: xflags & 2 (dK), & 4 (dV) mark the second of the two launches that build them up.
+// LD > D: xflags & 2 (dK), & 4 (dV) mark the second of the two launches that build them up.
 // ---------------------------------------------------------------------------
 template <int MODE, int D, bool CAUSAL, int LD>
 __global__ __launch_bounds__(4 * D, 2) void ks_bwd_dkv(
@@ -1030,17 +1034,21 @@ int mode_of(const Problem &pr)
 
 #define LA_BY_MODE(CALL)                                   \
     switch (mode_of(pr) * 1024 + pr.D + (ld == 256)) {     \
+        case P32 * 1024 + 16: return CALL(P32, 32, 16);    \
         case P32 * 1024 + 32: return CALL(P32, 32, 32);    \
         case P32 * 1024 + 64: return CALL(P32, 64, 64);    \
         case P32 * 1024 + 128: return CALL(P32, 128, 128); \
         case P32 * 1024 + 129: return CALL(P32, 128, 256); \
+        case N32 * 1024 + 16: return CALL(N32, 32, 16);    \
         case N32 * 1024 + 32: return CALL(N32, 32, 32);    \
         case N32 * 1024 + 64: return CALL(N32, 64, 64);    \
         case N32 * 1024 + 128: return CALL(N32, 128, 128); \
+        case P16 * 1024 + 16: return CALL(P16, 32, 16);    \
         case P16 * 1024 + 32: return CALL(P16, 32, 32);    \
         case P16 * 1024 + 64: return CALL(P16, 64, 64);    \
         case P16 * 1024 + 128: return CALL(P16, 128, 128); \
         case P16 * 1024 + 129: return CALL(P16, 128, 256); \
+        case N16 * 1024 + 16: return CALL(N16, 32, 16);    \
         case N16 * 1024 + 32: return CALL(N16, 32, 32);    \
         case N16 * 1024 + 64: return CALL(N16, 64, 64);    \
         case N16 * 1024 + 128: return CALL(N16, 128, 128); \
