@@ -130,23 +130,35 @@ def la_saved_state_bytes(B, H, N, D, dt, causal):
     return int(load_library().la_saved_state_bytes(B, H, N, D, dt, int(bool(causal))))
 
 
+# A small call (a decode step, a toy layer) costs more in this file than on the GPU, so what is
+# done per tensor and per call is kept to integers: device indices, raw stream handles and
+# addresses, which ctypes converts by the declared argument types.
+
 def _check_tensors(ref, *ts):
+    dev = ref.get_device()
     for t in ts:
         if t is None:
             continue
         if not t.is_cuda or not t.is_contiguous():
             raise ValueError("tensors must be contiguous device tensors")
-        if t.device != ref.device:
+        if t.get_device() != dev:
             raise ValueError("tensors must live on one device")
 
 
-def _stream_ptr(stream, device):
-    s = torch.cuda.current_stream(device) if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
+def _stream_ptr(stream, ref):
+    """hipStream_t of ``stream``, or of the current stream of ref's device."""
+    if stream is not None:
+        return stream.cuda_stream
+    if _raw_stream is not None:
+        return _raw_stream(ref.get_device())
+    return torch.cuda.current_stream(ref.device).cuda_stream
 
 
 def _ptr(t):
-    return ctypes.c_void_p(None if t is None else t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def la_forward(Q, K, V, O, G, a, b, causal, workspace, stream=None):
@@ -174,7 +186,7 @@ def la_forward_static(Q, K, V, O, G, a, b, causal, stream=None):
         raise ValueError("G must be [B, H, N] float32 (or None)")
     rc = load_library().la_forward_static(_ptr(Q), _ptr(K), _ptr(V), _ptr(O), _ptr(G), B, H, N, D,
                                           float(a), float(b), int(bool(causal)), _dtype_code(Q),
-                                          _stream_ptr(stream, Q.device))
+                                          _stream_ptr(stream, Q))
     if rc != 0:
         raise LaError(rc, "la_forward_static")
 
@@ -192,7 +204,7 @@ def la_forward_save(Q, K, V, O, G, a, b, causal, workspace, saved, stream=None, 
 
 def _saved_args(saved, ref):
     if saved is None:
-        return ctypes.c_void_p(None), 0
+        return None, 0
     _check_tensors(ref, saved)
     return _ptr(saved), saved.numel() * saved.element_size()
 
@@ -200,9 +212,10 @@ def _saved_args(saved, ref):
 def _forward(Q, K, V, O, G, a, b, causal, workspace, saved, stream, trace, save):
     if Q.dim() != 4:
         raise ValueError("Q must be [B, H, N, D]")
-    B, H, N, D = Q.shape
+    shape = Q.shape
+    B, H, N, D = shape
     _check_tensors(Q, K, V, O, G, workspace)
-    if K.shape != Q.shape or V.shape != Q.shape or O.shape != Q.shape:
+    if K.shape != shape or V.shape != shape or O.shape != shape:
         raise ValueError("shape mismatch")
     if not (K.dtype == V.dtype == O.dtype == Q.dtype):
         raise TypeError("dtype mismatch")
@@ -214,15 +227,15 @@ def _forward(Q, K, V, O, G, a, b, causal, workspace, saved, stream, trace, save)
             workspace.numel() * workspace.element_size())
     tr = ctypes.byref(trace) if trace is not None else None
     if save == "qknorm":
-        rc = lib.la_forward_qknorm(*head, _stream_ptr(stream, Q.device), tr)
+        rc = lib.la_forward_qknorm(*head, _stream_ptr(stream, Q), tr)
     elif save == "qknorm_save":
         sp, sb = _saved_args(saved, Q)
-        rc = lib.la_forward_qknorm_save(*head, sp, sb, _stream_ptr(stream, Q.device), tr)
+        rc = lib.la_forward_qknorm_save(*head, sp, sb, _stream_ptr(stream, Q), tr)
     elif save:
         sp, sb = _saved_args(saved, Q)
-        rc = lib.la_forward_save(*head, sp, sb, _stream_ptr(stream, Q.device), tr)
+        rc = lib.la_forward_save(*head, sp, sb, _stream_ptr(stream, Q), tr)
     else:
-        rc = lib.la_forward_traced(*head, _stream_ptr(stream, Q.device), tr)
+        rc = lib.la_forward_traced(*head, _stream_ptr(stream, Q), tr)
     if rc != 0:
         raise LaError(rc, "la_forward_save" if save else "la_forward")
 
@@ -267,15 +280,15 @@ def _backward(Q, K, V, O, G, dO, dQ, dK, dV, a, b, causal, workspace, saved, str
             workspace.numel() * workspace.element_size())
     tr = ctypes.byref(trace) if trace is not None else None
     if use_saved == "qknorm":
-        rc = lib.la_backward_qknorm(*head, _stream_ptr(stream, Q.device), tr)
+        rc = lib.la_backward_qknorm(*head, _stream_ptr(stream, Q), tr)
     elif use_saved == "qknorm_save":
         sp, sb = _saved_args(saved, Q)
-        rc = lib.la_backward_qknorm_saved(*head, sp, sb, _stream_ptr(stream, Q.device), tr)
+        rc = lib.la_backward_qknorm_saved(*head, sp, sb, _stream_ptr(stream, Q), tr)
     elif use_saved:
         sp, sb = _saved_args(saved, Q)
-        rc = lib.la_backward_saved(*head, sp, sb, _stream_ptr(stream, Q.device), tr)
+        rc = lib.la_backward_saved(*head, sp, sb, _stream_ptr(stream, Q), tr)
     else:
-        rc = lib.la_backward_traced(*head, _stream_ptr(stream, Q.device), tr)
+        rc = lib.la_backward_traced(*head, _stream_ptr(stream, Q), tr)
     if rc != 0:
         raise LaError(rc, "la_backward_saved" if use_saved else "la_backward")
 
@@ -289,9 +302,10 @@ def la_decode_step(q, k, v, o, g, state, a, b, stream=None):
     state: float32 device tensor of la_decode_state_bytes(B, H, D) bytes, updated in place."""
     if q.dim() != 4:
         raise ValueError("q must be [B, H, T, D]")
-    B, H, T, D = q.shape
+    shape = q.shape
+    B, H, T, D = shape
     _check_tensors(q, k, v, o, g, state)
-    if k.shape != q.shape or v.shape != q.shape or o.shape != q.shape:
+    if k.shape != shape or v.shape != shape or o.shape != shape:
         raise ValueError("shape mismatch")
     if not (k.dtype == v.dtype == o.dtype == q.dtype) or state.dtype != torch.float32:
         raise TypeError("dtype mismatch")
@@ -299,7 +313,7 @@ def la_decode_step(q, k, v, o, g, state, a, b, stream=None):
         raise ValueError("g must be [B, H, T] float32 (or None)")
     rc = load_library().la_decode_step(_ptr(q), _ptr(k), _ptr(v), _ptr(o), _ptr(g), _ptr(state),
                                        state.numel() * 4, B, H, T, D, float(a), float(b),
-                                       _dtype_code(q), _stream_ptr(stream, q.device))
+                                       _dtype_code(q), _stream_ptr(stream, q))
     if rc != 0:
         raise LaError(rc, "la_decode_step")
 
@@ -316,7 +330,7 @@ def la_decode_prefill(K, V, state, accumulate, workspace, stream=None):
                                           N, D, _dtype_code(K), int(bool(accumulate)),
                                           _ptr(workspace),
                                           workspace.numel() * workspace.element_size(),
-                                          _stream_ptr(stream, K.device))
+                                          _stream_ptr(stream, K))
     if rc != 0:
         raise LaError(rc, "la_decode_prefill")
 
@@ -338,7 +352,7 @@ def la_backward_ab(Q, K, V, O, G, dO, dab, a, b, causal, workspace, stream=None)
                                        _ptr(dab), B, H, N, D, float(a), float(b),
                                        int(bool(causal)), _dtype_code(Q), _ptr(workspace),
                                        workspace.numel() * workspace.element_size(),
-                                       _stream_ptr(stream, Q.device))
+                                       _stream_ptr(stream, Q))
     if rc != 0:
         raise LaError(rc, "la_backward_ab")
 

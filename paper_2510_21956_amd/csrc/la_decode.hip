@@ -109,7 +109,7 @@ __global__ __launch_bounds__((DC<D>::NT)) void k_decode(const T *__restrict__ Q,
             const int col = t + m * NT;
             if (col < D) {
                 float lin = 0.f, qs = 0.f;
-#pragma unroll
+#pragma unroll 4
                 for (int x = 0; x < NW; ++x) {
                     lin += part[buf][x][col];
                     qs += partz[buf][x];
