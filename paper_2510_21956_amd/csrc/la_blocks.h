@@ -30,6 +30,17 @@ __device__ __forceinline__ bf4v to_bf4(f4v x)
 }
 __device__ __forceinline__ f4v bf4_to_float(bf4v x) { return __builtin_convertvector(x, f4v); }
 
+// Workgroup barrier after which every wave sees what the others wrote to LDS.  The wait is spelt
+// out: where the barrier stands at the top of a loop the compiler has left out the one that
+// __syncthreads() implies after LDS writes at the end of the loop body (seen in the listings of
+// 60 of these kernels; with it missing, two runs on the same inputs differed once).
+// 0xc07f: lgkmcnt(0), the other counters untouched.
+__device__ __forceinline__ void block_sync()
+{
+    __builtin_amdgcn_s_waitcnt(0xc07f);
+    __syncthreads();
+}
+
 // x[c0 + r] of a per-row float array of N entries (c0 < N, r < 64); 0 beyond the end.
 __device__ __forceinline__ float load_row_float(const float *x, long c0, int N, int r)
 {
@@ -77,6 +88,14 @@ struct Blk {
     __device__ __forceinline__ void set(int i, float x) { v[i] = x; }
 };
 
+// Rows of a 16-row block that exist.  The clamp is a vector instruction whatever its operand; its
+// result is named uniform, or every store whose descriptor it goes into becomes a loop over
+// the lanes' descriptors.
+__device__ __forceinline__ int valid_rows(int n)
+{
+    return __builtin_amdgcn_readfirstlane(n < 0 ? 0 : (n > 16 ? 16 : n));
+}
+
 // Store the wave's 16 x 16 output block.  On entry lane (c, g) holds columns col0 + 4g..4g+3
 // of block row c.  Neighbouring lanes would write to different rows, which the memory
 // pipeline cannot merge, so the values are first exchanged between lanes (no memory
@@ -97,7 +116,7 @@ __device__ __forceinline__ void store_block(T *base, int ld, int col0, int rows_
 {
     const int src = 16 * (l % 4) + l / 4;  // lane that holds (row l/4, column quad l%4)
     const int row = l / 4, cq = l % 4;
-    const int nrows = rows_valid < 0 ? 0 : (rows_valid > 16 ? 16 : rows_valid);
+    const int nrows = valid_rows(rows_valid);
     const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
         base, 0, nrows * ld * (int)sizeof(T), kBufferFlags);
     const int off = (row * ld + col0 + 4 * cq) * (int)sizeof(T);
@@ -166,7 +185,7 @@ __device__ __forceinline__ void project_blocks(float (&x)[NBK][4], const float (
         s = reduce_lane_groups(s);
         if (g == 0) dots[w * C + m * 16 + c] = s;
     }
-    __syncthreads();
+    block_sync();
 #pragma unroll
     for (int m = 0; m < NBK; ++m) {
         float dot = 0.f;

@@ -527,7 +527,7 @@ __device__ __forceinline__ void rank_update(Blk (&st)[D / 16], const __bf16 *at,
 __device__ __forceinline__ void store_cols_block(float *base, int ld, int col0, int rows_valid, int c,
                                                  int g, f4v x, bool add = false)
 {
-    const int nrows = rows_valid < 0 ? 0 : (rows_valid > 16 ? 16 : rows_valid);
+    const int nrows = valid_rows(rows_valid);
     const __amdgpu_buffer_rsrc_t rsrc =
         __builtin_amdgcn_make_buffer_rsrc(base, 0, nrows * ld * 4, kBufferFlags);
     const int off = (4 * g * ld + col0 + c) * 4;
@@ -547,7 +547,7 @@ __device__ __forceinline__ void store_cols_block(float *base, int ld, int col0, 
 __device__ __forceinline__ void store_cols_block(__bf16 *base, int ld, int col0, int rows_valid, int c,
                                                  int g, f4v x, bool = false)
 {
-    const int nrows = rows_valid < 0 ? 0 : (rows_valid > 16 ? 16 : rows_valid);
+    const int nrows = valid_rows(rows_valid);
     const __amdgpu_buffer_rsrc_t rsrc =
         __builtin_amdgcn_make_buffer_rsrc(base, 0, nrows * ld * 2, kBufferFlags);
     const bool odd = c & 1;
@@ -579,7 +579,7 @@ __device__ __forceinline__ void project_cols(f4v (&x)[2], const f4v (&xh)[2], fl
         for (int e = 0; e < 4; ++e) s[e] = reduce_adjacent<16>(x[m][e] * xh[m][e]);
         if (c == 0) *reinterpret_cast<f4v *>(dots + w * CR + m * 16 + 4 * g) = s;
     }
-    __syncthreads();
+    block_sync();
 #pragma unroll
     for (int m = 0; m < 2; ++m) {
         f4v dot = {0.f, 0.f, 0.f, 0.f};

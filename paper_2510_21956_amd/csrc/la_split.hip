@@ -219,10 +219,10 @@ __global__ __launch_bounds__(4 * D, 2) void ks_kv_state(
         sets[i].v.load(Vp, min(row0 + i * CR, c_last), N);
     }
     auto chunk = [&](long c0, Set &cur) __attribute__((always_inline)) {
-        __syncthreads();
+        block_sync();
         stage<MD::NORM, false, LQ>(cur.k, Kt, MD::RN ? ik : nullptr);
         cur.v.template store<false, LV>(Vt);
-        __syncthreads();
+        block_sync();
         const long cn = min(c0 + MD::DEPTH * CR, c_last);
         cur.k.load(Kp, cn, N);
         cur.v.load(Vp, cn, N);
@@ -357,7 +357,7 @@ __global__ __launch_bounds__(4 * D, 2) void ks_fwd_apply(
     }
     auto chunk = [&](long c0, Set &cur) __attribute__((always_inline)) {
         const bool lo_on = c0 < sm.lo_rows;  // second plane of the intermediates: early rows
-        __syncthreads();  // every wave is done with the previous chunk's tiles; zs is written
+        block_sync();  // every wave is done with the previous chunk's tiles; zs is written
         {
             f4v x[2] = {cur.q.value(0), cur.q.value(1)};
             if constexpr (MD::NORM) normalise_quads<CH>(x, MD::RN ? iq : nullptr);
@@ -377,7 +377,7 @@ __global__ __launch_bounds__(4 * D, 2) void ks_fwd_apply(
             stage<MD::NORM, false, LQ>(cur.k, Kt, MD::RN ? ik : nullptr);
             cur.v.template store<false, LV>(Vt);
         }
-        __syncthreads();
+        block_sync();
         const long cn = min(c0 + MD::DEPTH * CR, c_last);
         cur.q.load(Qp, cn, N);
 
@@ -409,7 +409,7 @@ __global__ __launch_bounds__(4 * D, 2) void ks_fwd_apply(
             load_cols<D, LV>(vf, Vt, ln.local(ln.col), w);
             cur.v.load(Vp, cn, N);
         }
-        __syncthreads();
+        block_sync();
 
         // ---- phase B: denominators; V^T P^T on top, divide, store ----
         if (l < CR) {
@@ -577,7 +577,7 @@ __global__ __launch_bounds__(4 * D, 2) void ks_bwd_dq(
     post_factors(row0, sets[0].g, 0);
     // nxt: the set that holds the chunk after this one
     auto chunk = [&](long c0, Set &cur, Set &nxt, int par) __attribute__((always_inline)) {
-        __syncthreads();
+        block_sync();
         const float *rs = rsb[par];
         const bool lo_on = c0 < sm.lo_rows;  // second plane of the intermediates: early rows
         if (need_Q) stage<MD::NORM, false, LQ>(cur.q, Qt, PROJ ? qinv : nullptr, QT ? rs : nullptr);
@@ -603,7 +603,7 @@ __global__ __launch_bounds__(4 * D, 2) void ks_bwd_dq(
             cur.v.template store<false, LV>(Vt);
             stage<MD::NORM, false, LQ>(cur.k, Kt, MD::RN ? ik : nullptr);
         }
-        __syncthreads();
+        block_sync();
         const long cn = min(c0 + MD::DEPTH * CR, c_last);
         cur.g = load_row_float(Gp, cn, N, t % CR);
         cur.d.load(dOp, cn, N);
@@ -634,7 +634,7 @@ __global__ __launch_bounds__(4 * D, 2) void ks_bwd_dq(
         if constexpr (CAUSAL) {
             load_cols<D, LQ>(kf, Kt, ln.local(ln.col), w);
             cur.k.load(Kp, cn, N);
-            __syncthreads();
+            block_sync();
         }
 
         // ---- phase B: K^T Cm'^T on top, scale, store ----
@@ -816,7 +816,7 @@ __global__ __launch_bounds__(4 * D, 2) void ks_bwd_dkv(
         const long c0 = row0 + ci * CR;
         const float *rs = rsb[par], *dl = dlb[par];
         const bool lo_on = c0 < sm.lo_rows;  // second plane of the intermediates: early rows
-        __syncthreads();
+        block_sync();
         stage<MD::NORM, true, LQ>(cur.k, Kt, PROJ ? kinv : nullptr);
         cur.v.template store<true, LV>(Vt);
         if constexpr (CAUSAL) {
@@ -827,7 +827,7 @@ __global__ __launch_bounds__(4 * D, 2) void ks_bwd_dkv(
             }
             cur.d.template store<false, LV>(dOt);
         }
-        __syncthreads();
+        block_sync();
         const long cn = row0 + max(ci - MD::DEPTH, 0L) * CR;
         cur.k.load(Kp, cn, N);
         cur.v.load(Vp, cn, N);
@@ -866,7 +866,7 @@ __global__ __launch_bounds__(4 * D, 2) void ks_bwd_dkv(
         with_planes<LX>(lo_on, [&](auto n) { state_product<D, n.value, LV, SWAP>(kh, kl, Rb, Vt, ln); });
         if constexpr (CAUSAL) {
             cur.q.load(Qp, cn, N);
-            __syncthreads();
+            block_sync();
         }
 
         // ---- phase B ----

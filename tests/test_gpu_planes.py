@@ -1,0 +1,108 @@
+"""The plane-split matrix-core kernels at the sizes where they can go wrong: chunk and segment
+edges, every tile form, the padded head size, exact scaling, non-finite inputs."""
+import numpy as np
+import pytest
+import torch
+
+from la_testlib import TOL, excess, run_gpu, scratch, to_f64, upload_case
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def la():
+    import paper_2510_21956_amd as la
+    la.load_library()
+    return la
+
+
+
+def _run_qknorm(la, dev, a, b, causal):
+    Q, K, V, dO = dev["Q"], dev["K"], dev["V"], dev["dO"]
+    B, H, N, D = Q.shape
+    dt = la.LA_F32 if Q.dtype == torch.float32 else la.LA_BF16
+    O, G = torch.empty_like(Q), torch.empty((B, H, N), device="cuda")
+    dQ, dK, dV = torch.empty_like(Q), torch.empty_like(Q), torch.empty_like(Q)
+    la.la_forward_qknorm(Q, K, V, O, G, a, b, causal,
+                         scratch(la.la_workspace_bytes(B, H, N, D, dt, causal, 0), "cuda"))
+    la.la_backward_qknorm(Q, K, V, O, G, dO, dQ, dK, dV, a, b, causal,
+                          scratch(la.la_workspace_bytes(B, H, N, D, dt, causal, 1), "cuda"))
+    return O, G, dQ, dK, dV
+
+
+# one row, either side of a chunk (32), of a segment of two chunks (64) and of three segments
+@pytest.mark.parametrize("N", [1, 31, 33, 64, 65, 161])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("D", [16, 32, 64, 128])
+def test_edges_against_plain_alu(la, D, dtype, N):
+    """Every output against the plain-ALU kernels on the same inputs, masked and not, plain and
+    normalising; the tolerance is the parity tests' own (twice, as both sides may use it up)."""
+    dev, _ = upload_case(1, 2, N, D, dtype, 4200 + D + N, [0, 1])
+    for causal in (True, False):
+        for run in (run_gpu, _run_qknorm):
+            try:
+                la.la_debug_override(64, 0)
+                got = run(la, dev, 1.0, 0.5, causal)
+                la.la_debug_override(64, 1)
+                want = run(la, dev, 1.0, 0.5, causal)
+            finally:
+                la.la_debug_override(0, 0)
+            for name, x, y in zip(("O", "G", "dQ", "dK", "dV"), got, want):
+                # N = 1: dQ = dK = 0 exactly; rounding noise at the scale of V, dO ~ 1
+                floor = 2 * TOL[dtype] if N == 1 and name in ("dQ", "dK") else 0.0
+                tol = 2 * (TOL["f32"] if name == "G" else TOL[dtype])
+                if dtype == "bf16" and name in ("dQ", "dK"):
+                    # each side's backward pass reads its own O, rounded to bf16: that rounding
+                    # alone moves the early rows by up to 1.9 times the tolerance
+                    tol *= 2
+                e = excess(to_f64(x), to_f64(y), tol, floor)
+                assert e <= 1.0, (D, dtype, N, causal, run.__name__, name, e)
+
+
+@pytest.mark.parametrize("D", [64, 128])
+def test_fp32_is_fp32(la, oracle_mod, D):
+    """Six bf16 products a float product keep 24 bits: the 2-norm error against 64 bits stays at
+    a few roundings of the running sums (N / 32 = 64 additions, sqrt(64) 2^-25 = 2.4e-7)."""
+    N, slices = 2048, [0, 1]
+    dev, ref = upload_case(1, 2, N, D, "f32", 77 + D, slices)
+    O, G, dQ, dK, dV = run_gpu(la, dev, 1.0, 0.5, True)
+    Or, Gr = oracle_mod.forward_rec(ref["Q"], ref["K"], ref["V"], 1.0, 0.5, True)
+    want = (Or, Gr) + tuple(oracle_mod.backward_rec(ref["Q"], ref["K"], ref["V"], Or, Gr, ref["dO"],
+                                                    1.0, 0.5, True))
+    for name, x, y in zip(("O", "G", "dQ", "dK", "dV"), (O, G, dQ, dK, dV), want):
+        x = to_f64(x).reshape(y.shape)
+        e = np.linalg.norm(x - y) / np.linalg.norm(y)
+        assert e <= 2.4e-7, (name, e)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_powers_of_two_scale_exactly(la, dtype):
+    """V and dO enter linearly and every plane scales with its value, so a power of two goes
+    through all kernels without touching a bit."""
+    dev, _ = upload_case(1, 2, 200, 64, dtype, 9, [0, 1])
+    base = run_gpu(la, dev, 1.0, 0.5, True)
+    for p in (-60, 60):
+        s = 2.0 ** p
+        d2 = dict(dev)
+        d2["V"] = dev["V"] * s
+        O, _, _, _, _ = run_gpu(la, d2, 1.0, 0.5, True)
+        assert torch.equal(O, base[0] * s), ("O", p)
+        d3 = dict(dev)
+        d3["dO"] = dev["dO"] * s
+        got = run_gpu(la, d3, 1.0, 0.5, True)
+        for name, x, y in zip(("dQ", "dK", "dV"), got[2:], base[2:]):
+            assert torch.equal(x, y * s), (name, p)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("D", [16, 64, 128])
+def test_nonfinite_stays_in_its_column(la, D, dtype):
+    """An infinity in one column of V reaches no other column of O."""
+    dev, _ = upload_case(1, 1, 150, D, dtype, 31, [0])
+    clean = run_gpu(la, dev, 1.0, 0.5, True)[0]
+    V = dev["V"].clone()
+    V[0, 0, 40, 5] = float("inf")
+    O = run_gpu(la, dict(dev, V=V), 1.0, 0.5, True)[0]
+    keep = [j for j in range(D) if j != 5]
+    assert torch.equal(O[..., keep], clean[..., keep])
+    assert not torch.isfinite(O[0, 0, 40:, 5].float()).any()
