@@ -30,7 +30,7 @@ static bool supported_d(int D) { return D == 16 || D == 32 || D == 64 || D == 12
 // next to the rows it covers (a sixth of their bytes at the shortest: short sequences in few
 // slices would otherwise leave most of the chip idle).  la_debug_override can force a length
 // (rounded up to 64).
-Plan make_plan(int B, int H, int N, int D, la_dtype dt, int causal, int is_backward)
+Plan make_plan(int B, int H, int N, int D, la_dtype dt, int causal, int is_backward, bool pad16)
 {
     Plan p;
     const long BH = (long)B * H;
@@ -66,8 +66,8 @@ Plan make_plan(int B, int H, int N, int D, la_dtype dt, int causal, int is_backw
             if (seg_row(p.map, p.nseg - 1, p.nseg, N) >= N) p.map.cost_seg = 0;
         }
     }
-    // D = 16 runs on the tiles of D = 32
-    const size_t SD = D == 16 ? 32 : D, DD = SD * SD;
+    // D = 16 runs on the tiles of D = 32 (pad16), or on the plain-ALU kernels
+    const size_t SD = D == 16 && pad16 ? 32 : D, DD = SD * SD;
     p.slot_floats = round_up(is_backward ? 2 * DD + 4 * SD : DD + 2 * SD, 64);
     const size_t slots = (size_t)BH * p.nseg * p.slot_floats;
     p.delta_offset_floats = round_up(slots, 64);
@@ -254,7 +254,7 @@ static la_status forward_impl(const void *Q, const void *K, const void *V, void 
                               int B, int H, int N, int D, float a, float b, int causal,
                               la_dtype dt, void *workspace, size_t workspace_bytes, bool save,
                               void *saved, size_t saved_bytes, void *hip_stream, la_trace *trace,
-                              int norm_qk = 0)
+                              int norm_qk = 0, bool pad16 = true)
 {
     la_status s = la::check_shape(B, H, N, D, dt);
     if (s != LA_OK) return s;
@@ -263,7 +263,7 @@ static la_status forward_impl(const void *Q, const void *K, const void *V, void 
     if (!la::aligned16(Q) || !la::aligned16(K) || !la::aligned16(V) || !la::aligned16(O) ||
         !la::aligned16(G))
         return LA_ERR_ALIGN;
-    la::Plan pl = la::make_plan(B, H, N, D, dt, causal, 0);
+    la::Plan pl = la::make_plan(B, H, N, D, dt, causal, 0, pad16);
     if (!la::grid_ok(B, H, pl)) return LA_ERR_SHAPE;
     if (!workspace || workspace_bytes < pl.total_bytes || (((uintptr_t)workspace) & 255u))
         return LA_ERR_WORKSPACE;
@@ -286,7 +286,7 @@ static la_status forward_impl(const void *Q, const void *K, const void *V, void 
     }
     if (hipPeekAtLastError() != hipSuccess) return LA_ERR_LAUNCH;  // left pending, nothing enqueued
     la::Tracer tc(trace, (hipStream_t)hip_stream);
-    if (fast || la::use_padded(pr))
+    if (fast || (pad16 && la::use_padded(pr)))
         return la::fast_forward(pr, pl, Q, K, V, O, G, (float *)workspace, sv,
                                 (hipStream_t)hip_stream, tc);
     if (D == 256)
@@ -403,15 +403,22 @@ la_status la_forward_static(const void *Q, const void *K, const void *V, void *O
     la_status s = la::check_shape(B, H, N, D, dt);
     if (s != LA_OK) return s;
     if (!Q || !K || !V || !O) return LA_ERR_NULL;
-    const la::Plan pl = la::make_plan(B, H, N, D, dt, causal, 0);
+    la::Plan pl = la::make_plan(B, H, N, D, dt, causal, 0);
     if (!la::grid_ok(B, H, pl)) return LA_ERR_SHAPE;
+    // Head size 16 in thousands of slices: the states of the padded tiles, four times the size,
+    // may not fit where those of the plain-ALU kernels do.
+    bool pad16 = true;
+    if (D == 16 && pl.total_bytes > (size_t)LA_STATIC_SCRATCH_BYTES) {
+        pad16 = false;
+        pl = la::make_plan(B, H, N, D, dt, causal, 0, pad16);
+    }
     if (pl.total_bytes > (size_t)LA_STATIC_SCRATCH_BYTES) return LA_ERR_WORKSPACE;
     void *ws = static_scratch();
     if (!ws) return LA_ERR_LAUNCH;
     // nothing in the forward workspace has to start at zero: every slot that is read has
     // been written by this call's own kernels first
     return forward_impl(Q, K, V, O, G, B, H, N, D, a, b, causal, dt, ws, LA_STATIC_SCRATCH_BYTES,
-                        false, nullptr, 0, hip_stream, nullptr);
+                        false, nullptr, 0, hip_stream, nullptr, 0, pad16);
 }
 
 la_status la_backward_ab(const void *Q, const void *K, const void *V, const void *O,

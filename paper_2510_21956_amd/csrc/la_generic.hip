@@ -1,7 +1,7 @@
 // Generic linear-attention kernels: plain fp32 ALU arithmetic on LDS tiles, any
-// supported D and either I/O type.  They serve the head sizes and cases the
-// matrix-core kernels do not cover, and they define the chunk algebra the fast
-// kernels follow.
+// supported D and either I/O type.  They serve la_backward_ab, la_decode_prefill and (thousands
+// of slices) la_forward_static at D = 16 and the test hook, and they define the chunk algebra
+// the matrix-core kernels follow.
 //
 // One workgroup handles one (slice, segment).  A segment is processed in
 // chunks of C rows; the running sums of Eq. xy / Eq. endd live in LDS for the

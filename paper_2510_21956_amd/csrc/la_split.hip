@@ -25,6 +25,16 @@
 // so no scaled copy of dO is kept next to dO itself.  With one-plane tiles, which must stay
 // exact, the weight blocks carry the 1/g, and the wave's own 32 x 16 operand of R's update is
 // scaled in registers.
+//
+// What bounds them (counters of the masked kernels).  fp32: the matrix pipe, the vector ALU
+// (splitting inputs and states) and LDS reads take 30 to 45 % of the clocks each and overlap
+// only in part, two waves a SIMD: 64 slices of 10^4 rows, D = 128, forward / ascending /
+// descending sweep 411 / 543 / 719 us against 489 / 646 / 863 us on the fp32 matrix pipe; D = 64,
+// 64 slices of 4096 rows, 70 / 91 / 113 against 79 / 98 / 110.  bf16, D = 128: memory, with 40 KB
+// in flight per CU, and the vector ALU (43 % in the descending sweep): 128 slices of 2048 rows
+// 63 / 85 / 105 us against 65 / 97 / 100 on kernels with chunks of 64 rows and two tiles a tensor;
+// D = 64, 36 slices of 5003 rows, with two workgroups a CU instead of one, 28 / 33 / 39 against
+// 41 / 51 / 56.  bf16 with normalised rows: 104 / 151 / 192 against 221 / 316 / 402 on fp32 tiles.
 #include "la_planes.h"
 
 namespace la {
@@ -160,10 +170,8 @@ __device__ __forceinline__ void factor_frag(bf8v (&o)[3], const float *r, int g)
                   *reinterpret_cast<const f4v *>(r + 16 + 4 * g), o);
 }
 
-// ---------------------------------------------------------------------------
-// Phase 1: per-segment S = sum k v^T, z = sum k, p = sum v (Eq. xy without the factors), to
-// slot `seg + slot_shift` as [S | z | p], or [S^T | z] (TRANSPOSED) for the backward pass.
-// ---------------------------------------------------------------------------
+// One tensor's chunk into its tile: normalised (NORM, fp32) and times scale[row], if given, on
+// the way.  1 / |row| goes to inv_out.
 template <bool NORM, bool OP, int L, typename CH>
 __device__ __forceinline__ void stage(const CH &ch, __bf16 *tile, float *inv_out = nullptr,
                                       const float *scale = nullptr)
@@ -185,10 +193,14 @@ __device__ __forceinline__ void stage(const CH &ch, __bf16 *tile, float *inv_out
     }
 }
 
+// ---------------------------------------------------------------------------
+// Phase 1: per-segment S = sum k v^T, z = sum k, p = sum v (Eq. xy without the factors), to
+// slot `seg + slot_shift` as [S | z | p], or [S^T | z] (TRANSPOSED) for the backward pass.
+// ---------------------------------------------------------------------------
 template <int MODE, int D, bool TRANSPOSED, int LD>
 __global__ __launch_bounds__(4 * D, 2) void ks_kv_state(
-    const typename Mode<MODE>::TIO *__restrict__ K, const typename Mode<MODE>::TIO *__restrict__ V, float *__restrict__ ws, int N, int nseg,
-    int nseg_run, SegMap sm, size_t slot_floats, int slot_shift)
+    const typename Mode<MODE>::TIO *__restrict__ K, const typename Mode<MODE>::TIO *__restrict__ V,
+    float *__restrict__ ws, int N, int nseg, int nseg_run, SegMap sm, size_t slot_floats, int slot_shift)
 {
     typedef Mode<MODE> MD;
     typedef typename MD::TIO TIO;
@@ -283,8 +295,8 @@ __global__ __launch_bounds__(4 * D, 2) void ks_kv_state(
 template <int MODE, int D, bool CAUSAL, int LD>
 __global__ __launch_bounds__(4 * D, 2) void ks_fwd_apply(
     const typename Mode<MODE>::TIO *__restrict__ Q, const typename Mode<MODE>::TIO *__restrict__ K,
-    const typename Mode<MODE>::TIO *__restrict__ V, typename Mode<MODE>::TIO *__restrict__ O, float *__restrict__ G, const float *__restrict__ ws,
-    float *__restrict__ saved, int N, int nseg, SegMap sm, size_t slot_floats, size_t saved_floats,
+    const typename Mode<MODE>::TIO *__restrict__ V, typename Mode<MODE>::TIO *__restrict__ O,
+    float *__restrict__ G, const float *__restrict__ ws, float *__restrict__ saved, int N, int nseg, SegMap sm, size_t slot_floats, size_t saved_floats,
     float a, float b, int xflags, const float *__restrict__ Gin, float *__restrict__ Fraw)
 {
     typedef Mode<MODE> MD;

@@ -106,3 +106,19 @@ def test_nonfinite_stays_in_its_column(la, D, dtype):
     keep = [j for j in range(D) if j != 5]
     assert torch.equal(O[..., keep], clean[..., keep])
     assert not torch.isfinite(O[0, 0, 40:, 5].float()).any()
+
+
+def test_static_forward_head_size_16_many_slices(la):
+    """8000 slices at D = 16: the padded tiles' states exceed the static scratch, the plain-ALU
+    kernels' fit, and the call is served as it was."""
+    B, H, N, D = 80, 100, 6, 16
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(5)
+    Q, K, V = (torch.randn((B, H, N, D), device="cuda", generator=gen) * 0.25 for _ in range(3))
+    assert la.la_workspace_bytes(B, H, N, D, la.LA_F32, True, 0) > la.LA_STATIC_SCRATCH_BYTES
+    O, G = torch.empty_like(Q), torch.empty((B, H, N), device="cuda")
+    la.la_forward_static(Q, K, V, O, G, 1.0, 0.5, True)
+    P = torch.tril(1.0 + 0.5 * torch.matmul(Q.double(), K.double().transpose(2, 3).contiguous()))
+    want = torch.matmul(P, V.double()) / P.sum(3, keepdim=True)
+    assert excess(to_f64(O), to_f64(want), TOL["f32"]) <= 1.0
+    assert excess(to_f64(G), to_f64(P.sum(3)), TOL["f32"]) <= 1.0
