@@ -135,7 +135,11 @@ def la_saved_state_bytes(B, H, N, D, dt, causal):
 # addresses, which ctypes converts by the declared argument types.
 
 def _check_tensors(ref, *ts):
+    """Every tensor of a call, the first one included, is packed and on ref's device: the
+    kernels read B*H*N*D elements from its address, whatever its strides say."""
     dev = ref.get_device()
+    if not ref.is_cuda or not ref.is_contiguous():
+        raise ValueError("tensors must be contiguous device tensors")
     for t in ts:
         if t is None:
             continue
