@@ -4,7 +4,8 @@ import numpy as np
 import pytest
 import torch
 
-from la_testlib import TOL, excess, run_gpu, scratch, to_f64, upload_case
+from la_testlib import (TOL, excess, gpu_backward, gpu_forward, run_gpu, scratch, to_f64,
+                        upload_case)
 
 pytestmark = pytest.mark.gpu
 
@@ -122,3 +123,25 @@ def test_static_forward_head_size_16_many_slices(la):
     want = torch.matmul(P, V.double()) / P.sum(3, keepdim=True)
     assert excess(to_f64(O), to_f64(want), TOL["f32"]) <= 1.0
     assert excess(to_f64(G), to_f64(P.sum(3)), TOL["f32"]) <= 1.0
+
+
+@pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("N", [250, 4000])
+def test_head_size_16_bf16_has_32_bit_intermediates(la, N, causal):
+    """bf16 at D = 16: nothing but the outputs is rounded to bf16, so that on the same O and g they
+    are the plain-ALU kernels' but for values that lie within a few fp32 roundings of a tie.
+    Two fp32 evaluations differ by some 1e-6 of a value (ten times that in dQ, dK, which are
+    differences); a bf16 interval is 2^-8 of it, so well under 1 % of the values fall on either
+    side of a tie.  An intermediate in one bf16 plane makes it 5 to 50 %."""
+    dev, _ = upload_case(1, 4, N, 16, "bf16", 77, [])
+    try:
+        O, G = gpu_forward(la, dev, 1.0, 0.5, causal)
+        got = (O,) + gpu_backward(la, dev, O, G, 1.0, 0.5, causal)
+        la.la_debug_override(0, 1)
+        want = (gpu_forward(la, dev, 1.0, 0.5, causal)[0],) + gpu_backward(la, dev, O, G, 1.0, 0.5,
+                                                                          causal)
+    finally:
+        la.la_debug_override(0, 0)
+    for name, x, y in zip(("O", "dQ", "dK", "dV"), got, want):
+        share = float((x != y).float().mean())
+        assert share <= 0.01, (name, share)
