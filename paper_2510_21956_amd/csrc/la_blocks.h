@@ -30,17 +30,6 @@ __device__ __forceinline__ bf4v to_bf4(f4v x)
 }
 __device__ __forceinline__ f4v bf4_to_float(bf4v x) { return __builtin_convertvector(x, f4v); }
 
-// Workgroup barrier after which every wave sees what the others wrote to LDS.  The wait is spelt
-// out: where the barrier stands at the top of a loop the compiler has left out the one that
-// __syncthreads() implies after LDS writes at the end of the loop body (seen in the listings of
-// 60 of these kernels; with it missing, two runs on the same inputs differed once).
-// 0xc07f: lgkmcnt(0), the other counters untouched.
-__device__ __forceinline__ void block_sync()
-{
-    __builtin_amdgcn_s_waitcnt(0xc07f);
-    __syncthreads();
-}
-
 // x[c0 + r] of a per-row float array of N entries (c0 < N, r < 64); 0 beyond the end.
 __device__ __forceinline__ float load_row_float(const float *x, long c0, int N, int r)
 {

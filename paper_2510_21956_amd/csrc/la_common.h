@@ -26,6 +26,18 @@ __device__ __forceinline__ bf16_t float_to_bf16(float f)
     return (bf16_t)(u >> 16);
 }
 
+// Workgroup barrier after which every wave sees what the others wrote to LDS.  The wait is spelt
+// out: where the barrier stands at the top of a loop the compiler has left out the one that
+// __syncthreads() implies after LDS writes at the end of the loop body (seen in the listings of
+// 60 of the matrix-core kernels; with it missing, two runs on the same inputs differed once).
+// Every barrier of the library is this one, also where today's listing would have the wait.
+// 0xc07f: lgkmcnt(0), the other counters untouched.
+__device__ __forceinline__ void block_sync()
+{
+    __builtin_amdgcn_s_waitcnt(0xc07f);
+    __syncthreads();
+}
+
 __device__ __forceinline__ float load_elem(const float *p, size_t i) { return p[i]; }
 __device__ __forceinline__ float load_elem(const bf16_t *p, size_t i) { return bf16_to_float(p[i]); }
 __device__ __forceinline__ void store_elem(float *p, size_t i, float x) { p[i] = x; }

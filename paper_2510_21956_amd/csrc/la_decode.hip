@@ -105,7 +105,7 @@ __global__ __launch_bounds__((DC<D>::NT)) void k_decode(const T *__restrict__ Q,
         if (t % 64 < LR) *reinterpret_cast<f4 *>(&part[buf][w][j]) = f;
         if (t % 64 == 0) partz[buf][w] = qz;
         cnt += 1.f;
-        __syncthreads();
+        block_sync();
 #pragma unroll
         for (int m = 0; m < NO; ++m) {
             const int col = t + m * NT;
@@ -132,7 +132,7 @@ __global__ __launch_bounds__((DC<D>::NT)) void k_decode(const T *__restrict__ Q,
             st[D * D + D + col] = p[m];
         }
     }
-    __syncthreads();  // every thread has read the count
+    block_sync();  // every thread has read the count
     if (t == 0) st[D * D + 2 * D] = cnt;
 }
 
@@ -217,7 +217,7 @@ __global__ __launch_bounds__(256) void k_dot_partial(const T *__restrict__ X,
     for (size_t e = lo + threadIdx.x; e < hi; e += 256) s += load_elem(X, e) * load_elem(Y, e);
     s = wave_sum(s);
     if (threadIdx.x % 64 == 0) red[threadIdx.x / 64] = s;
-    __syncthreads();
+    block_sync();
     if (threadIdx.x == 0) partials[blockIdx.x] = (red[0] + red[1]) + (red[2] + red[3]);
 }
 // Stage 2: one workgroup adds the partials in a fixed order and writes the two scaled results.
@@ -230,7 +230,7 @@ __global__ __launch_bounds__(256) void k_dot_final(const float *__restrict__ par
     for (int e = threadIdx.x; e < np; e += 256) s += partials[e];
     s = wave_sum(s);
     if (threadIdx.x % 64 == 0) red[threadIdx.x / 64] = s;
-    __syncthreads();
+    block_sync();
     if (threadIdx.x == 0) {
         const float tot = (red[0] + red[1]) + (red[2] + red[3]);
         out[0] = scale0 * tot;

@@ -94,13 +94,13 @@ __global__ __launch_bounds__(NT) void k_fwd_state(const T *__restrict__ K, const
     for (int r = 0; r < PER; ++r) acc[r] = 0.f;
     float vec = 0.f;  // t < D: p[t]; D <= t < 2D: z[t-D]
     for (long c0 = row0; c0 < row1; c0 += C) {
-        __syncthreads();
+        block_sync();
         load_tile<T, D, C>(k, Kp, c0, row1);
         load_tile<T, D, C>(v, Vp, c0, row1);
-        __syncthreads();
+        block_sync();
         if (norm) {
             normalise_tiles<D, C>(k, nullptr);
-            __syncthreads();
+            block_sync();
         }
         for (int n = 0; n < C; ++n) {
             float vj = v[n * LD + j];
@@ -158,31 +158,31 @@ __global__ __launch_bounds__(NT) void k_bwd_state(const T *__restrict__ Q, const
     float vecA = 0.f;  // t < D: w[t]; D <= t < 2D: u[t-D]
     float vecZ = 0.f;  // t < D: z[t]
     for (long c0 = row0; c0 < row1; c0 += C) {
-        __syncthreads();
+        block_sync();
         load_tile<T, D, C>(q, Qp, c0, row1);
         if (need_S) {
             load_tile<T, D, C>(k, Kp, c0, row1);
             load_tile<T, D, C>(v, Vp, c0, row1);
         }
         load_omega_hat<T, D, C>(oh, dOp, Gp, c0, row1);
-        __syncthreads();
+        block_sync();
         if (norm) {
             normalise_tiles<D, C>(q, need_S ? k : nullptr);
-            __syncthreads();
+            block_sync();
         }
         for (int e = t; e < C * D; e += NT) {
             int i = e / D, jj = e % D;
             long r = c0 + i;
             tmp[i * LD + jj] = (r < row1) ? load_elem(Op, (size_t)r * D + jj) * oh[i * LD + jj] : 0.f;
         }
-        __syncthreads();
+        block_sync();
         if (t < C) {
             float s = 0.f;
             for (int jj = 0; jj < D; ++jj) s += tmp[t * LD + jj];
             dl[t] = s;
             if (c0 + t < row1) dp[c0 + t] = s;
         }
-        __syncthreads();
+        block_sync();
         for (int n = 0; n < C; ++n) {
             float ohj = oh[n * LD + j];
 #pragma unroll
@@ -293,23 +293,23 @@ __global__ __launch_bounds__(NT) void k_fwd_apply(const T *__restrict__ Q, const
     }
 
     for (long c0 = row0; c0 < row1; c0 += C) {
-        __syncthreads();
+        block_sync();
         load_tile<T, D, C>(q, Qp, c0, row1);
         if (causal) {
             load_tile<T, D, C>(k, Kp, c0, row1);
             load_tile<T, D, C>(v, Vp, c0, row1);
         }
-        __syncthreads();
+        block_sync();
         if (norm) {
             normalise_tiles<D, C>(q, causal ? k : nullptr);
-            __syncthreads();
+            block_sync();
         }
         if (causal) {
             for (int e = t; e < C * C; e += NT) {
                 int i = e / C, n = e % C;
                 P[i * PL + n] = (n <= i) ? a + b * dot_lds<D>(q + i * LD, k + n * LD) : 0.f;
             }
-            __syncthreads();
+            block_sync();
         }
         if (t < C) {
             float s = b * dot_lds<D>(q + t * LD, z);
@@ -322,7 +322,7 @@ __global__ __launch_bounds__(NT) void k_fwd_apply(const T *__restrict__ Q, const
             g[t] = s;
             if (G && c0 + t < row1) Gp[c0 + t] = s;
         }
-        __syncthreads();
+        block_sync();
         for (int e = t; e < C * D; e += NT) {
             int i = e / D, j = e % D;
             float lin = 0.f;
@@ -334,7 +334,7 @@ __global__ __launch_bounds__(NT) void k_fwd_apply(const T *__restrict__ Q, const
             if (c0 + i < row1) store_elem(Op, (size_t)(c0 + i) * D + j, f / g[i]);
         }
         if (causal) {
-            __syncthreads();
+            block_sync();
             for (int e = t; e < D * D; e += NT) {
                 int m = e / D, j = e % D;
                 float s = 0.f;
@@ -398,22 +398,22 @@ __global__ __launch_bounds__(NT) void k_bwd_apply(
     if (t < D) z[t] = zero_S ? 0.f : slot[D * D + t];
     for (long ci = 0; ci < nchunks; ++ci) {
         const long c0 = row0 + ci * C;
-        __syncthreads();
+        block_sync();
         load_tile<T, D, C>(k, Kp, c0, row1);
         load_tile<T, D, C>(v, Vp, c0, row1);
         load_omega_hat<T, D, C>(oh, dOp, Gp, c0, row1);
         if (t < C) dl[t] = (c0 + t < row1) ? dp[c0 + t] : 0.f;
-        __syncthreads();
+        block_sync();
         if (norm) {
             normalise_tiles<D, C>(k, nullptr);
-            __syncthreads();
+            block_sync();
         }
         if (causal) {
             for (int e = t; e < C * C; e += NT) {
                 int i = e / C, n = e % C;
                 Cm[i * PL + n] = (n <= i) ? dot_lds<D>(oh + i * LD, v + n * LD) - dl[i] : 0.f;
             }
-            __syncthreads();
+            block_sync();
         }
         for (int e = t; e < C * D; e += NT) {
             int i = e / D, x = e % D;
@@ -426,7 +426,7 @@ __global__ __launch_bounds__(NT) void k_bwd_apply(
             if (c0 + i < row1) store_elem(dQp, (size_t)(c0 + i) * D + x, b * sq);
         }
         if (causal) {
-            __syncthreads();
+            block_sync();
             for (int e = t; e < D * D; e += NT) {
                 int m = e / D, j = e % D;
                 float s = 0.f;
@@ -442,7 +442,7 @@ __global__ __launch_bounds__(NT) void k_bwd_apply(
     }
 
     // ---- sweep 2: descending, dK and dV ----
-    __syncthreads();
+    block_sync();
     const bool zero_R = causal && seg == nseg - 1;
     for (int e = t; e < D * D; e += NT)
         St[(e / D) * LD + (e % D)] = zero_R ? 0.f : slot[D * D + D + e];
@@ -452,16 +452,16 @@ __global__ __launch_bounds__(NT) void k_bwd_apply(
     }
     for (long ci = nchunks - 1; ci >= 0; --ci) {
         const long c0 = row0 + ci * C;
-        __syncthreads();
+        block_sync();
         load_tile<T, D, C>(q, Qp, c0, row1);
         load_tile<T, D, C>(k, Kp, c0, row1);
         load_tile<T, D, C>(v, Vp, c0, row1);
         load_omega_hat<T, D, C>(oh, dOp, Gp, c0, row1);
         if (t < C) dl[t] = (c0 + t < row1) ? dp[c0 + t] : 0.f;
-        __syncthreads();
+        block_sync();
         if (norm) {
             normalise_tiles<D, C>(q, k);
-            __syncthreads();
+            block_sync();
         }
         if (causal) {
             for (int e = t; e < C * C; e += NT) {
@@ -470,7 +470,7 @@ __global__ __launch_bounds__(NT) void k_bwd_apply(
                 Cm[i * PL + n] = on ? dot_lds<D>(oh + i * LD, v + n * LD) - dl[i] : 0.f;
                 W[i * PL + n] = on ? a + b * dot_lds<D>(q + i * LD, k + n * LD) : 0.f;
             }
-            __syncthreads();
+            block_sync();
         }
         for (int e = t; e < C * D; e += NT) {
             int i = e / D, x = e % D;
@@ -495,7 +495,7 @@ __global__ __launch_bounds__(NT) void k_bwd_apply(
             }
         }
         if (causal) {
-            __syncthreads();
+            block_sync();
             for (int e = t; e < D * D; e += NT) {
                 int r = e / D, j = e % D;
                 float s = 0.f;

@@ -126,7 +126,7 @@ __global__ __launch_bounds__(WNT) void k_wide(const T *__restrict__ XA, const T 
     };
     int pb = 0;
     for (long grp = 0; grp < ngroups; ++grp) {
-        __syncthreads();  // the previous group's rows are done with the staged tiles
+        block_sync();  // the previous group's rows are done with the staged tiles
         // (the group is fetched here and not a group ahead: values held across the walk below
         // would push the state out of the register file, and the exposed latency is paid once
         // per sixteen rows)
@@ -150,7 +150,7 @@ __global__ __launch_bounds__(WNT) void k_wide(const T *__restrict__ XA, const T 
             *reinterpret_cast<float4 *>(&Cch[wv][4 * l]) =
                 make_float4(fc[0] * scl, fc[1] * scl, fc[2] * scl, fc[3] * scl);
         }
-        __syncthreads();
+        block_sync();
         const long left = nrows - grp * WCH;
         const int nr = left < WCH ? (int)left : WCH;
         for (int r = 0; r < nr; ++r) {
@@ -168,7 +168,7 @@ __global__ __launch_bounds__(WNT) void k_wide(const T *__restrict__ XA, const T 
                 if (pass == 1) {
                     prod = wsum(prod);
                     if (l == 0) red[wv] = prod;
-                    __syncthreads();
+                    block_sync();
                     if (t == 0) {
                         float s = 0.f;
                         for (int u = 0; u < D / 64; ++u) s += red[u];
@@ -211,7 +211,7 @@ __global__ __launch_bounds__(WNT) void k_wide(const T *__restrict__ XA, const T 
                 if (q % 8 == 4) __builtin_amdgcn_sched_barrier(0);
             }
             if (pass == 1) part[pb][rg][yl] = lin;
-            __syncthreads();
+            block_sync();
             if (pass == 1 && t < YC) {  // row group 0: column y = half * YC + t
                 float lsum = 0.f;
 #pragma unroll
@@ -236,7 +236,7 @@ __global__ __launch_bounds__(WNT) void k_wide(const T *__restrict__ XA, const T 
         float *slot = ws + ((size_t)bh * nseg + seg + slot_shift) * slot_floats + slot_off;
 #pragma unroll
         for (int i = 0; i < RPT; ++i) slot[(size_t)(rg * RPT + i) * D + y] = M[i];
-        __syncthreads();
+        block_sync();
         if (t < YC) slot[D * D + y] = yvec;  // row group 0
         if (t < D && half == 0) slot[D * D + D + t] = xv[t];
     }
