@@ -403,8 +403,8 @@ __global__ __launch_bounds__(4 * D, 2) void ks_fwd_apply(
             for (int pidx = w; pidx < 3; pidx += NW) {
                 const int ib = pidx ? 1 : 0, nb = pidx == 2 ? 1 : 0;
                 f4v pa = block_product<D, LQ, LQ>(Kt, nb, Qt, ib, ln);
-                if constexpr (MD::RN)
-                    pa *= iq[ib * 16 + c] * *reinterpret_cast<const f4v *>(ik + nb * 16 + 4 * g);
+                if constexpr (MD::RN)  // one factor after the other: their product may overflow
+                    pa = (pa * iq[ib * 16 + c]) * *reinterpret_cast<const f4v *>(ik + nb * 16 + 4 * g);
                 const int last = nb == ib ? c : 15;  // last row n at or before row i
                 f4v x;
 #pragma unroll
@@ -863,7 +863,7 @@ __global__ __launch_bounds__(4 * D, 2) void ks_bwd_dkv(
                 } else {
                     f4v pw = block_product<D, LQ, LQ>(Qt, ib, Kt, nb, ln);
                     if constexpr (MD::RN)
-                        pw *= kinv[nb * 16 + c] * *reinterpret_cast<const f4v *>(iq + ib * 16 + 4 * g);
+                        pw = (pw * kinv[nb * 16 + c]) * *reinterpret_cast<const f4v *>(iq + ib * 16 + 4 * g);
                     const f4v r4 = *reinterpret_cast<const f4v *>(rs + ib * 16 + 4 * g);
                     if constexpr (QT) x = a * r4 + b * pw;
                     else x = (a + b * pw) * r4;

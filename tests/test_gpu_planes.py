@@ -145,3 +145,21 @@ def test_head_size_16_bf16_has_32_bit_intermediates(la, N, causal):
     for name, x, y in zip(("O", "dQ", "dK", "dV"), got, want):
         share = float((x != y).float().mean())
         assert share <= 0.01, (name, share)
+
+
+@pytest.mark.parametrize("p", [-68, 58])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("D", [16, 32, 64, 128])
+def test_qknorm_takes_any_row_length(la, D, dtype, p):
+    """Rows of Q and K scaled by a power of two: the same O, g and dV, dQ and dK scaled back.  At
+    2^-68 a row's squared length is subnormal (2^-134 D, in steps of 2^-149: 2^-11 at worst, far
+    below the bf16 tolerance; the fp32 rows are scaled by 2^-60, where it is not)."""
+    if dtype == "f32":
+        p = max(p, -60)
+    dev, _ = upload_case(1, 2, 200, D, dtype, 9, [0, 1], normalise=False)
+    base = _run_qknorm(la, dev, 1.0, 0.5, True)
+    s = 2.0 ** p
+    got = _run_qknorm(la, dict(dev, Q=dev["Q"] * s, K=dev["K"] * s), 1.0, 0.5, True)
+    for name, x, y in zip(("O", "G", "dQ", "dK", "dV"), got, base):
+        x = to_f64(x) * (s if name in ("dQ", "dK") else 1.0)
+        assert excess(x, to_f64(y), TOL[dtype]) <= 1.0, (name, p)
