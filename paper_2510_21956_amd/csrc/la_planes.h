@@ -52,6 +52,34 @@ __device__ __forceinline__ void split4(f4v x, bf4v (&o)[L])
                      __uint_as_float(b & 0xffff0000u)};
     }
 }
+// Largest magnitude of eight values (a NaN counts as nothing).  split4 leaves NaN behind an infinite
+// first plane (infinity minus itself): where this exceeds kLargestBf16.
+constexpr float kLargestBf16 = 0x1.fep127f;
+__device__ __forceinline__ float largest(f4v x, f4v y)
+{
+    float m;
+    asm("v_max3_f32 %0, |%1|, |%2|, |%3|" : "=v"(m) : "v"(x[0]), "v"(x[1]), "v"(x[2]));
+    asm("v_max3_f32 %0, %1, |%2|, |%3|" : "=v"(m) : "v"(m), "v"(x[3]), "v"(y[0]));
+    asm("v_max3_f32 %0, %1, |%2|, |%3|" : "=v"(m) : "v"(m), "v"(y[1]), "v"(y[2]));
+    asm("v_max_f32 %0, %1, |%2|" : "=v"(m) : "v"(m), "v"(y[3]));
+    return m;
+}
+// The three planes of any four floats.  A finite value takes the largest bf16 at most as its first
+// plane; an infinity becomes +-1, 0, +-infinity: its only infinite product with another split
+// value is the one with that value's first plane, which has the sign of the whole product.
+__device__ __forceinline__ void split4_any(f4v x, bf4v (&o)[3])
+{
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const bool inf = __builtin_isinf(x[e]);
+        const float first = inf ? __builtin_copysignf(1.f, x[e])
+                                : __builtin_fminf(__builtin_fmaxf(x[e], -kLargestBf16), kLargestBf16);
+        o[0][e] = (__bf16)first;
+        const float rest = x[e] - (float)o[0][e];
+        o[1][e] = (__bf16)(inf ? 0.f : rest);
+        o[2][e] = (__bf16)(inf ? x[e] : rest - (float)o[1][e]);
+    }
+}
 __device__ __forceinline__ bf8v join(bf4v lo, bf4v hi)
 {
     return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
@@ -352,6 +380,25 @@ struct Chunk {
         } else {
             const f4v x[2] = {value(0), value(1)};
             store_values<OP, L>(tile, x);
+        }
+    }
+    // Above kLargestBf16: store<OP, 3> left NaN behind an infinite plane, and the tile is written
+    // once more.
+    __device__ __forceinline__ float top() const
+    {
+        if constexpr (F32) return largest(value(0), value(1));
+        else return 0.f;
+    }
+    template <bool OP>
+    __device__ __forceinline__ void store_any(__bf16 *tile) const
+    {
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            __bf16 *dst = tile + (OP ? Tile<D>::op_quad(row(k), quad(k)) : Tile<D>::nat_quad(row(k), quad(k)));
+            bf4v o[3];
+            split4_any(value(k), o);
+#pragma unroll
+            for (int p = 0; p < 3; ++p) *reinterpret_cast<bf4v *>(dst + p * Tile<D>::PLANE) = o[p];
         }
     }
 };

@@ -238,6 +238,7 @@ __global__ __launch_bounds__(4 * D, 2) void ks_kv_state(
         block_sync();
         stage<MD::NORM, false, LQ>(cur.k, Kt, MD::RN ? ik : nullptr);
         cur.v.template store<false, LV>(Vt);
+        if (__builtin_expect(cur.v.top() > kLargestBf16, 0)) cur.v.template store_any<false>(Vt);
         block_sync();
         const long cn = min(c0 + MD::DEPTH * CR, c_last);
         cur.k.load(Kp, cn, N);
@@ -392,6 +393,7 @@ __global__ __launch_bounds__(4 * D, 2) void ks_fwd_apply(
         if constexpr (CAUSAL) {
             stage<MD::NORM, false, LQ>(cur.k, Kt, MD::RN ? ik : nullptr);
             cur.v.template store<false, LV>(Vt);
+            if (__builtin_expect(cur.v.top() > kLargestBf16, 0)) cur.v.template store_any<false>(Vt);
         }
         block_sync();
         const long cn = min(c0 + MD::DEPTH * CR, c_last);
@@ -619,6 +621,10 @@ __global__ __launch_bounds__(4 * D, 2) void ks_bwd_dq(
             cur.v.template store<false, LV>(Vt);
             stage<MD::NORM, false, LQ>(cur.k, Kt, MD::RN ? ik : nullptr);
         }
+        if (__builtin_expect(max(cur.d.top(), CAUSAL ? cur.v.top() : 0.f) > kLargestBf16, 0)) {
+            cur.d.template store_any<true>(dOt);
+            if constexpr (CAUSAL) cur.v.template store_any<false>(Vt);
+        }
         block_sync();
         const long cn = min(c0 + MD::DEPTH * CR, c_last);
         cur.g = load_row_float(Gp, cn, N, t % CR);
@@ -842,6 +848,10 @@ __global__ __launch_bounds__(4 * D, 2) void ks_bwd_dkv(
                 if (CH::leader()) store_factor<3>(fdl[par], r, dl[r] * rs[r] * iq[r]);
             }
             cur.d.template store<false, LV>(dOt);
+        }
+        if (__builtin_expect(max(cur.v.top(), CAUSAL ? cur.d.top() : 0.f) > kLargestBf16, 0)) {
+            cur.v.template store_any<true>(Vt);
+            if constexpr (CAUSAL) cur.d.template store_any<false>(dOt);
         }
         block_sync();
         const long cn = row0 + max(ci - MD::DEPTH, 0L) * CR;

@@ -163,3 +163,42 @@ def test_qknorm_takes_any_row_length(la, D, dtype, p):
     for name, x, y in zip(("O", "G", "dQ", "dK", "dV"), got, base):
         x = to_f64(x) * (s if name in ("dQ", "dK") else 1.0)
         assert excess(x, to_f64(y), TOL[dtype]) <= 1.0, (name, p)
+
+
+@pytest.mark.parametrize("sign", [1.0, -1.0])
+@pytest.mark.parametrize("D", [16, 32, 64, 128])
+def test_fp32_infinity_keeps_its_sign(la, D, sign):
+    """An infinite value of row 40 is +-infinity in rows 40 to 63 of O, the rest of its chunk, where
+    every weight 1 + 0.5 q.k is positive, and it spoils the later rows of its column.  (D = 256 adds
+    the weight up from two halves of either sign.)"""
+    dev, _ = upload_case(1, 1, 150, D, "f32", 31, [0])
+    V = dev["V"].clone()
+    V[0, 0, 40, 5] = sign * float("inf")
+    O = run_gpu(la, dict(dev, V=V), 1.0, 0.5, True)[0][0, 0, :, 5]
+    assert torch.isfinite(O[:32]).all()
+    assert (O[40:64] == sign * float("inf")).all()
+    assert not torch.isfinite(O[64:]).any()
+
+
+@pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("D", [16, 32, 64, 128, 256])
+def test_largest_floats(la, D, causal):
+    """The largest float in V and in dO, with weights a = 1/4 that leave its sums finite: o_i is the
+    mean of the rows it sees, dv_n the sum of dO_i / (their number) over the rows that see it."""
+    N, top = 150, float(np.finfo(np.float32).max)
+    dev, _ = upload_case(1, 1, N, D, "f32", 32, [0])
+    V = dev["V"] * 0.01
+    V[0, 0, 40, 5] = -top
+    O, _, _, _, _ = run_gpu(la, dict(dev, V=V), 0.25, 0.0, causal)
+    n = torch.arange(1, N + 1, device="cuda", dtype=torch.float64)
+    want = V[0, 0].double().cumsum(0) / n[:, None] if causal else V[0, 0].double().mean(0).expand(N, D)
+    keep = torch.arange(N, device="cuda") >= (40 if causal else 0)  # rows that see row 40
+    assert excess(to_f64(O[0, 0, keep, 5]), to_f64(want[keep, 5]), TOL["f32"]) <= 1.0
+
+    V, dO = dev["V"] * 0.01, dev["dO"].clone()
+    dO[0, 0, 40, 5] = top
+    dV = run_gpu(la, dict(dev, V=V, dO=dO), 0.25, 0.0, causal)[4]
+    x = dO[0, 0].double() / (n if causal else float(N) * torch.ones_like(n))[:, None]
+    want = x.flip(0).cumsum(0).flip(0) if causal else x.sum(0).expand(N, D)
+    keep = torch.arange(N, device="cuda") <= (40 if causal else N)
+    assert excess(to_f64(dV[0, 0, keep, 5]), to_f64(want[keep, 5]), TOL["f32"]) <= 1.0
