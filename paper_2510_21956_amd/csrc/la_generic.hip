@@ -223,7 +223,8 @@ __global__ __launch_bounds__(NT) void k_bwd_state(const T *__restrict__ Q, const
 // floats [off, off+len) of every slot of a slice, over slots lo..hi.
 //   mode 0: slot[s] += slot[s-1] for s = lo+1..hi   (running sum, ascending)
 //   mode 1: slot[s] += slot[s+1] for s = hi-1..lo   (running sum, descending)
-//   mode 2: slot[0] = sum of slots lo..hi           (no mask: every row sees every row)
+//   mode 2: slot[0] = sum of slots lo..hi           (no mask: every row sees every row), with
+//           what the additions lose: some hundred slots of one long slice add up
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(NT) void k_scan_slots(float *__restrict__ ws, int nseg,
                                                    size_t slot_floats, int off, int len, int mode,
@@ -236,7 +237,7 @@ __global__ __launch_bounds__(NT) void k_scan_slots(float *__restrict__ ws, int n
     // memory round trip per eight slots instead of one per slot (the sums are formed in the
     // same order either way).
     constexpr int BATCH = 8;
-    float run = 0.f;
+    float run = 0.f, lost = 0.f;
     const int n = hi - lo + 1;
     for (int i0 = 0; i0 < n; i0 += BATCH) {
         float x[BATCH];
@@ -249,12 +250,14 @@ __global__ __launch_bounds__(NT) void k_scan_slots(float *__restrict__ ws, int n
         for (int i = 0; i < BATCH; ++i) {
             const int k = i0 + i, sl = mode == 1 ? hi - k : lo + k;
             if (k < n) {
-                run = k == 0 ? x[i] : run + x[i];
+                const float sum = run + x[i], y = sum - run;
+                lost += (run - (sum - y)) + (x[i] - y);  // used by mode 2
+                run = sum;
                 if (mode != 2 && k > 0) p[(size_t)sl * slot_floats] = run;
             }
         }
     }
-    if (mode == 2) p[0] = run;
+    if (mode == 2) p[0] = __builtin_isfinite(run) ? run + lost : run;
 }
 
 // ---------------------------------------------------------------------------

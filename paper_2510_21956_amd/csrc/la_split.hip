@@ -61,13 +61,16 @@ struct Mode {
 
 // A wave's 16 entries of a vector sum (z, p, u, w) in the layout of its output blocks: one
 // column a lane (SWAP), or the columns 4g .. 4g+3 of the lane group.
-template <bool SWAP>
+// LONG: summed with what the additions lose (a sum that only leaves the kernel).
+template <bool SWAP, bool LONG = false>
 struct Sum {
-    typename std::conditional<SWAP, float, f4v>::type v;
+    typedef typename std::conditional<SWAP, float, f4v>::type T;
+    T v;
+    LongSum<T> run;
     __device__ __forceinline__ Sum()
     {
-        if constexpr (SWAP) v = 0.f;
-        else v = f4v{0.f, 0.f, 0.f, 0.f};
+        v = T{};
+        run = LongSum<T>{};
     }
     __device__ __forceinline__ void load(const float *p, int w, int c, int g)
     {
@@ -76,18 +79,32 @@ struct Sum {
     }
     __device__ __forceinline__ void store(float *p, int w, int c, int g) const
     {
+        T x = v;
+        if constexpr (LONG) x = total(run);
         if constexpr (SWAP) {
-            if (g == 0) p[w * 16 + c] = v;
+            if (g == 0) p[w * 16 + c] = x;
         } else {
-            if (c == 0) *reinterpret_cast<f4v *>(p + w * 16 + 4 * g) = v;
+            if (c == 0) *reinterpret_cast<f4v *>(p + w * 16 + 4 * g) = x;
         }
     }
     // += sum over the chunk rows of f's columns, weighted by the factor planes in wgt
     template <int LF, int LW>
     __device__ __forceinline__ void add(const bf8v (&f)[LF], const bf8v (&wgt)[LW])
     {
-        if constexpr (SWAP) v += step_product<LW, LF>(wgt, f)[0];
-        else v += step_product<LF, LW>(f, wgt);
+        if constexpr (LONG) {
+            f4v hi = {0.f, 0.f, 0.f, 0.f}, lo = hi;
+            if constexpr (SWAP) {
+                mma_planes<LW, LF>(hi, lo, wgt, f);
+                run.add(hi[0], lo[0]);
+            } else {
+                mma_planes<LF, LW>(hi, lo, f, wgt);
+                run.add(hi, lo);
+            }
+        } else if constexpr (SWAP) {
+            v += step_product<LW, LF>(wgt, f)[0];
+        } else {
+            v += step_product<LF, LW>(f, wgt);
+        }
     }
 };
 // Per-row factors of the chunk for output block m: the lane's four rows (SWAP) or its one row.
@@ -209,10 +226,10 @@ __global__ __launch_bounds__(4 * D, 2) void ks_kv_state(
     typedef Mode<MODE> MD;
     typedef typename MD::TIO TIO;
     constexpr int LQ = MD::LQ, LV = MD::LV, NRB = D / 16, PL = Tile<D>::PLANE;
+    constexpr int NT = MD::DEPTH, TP = (LQ + LV) * PL;  // tile pairs staged at a time, elements of one
     typedef Chunk<TIO, D, LD> CH;
-    __shared__ __align__(16) __bf16 lds[(LQ + LV) * PL];
-    __shared__ __align__(16) float ik[MD::RN ? CR : 4];  // 1 / |k|
-    __bf16 *Kt = lds, *Vt = lds + LQ * PL;
+    __shared__ __align__(16) __bf16 lds[NT * TP];
+    __shared__ __align__(16) float ikb[MD::RN ? NT * CR : 4];  // 1 / |k|
     const int bh = blockIdx.x / nseg_run, seg = blockIdx.x % nseg_run;
     const TIO *Kp = K + (size_t)bh * N * LD, *Vp = V + (size_t)bh * N * LD;
     const long row0 = seg_row(sm, seg, nseg, N), row1 = seg_row(sm, seg + 1, nseg, N);
@@ -224,33 +241,33 @@ __global__ __launch_bounds__(4 * D, 2) void ks_kv_state(
     Blk st[NRB];
 #pragma unroll
     for (int rb = 0; rb < NRB; ++rb) st[rb].zero();
-    f4v zacc = {0.f, 0.f, 0.f, 0.f}, pacc = zacc;  // z, p [16w + 4g + e]
+    LongSum<f4v> zacc{}, pacc{};  // z, p [16w + 4g + e]
     struct Set {
         CH k, v;
-    } sets[MD::DEPTH];
+    } sets[NT];
     const long c_last = row0 + (row1 - row0 - 1) / CR * CR;
-#pragma unroll
-    for (int i = 0; i < MD::DEPTH; ++i) {
-        sets[i].k.load(Kp, min(row0 + i * CR, c_last), N);
-        sets[i].v.load(Vp, min(row0 + i * CR, c_last), N);
-    }
-    auto chunk = [&](long c0, Set &cur) __attribute__((always_inline)) {
-        block_sync();
-        stage<MD::NORM, false, LQ>(cur.k, Kt, MD::RN ? ik : nullptr);
-        cur.v.template store<false, LV>(Vt);
-        if (__builtin_expect(cur.v.top() > kLargestBf16, 0)) cur.v.template store_any<false>(Vt);
-        block_sync();
-        const long cn = min(c0 + MD::DEPTH * CR, c_last);
-        cur.k.load(Kp, cn, N);
-        cur.v.load(Vp, cn, N);
+    auto request = [&](long c0, int i) __attribute__((always_inline)) {
+        sets[i].k.load(Kp, min(c0 + i * CR, c_last), N);
+        sets[i].v.load(Vp, min(c0 + i * CR, c_last), N);
+    };
+    auto put = [&](int i) __attribute__((always_inline)) {
+        __bf16 *Kt = lds + i * TP, *Vt = Kt + LQ * PL;
+        stage<MD::NORM, false, LQ>(sets[i].k, Kt, MD::RN ? ikb + i * CR : nullptr);
+        sets[i].v.template store<false, LV>(Vt);
+        if (__builtin_expect(sets[i].v.top() > kLargestBf16, 0)) sets[i].v.template store_any<false>(Vt);
+    };
+    // one tile pair into the sums
+    auto one_tile = [&](int i) __attribute__((always_inline)) {
+        const __bf16 *Kt = lds + i * TP, *Vt = Kt + LQ * PL;
+        const float *ik = ikb + (MD::RN ? i * CR : 0);
         bf8v kf[LQ];
         load_cols<D, LQ>(kf, Kt, ln.local(ln.col), w);
         if constexpr (MD::RN) {
             bf8v fk[3];
             factor_frag(fk, ik, g);
-            zacc += step_product<LQ, 3>(kf, fk);
+            add_product(zacc, kf, fk);
         } else {
-            zacc += step_product<LQ, 1>(kf, one);
+            add_product(zacc, kf, one);
         }
         if constexpr (TRANSPOSED) {
             if constexpr (MD::RN) {
@@ -263,7 +280,7 @@ __global__ __launch_bounds__(4 * D, 2) void ks_kv_state(
         } else {
             bf8v vf[LV];
             load_cols<D, LV>(vf, Vt, ln.local(ln.col), w);
-            pacc += step_product<LV, 1>(vf, one);
+            add_product(pacc, vf, one);
             if constexpr (MD::RN) {
                 bf8v vh[3];
                 scale_frag<3>(vh, vf, ik, g);
@@ -273,9 +290,35 @@ __global__ __launch_bounds__(4 * D, 2) void ks_kv_state(
             }
         }
     };
-    for (long c0 = row0; c0 < row1; c0 += MD::DEPTH * CR) {
-        chunk(c0, sets[0]);
-        if (MD::DEPTH == 2 && c0 + CR < row1) chunk(c0 + CR, sets[MD::DEPTH - 1]);
+#pragma unroll
+    for (int i = 0; i < NT; ++i) request(row0, i);
+    for (long c0 = row0; c0 < row1; c0 += NT * CR) {
+        const bool two = NT == 2 && c0 + CR < row1;
+        block_sync();
+        put(0);
+        if (NT == 2) request(c0 + NT * CR, 0);
+        if (two) put(NT - 1);
+        block_sync();
+        request(c0 + NT * CR, NT - 1);
+        if (LQ * LV == 1 && !MD::RN && two) {
+            const __bf16 *K0 = lds, *V0 = K0 + LQ * PL, *K1 = lds + (NT - 1) * TP, *V1 = K1 + LQ * PL;
+            const f4v zero = {0.f, 0.f, 0.f, 0.f};
+            bf8v k0[1], k1[1], v0[1], v1[1];
+            load_cols<D, 1>(k0, K0, ln.local(ln.col), w);
+            load_cols<D, 1>(k1, K1, ln.local(ln.col), w);
+            zacc.add(mfma(k1[0], one[0], mfma(k0[0], one[0], zero)));
+            if constexpr (TRANSPOSED) {
+                rank_update_two<D>(st, V0, V1, k0[0], k1[0], ln);
+            } else {
+                load_cols<D, 1>(v0, V0, ln.local(ln.col), w);
+                load_cols<D, 1>(v1, V1, ln.local(ln.col), w);
+                pacc.add(mfma(v1[0], one[0], mfma(v0[0], one[0], zero)));
+                rank_update_two<D>(st, K0, K1, v0[0], v1[0], ln);
+            }
+        } else {
+            one_tile(0);
+            if (two) one_tile(NT - 1);
+        }
     }
     float *slot = ws + ((size_t)bh * nseg + seg + slot_shift) * slot_floats;
 #pragma unroll
@@ -283,8 +326,8 @@ __global__ __launch_bounds__(4 * D, 2) void ks_kv_state(
 #pragma unroll
         for (int i = 0; i < 4; ++i) slot[(rb * 16 + 4 * g + i) * D + w * 16 + c] = st[rb].get(i);
     if (c == 0) {
-        *reinterpret_cast<f4v *>(slot + D * D + w * 16 + 4 * g) = zacc;
-        if constexpr (!TRANSPOSED) *reinterpret_cast<f4v *>(slot + D * D + D + w * 16 + 4 * g) = pacc;
+        *reinterpret_cast<f4v *>(slot + D * D + w * 16 + 4 * g) = total(zacc);
+        if constexpr (!TRANSPOSED) *reinterpret_cast<f4v *>(slot + D * D + D + w * 16 + 4 * g) = total(pacc);
     }
 }
 
@@ -552,7 +595,8 @@ __global__ __launch_bounds__(4 * D, 2) void ks_bwd_dq(
         accR[jb].zero();
         st[jb].zero();
     }
-    Sum<SWAP> zacc, uacc, wacc;  // z, u, w
+    Sum<SWAP> zacc, uacc;      // z, u
+    Sum<SWAP, !CAUSAL> wacc;  // w: without the mask, most of dV
     if (!zero_init) {
 #pragma unroll
         for (int jb = 0; jb < NRB; ++jb)

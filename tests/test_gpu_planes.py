@@ -203,3 +203,38 @@ def test_largest_floats(la, D, causal):
     want = x.flip(0).cumsum(0).flip(0) if causal else x.sum(0).expand(N, D)
     keep = torch.arange(N, device="cuda") <= (40 if causal else N)
     assert excess(to_f64(dV[0, 0, keep, 5]), to_f64(want[keep, 5]), TOL["f32"]) <= 1.0
+
+
+@pytest.mark.parametrize("D", [32, 64, 128])
+def test_unmasked_sums_keep_24_bits(la, oracle_mod, D):
+    """Without the mask O is mostly p / N and dV mostly w, sums over all rows: they carry what
+    their additions lose, so that what is left are the roundings of p, of the two terms, their sum,
+    1/g and the product: five of 2^-24 / sqrt(3) rms at most, 7.7e-8 (plain sums: 2.3e-7 to 2.9e-7)."""
+    N, slices = 20000, [0, 1, 2, 3]
+    dev, ref = upload_case(1, 4, N, D, "f32", 770 + D, slices)
+    O, G, _, _, dV = run_gpu(la, dev, 1.0, 0.5, False)
+    Or, Gr = oracle_mod.forward_rec(ref["Q"], ref["K"], ref["V"], 1.0, 0.5, False)
+    dVr = oracle_mod.backward_rec(ref["Q"], ref["K"], ref["V"], Or, Gr, ref["dO"], 1.0, 0.5, False)[2]
+    for name, x, y in (("O", O, Or), ("dV", dV, dVr)):
+        e = np.linalg.norm(to_f64(x).reshape(y.shape) - y) / np.linalg.norm(y)
+        assert e <= 7.7e-8, (name, e)
+
+
+def test_prefill_sums_bf16(la):
+    """The state after a bf16 prompt: every product is exact in fp32, and a segment's S takes one
+    rounded addition per 64 rows, here 64 of them.  A sum of n like terms grows as sqrt(i), so its n
+    roundings (2^-24 / sqrt(3) rms of the sum then held) come to sqrt(n / 2) 3.4e-8 = 1.9e-7 of it at
+    the end; the rows within an instruction add half as much."""
+    B, H, N, D = 16, 16, 4096, 128
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(8)
+    K, V = (torch.randn((B, H, N, D), device="cuda", generator=gen).bfloat16() for _ in range(2))
+    state = torch.zeros((B * H, la.la_decode_state_bytes(B, H, D) // 4 // (B * H)), device="cuda")
+    la.la_decode_prefill(K, V, state, 0,
+                         scratch(la.la_workspace_bytes(B, H, N, D, la.LA_BF16, False, 0), "cuda"))
+    k, v, st = K[0].double(), V[0].double(), state[:H].double()
+    want = {"S": torch.matmul(k.transpose(1, 2).contiguous(), v).reshape(H, -1), "z": k.sum(1), "p": v.sum(1)}
+    got = {"S": st[:, :D * D], "z": st[:, D * D:D * D + D], "p": st[:, D * D + D:D * D + 2 * D]}
+    for name, bound in (("S", 2.1e-7), ("z", 6e-8), ("p", 6e-8)):
+        e = float((got[name] - want[name]).norm() / want[name].norm())
+        assert e <= bound, (name, e)
