@@ -12,6 +12,8 @@
 // threads), each with a few of them, have the whole state in flight at once.  One row, 128
 // slices, D = 128: 4.6 us (3.6 TB/s of state), 5.7 with 256 threads of single floats; 64 slices,
 // D = 256: 8.6 us, 30.8 before.
+#include <type_traits>
+
 #include "la_common.h"
 
 namespace la {
@@ -136,40 +138,54 @@ __global__ __launch_bounds__((DC<D>::NT)) void k_decode(const T *__restrict__ Q,
     if (t == 0) st[D * D + 2 * D] = cnt;
 }
 
-// Sum of element e over the slots of a slice, in ascending order; eight loads in flight.
-__device__ __forceinline__ float sum_slots(const float *src, int e, int nseg, size_t slot_floats)
+// Sum of W floats at e over the slots of a slice, in ascending order; sixteen loads in flight.
+template <int W>
+__device__ __forceinline__ auto sum_slots(const float *src, int e, int nseg, size_t slot_floats)
 {
-    float run = 0.f;
-    for (int s0 = 0; s0 < nseg; s0 += 8) {
-        float x[8];
+    typedef typename std::conditional<W == 4, f4, float>::type T;
+    constexpr int BATCH = 16;
+    T run{};
+    for (int s0 = 0; s0 < nseg; s0 += BATCH) {
+        T x[BATCH];
 #pragma unroll
-        for (int i = 0; i < 8; ++i) x[i] = s0 + i < nseg ? src[(size_t)(s0 + i) * slot_floats + e] : 0.f;
+        for (int i = 0; i < BATCH; ++i)
+            x[i] = s0 + i < nseg ? *reinterpret_cast<const T *>(src + (size_t)(s0 + i) * slot_floats + e) : T{};
 #pragma unroll
-        for (int i = 0; i < 8; ++i)
+        for (int i = 0; i < BATCH; ++i)
             if (s0 + i < nseg) run = s0 + i == 0 ? x[i] : run + x[i];
     }
     return run;
 }
+template <typename T>
+__device__ __forceinline__ void put(float *dst, T x, int accumulate)
+{
+    T *d = reinterpret_cast<T *>(dst);
+    *d = accumulate ? *d + x : x;
+}
 
-// state (+)= the sums of [S | z | p] over the slots of every slice, count (+)= N
-template <int DUMMY>
+// state (+)= the sums of [S | z | p] over the slots of every slice, count (+)= N; W floats a thread.
+// With few slots a slice this is a copy, bound by memory: 16 bytes a thread (1024 slices of 20 rows,
+// D = 128, bf16, with the sums kernel: 37 us; 92 with 4 bytes).  With many, which only few slices
+// have, the round trips along the slots bound it: more threads, 4 bytes each (one slice of 60000
+// rows, 468 slots, D = 64, bf16: 22 us; 31 with 16 bytes).
+constexpr int kManySlots = 32;
+template <int W>
 __global__ __launch_bounds__(256) void k_state_from_totals(const float *__restrict__ ws,
                                                            float *__restrict__ state, int D,
                                                            int nseg, size_t slot_floats,
                                                            size_t state_floats, int N,
                                                            int accumulate)
 {
-    const int bh = blockIdx.x, len = D * D + 2 * D;
+    const int bh = blockIdx.x, len = D * D + 2 * D, e = W * (blockIdx.y * 256 + threadIdx.x);
     const float *src = ws + (size_t)bh * nseg * slot_floats;
     float *dst = state + (size_t)bh * state_floats;
-    for (int e = blockIdx.y * 256 + threadIdx.x; e <= len; e += gridDim.y * 256) {
-        const float x = e < len ? sum_slots(src, e, nseg, slot_floats) : (float)N;
-        dst[e] = accumulate ? dst[e] + x : x;
-    }
+    if (e < len) put(dst + e, sum_slots<W>(src, e, nseg, slot_floats), accumulate);
+    else if (e == len) put(dst + e, (float)N, accumulate);
 }
 
 // The same for D = 256 from the slots of the block problem (k block i, v block j) at D = 128:
 // S block (i, j); z block i (taken when j = 0); p block j (when i = 0); the count once.
+template <int W>
 __global__ __launch_bounds__(256) void k_state_block_from_totals(const float *__restrict__ ws,
                                                                  float *__restrict__ state,
                                                                  int nseg, size_t slot_floats,
@@ -177,30 +193,23 @@ __global__ __launch_bounds__(256) void k_state_block_from_totals(const float *__
                                                                  int bj, int N, int accumulate)
 {
     constexpr int H = 128, D = 256;
-    const int bh = blockIdx.x, len = H * H + 2 * H;
+    const int bh = blockIdx.x, len = H * H + 2 * H, e = W * (blockIdx.y * 256 + threadIdx.x);
     const float *src = ws + (size_t)bh * nseg * slot_floats;
     float *dst = state + (size_t)bh * state_floats;
-    for (int e = blockIdx.y * 256 + threadIdx.x; e <= len; e += gridDim.y * 256) {
-        float x;
-        int to;
-        if (e < H * H) {
-            x = sum_slots(src, e, nseg, slot_floats);
-            to = (bi * H + e / H) * D + bj * H + e % H;
-        } else if (e < H * H + H) {
-            if (bj != 0) continue;
-            x = sum_slots(src, e, nseg, slot_floats);
-            to = D * D + bi * H + (e - H * H);
-        } else if (e < len) {
-            if (bi != 0) continue;
-            x = sum_slots(src, e, nseg, slot_floats);
-            to = D * D + D + bj * H + (e - H * H - H);
-        } else {
-            if (bi != 0 || bj != 0) continue;
-            x = (float)N;
-            to = D * D + 2 * D;
-        }
-        dst[to] = accumulate ? dst[to] + x : x;
+    int to;
+    if (e < H * H) {
+        to = (bi * H + e / H) * D + bj * H + e % H;
+    } else if (e < H * H + H) {
+        if (bj != 0) return;
+        to = D * D + bi * H + (e - H * H);
+    } else if (e < len) {
+        if (bi != 0) return;
+        to = D * D + D + bj * H + (e - H * H - H);
+    } else {
+        if (e == len && bi == 0 && bj == 0) put(dst + D * D + 2 * D, (float)N, accumulate);
+        return;
     }
+    put(dst + to, sum_slots<W>(src, e, nseg, slot_floats), accumulate);
 }
 
 // Stage 1 of sum(X * Y): workgroup w sums a fixed contiguous share into partials[w].
@@ -330,11 +339,15 @@ la_status decode_step(const void *Q, const void *K, const void *V, void *O, floa
     return decode_by_d<bf16_t>(Q, K, V, O, G, state, BH, Tn, D, sf, a, b, st);
 }
 
+// Thread blocks for len floats and the count, W floats a thread.
+static int state_blocks(int len, int W) { return (len / W + 1 + 255) / 256; }
+
 la_status state_from_totals(const float *ws, float *state, int BH, int D, int nseg,
                             size_t slot_floats, int N, int accumulate, hipStream_t st)
 {
-    const int len = D * D + 2 * D + 1;
-    k_state_from_totals<0><<<dim3(BH, (len + 255) / 256), dim3(256), 0, st>>>(
+    const int W = nseg > kManySlots ? 1 : 4;
+    auto *kernel = W == 4 ? k_state_from_totals<4> : k_state_from_totals<1>;
+    kernel<<<dim3(BH, state_blocks(D * D + 2 * D, W)), dim3(256), 0, st>>>(
         ws, state, D, nseg, slot_floats, decode_state_floats(D), N, accumulate);
     return hipGetLastError() == hipSuccess ? LA_OK : LA_ERR_LAUNCH;
 }
@@ -343,8 +356,9 @@ la_status state_block_from_totals(const float *ws, float *state, int BH, int nse
                                   size_t slot_floats, int bi, int bj, int N, int accumulate,
                                   hipStream_t st)
 {
-    const int len = 128 * 128 + 2 * 128 + 1;
-    k_state_block_from_totals<<<dim3(BH, (len + 255) / 256), dim3(256), 0, st>>>(
+    const int W = nseg > kManySlots ? 1 : 4;
+    auto *kernel = W == 4 ? k_state_block_from_totals<4> : k_state_block_from_totals<1>;
+    kernel<<<dim3(BH, state_blocks(128 * 128 + 2 * 128, W)), dim3(256), 0, st>>>(
         ws, state, nseg, slot_floats, decode_state_floats(256), bi, bj, N, accumulate);
     return hipGetLastError() == hipSuccess ? LA_OK : LA_ERR_LAUNCH;
 }

@@ -122,3 +122,27 @@ def test_decode_argument_errors(la):
         la.la_decode_step(q48, q48.clone(), q48.clone(), q48.clone(), None, st, 1.0, 0.5)
     assert e.value.code == 3
     assert la.la_decode_state_bytes(1, 1, 48) == 0
+
+
+# one slot a slice, a batch of sixteen and one more, either side of the change to 4 bytes a thread
+@pytest.mark.parametrize("nseg", [1, 16, 17, 32, 33, 50])
+@pytest.mark.parametrize("D", [16, 64, 256])
+def test_prefill_adds_any_number_of_slots(la, D, nseg):
+    B, H, N = 1, 2, 64 * nseg - 3
+    dev, ref = draw(B * H, N, D, "f32", 900 + nseg)
+    K, V = dev["K"].view(B, H, N, D), dev["V"].view(B, H, N, D)
+    state = torch.zeros(la.la_decode_state_bytes(B, H, D) // 4, device="cuda")
+    try:
+        la.la_debug_override(64, 0)
+        ws = scratch(la.la_workspace_bytes(B, H, N, D, la.LA_F32, False, 0), "cuda")
+        la.la_decode_prefill(K, V, state, 0, ws)
+        once = canonical_state(state, B * H, D)
+        la.la_decode_prefill(K, V, state, 1, ws)
+        twice = canonical_state(state, B * H, D)
+    finally:
+        la.la_debug_override(0, 0)
+    k, v = ref["K"], ref["V"]
+    want = np.concatenate([np.einsum("bnr,bnj->brj", k, v).reshape(B * H, -1), k.sum(1), v.sum(1),
+                           np.full((B * H, 1), float(N))], axis=1)
+    assert excess(once, want, TOL["f32"]) <= 1.0
+    assert np.array_equal(twice, 2.0 * once)
