@@ -233,10 +233,11 @@ __global__ __launch_bounds__(NT) void k_scan_slots(float *__restrict__ ws, int n
     int e = blockIdx.y * NT + threadIdx.x;
     if (e >= len || hi < lo) return;
     float *p = ws + (size_t)blockIdx.x * nseg * slot_floats + off + e;
-    // The slots are read eight at a time before anything is added or written back: one
-    // memory round trip per eight slots instead of one per slot (the sums are formed in the
-    // same order either way).
-    constexpr int BATCH = 8;
+    // The slots are read sixteen at a time before anything is added or written back: one
+    // memory round trip per sixteen slots instead of one per slot (the sums are formed in the
+    // same order either way).  A step on one slice of 60000 rows (468 slots), bf16, D = 64: 143 us
+    // with 8, 133 with 16, 134 with 32; 36 slices of 14 slots: 108.7, 107.8, 110.7.
+    constexpr int BATCH = 16;
     float run = 0.f, lost = 0.f;
     const int n = hi - lo + 1;
     for (int i0 = 0; i0 < n; i0 += BATCH) {
