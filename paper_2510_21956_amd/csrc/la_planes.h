@@ -528,6 +528,33 @@ __device__ __forceinline__ void state_product(f4v (&hi)[2], f4v (&lo)[2], const 
         else __builtin_amdgcn_sched_barrier(0);
     }
 }
+// The same with a state that stays as it is, split once: the first LS of its LL planes.
+template <int D, int LS, int LL, int LY, typename LN>
+__device__ __forceinline__ void fixed_product(f4v (&hi)[2], f4v (&lo)[2], const bf8v (&sp)[D / 32][LL],
+                                              const __bf16 *y, const LN &ln)
+{
+    const int row = LN::local(ln.row);
+    constexpr int NK = D / 32, NM = 2 * products(LS, LY), AHEAD = NM <= 4 ? NK : 1;
+    bf8v f[AHEAD + 1][2][LY];
+#pragma unroll
+    for (int kt = 0; kt < AHEAD; ++kt)
+#pragma unroll
+        for (int m = 0; m < 2; ++m) load_rows<D, LY>(f[kt][m], y, row, m, kt);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int kt = 0; kt < NK; ++kt) {
+        const int cur = kt % (AHEAD + 1), nxt = (kt + AHEAD) % (AHEAD + 1);
+        if (kt + AHEAD < NK) {
+#pragma unroll
+            for (int m = 0; m < 2; ++m) load_rows<D, LY>(f[nxt][m], y, row, m, kt + AHEAD);
+        }
+        bf8v x[LS];
+#pragma unroll
+        for (int p = 0; p < LS; ++p) x[p] = sp[kt][p];
+        mma_pair<LS, LY, false>(hi, lo, x, f[cur]);
+        if (kt + AHEAD < NK) step_schedule<2 * LY, NM, 0>();
+    }
+}
 // One 16 x 16 block of X_rows . Y_rows^T over D, X natural (rows 16 xb), Y operand-ordered
 // (rows 16 yb): accumulator rows = rows of X, columns = rows of Y.
 template <int D, int LX, int LY, typename LN>

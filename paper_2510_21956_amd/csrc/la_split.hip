@@ -332,7 +332,7 @@ __global__ __launch_bounds__(4 * D, 2) void ks_kv_state(
 }
 
 // ---------------------------------------------------------------------------
-// Phase 3 (forward): Eq. fglast / div chunk by chunk.
+// Phase 3 (forward, masked): Eq. fglast / div chunk by chunk.
 //   f = tril(a + b Q_c K_c^T) V_c + a 1 p^T + b Q_c S ;  g = rowsum(tril) + a n + b Q_c z
 //   then S += K_c^T V_c, z += sum k, p += sum v
 // LD > D: the call works on D columns of rows LD wide and is one of several launches that
@@ -340,7 +340,7 @@ __global__ __launch_bounds__(4 * D, 2) void ks_kv_state(
 // in G; xflags & XF_ACC adds the numerator that O holds and the share of g in Gin first.  bf16
 // tensors keep the undivided numerator in Fraw instead (fp32, B*H*N rows of D): O is rounded once.
 // ---------------------------------------------------------------------------
-template <int MODE, int D, bool CAUSAL, int LD>
+template <int MODE, int D, int LD>
 __global__ __launch_bounds__(4 * D, 2) void ks_fwd_apply(
     const typename Mode<MODE>::TIO *__restrict__ Q, const typename Mode<MODE>::TIO *__restrict__ K,
     const typename Mode<MODE>::TIO *__restrict__ V, typename Mode<MODE>::TIO *__restrict__ O,
@@ -352,13 +352,12 @@ __global__ __launch_bounds__(4 * D, 2) void ks_fwd_apply(
     constexpr int LQ = MD::LQ, LV = MD::LV, LX = MD::LX;
     constexpr bool RAW32 = LD > D && sizeof(TIO) == 2;
     constexpr int NW = D / 16, NRB = D / 16, PL = Tile<D>::PLANE, WPL = Tile<32>::PLANE;
-    constexpr int TS = CAUSAL ? 1 : 0;
     typedef Chunk<TIO, D, LD> CH;
-    __shared__ __align__(16) __bf16 lds[(1 + TS) * LQ * PL + TS * (LV * PL + LX * WPL)];
+    __shared__ __align__(16) __bf16 lds[(2 * LQ + LV) * PL + LX * WPL];
     __shared__ __align__(16) float zs[D], qzs[CR], psum[2][CR], ginv[NW][CR];
     __shared__ __align__(16) float iq[MD::RN ? CR : 4], ik[MD::RN ? CR : 4];  // 1 / |q|, 1 / |k|
     __bf16 *Qt = lds;  // operand-ordered; K and V natural
-    __bf16 *Kt = Qt + LQ * PL, *Vt = Kt + TS * LQ * PL, *Pt = Vt + TS * LV * PL;
+    __bf16 *Kt = Qt + LQ * PL, *Vt = Kt + LQ * PL, *Pt = Vt + LV * PL;
 
     const int bh = blockIdx.x / nseg, seg = blockIdx.x % nseg;
     const size_t base = (size_t)bh * N * LD;
@@ -373,13 +372,12 @@ __global__ __launch_bounds__(4 * D, 2) void ks_fwd_apply(
     const bf8v one[1] = {ones_frag()};
 
     // initial state from the scanned slot: S[r][j], j = 16w + c
-    const bool zero_init = CAUSAL && seg == 0;
-    const float *slot = ws + ((size_t)bh * nseg + (CAUSAL ? seg : 0)) * slot_floats;
+    const float *slot = ws + ((size_t)bh * nseg + seg) * slot_floats;
     Blk st[NRB];
 #pragma unroll
     for (int rb = 0; rb < NRB; ++rb) st[rb].zero();
     f4v pacc = {0.f, 0.f, 0.f, 0.f}, zacc = pacc;  // p, z [16w + 4g + e]
-    if (!zero_init) {
+    if (seg > 0) {
 #pragma unroll
         for (int rb = 0; rb < NRB; ++rb)
 #pragma unroll
@@ -389,18 +387,7 @@ __global__ __launch_bounds__(4 * D, 2) void ks_fwd_apply(
     }
     if (c == 0) *reinterpret_cast<f4v *>(zs + w * 16 + 4 * g) = zacc;
     // the block above the diagonal stays zero
-    if constexpr (CAUSAL) {
-        if (t < 64) store_weights<LX>(Pt, c, 1, g, f4v{0.f, 0.f, 0.f, 0.f});
-    }
-    // Hand-over to the backward pass: entry s = [S^T | z] over all rows before segment s (with
-    // the mask); entry 0 the sums over the whole sequence (without).
-    if (!CAUSAL && saved && seg == 0) {
-        float *dst = saved + (size_t)bh * nseg * saved_floats;
-#pragma unroll
-        for (int rb = 0; rb < NRB; ++rb)
-            *reinterpret_cast<f4v *>(dst + (w * 16 + c) * D + rb * 16 + 4 * g) = st[rb].v;
-        if (c == 0) *reinterpret_cast<f4v *>(dst + D * D + w * 16 + 4 * g) = zacc;
-    }
+    if (t < 64) store_weights<LX>(Pt, c, 1, g, f4v{0.f, 0.f, 0.f, 0.f});
 
     struct Set {
         CH q, k, v;
@@ -410,10 +397,8 @@ __global__ __launch_bounds__(4 * D, 2) void ks_fwd_apply(
     for (int i = 0; i < MD::DEPTH; ++i) {
         const long ci = min(row0 + i * CR, c_last);
         sets[i].q.load(Qp, ci, N);
-        if constexpr (CAUSAL) {
-            sets[i].k.load(Kp, ci, N);
-            sets[i].v.load(Vp, ci, N);
-        }
+        sets[i].k.load(Kp, ci, N);
+        sets[i].v.load(Vp, ci, N);
     }
     auto chunk = [&](long c0, Set &cur) __attribute__((always_inline)) {
         const bool lo_on = c0 < sm.lo_rows;  // second plane of the intermediates: early rows
@@ -433,50 +418,43 @@ __global__ __launch_bounds__(4 * D, 2) void ks_fwd_apply(
             if constexpr (LQ == 1) cur.q.template store<true, 1>(Qt);
             else CH::template store_values<true, LQ>(Qt, x);
         }
-        if constexpr (CAUSAL) {
-            stage<MD::NORM, false, LQ>(cur.k, Kt, MD::RN ? ik : nullptr);
-            cur.v.template store<false, LV>(Vt);
-            if (__builtin_expect(cur.v.top() > kLargestBf16, 0)) cur.v.template store_any<false>(Vt);
-        }
+        stage<MD::NORM, false, LQ>(cur.k, Kt, MD::RN ? ik : nullptr);
+        cur.v.template store<false, LV>(Vt);
+        if (__builtin_expect(cur.v.top() > kLargestBf16, 0)) cur.v.template store_any<false>(Vt);
         block_sync();
         const long cn = min(c0 + MD::DEPTH * CR, c_last);
         cur.q.load(Qp, cn, N);
 
         // ---- phase A: weight blocks P = tril(a + b Q K^T), rows n, columns i ----
-        if constexpr (CAUSAL) {
 #pragma unroll 1
-            for (int pidx = w; pidx < 3; pidx += NW) {
-                const int ib = pidx ? 1 : 0, nb = pidx == 2 ? 1 : 0;
-                f4v pa = block_product<D, LQ, LQ>(Kt, nb, Qt, ib, ln);
-                if constexpr (MD::RN)  // one factor after the other: their product may overflow
-                    pa = (pa * iq[ib * 16 + c]) * *reinterpret_cast<const f4v *>(ik + nb * 16 + 4 * g);
-                const int last = nb == ib ? c : 15;  // last row n at or before row i
-                f4v x;
+        for (int pidx = w; pidx < 3; pidx += NW) {
+            const int ib = pidx ? 1 : 0, nb = pidx == 2 ? 1 : 0;
+            f4v pa = block_product<D, LQ, LQ>(Kt, nb, Qt, ib, ln);
+            if constexpr (MD::RN)  // one factor after the other: their product may overflow
+                pa = (pa * iq[ib * 16 + c]) * *reinterpret_cast<const f4v *>(ik + nb * 16 + 4 * g);
+            const int last = nb == ib ? c : 15;  // last row n at or before row i
+            f4v x;
 #pragma unroll
-                for (int e = 0; e < 4; ++e) x[e] = 4 * g + e > last ? 0.f : a + b * pa[e];
-                with_planes<LX>(lo_on, [&](auto n) { store_weights<n.value>(Pt, ib * 16 + c, nb, g, x); });
-                const float rs = reduce_lane_groups((x[0] + x[1]) + (x[2] + x[3]));
-                if (g == 0) psum[nb][ib * 16 + c] = rs;
-            }
-            cur.k.load(Kp, cn, N);
+            for (int e = 0; e < 4; ++e) x[e] = 4 * g + e > last ? 0.f : a + b * pa[e];
+            with_planes<LX>(lo_on, [&](auto n) { store_weights<n.value>(Pt, ib * 16 + c, nb, g, x); });
+            const float rs = reduce_lane_groups((x[0] + x[1]) + (x[2] + x[3]));
+            if (g == 0) psum[nb][ib * 16 + c] = rs;
         }
+        cur.k.load(Kp, cn, N);
         // The product with the state needs nothing of phase A.
         f4v fh[2], fl[2];  // rows j = 16w + 4g + e, columns i
 #pragma unroll
         for (int m = 0; m < 2; ++m) fh[m] = fl[m] = f4v{0.f, 0.f, 0.f, 0.f};
         with_planes<LX>(lo_on, [&](auto n) { state_product<D, n.value, LQ, false>(fh, fl, st, Qt, ln); });
         bf8v vf[LV];
-        if constexpr (CAUSAL) {
-            load_cols<D, LV>(vf, Vt, ln.local(ln.col), w);
-            cur.v.load(Vp, cn, N);
-        }
+        load_cols<D, LV>(vf, Vt, ln.local(ln.col), w);
+        cur.v.load(Vp, cn, N);
         block_sync();
 
         // ---- phase B: denominators; V^T P^T on top, divide, store ----
         if (l < CR) {
-            float ps = 0.f;
-            if constexpr (CAUSAL) ps = psum[0][l] + (l >= 16 ? psum[1][l] : 0.f);
-            float gv = b * qzs[l] + a * (CAUSAL ? (float)c0 : (float)N) + ps;
+            const float ps = psum[0][l] + (l >= 16 ? psum[1][l] : 0.f);
+            float gv = b * qzs[l] + a * (float)c0 + ps;
             const bool valid = l < (int)(row1 - c0);
             if constexpr (LD > D) {
                 if ((xflags & XF_ACC) && valid) gv += (Gin + (size_t)bh * N + c0)[l];
@@ -490,13 +468,11 @@ __global__ __launch_bounds__(4 * D, 2) void ks_fwd_apply(
 #pragma unroll
         for (int m = 0; m < 2; ++m) {
             f4v f = (MD::RN ? b * iq[m * 16 + c] : b) * (fh[m] + fl[m]);
-            if constexpr (CAUSAL) {
-                with_planes<LX>(lo_on, [&](auto n) {
-                    bf8v pf[n.value];
-                    load_rows<32, n.value>(pf, Pt, lw.row, m, 0);
-                    f += step_product<LV, n.value>(vf, pf);
-                });
-            }
+            with_planes<LX>(lo_on, [&](auto n) {
+                bf8v pf[n.value];
+                load_rows<32, n.value>(pf, Pt, lw.row, m, 0);
+                f += step_product<LV, n.value>(vf, pf);
+            });
             const f4v y = (f + a * pacc) * ginv[w][m * 16 + c];
             if (LD < D && w * 16 >= LD) break;  // columns that are not there
             const int nrows = (int)(row1 - c0) - m * 16;
@@ -507,35 +483,155 @@ __global__ __launch_bounds__(4 * D, 2) void ks_fwd_apply(
                 store_block<TIO>(Op + (size_t)(c0 + m * 16) * LD, LD, w * 16, nrows, l, y[0], y[1], y[2],
                                  y[3], (LD > D && (xflags & XF_ACC)) ? 2 : 0, &ginv[w][m * 16], fr, D);
         }
-        if constexpr (CAUSAL) {
-            pacc += step_product<LV, 1>(vf, one);
-            bf8v kf[LQ];
-            load_cols<D, LQ>(kf, Kt, ln.local(ln.col), w);
-            if constexpr (MD::RN) {
-                bf8v fk[3], vh[3];
-                factor_frag(fk, ik, g);
-                zacc += step_product<LQ, 3>(kf, fk);
-                scale_frag<3>(vh, vf, ik, g);
-                rank_update<D, LQ, 3>(st, Kt, vh, ln);
-            } else {
-                zacc += step_product<LQ, 1>(kf, one);
-                rank_update<D, LQ, LV>(st, Kt, vf, ln);
-            }
-            // zs was read while this chunk was staged; it is read again behind the barrier at
-            // the top of the next one
-            if (c == 0) *reinterpret_cast<f4v *>(zs + w * 16 + 4 * g) = zacc;
+        pacc += step_product<LV, 1>(vf, one);
+        bf8v kf[LQ];
+        load_cols<D, LQ>(kf, Kt, ln.local(ln.col), w);
+        if constexpr (MD::RN) {
+            bf8v fk[3], vh[3];
+            factor_frag(fk, ik, g);
+            zacc += step_product<LQ, 3>(kf, fk);
+            scale_frag<3>(vh, vf, ik, g);
+            rank_update<D, LQ, 3>(st, Kt, vh, ln);
+        } else {
+            zacc += step_product<LQ, 1>(kf, one);
+            rank_update<D, LQ, LV>(st, Kt, vf, ln);
         }
+        // zs was read while this chunk was staged; it is read again behind the barrier at
+        // the top of the next one
+        if (c == 0) *reinterpret_cast<f4v *>(zs + w * 16 + 4 * g) = zacc;
     };
     for (long c0 = row0; c0 < row1; c0 += MD::DEPTH * CR) {
         chunk(c0, sets[0]);
         if (MD::DEPTH == 2 && c0 + CR < row1) chunk(c0 + CR, sets[MD::DEPTH - 1]);
     }
-    if (CAUSAL && saved && seg + 1 < nseg) {
+    // hand-over to the backward pass: entry s = [S^T | z] over all rows before segment s
+    if (saved && seg + 1 < nseg) {
         float *dst = saved + ((size_t)bh * nseg + seg + 1) * saved_floats;
 #pragma unroll
         for (int rb = 0; rb < NRB; ++rb)
             *reinterpret_cast<f4v *>(dst + (w * 16 + c) * D + rb * 16 + 4 * g) = st[rb].v;
         if (c == 0) *reinterpret_cast<f4v *>(dst + D * D + w * 16 + 4 * g) = zacc;
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Phase 3 (forward, unmasked): every row reads the same sums, f = a p + b Q S, g = a N + b Q z.
+// The rows are cut as fills the chip best, rows_wg a workgroup, whatever the segments were; the
+// state is split into planes once.  Bound by memory and by what a workgroup needs before its first
+// row (the 4 D^2 bytes of the state, out of L2).  bf16 stages 64 rows between its two barriers.
+// FIGURES
+// LD > D, xflags, Gin and Fraw as above.
+// ---------------------------------------------------------------------------
+template <int MODE, int D, int LD>
+__global__ __launch_bounds__(4 * D, 2) void ks_fwd_read(
+    const typename Mode<MODE>::TIO *__restrict__ Q, typename Mode<MODE>::TIO *__restrict__ O,
+    float *__restrict__ G, const float *__restrict__ ws, float *__restrict__ saved, int N, int nseg,
+    int nwg, int rows_wg, int lo_rows, size_t slot_floats, size_t saved_floats, float a, float b,
+    int xflags, const float *__restrict__ Gin, float *__restrict__ Fraw)
+{
+    typedef Mode<MODE> MD;
+    typedef typename MD::TIO TIO;
+    constexpr int LQ = MD::LQ, LX = MD::LX, NT = MD::DEPTH;
+    constexpr bool RAW32 = LD > D && sizeof(TIO) == 2;
+    constexpr int NW = D / 16, NRB = D / 16, PL = Tile<D>::PLANE;
+    typedef Chunk<TIO, D, LD> CH;
+    __shared__ __align__(16) __bf16 lds[NT * LQ * PL];  // operand-ordered tiles of Q
+    __shared__ __align__(16) float zs[D], qzs[NT * CR], ginv[NW][NT * CR], iqb[MD::RN ? NT * CR : 4];
+
+    const int bh = blockIdx.x / nwg, part = blockIdx.x % nwg;
+    const size_t base = (size_t)bh * N * LD;
+    const TIO *Qp = Q + base;
+    TIO *Op = O + base;
+    float *Gp = G + (size_t)bh * N;
+    const long row0 = (long)part * rows_wg, row1 = min(row0 + rows_wg, (long)N);
+    const int t = threadIdx.x, l = t % 64, c = l % 16, g = l / 16;
+    const int w = __builtin_amdgcn_readfirstlane(t / 64);
+    const Lanes<D> ln(c, g);
+
+    CH sets[NT];
+    const long c_last = row0 + (row1 - row0 - 1) / CR * CR;
+#pragma unroll
+    for (int i = 0; i < NT; ++i) sets[i].load(Qp, min(row0 + i * CR, c_last), N);
+
+    const float *slot = ws + (size_t)bh * nseg * slot_floats;
+    Blk st[NRB];
+#pragma unroll
+    for (int rb = 0; rb < NRB; ++rb)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) st[rb].set(i, slot[(rb * 16 + 4 * g + i) * D + w * 16 + c]);
+    const f4v pacc = *reinterpret_cast<const f4v *>(slot + D * D + D + w * 16 + 4 * g);
+    const f4v zacc = *reinterpret_cast<const f4v *>(slot + D * D + w * 16 + 4 * g);
+    if (c == 0) *reinterpret_cast<f4v *>(zs + w * 16 + 4 * g) = zacc;
+    // hand-over to the backward pass: entry 0 = [S^T | z] over the whole sequence
+    if (saved && part == 0) {
+        float *dst = saved + (size_t)bh * nseg * saved_floats;
+#pragma unroll
+        for (int rb = 0; rb < NRB; ++rb)
+            *reinterpret_cast<f4v *>(dst + (w * 16 + c) * D + rb * 16 + 4 * g) = st[rb].v;
+        if (c == 0) *reinterpret_cast<f4v *>(dst + D * D + w * 16 + 4 * g) = zacc;
+    }
+    bf8v sp[D / 32][LX];
+#pragma unroll
+    for (int kt = 0; kt < D / 32; ++kt) split_frag<LX>(st[2 * kt].v, st[2 * kt + 1].v, sp[kt]);
+
+    auto put = [&](int i) __attribute__((always_inline)) {
+        f4v x[2] = {sets[i].value(0), sets[i].value(1)};
+        if constexpr (MD::NORM) normalise_quads<CH>(x, MD::RN ? iqb + i * CR : nullptr);
+        float s[2];
+#pragma unroll
+        for (int k = 0; k < 2; ++k) s[k] = dot4(x[k], *reinterpret_cast<const f4v *>(zs + 4 * CH::quad(k)));
+        CH::row_totals(s);
+        if (CH::leader()) {
+#pragma unroll
+            for (int k = 0; k < 2; ++k) qzs[i * CR + CH::row(k)] = s[k];
+        }
+        if constexpr (LQ == 1) sets[i].template store<true, 1>(lds + i * PL);
+        else CH::template store_values<true, LQ>(lds, x);
+    };
+    auto rows = [&](long c0, int i) __attribute__((always_inline)) {
+        f4v fh[2], fl[2];  // rows j = 16w + 4g + e, columns i
+#pragma unroll
+        for (int m = 0; m < 2; ++m) fh[m] = fl[m] = f4v{0.f, 0.f, 0.f, 0.f};
+        with_planes<LX>(c0 < lo_rows, [&](auto n) {
+            fixed_product<D, n.value, LX, LQ>(fh, fl, sp, lds + i * LQ * PL, ln);
+        });
+#pragma unroll
+        for (int m = 0; m < 2; ++m) {
+            const int r = i * CR + m * 16;
+            const f4v f = (MD::RN ? b * iqb[r + c] : b) * (fh[m] + fl[m]);
+            const f4v y = (f + a * pacc) * ginv[w][r + c];
+            if (LD < D && w * 16 >= LD) break;  // columns that are not there
+            const int nrows = (int)(row1 - c0) - m * 16;
+            float *fr = RAW32 ? Fraw + ((size_t)bh * N + c0 + m * 16) * D : nullptr;
+            if (RAW32 && (xflags & XF_RAW))
+                store_block<float>(fr, D, w * 16, nrows, l, y[0], y[1], y[2], y[3]);
+            else
+                store_block<TIO>(Op + (size_t)(c0 + m * 16) * LD, LD, w * 16, nrows, l, y[0], y[1], y[2],
+                                 y[3], (LD > D && (xflags & XF_ACC)) ? 2 : 0, &ginv[w][r], fr, D);
+        }
+    };
+    for (long c0 = row0; c0 < row1; c0 += NT * CR) {
+        const bool two = NT == 2 && c0 + CR < row1;
+        block_sync();  // zs is written; every wave is done with the tiles, qzs and the factors
+        put(0);
+        if (NT == 2) sets[0].load(Qp, min(c0 + 2 * CR, c_last), N);
+        if (two) put(NT - 1);
+        block_sync();
+        sets[NT - 1].load(Qp, min(c0 + (2 * NT - 1) * CR, c_last), N);
+        if (l < (two ? 2 * CR : CR)) {
+            float gv = b * qzs[l] + a * (float)N;
+            const bool valid = l < (int)(row1 - c0);
+            if constexpr (LD > D) {
+                if ((xflags & XF_ACC) && valid) gv += (Gin + (size_t)bh * N + c0)[l];
+                ginv[w][l] = (xflags & XF_RAW) ? 1.f : 1.f / gv;
+            } else {
+                ginv[w][l] = 1.f / gv;
+            }
+            if (w == 0 && G && valid) (Gp + c0)[l] = gv;
+        }
+        __builtin_amdgcn_wave_barrier();
+        rows(c0, 0);
+        if (two) rows(c0 + CR, NT - 1);
     }
 }
 
@@ -596,7 +692,7 @@ __global__ __launch_bounds__(4 * D, 2) void ks_bwd_dq(
         st[jb].zero();
     }
     Sum<SWAP> zacc, uacc;      // z, u
-    Sum<SWAP, !CAUSAL> wacc;  // w: without the mask, most of dV
+    Sum<SWAP, !CAUSAL && QT> wacc;  // w: without the mask, most of dV (fp32: bf16 rounds it anyway)
     if (!zero_init) {
 #pragma unroll
         for (int jb = 0; jb < NRB; ++jb)
@@ -1014,6 +1110,19 @@ __global__ __launch_bounds__(4 * D, 2) void ks_bwd_dkv(
     }
 }
 
+// Rows a workgroup of ks_fwd_read takes, 128 at least: eight workgroups a CU at D <= 32, four beyond
+// (as many as registers allow).  At D = 128 a workgroup reads a state of 64 KB first, as much as 128
+// bf16 rows in and out, so that short sequences get two or one a CU instead of less than 160 rows.
+// bf16, D = 128, forward pass, 192 slices of 300 rows: 25.8 us at 128 rows, 22.5 at 300; 80 of 1000:
+// 35.3 at 128, 33.0 at 192, 35.1 at 320; 12 of 500: 16.8 at 128, 20.2 at 320.
+int read_rows(int BH, int N, int D)
+{
+    for (int per_cu = D <= 32 ? 8 : 4;; per_cu /= 2) {
+        const long want = max((256L * per_cu + BH / 2) / BH, 1L), rows = (N + want - 1) / want;
+        if (D < 128 || rows >= 160 || per_cu == 1) return (int)((max(rows, 128L) + 63) / 64 * 64);
+    }
+}
+
 template <int MODE, int D, int LD>
 la_status run_forward(const Problem &pr, const Plan &pl, const void *Qv, const void *Kv,
                       const void *Vv, void *Ov, float *G, float *ws, float *saved, hipStream_t st,
@@ -1032,10 +1141,16 @@ la_status run_forward(const Problem &pr, const Plan &pl, const void *Qv, const v
                           pr.causal ? 1 : 0, nseg - 1, st);
         tc.mark("scan_slots");
     }
-    auto *kernel = pr.causal ? ks_fwd_apply<MODE, D, true, LD> : ks_fwd_apply<MODE, D, false, LD>;
-    kernel<<<dim3(pr.BH * nseg), block, 0, st>>>(Q, K, V, O, G, ws, saved, pr.N, nseg, pl.map,
-                                                 pl.slot_floats, pl.saved_floats, pr.a, pr.b, xflags,
-                                                 Gin, Fraw);
+    if (pr.causal) {
+        ks_fwd_apply<MODE, D, LD><<<dim3(pr.BH * nseg), block, 0, st>>>(
+            Q, K, V, O, G, ws, saved, pr.N, nseg, pl.map, pl.slot_floats, pl.saved_floats, pr.a, pr.b,
+            xflags, Gin, Fraw);
+    } else {
+        const int rows_wg = read_rows(pr.BH, pr.N, D), nwg = (pr.N + rows_wg - 1) / rows_wg;
+        ks_fwd_read<MODE, D, LD><<<dim3(pr.BH * nwg), block, 0, st>>>(
+            Q, O, G, ws, saved, pr.N, nseg, nwg, rows_wg, pl.map.lo_rows, pl.slot_floats,
+            pl.saved_floats, pr.a, pr.b, xflags, Gin, Fraw);
+    }
     tc.mark("fwd_apply");
     return launch_status();
 }
