@@ -23,9 +23,15 @@ static bool supported_d(int D) { return D == 16 || D == 32 || D == 64 || D == 12
 // unit then gets the same number of equally long segments in a single round.  The sweeps of
 // the backward pass set that number (registers and LDS): one at D = 128 and two at D = 64
 // (measured at D = 64, bf16, 36 slices of 5003 rows: 159 us a step for one, 117 for two, 127
-// for three; fp32, 64 slices of 4096: 377, 305, 361), four at D = 32.  Without the mask the
-// ascending sweep, which holds two states, sets it: two (fp32) or three (bf16) at D = 64, one
-// at D = 128 (fp32, 32 slices of 8192 rows: 417 us a step, 445 for two, 488 for four).
+// for three; fp32, 64 slices of 4096: 377, 305, 361), four at D = 32.  The same without the mask
+// (us a step for one, two, three: D = 128, fp32, 4 slices of 10^5 rows 676, 714, 745; bf16, 32 of
+// 8192 225, 244, 247, and the forward pass alone 69, 76, 80, the sums for a prompt alone 17, 19, 19
+// (32 of 3001); D = 64, bf16, 64 of 16384 412, 362, 371, 80 of 3000 120, 105, 121; D = 32, bf16,
+// 16 of 131072 599, 407, 358, and 350 for four).
+// At D = 64 without the mask the nearest number may leave some compute units a segment more than
+// others where one segment more a slice would not: 192 slices of 1000 rows, three segments of 384
+// rows (three a unit at most, 576 in all) or four of 256 (768): 163 and 151 us a step in fp32, 96
+// and 91 in bf16.
 // Segments are also kept long enough that the D x D state a segment hands over stays small
 // next to the rows it covers (a sixth of their bytes at the shortest: short sequences in few
 // slices would otherwise leave most of the chip idle).  la_debug_override can force a length
@@ -35,12 +41,16 @@ Plan make_plan(int B, int H, int N, int D, la_dtype dt, int causal, int is_backw
     Plan p;
     const long BH = (long)B * H;
     const int min_len = (D >= 128) ? 192 : 128;
-    const long resident = D == 256 ? 1
-                          : D <= 32 ? 4
-                          : D == 64 ? (!causal && dt == LA_BF16 ? 3 : 2)
-                                    : 1;
+    const long resident = D == 256 ? 1 : D <= 32 ? 4 : D == 64 ? 2 : 1;
     const long target = 256 * resident;
     long want = (target + BH / 2) / BH;  // nearest number of segments per slice
+    if (!causal && D == 64 && BH * (want + 1) <= 1024) {
+        // rows of the compute unit with the most segments
+        const auto load = [&](long n) {
+            return (BH * n + 255) / 256 * (long)round_up((size_t)((N + n - 1) / n), 64);
+        };
+        if (want >= 1 && 10 * load(want + 1) <= 9 * load(want)) ++want;
+    }
     long max_by_len = N / min_len;
     if (max_by_len < 1) max_by_len = 1;
     if (want > max_by_len) want = max_by_len;
