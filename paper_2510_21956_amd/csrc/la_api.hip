@@ -165,11 +165,11 @@ static bool use_padded(const Problem &pr)
     return pr.D == 16 && !g_force_generic.load(std::memory_order_relaxed);
 }
 
+// The matrix-core kernels on tiles of the head size itself, with the hand-over buffer.
 // la_debug_override can force the plain-ALU kernels (for A/B comparison and debugging).
-static bool use_fast(const Problem &pr, int is_backward)
+static bool use_fast(const Problem &pr)
 {
-    if (g_force_generic.load(std::memory_order_relaxed)) return false;
-    return fast_supported(pr, is_backward);
+    return (pr.D == 32 || pr.D == 64 || pr.D == 128) && !g_force_generic.load(std::memory_order_relaxed);
 }
 
 
@@ -242,7 +242,7 @@ size_t la_workspace_bytes(int B, int H, int N, int D, la_dtype dt, int causal, i
     if (!la::grid_ok(B, H, pl)) return 0;
     if (is_backward == 3) {
         la::Problem pr{B * H, N, D, 1.f, 1.f, causal ? 1 : 0, dt};
-        return la::ab_layout(pl, (size_t)B * H * N, D, dt, la::use_fast(pr, 1) || D == 256)
+        return la::ab_layout(pl, (size_t)B * H * N, D, dt, la::use_fast(pr) || D == 256)
             .total_bytes;
     }
     if (is_backward != 2) return pl.total_bytes;
@@ -254,7 +254,7 @@ size_t la_saved_state_bytes(int B, int H, int N, int D, la_dtype dt, int causal)
 {
     if (la::check_shape(B, H, N, D, dt) != LA_OK) return 0;
     la::Problem pr{B * H, N, D, 1.f, 0.f, causal ? 1 : 0, dt};
-    if (!la::use_fast(pr, 0) || !la::use_fast(pr, 1)) return 0;
+    if (!la::use_fast(pr)) return 0;
     return la::make_plan(B, H, N, D, dt, causal, 0).saved_bytes;
 }
 
@@ -278,10 +278,10 @@ static la_status forward_impl(const void *Q, const void *K, const void *V, void 
     if (!workspace || workspace_bytes < pl.total_bytes || (((uintptr_t)workspace) & 255u))
         return LA_ERR_WORKSPACE;
     la::Problem pr{B * H, N, D, a, b, causal ? 1 : 0, dt, norm_qk};
-    const bool fast = la::use_fast(pr, 0);
+    const bool fast = la::use_fast(pr);
     if (!fast) pl.map.cost_seg = 0;  // the plain-ALU kernels cut uniformly (same segment count)
     float *sv = nullptr;
-    if (save && fast && la::use_fast(pr, 1)) {
+    if (save && fast) {
         if (!saved || saved_bytes < pl.saved_bytes || (((uintptr_t)saved) & 255u))
             return LA_ERR_WORKSPACE;
         sv = (float *)saved;
@@ -297,8 +297,8 @@ static la_status forward_impl(const void *Q, const void *K, const void *V, void 
     if (hipPeekAtLastError() != hipSuccess) return LA_ERR_LAUNCH;  // left pending, nothing enqueued
     la::Tracer tc(trace, (hipStream_t)hip_stream);
     if (fast || (pad16 && la::use_padded(pr)))
-        return la::fast_forward(pr, pl, Q, K, V, O, G, (float *)workspace, sv,
-                                (hipStream_t)hip_stream, tc);
+        return la::planes_forward(pr, pl, D, Q, K, V, O, G, (float *)workspace, sv,
+                                  (hipStream_t)hip_stream, tc);
     if (D == 256)
         return la::forward_256(pr, pl, B, H, Q, K, V, O, G, (float *)workspace,
                                (hipStream_t)hip_stream, tc);
@@ -332,13 +332,13 @@ static la_status backward_impl(const void *Q, const void *K, const void *V, cons
     if (!workspace || workspace_bytes < need || (((uintptr_t)workspace) & 255u))
         return LA_ERR_WORKSPACE;
     la::Problem pr{B * H, N, D, a, b, causal ? 1 : 0, dt, norm_qk};
-    const bool fast = la::use_fast(pr, 1);
+    const bool fast = la::use_fast(pr);
     if (!fast) {  // the plain-ALU kernels cut uniformly (same segment count)
         pl.map.cost_seg = 0;
         pf.map.cost_seg = 0;
     }
     const float *sv = nullptr;
-    if (use_saved && fast && la::use_fast(pr, 0)) {
+    if (use_saved && fast) {
         if (!saved || saved_bytes < pl.saved_bytes || (((uintptr_t)saved) & 255u))
             return LA_ERR_WORKSPACE;
         sv = (const float *)saved;
@@ -354,13 +354,13 @@ static la_status backward_impl(const void *Q, const void *K, const void *V, cons
     if (hipPeekAtLastError() != hipSuccess) return LA_ERR_LAUNCH;  // left pending, nothing enqueued
     hipStream_t st = (hipStream_t)hip_stream;
     la::Tracer tc(trace, st);
+    const bool planes = fast || la::use_padded(pr);
     if (recompute) {
         char *wsb = (char *)workspace;
         void *o2 = wsb + rc.o_off;
         float *g2 = (float *)(wsb + rc.g_off);
-        const bool ffast = la::use_fast(pr, 0) || la::use_padded(pr);
-        s = ffast ? la::fast_forward(pr, pf, Q, K, V, o2, g2, (float *)(wsb + rc.fwd_ws_off),
-                                     nullptr, st, tc)
+        s = planes ? la::planes_forward(pr, pf, D, Q, K, V, o2, g2, (float *)(wsb + rc.fwd_ws_off),
+                                        nullptr, st, tc)
             : D == 256
                 ? la::forward_256(pr, pf, B, H, Q, K, V, o2, g2, (float *)(wsb + rc.fwd_ws_off), st,
                                   tc)
@@ -370,9 +370,8 @@ static la_status backward_impl(const void *Q, const void *K, const void *V, cons
         if (!O) O = o2;
         if (!G) G = g2;
     }
-    const bool planes = fast || la::use_padded(pr);
-    s = planes ? la::fast_backward(pr, pl, Q, K, V, O, G, dO, dQ, dK, dV, (float *)workspace, sv, st,
-                                 tc)
+    s = planes ? la::planes_backward(pr, pl, D, Q, K, V, O, G, dO, dQ, dK, dV, (float *)workspace, sv,
+                                     st, tc)
         : D == 256
             ? la::backward_256(pr, pl, B, H, Q, K, V, O, G, dO, dQ, dK, dV, (float *)workspace, st,
                                tc)
@@ -448,7 +447,7 @@ la_status la_backward_ab(const void *Q, const void *K, const void *V, const void
     if (!la::grid_ok(B, H, pl)) return LA_ERR_SHAPE;
     // the sweep below runs with b = 1: its scale is taken out again by the formula
     la::Problem pr{B * H, N, D, a, 1.f, causal ? 1 : 0, dt};
-    const bool fast = la::use_fast(pr, 1);
+    const bool fast = la::use_fast(pr);
     const size_t T = (size_t)B * H * N;
     const la::AbLayout lay = la::ab_layout(pl, T, D, dt, fast || D == 256);
     if (!workspace || workspace_bytes < lay.total_bytes || (((uintptr_t)workspace) & 255u))
@@ -463,14 +462,14 @@ la_status la_backward_ab(const void *Q, const void *K, const void *V, const void
     hipStream_t st = (hipStream_t)hip_stream;
     char *wsb = (char *)workspace;
     void *dq1 = wsb + lay.dq_off;
+    la::Tracer tc(nullptr, st);
     if (fast) {
-        s = la::fast_backward_dq(pr, pl, Q, K, V, O, G, dO, dq1, (float *)workspace, st);
+        s = la::planes_backward(pr, pl, D, Q, K, V, O, G, dO, dq1, nullptr, nullptr, (float *)workspace,
+                                nullptr, st, tc);
     } else if (D == 256) {
-        la::Tracer tc(nullptr, st);
         s = la::backward_256(pr, pl, B, H, Q, K, V, O, G, dO, dq1, nullptr, nullptr,
                              (float *)workspace, st, tc);
     } else {
-        la::Tracer tc(nullptr, st);
         s = la::generic_backward(pr, pl, Q, K, V, O, G, dO, dq1, wsb + lay.dk_off,
                                  wsb + lay.dv_off, (float *)workspace, st, tc);
     }
@@ -577,8 +576,8 @@ la_status la_decode_prefill(const void *K, const void *V, float *state, size_t s
     if (D == 256)
         return la::split_prefill(pr, la::make_plan(B, H, N, 128, dt, 0, 0), K, V,
                                  (float *)workspace, state, accumulate ? 1 : 0, st);
-    s = la::use_fast(pr, 0) ? la::fast_kv_totals(pr, pl, K, V, (float *)workspace, st)
-                            : la::generic_kv_totals(pr, pl, K, V, (float *)workspace, st);
+    s = la::use_fast(pr) ? la::planes_totals(pr, pl, D, K, V, (float *)workspace, st)
+                         : la::generic_kv_totals(pr, pl, K, V, (float *)workspace, st);
     if (s != LA_OK) return s;
     return la::state_from_totals((const float *)workspace, state, B * H, D, pl.nseg, pl.slot_floats,
                                  N, accumulate ? 1 : 0, st);

@@ -139,23 +139,21 @@ __device__ __forceinline__ void store_block(T *base, int ld, int col0, int rows_
     }
 }
 
-// One 16-row block of a gradient.  With LD > D (a block of D columns of rows LD wide) the
-// gradient is the sum of two launches: fp32 tensors add in place (`add` in the second launch);
-// bf16 tensors keep the first launch's share in `part` (fp32, rows of D: early rows of a masked
-// pass are small differences of large shares) and the second launch adds it and rounds once.
-template <typename TIO, int D, int LD>
-__device__ __forceinline__ void store_grad_block(TIO *out, float *part, bool add, int col0,
+// One 16-row block of a bf16 gradient.  With LD > D (a block of D columns of rows LD wide) the
+// gradient is the sum of two launches: the first keeps its share in `part` (fp32, rows of D: early
+// rows of a masked pass are small differences of large shares) and the second (`add`) adds it and
+// rounds once.  (fp32 gradients are stored by columns and added up in place.)
+template <int D, int LD>
+__device__ __forceinline__ void store_grad_block(__bf16 *out, float *part, bool add, int col0,
                                                  int rows_valid, int l, float x0, float x1,
                                                  float x2, float x3)
 {
     if constexpr (LD <= D)
-        store_block<TIO>(out, LD, col0, rows_valid, l, x0, x1, x2, x3);
-    else if constexpr (sizeof(TIO) == 4)
-        store_block<TIO>(out, LD, col0, rows_valid, l, x0, x1, x2, x3, add ? 1 : 0);
+        store_block<__bf16>(out, LD, col0, rows_valid, l, x0, x1, x2, x3);
     else if (!add)
         store_block<float>(part, D, col0, rows_valid, l, x0, x1, x2, x3);
     else
-        store_block<TIO>(out, LD, col0, rows_valid, l, x0, x1, x2, x3, 1, nullptr, part, D);
+        store_block<__bf16>(out, LD, col0, rows_valid, l, x0, x1, x2, x3, 1, nullptr, part, D);
 }
 
 // Backward of the row normalisation (Sec. 3.3) on gradient blocks still in registers:

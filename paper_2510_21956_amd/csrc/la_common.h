@@ -144,20 +144,14 @@ struct Tracer {
 void launch_scan_slots(float *ws, int BH, int nseg, size_t slot_floats, int off, int len, int mode,
                        int lo, int hi, hipStream_t st);
 
-// Matrix-core path (la_fast.hip): D = 32, 64 and 128, fp32 and bf16, both passes.
-bool fast_supported(const Problem &pr, int is_backward);
+// Matrix-core kernels (la_split.hip): D = 16 (on the tiles of 32), 32, 64, 128 (ld == D), or 128
+// columns of rows ld = 256 wide, one of several launches that build the results up (without
+// normalisation): xflags, Gin, Fraw and BlockPass as in split_forward / split_backward.
 // `saved` (may be null) is the forward-to-backward hand-over buffer described in Plan.
-la_status fast_backward(const Problem &pr, const Plan &pl, const void *Q, const void *K,
-                        const void *V, const void *O, const float *G, const void *dO, void *dQ,
-                        void *dK, void *dV, float *ws, const float *saved, hipStream_t st,
-                        Tracer &tc);
-la_status fast_forward(const Problem &pr, const Plan &pl, const void *Q, const void *K,
-                       const void *V, void *O, float *G, float *ws, float *saved, hipStream_t st,
-                       Tracer &tc);
-
-// Matrix-core kernels (la_split.hip): D = 32, 64, 128 (ld == D), or 128 columns of rows
-// ld = 256 wide, one of several launches that build the results up (without normalisation):
-// xflags, Gin, Fraw and BlockPass as in split_forward / split_backward.  dK == nullptr: dQ only.
+// dK == nullptr: the ascending sweep alone, dQ for the coefficients in pr.
+// planes_totals: the per-segment sums over the whole sequence, S = sum k v^T, z = sum k, p = sum v,
+// in the slots of every slice as [S | z | p] (forward plan without the mask); state_from_totals adds
+// the slots up.
 struct BlockPass {
     int xflags = 0;
     float *Pq = nullptr, *Pk = nullptr, *Pv = nullptr;
@@ -172,10 +166,6 @@ la_status planes_backward(const Problem &pr, const Plan &pl, int ld, const void 
 la_status planes_totals(const Problem &pr, const Plan &pl, int ld, const void *K, const void *V,
                         float *ws, hipStream_t st);
 
-// The ascending sweep of the backward pass alone: dQ for the coefficients in pr (matrix-core path).
-la_status fast_backward_dq(const Problem &pr, const Plan &pl, const void *Q, const void *K,
-                           const void *V, const void *O, const float *G, const void *dO, void *dQ,
-                           float *ws, hipStream_t st);
 // sum over all elements of X * Y (n elements of dt) -> out[0] = scale0 * sum, out[1] = scale1 * sum;
 // `partials` is scratch of at least reduce_dot_partials() floats.  Fixed summation order.
 int reduce_dot_partials();
@@ -186,10 +176,7 @@ la_status reduce_dot(const void *X, const void *Y, size_t n, la_dtype dt, float 
 // for every one of `rows` rows of D elements, xhat = x / ||x||.
 la_status project_rows(const void *X, void *dX, size_t rows, int D, la_dtype dt, hipStream_t st);
 
-// Per-segment sums over the whole sequence, S = sum k v^T, z = sum k, p = sum v, in the slots of
-// every slice as [S | z | p] (forward plan without the mask); state_from_totals adds the slots up.
-la_status fast_kv_totals(const Problem &pr, const Plan &pl, const void *K, const void *V,
-                         float *ws, hipStream_t st);
+// The same sums as planes_totals.
 la_status generic_kv_totals(const Problem &pr, const Plan &pl, const void *K, const void *V,
                             float *ws, hipStream_t st);
 
@@ -206,7 +193,7 @@ la_status state_from_totals(const float *ws, float *state, int BH, int D, int ns
                             size_t slot_floats, int N, int accumulate, hipStream_t st);
 
 // Head size 256 as passes of the D = 128 matrix-core kernels over column blocks of the
-// 256-wide rows; `pl` is the plan of the D = 128 problem (la_fast.hip).  dK == nullptr runs
+// 256-wide rows (la_fast.hip); `pl` is the plan of the D = 128 problem.  dK == nullptr runs
 // the ascending sweeps (dQ) only.
 // What split_forward / split_backward keep behind the D = 128 plan's workspace (offsets and
 // total in floats, T = token-heads).  Forward: one float per token-head (g_off) and, for bf16

@@ -1,22 +1,8 @@
-// Dispatch of the matrix-core kernels (la_split.hip): D = 32, 64, 128, and D = 256 as passes of
-// the D = 128 kernels over blocks of 128 columns (split_forward / split_backward).
+// D = 256 as passes of the D = 128 matrix-core kernels (la_split.hip) over blocks of 128 columns
+// (split_forward, split_backward, split_prefill).
 #include "la_blocks.h"
 
 namespace la {
-
-la_status fast_kv_totals(const Problem &pr, const Plan &pl, const void *K, const void *V,
-                         float *ws, hipStream_t st)
-{
-    return planes_totals(pr, pl, pr.D, K, V, ws, st);
-}
-
-la_status fast_backward_dq(const Problem &pr, const Plan &pl, const void *Q, const void *K,
-                           const void *V, const void *O, const float *G, const void *dO, void *dQ,
-                           float *ws, hipStream_t st)
-{
-    Tracer tc(nullptr, st);
-    return planes_backward(pr, pl, pr.D, Q, K, V, O, G, dO, dQ, nullptr, nullptr, ws, nullptr, st, tc);
-}
 
 // Head size 256 on the D = 128 kernels.  With q = [q1 q2], k = [k1 k2] (halves of 128) the
 // weight a + b q.k is (a + b q1.k1) + (0 + b q2.k2), and with v = [v1 v2] every sum of
@@ -106,27 +92,6 @@ la_status split_backward(const Problem &pr, const Plan &pl, const void *Q, const
             tc.mark("bwd_block_pass");
         }
     return LA_OK;
-}
-
-bool fast_supported(const Problem &pr, int is_backward)
-{
-    (void)is_backward;
-    return pr.D == 32 || pr.D == 64 || pr.D == 128;
-}
-
-la_status fast_backward(const Problem &pr, const Plan &pl, const void *Q, const void *K,
-                        const void *V, const void *O, const float *G, const void *dO, void *dQ,
-                        void *dK, void *dV, float *ws, const float *saved, hipStream_t st,
-                        Tracer &tc)
-{
-    return planes_backward(pr, pl, pr.D, Q, K, V, O, G, dO, dQ, dK, dV, ws, saved, st, tc);
-}
-
-la_status fast_forward(const Problem &pr, const Plan &pl, const void *Q, const void *K,
-                       const void *V, void *O, float *G, float *ws, float *saved, hipStream_t st,
-                       Tracer &tc)
-{
-    return planes_forward(pr, pl, pr.D, Q, K, V, O, G, ws, saved, st, tc);
 }
 
 }  // namespace la

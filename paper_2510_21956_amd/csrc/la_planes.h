@@ -653,11 +653,10 @@ __device__ __forceinline__ void rank_update_two(Blk (&st)[D / 16], const __bf16 
 }
 
 // ---- output blocks -------------------------------------------------------------------------------
-// Store a 16 x 16 block of which lane (c, g) holds rows 4g .. 4g+3 of column col0 + c: the 16
-// lanes of a group write one 64-byte run of a row (fp32), or, after neighbouring lanes have
-// exchanged halves, eight pairs (bf16).  The buffer descriptor covers the block's first
-// `rows_valid` rows (at most 16, possibly none): stores beyond them are dropped.
-// add: what the block holds already is added first (fp32).
+// Store a 16 x 16 fp32 block of which lane (c, g) holds rows 4g .. 4g+3 of column col0 + c: the 16
+// lanes of a group write one 64-byte run of a row.  The buffer descriptor covers the block's
+// first `rows_valid` rows (at most 16, possibly none): stores beyond them are dropped.
+// add: what the block holds already is added first.
 __device__ __forceinline__ void store_cols_block(float *base, int ld, int col0, int rows_valid, int c,
                                                  int g, f4v x, bool add = false)
 {
@@ -677,24 +676,6 @@ __device__ __forceinline__ void store_cols_block(float *base, int ld, int col0, 
 #pragma unroll
     for (int e = 0; e < 4; ++e)
         __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(x[e]), rsrc, off + e * ld * 4, 0, 0);
-}
-__device__ __forceinline__ void store_cols_block(__bf16 *base, int ld, int col0, int rows_valid, int c,
-                                                 int g, f4v x, bool = false)
-{
-    const int nrows = valid_rows(rows_valid);
-    const __amdgpu_buffer_rsrc_t rsrc =
-        __builtin_amdgcn_make_buffer_rsrc(base, 0, nrows * ld * 2, kBufferFlags);
-    const bool odd = c & 1;
-    const int off = ((4 * g + (odd ? 1 : 0)) * ld + col0 + (c & ~1)) * 2;
-#pragma unroll
-    for (int h = 0; h < 4; h += 2) {
-        // even lanes take row h, odd lanes row h + 1, both columns of the pair
-        const float keep = odd ? x[h + 1] : x[h], send = odd ? x[h] : x[h + 1];
-        const float got = __builtin_bit_cast(
-            float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, send), 0xB1, 0xf, 0xf, true));
-        const bf2v p = __builtin_convertvector((f2v{odd ? got : keep, odd ? keep : got}), bf2v);
-        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, p), rsrc, off + h * ld * 2, 0, 0);
-    }
 }
 
 // Backward of the row normalisation (Sec. 3.3) on gradient blocks still in registers:

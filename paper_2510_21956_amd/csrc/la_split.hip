@@ -130,7 +130,7 @@ __device__ __forceinline__ void store_grad(TIO *out, float *part, bool add, int 
     if constexpr (SWAP)
         store_cols_block(out, LD, w * 16, rows_valid, l % 16, l / 16, x, LD > D && add);
     else
-        store_grad_block<TIO, D, LD>(out, part, add, w * 16, rows_valid, l, x[0], x[1], x[2], x[3]);
+        store_grad_block<D, LD>(out, part, add, w * 16, rows_valid, l, x[0], x[1], x[2], x[3]);
 }
 // Backward of the row normalisation on the two output blocks; xhat = scale * the tile's rows.
 template <bool SWAP, bool OP, int D, int LQ>
