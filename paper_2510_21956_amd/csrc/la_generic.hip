@@ -226,6 +226,7 @@ __global__ __launch_bounds__(NT) void k_bwd_state(const T *__restrict__ Q, const
 //   mode 2: slot[0] = sum of slots lo..hi           (no mask: every row sees every row), with
 //           what the additions lose: some hundred slots of one long slice add up
 // ---------------------------------------------------------------------------
+template <int BATCH>
 __global__ __launch_bounds__(NT) void k_scan_slots(float *__restrict__ ws, int nseg,
                                                    size_t slot_floats, int off, int len, int mode,
                                                    int lo, int hi)
@@ -233,11 +234,11 @@ __global__ __launch_bounds__(NT) void k_scan_slots(float *__restrict__ ws, int n
     int e = blockIdx.y * NT + threadIdx.x;
     if (e >= len || hi < lo) return;
     float *p = ws + (size_t)blockIdx.x * nseg * slot_floats + off + e;
-    // The slots are read sixteen at a time before anything is added or written back: one
-    // memory round trip per sixteen slots instead of one per slot (the sums are formed in the
-    // same order either way).  A step on one slice of 60000 rows (468 slots), bf16, D = 64: 143 us
-    // with 8, 133 with 16, 134 with 32; 36 slices of 14 slots: 108.7, 107.8, 110.7.
-    constexpr int BATCH = 16;
+    // The slots are read BATCH at a time before anything is added or written back: one memory
+    // round trip per BATCH slots instead of one per slot (the sums are formed in the same order
+    // either way).  A step on one slice of 60000 rows (468 slots), bf16, D = 64: 143 us with 8, 133
+    // with 16, 134 with 32; 36 slices of 14 slots: 108.7, 107.8, 110.7.  Up to eight slots take 8
+    // (192 slices of 3: 7.0 us a scan, 7.7 with 16).
     float run = 0.f, lost = 0.f;
     const int n = hi - lo + 1;
     for (int i0 = 0; i0 < n; i0 += BATCH) {
@@ -535,7 +536,7 @@ la_status fwd_impl(const Problem &pr, const Plan &pl, const T *Q, const T *K, co
             K, V, ws, pr.N, nseg, nrun, pl.seg_len, pl.slot_floats, pr.causal ? 1 : 0, pr.norm_qk);
         tc.mark("generic_fwd_state");
         const int len = D * D + 2 * D;
-        k_scan_slots<<<dim3(pr.BH, (len + NT - 1) / NT), dim3(NT), 0, st>>>(
+        k_scan_slots<16><<<dim3(pr.BH, (len + NT - 1) / NT), dim3(NT), 0, st>>>(
             ws, nseg, pl.slot_floats, 0, len, pr.causal ? 0 : 2, pr.causal ? 1 : 0, nseg - 1);
         tc.mark("scan_slots");
     }
@@ -559,13 +560,13 @@ la_status bwd_impl(const Problem &pr, const Plan &pl, const T *Q, const T *K, co
     tc.mark("generic_bwd_state");
     const int lenS = D * D + D, lenR = D * D + 2 * D;
     if (pr.causal) {
-        k_scan_slots<<<dim3(pr.BH, (lenS + NT - 1) / NT), dim3(NT), 0, st>>>(
+        k_scan_slots<16><<<dim3(pr.BH, (lenS + NT - 1) / NT), dim3(NT), 0, st>>>(
             ws, nseg, pl.slot_floats, 0, lenS, 0, 1, nseg - 1);
-        k_scan_slots<<<dim3(pr.BH, (lenR + NT - 1) / NT), dim3(NT), 0, st>>>(
+        k_scan_slots<16><<<dim3(pr.BH, (lenR + NT - 1) / NT), dim3(NT), 0, st>>>(
             ws, nseg, pl.slot_floats, lenS, lenR, 1, 0, nseg - 2);
         tc.mark("scan_slots");
     } else {
-        k_scan_slots<<<dim3(pr.BH, (lenS + lenR + NT - 1) / NT), dim3(NT), 0, st>>>(
+        k_scan_slots<16><<<dim3(pr.BH, (lenS + lenR + NT - 1) / NT), dim3(NT), 0, st>>>(
             ws, nseg, pl.slot_floats, 0, lenS + lenR, 2, 0, nseg - 1);
         tc.mark("scan_slots");
     }
@@ -615,8 +616,9 @@ void launch_scan_slots(float *ws, int BH, int nseg, size_t slot_floats, int off,
 {
     // a running sum over a single slot changes nothing; the total of a single slot 0 neither
     if (hi < lo || (hi == lo && (mode != 2 || lo == 0))) return;
-    k_scan_slots<<<dim3(BH, (len + NT - 1) / NT), dim3(NT), 0, st>>>(ws, nseg, slot_floats, off,
-                                                                    len, mode, lo, hi);
+    auto *kernel = hi - lo < 8 ? k_scan_slots<8> : k_scan_slots<16>;
+    kernel<<<dim3(BH, (len + NT - 1) / NT), dim3(NT), 0, st>>>(ws, nseg, slot_floats, off, len, mode,
+                                                               lo, hi);
 }
 
 namespace {

@@ -103,25 +103,22 @@ __device__ __forceinline__ bf8v ones_frag()
 }
 
 // ---- long sums -----------------------------------------------------------------------------------
-// A running sum with what its additions lost (Knuth's two-sum).  A segment's vector sums take one
-// addition per 32 rows, and without the mask they are most of an output row: O = (a p + ...) / g with
-// |p| ~ sqrt(N), the rest ~ sqrt(N / D).  Against 64 bits, unmasked fp32, O over 16384 rows at D = 64:
-// 2.3e-7 with plain sums, 0.7e-7 with these; 20000 rows at D = 128: 2.6e-7 and 0.6e-7.
+// A running sum with what its additions lost (Dekker's fast two-sum: exact where the sum is the larger
+// operand, which it is but for the first few additions, whose roundings are small next to the end's).
+// A segment's vector sums take one addition per 32 rows, and without the mask they are most of an
+// output row: O = (a p + ...) / g with |p| ~ sqrt(N), the rest ~ sqrt(N / D).  Against 64 bits, unmasked
+// fp32, O over 16384 rows at D = 64: 2.3e-7 with plain sums, 0.7e-7 with these; 20000 rows at D = 128:
+// 2.6e-7 and 0.6e-7.
 template <typename V>
 struct LongSum {
     V s, lost;
-    __device__ __forceinline__ void add(V x)
-    {
-        const V t = s + x, y = t - s;
-        lost += (s - (t - y)) + (x - y);
-        s = t;
-    }
     // += a product of the first planes and the products of the further ones, two accumulators: on
-    // one, the small products are cut off at the large one's last bit, to one side.
+    // one, the small products are cut off at the large one's last bit.
     __device__ __forceinline__ void add(V hi, V lo)
     {
-        add(hi);
-        lost += lo;
+        const V t = s + hi;
+        lost += (hi - (t - s)) + lo;
+        s = t;
     }
 };
 // The sum; where it is not finite, neither is a number what it lost.
@@ -184,13 +181,6 @@ constexpr int products(int LA, int LB)
     for (int p = 0; p < LA; ++p)
         for (int q = 0; q < LB; ++q) n += p + q <= M;
     return n;
-}
-template <int LA, int LB>
-__device__ __forceinline__ void add_product(LongSum<f4v> &x, const bf8v (&a)[LA], const bf8v (&b)[LB])
-{
-    f4v hi = {0.f, 0.f, 0.f, 0.f}, lo = hi;
-    mma_planes<LA, LB>(hi, lo, a, b);
-    x.add(hi, lo);
 }
 // The whole product of one step, smallest terms first, on one accumulator that starts at zero.
 template <int LA, int LB>

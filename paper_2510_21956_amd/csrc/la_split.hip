@@ -216,9 +216,11 @@ __device__ __forceinline__ void stage(const CH &ch, __bf16 *tile, float *inv_out
 
 // ---------------------------------------------------------------------------
 // Phase 1: per-segment S = sum k v^T, z = sum k, p = sum v (Eq. xy without the factors), to
-// slot `seg + slot_shift` as [S | z | p], or [S^T | z] (TRANSPOSED) for the backward pass.
+// slot `seg + slot_shift` as [S | z | p], or [S^T | z] (TRANSPOSED) for the backward pass.  LONG: z and p
+// with what their additions lose (unmasked passes and prompt states; masked rows see them through
+// plain running sums anyway).
 // ---------------------------------------------------------------------------
-template <int MODE, int D, bool TRANSPOSED, int LD>
+template <int MODE, int D, bool TRANSPOSED, int LD, bool LONG>
 __global__ __launch_bounds__(4 * D, 2) void ks_kv_state(
     const typename Mode<MODE>::TIO *__restrict__ K, const typename Mode<MODE>::TIO *__restrict__ V,
     float *__restrict__ ws, int N, int nseg, int nseg_run, SegMap sm, size_t slot_floats, int slot_shift)
@@ -235,13 +237,18 @@ __global__ __launch_bounds__(4 * D, 2) void ks_kv_state(
     const long row0 = seg_row(sm, seg, nseg, N), row1 = seg_row(sm, seg + 1, nseg, N);
     const int t = threadIdx.x, l = t % 64, c = l % 16, g = l / 16;
     const int w = __builtin_amdgcn_readfirstlane(t / 64);
-    const Lanes<D> ln(c, g);
+    const Lanes<D, (D == 64 && LV == 3)> ln(c, g);
     const bf8v one[1] = {ones_frag()};
 
     Blk st[NRB];
 #pragma unroll
     for (int rb = 0; rb < NRB; ++rb) st[rb].zero();
     LongSum<f4v> zacc{}, pacc{};  // z, p [16w + 4g + e]
+    const f4v zero = {0.f, 0.f, 0.f, 0.f};
+    auto add = [&](LongSum<f4v> &x, f4v hi, f4v lo) __attribute__((always_inline)) {
+        if constexpr (LONG) x.add(hi, lo);
+        else x.s += hi + lo;
+    };
     struct Set {
         CH k, v;
     } sets[NT];
@@ -256,19 +263,23 @@ __global__ __launch_bounds__(4 * D, 2) void ks_kv_state(
         sets[i].v.template store<false, LV>(Vt);
         if (__builtin_expect(sets[i].v.top() > kLargestBf16, 0)) sets[i].v.template store_any<false>(Vt);
     };
-    // one tile pair into the sums
+    // One tile pair into the sums.  In bf16, z and p take their products in when the update of S has
+    // run; fp32 has no registers to keep them that long (128 at D = 64, four workgroups a CU).
+    constexpr bool DEFER = LV == 1;
     auto one_tile = [&](int i) __attribute__((always_inline)) {
         const __bf16 *Kt = lds + i * TP, *Vt = Kt + LQ * PL;
         const float *ik = ikb + (MD::RN ? i * CR : 0);
+        f4v zh = zero, zl = zero, ph = zero, pl = zero;
         bf8v kf[LQ];
         load_cols<D, LQ>(kf, Kt, ln.local(ln.col), w);
         if constexpr (MD::RN) {
             bf8v fk[3];
             factor_frag(fk, ik, g);
-            add_product(zacc, kf, fk);
+            mma_planes<LQ, 3>(zh, zl, kf, fk);
         } else {
-            add_product(zacc, kf, one);
+            mma_planes<LQ, 1>(zh, zl, kf, one);
         }
+        if constexpr (!DEFER) add(zacc, zh, zl);
         if constexpr (TRANSPOSED) {
             if constexpr (MD::RN) {
                 bf8v kh[3];
@@ -280,7 +291,8 @@ __global__ __launch_bounds__(4 * D, 2) void ks_kv_state(
         } else {
             bf8v vf[LV];
             load_cols<D, LV>(vf, Vt, ln.local(ln.col), w);
-            add_product(pacc, vf, one);
+            mma_planes<LV, 1>(ph, pl, vf, one);
+            if constexpr (!DEFER) add(pacc, ph, pl);
             if constexpr (MD::RN) {
                 bf8v vh[3];
                 scale_frag<3>(vh, vf, ik, g);
@@ -288,7 +300,9 @@ __global__ __launch_bounds__(4 * D, 2) void ks_kv_state(
             } else {
                 rank_update<D, LQ, LV>(st, Kt, vf, ln);
             }
+            if constexpr (DEFER) add(pacc, ph, pl);
         }
+        if constexpr (DEFER) add(zacc, zh, zl);
     };
 #pragma unroll
     for (int i = 0; i < NT; ++i) request(row0, i);
@@ -302,19 +316,20 @@ __global__ __launch_bounds__(4 * D, 2) void ks_kv_state(
         request(c0 + NT * CR, NT - 1);
         if (LQ * LV == 1 && !MD::RN && two) {
             const __bf16 *K0 = lds, *V0 = K0 + LQ * PL, *K1 = lds + (NT - 1) * TP, *V1 = K1 + LQ * PL;
-            const f4v zero = {0.f, 0.f, 0.f, 0.f};
             bf8v k0[1], k1[1], v0[1], v1[1];
             load_cols<D, 1>(k0, K0, ln.local(ln.col), w);
             load_cols<D, 1>(k1, K1, ln.local(ln.col), w);
-            zacc.add(mfma(k1[0], one[0], mfma(k0[0], one[0], zero)));
+            const f4v zh = mfma(k1[0], one[0], mfma(k0[0], one[0], zero));
             if constexpr (TRANSPOSED) {
                 rank_update_two<D>(st, V0, V1, k0[0], k1[0], ln);
             } else {
                 load_cols<D, 1>(v0, V0, ln.local(ln.col), w);
                 load_cols<D, 1>(v1, V1, ln.local(ln.col), w);
-                pacc.add(mfma(v1[0], one[0], mfma(v0[0], one[0], zero)));
+                const f4v ph = mfma(v1[0], one[0], mfma(v0[0], one[0], zero));
                 rank_update_two<D>(st, K0, K1, v0[0], v1[0], ln);
+                add(pacc, ph, zero);
             }
+            add(zacc, zh, zero);
         } else {
             one_tile(0);
             if (two) one_tile(NT - 1);
@@ -1134,7 +1149,8 @@ la_status run_forward(const Problem &pr, const Plan &pl, const void *Qv, const v
     const int nseg = pl.nseg, nrun = pr.causal ? nseg - 1 : nseg;
     const dim3 block(4 * D);
     if (nrun > 0) {
-        ks_kv_state<MODE, D, false, LD><<<dim3(pr.BH * nrun), block, 0, st>>>(
+        (pr.causal ? ks_kv_state<MODE, D, false, LD, false> : ks_kv_state<MODE, D, false, LD, true>)<<<
+            dim3(pr.BH * nrun), block, 0, st>>>(
             K, V, ws, pr.N, nseg, nrun, pl.map, pl.slot_floats, pr.causal ? 1 : 0);
         tc.mark("fwd_state");
         launch_scan_slots(ws, pr.BH, nseg, pl.slot_floats, 0, D * D + 2 * D, pr.causal ? 0 : 2,
@@ -1173,7 +1189,8 @@ la_status run_backward(const Problem &pr, const Plan &pl, const void *Qv, const 
     // forward-running sums before every segment: handed over by the forward pass, or
     // per-segment sums (none needed from a masked pass's last segment) and a scan here
     if (!saved && nrun > 0) {
-        ks_kv_state<MODE, D, true, LD><<<dim3(pr.BH * nrun), block, 0, st>>>(
+        (pr.causal ? ks_kv_state<MODE, D, true, LD, false> : ks_kv_state<MODE, D, true, LD, true>)<<<
+            dim3(pr.BH * nrun), block, 0, st>>>(
             K, V, ws, pr.N, nseg, nrun, pl.map, pl.slot_floats, pr.causal ? 1 : 0);
         tc.mark("bwd_state");
         launch_scan_slots(ws, pr.BH, nseg, pl.slot_floats, SL::ST, SL::R - SL::ST, pr.causal ? 0 : 2,
@@ -1205,7 +1222,7 @@ la_status run_totals(const Problem &pr, const Plan &pl, const void *K, const voi
                      hipStream_t st)
 {
     typedef typename Mode<MODE>::TIO TIO;
-    ks_kv_state<MODE, D, false, LD><<<dim3(pr.BH * pl.nseg), dim3(4 * D), 0, st>>>(
+    ks_kv_state<MODE, D, false, LD, true><<<dim3(pr.BH * pl.nseg), dim3(4 * D), 0, st>>>(
         (const TIO *)K, (const TIO *)V, ws, pr.N, pl.nseg, pl.nseg, pl.map, pl.slot_floats, 0);
     return launch_status();
 }
