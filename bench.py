@@ -244,7 +244,7 @@ def extras(torch, wl, la):
                                   cfg.b, cfg.causal, wsb), 30)}
     del t, wsf, wsb
     torch.cuda.empty_cache()
-    # the same with bf16 tensors (fp32 tiles on chip): the shape that stands in for an LLM layer
+    # the same with bf16 tensors (raw rows on chip): the shape that stands in for an LLM layer
     cfg4 = wl.CONFIGS[3]
     t = make_device_inputs(cfg4, torch, 1)[0]
     t["Q"] = (t["Q"] * 3.0).contiguous()

@@ -41,6 +41,13 @@
  *   - Numerical precondition (not checked): g_i != 0.  It holds when
  *     a > |b| * max|q.k|, e.g. unit-norm rows of Q and K (the normalisation of
  *     Sec. 3.3, which is the caller's job) with a = 1, b = 0.5.
+ *   - Range of float32 tensors: an element is carried exactly for
+ *     magnitudes from 2^-109 (1.5e-33) to the largest float; below, it keeps
+ *     an absolute error of up to 2^-134 (so 10 bits are left at 2^-124).
+ *     An infinity or a NaN in V or dO spoils its column of O and dV from the
+ *     row's aligned block of 32 rows on (for dV: up to it), earlier rows of
+ *     that block included; in fp32 an infinity in V is an infinity in the rows
+ *     of its block that see it where all their weights are of one sign.
  */
 #ifndef LA_H_
 #define LA_H_
@@ -143,6 +150,8 @@ LA_API la_status la_backward(const void *Q, const void *K, const void *V,
  * With bfloat16 tensors the rows stay as they are on chip and the factors 1/||q||, 1/||k|| go
  * to quantities that are float32 anyway, so that the normalised rows are not rounded to
  * bfloat16 again (about 1.8 times the time of the plain bfloat16 calls at D = 128).
+ * The squared length of a row has to be a float: lengths from 1e-19 (fewer digits down to 1e-22) to
+ * 1.8e19.
  */
 LA_API la_status la_forward_qknorm(const void *Q, const void *K, const void *V,
                      void *O, float *G,
@@ -244,8 +253,9 @@ LA_API la_status la_decode_prefill(const void *K, const void *V,
  * device array inside the library (LA_STATIC_SCRATCH_BYTES per GPU, held until
  * the process ends).  The call allocates nothing and frees nothing.  Problems
  * whose la_workspace_bytes(..., 0) exceeds LA_STATIC_SCRATCH_BYTES are
- * rejected with LA_ERR_WORKSPACE (nothing enqueued); the five benchmark
- * configurations fit.  All calls on one GPU share the array: calls that
+ * rejected with LA_ERR_WORKSPACE (nothing enqueued), but for D = 16, where the
+ * call takes kernels with a quarter of that workspace instead and serves up to
+ * 26214 slices; the five benchmark configurations fit.  All calls on one GPU share the array: calls that
  * overlap in time on one GPU (different streams, different threads) race, and
  * the caller must order them.  The first call on each GPU resolves the
  * array's device address (make it outside graph capture); if that fails the

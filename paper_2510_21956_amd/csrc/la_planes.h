@@ -8,6 +8,8 @@
 // bf16 pipe is sixteen times as fast as the fp32 one (v_mfma_f32_16x16x32_bf16: 16 clocks for
 // 16 K flops; v_mfma_f32_16x16x4_f32: 32 clocks for 2 K), so the six take 3/8 of its time.
 // A bf16 tensor is its own first plane and takes three products against a split operand.
+// Exact means for magnitudes from 2^-109 on: below, x2 is subnormal in bf16 and what is lost of x is up
+// to 2^-134.  Above the largest bf16, 3.3895e38, the first plane would be infinite: split4_any.
 //
 // Tiles.  A tile is 32 chunk rows x D columns of one tensor in bf16, one after another for each
 // plane, rows D elements apart without padding.  Fragments are read two ways from the same

@@ -33,8 +33,9 @@
 // (splitting inputs and states) and LDS reads take 30 to 45 % of the clocks each and overlap
 // only in part, two waves a SIMD: 64 slices of 10^4 rows, D = 128, forward / ascending /
 // descending sweep 411 / 543 / 719 us against 489 / 646 / 863 us on the fp32 matrix pipe; D = 64,
-// 64 slices of 4096 rows, 70 / 91 / 113 against 79 / 98 / 110.  bf16, D = 128: memory, with 40 KB
-// in flight per CU, and the vector ALU (43 % in the descending sweep): 128 slices of 2048 rows
+// 64 slices of 4096 rows, 70 / 91 / 113 against 79 / 98 / 110.  bf16, D = 128: waiting, 38 to 44 % of a
+// wave's life, at the barriers between a chunk's phases and for memory with 40 KB in flight per CU
+// (vector ALU and LDS 33 % each in the descending sweep, matrix pipe 19 %): 128 slices of 2048 rows
 // 63 / 85 / 105 us against 65 / 97 / 100 on kernels with chunks of 64 rows and two tiles a tensor;
 // D = 64, 36 slices of 5003 rows, with two workgroups a CU instead of one, 28 / 33 / 39 against
 // 41 / 51 / 56.  bf16 with normalised rows: 104 / 151 / 192 against 221 / 316 / 402 on fp32 tiles.
@@ -657,6 +658,8 @@ __global__ __launch_bounds__(4 * D, 2) void ks_fwd_read(
 //   R += (Q/g)_c^T dO_c,  u += sum dprime (q/g),  w += sum dO / g
 // The state is held transposed (rows j, columns r): the product contracts over j.
 // LD > D: xflags & 1 marks the second of the two launches that build dQ up.
+// fp32 at D = 128 without the mask holds S^T, R and two chunks in 256 registers but for 6 to 10, which
+// go to scratch once a chunk (a state in its accumulators less would cost a pass over Q and dO).
 // ---------------------------------------------------------------------------
 template <int MODE, int D, bool CAUSAL, int LD>
 __global__ __launch_bounds__(4 * D, 2) void ks_bwd_dq(
