@@ -4,8 +4,8 @@ import numpy as np
 import pytest
 import torch
 
-from la_testlib import (TOL, excess, gpu_backward, gpu_forward, run_gpu, scratch, to_f64,
-                        upload_case)
+from la_testlib import (TOL, excess, gpu_backward, gpu_backward_saved, gpu_forward,
+                        gpu_forward_save, run_gpu, scratch, to_f64, upload_case)
 
 pytestmark = pytest.mark.gpu
 
@@ -265,3 +265,28 @@ def test_runs_are_bitwise_alike(la, D, dtype, norm, causal):
     for _ in range(4):
         for name, x, y in zip(("O", "G", "dQ", "dK", "dV"), run(la, dev, 1.0, 0.5, causal), first):
             assert torch.equal(x, y), name
+
+
+# evened-out segments (D = 64); four, two and one workgroup a CU for the rows (D = 128); more slices
+# than compute units
+@pytest.mark.parametrize("B,H,N,D", [(8, 24, 1000, 64), (8, 24, 900, 128), (4, 20, 1000, 128),
+                                     (8, 24, 300, 128), (32, 32, 70, 32)])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_unmasked_cuts(la, B, H, N, D, dtype):
+    """Without the mask the rows of the forward pass are cut by a rule of their own: every row is
+    written, and the sums handed over serve the backward pass like recomputed ones."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(B * N + D)
+    td = torch.float32 if dtype == "f32" else torch.bfloat16
+    dev = {n: (torch.randn((B, H, N, D), device="cuda", generator=gen) * sc).to(td)
+           for n, sc in (("Q", D ** -0.5), ("K", D ** -0.5), ("V", 1.0), ("dO", 1.0))}
+    O, G, saved = gpu_forward_save(la, dev, 1.0, 0.5, False)
+    q, k, v = (dev[n].double() for n in ("Q", "K", "V"))
+    S = torch.matmul(k.transpose(2, 3).contiguous(), v)
+    g = N + 0.5 * torch.matmul(q, k.sum(2).unsqueeze(3)).squeeze(3)
+    want = (v.sum(2, keepdim=True) + 0.5 * torch.matmul(q, S)) / g.unsqueeze(3)
+    assert excess(to_f64(O), to_f64(want), TOL[dtype]) <= 1.0
+    assert excess(to_f64(G), to_f64(g), TOL["f32"]) <= 1.0
+    got = gpu_backward_saved(la, dev, O, G, saved, 1.0, 0.5, False)
+    for x, y in zip(got, gpu_backward(la, dev, O, G, 1.0, 0.5, False)):
+        assert excess(to_f64(x), to_f64(y), TOL[dtype]) <= 1.0
