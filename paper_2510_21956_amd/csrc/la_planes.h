@@ -320,41 +320,47 @@ __device__ __forceinline__ void load_cols_op(bf8v (&f)[L], const __bf16 *tile, i
 }
 
 // ---- staging -----------------------------------------------------------------------------------
-// A workgroup of 4 D threads holds one chunk (32 x D) of a tensor as two quads (four columns
-// of a row) per thread.  fp32: quad t % (D/4) of rows t / (D/4) and that + 16; bf16: two
-// neighbouring quads of row t / (D/8).  Either way a wave loads whole consecutive rows, 16
-// bytes a lane.
-template <typename TIO, int D, int LD>
+// One chunk (32 x D) of a tensor in 16-byte loads, whole consecutive rows a wave.  A workgroup of 4 D
+// threads holds it as two quads (four columns of a row) per thread: fp32, quad t % (D/4) of rows
+// t / (D/4) and that + 16; bf16, two neighbouring quads of row t / (D/8).  With HALVES (8 D threads)
+// fp32 is one quad a thread, and a bf16 chunk is held by one half of the workgroup, which the caller
+// names.
+template <typename TIO, int D, int LD, bool HALVES = false>
 struct Chunk {
     static constexpr bool F32 = sizeof(TIO) == 4;
-    static constexpr int PER_ROW = F32 ? D / 4 : D / 8;  // lanes that share a row
-    static constexpr int NLD = F32 ? 2 : 1;              // 16-byte loads per thread
-    static constexpr int COLS = LD < D ? LD : D;         // columns there are; the others read as zeros
+    static constexpr int PER_ROW = F32 ? D / 4 : D / 8;    // lanes that share a row
+    static constexpr int NLD = F32 && !HALVES ? 2 : 1;     // 16-byte loads per thread
+    static constexpr int NQ = F32 && HALVES ? 1 : 2;       // quads per thread
+    static constexpr int COLS = LD < D ? LD : D;           // columns there are; the others read as zeros
     u4v raw[NLD];
 
-    static __device__ __forceinline__ int row(int k)
+    // t: the thread's index.  A kernel short of registers hands in a copy that the compiler does not
+    // recognise, so that what follows from it is worked out where it is used and not kept across the
+    // chunk loop.
+    static __device__ __forceinline__ int row(int k, int t = threadIdx.x)
     {
-        return (int)threadIdx.x / PER_ROW + (F32 ? 16 * k : 0);
+        if constexpr (F32) return t / PER_ROW + 16 * k;
+        else return (HALVES ? t % (4 * D) : t) / PER_ROW;
     }
-    static __device__ __forceinline__ int quad(int k)
+    static __device__ __forceinline__ int quad(int k, int t = threadIdx.x)
     {
-        return F32 ? (int)threadIdx.x % PER_ROW : 2 * ((int)threadIdx.x % PER_ROW) + k;
+        return F32 ? t % PER_ROW : 2 * (t % PER_ROW) + k;
     }
     // the lane that writes a per-row result
-    static __device__ __forceinline__ bool leader() { return threadIdx.x % PER_ROW == 0; }
+    static __device__ __forceinline__ bool leader(int t = threadIdx.x) { return t % PER_ROW == 0; }
 
     // Request chunk rows [c0, c0 + 32) of X, the base of a slice of N rows (c0 < N).  The
     // buffer descriptor covers the chunk's valid rows; rows beyond them read as zeros.
     // Nothing looks at the loaded values before the tile is written, so the loads stay in
     // flight over the chunk before.
-    __device__ __forceinline__ void load(const TIO *X, long c0, int N)
+    __device__ __forceinline__ void load(const TIO *X, long c0, int N, int t = threadIdx.x)
     {
         const long rows = (N - c0 < CR) ? N - c0 : CR;
         const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
             const_cast<TIO *>(X + (size_t)c0 * LD), 0, (int)(((rows - 1) * LD + COLS) * sizeof(TIO)),
             kBufferFlags);
-        int off = (row(0) * LD + 4 * quad(0)) * (int)sizeof(TIO);
-        if (LD < D && 4 * quad(0) >= COLS) off = 1 << 30;  // out of range
+        int off = (row(0, t) * LD + 4 * quad(0, t)) * (int)sizeof(TIO);
+        if (LD < D && 4 * quad(0, t) >= COLS) off = 1 << 30;  // out of range
 #pragma unroll
         for (int k = 0; k < NLD; ++k)
             raw[k] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, off + k * 16 * LD * (int)sizeof(TIO),
@@ -371,34 +377,40 @@ struct Chunk {
         }
     }
     // Per-quad partial sums -> row totals, in every lane that shares the row.
-    static __device__ __forceinline__ void row_totals(float (&s)[2])
+    static __device__ __forceinline__ void row_totals(float (&s)[NQ])
     {
         if constexpr (F32) {
-            s[0] = reduce_adjacent<PER_ROW>(s[0]);
-            s[1] = reduce_adjacent<PER_ROW>(s[1]);
+#pragma unroll
+            for (int k = 0; k < NQ; ++k) s[k] = reduce_adjacent<PER_ROW>(s[k]);
         } else {
             s[0] = s[1] = reduce_adjacent<PER_ROW>(s[0] + s[1]);
         }
     }
     // The tensor's own bf16 values into a one-plane tile.
     template <bool OP>
-    __device__ __forceinline__ void store_raw(__bf16 *tile) const
+    __device__ __forceinline__ void store_raw(__bf16 *tile, int t = threadIdx.x) const
     {
         static_assert(!F32, "fp32 tensors are split");
         if constexpr (!OP) {
-            *reinterpret_cast<u4v *>(tile + Tile<D>::nat_quad(row(0), quad(0))) = raw[0];
+            *reinterpret_cast<u4v *>(tile + Tile<D>::nat_quad(row(0, t), quad(0, t))) = raw[0];
         } else {
-            *reinterpret_cast<u2v *>(tile + Tile<D>::op_quad(row(0), quad(0))) = u2v{raw[0][0], raw[0][1]};
-            *reinterpret_cast<u2v *>(tile + Tile<D>::op_quad(row(0), quad(1))) = u2v{raw[0][2], raw[0][3]};
+            *reinterpret_cast<u2v *>(tile + Tile<D>::op_quad(row(0, t), quad(0, t))) = u2v{raw[0][0], raw[0][1]};
+            *reinterpret_cast<u2v *>(tile + Tile<D>::op_quad(row(0, t), quad(1, t))) = u2v{raw[0][2], raw[0][3]};
         }
     }
-    // Values x (two quads) into a tile of L planes.
-    template <bool OP, int L>
-    static __device__ __forceinline__ void store_values(__bf16 *tile, const f4v (&x)[2])
+    __device__ __forceinline__ void values(f4v (&x)[NQ]) const
     {
 #pragma unroll
-        for (int k = 0; k < 2; ++k) {
-            __bf16 *dst = tile + (OP ? Tile<D>::op_quad(row(k), quad(k)) : Tile<D>::nat_quad(row(k), quad(k)));
+        for (int k = 0; k < NQ; ++k) x[k] = value(k);
+    }
+    // Values x into a tile of L planes.
+    template <bool OP, int L>
+    static __device__ __forceinline__ void store_values(__bf16 *tile, const f4v (&x)[NQ],
+                                                        int t = threadIdx.x)
+    {
+#pragma unroll
+        for (int k = 0; k < NQ; ++k) {
+            __bf16 *dst = tile + (OP ? Tile<D>::op_quad(row(k, t), quad(k, t)) : Tile<D>::nat_quad(row(k, t), quad(k, t)));
             bf4v o[L];
             split4<L>(x[k], o);
 #pragma unroll
@@ -407,28 +419,29 @@ struct Chunk {
     }
     // The tensor as it is: its own bits (bf16, one plane) or all planes.
     template <bool OP, int L>
-    __device__ __forceinline__ void store(__bf16 *tile) const
+    __device__ __forceinline__ void store(__bf16 *tile, int t = threadIdx.x) const
     {
         if constexpr (!F32 && L == 1) {
-            store_raw<OP>(tile);
+            store_raw<OP>(tile, t);
         } else {
-            const f4v x[2] = {value(0), value(1)};
-            store_values<OP, L>(tile, x);
+            f4v x[NQ];
+            values(x);
+            store_values<OP, L>(tile, x, t);
         }
     }
     // Above kLargestBf16: store<OP, 3> left NaN behind an infinite plane, and the tile is written
     // once more.
     __device__ __forceinline__ float top() const
     {
-        if constexpr (F32) return largest(value(0), value(1));
+        if constexpr (F32) return largest(value(0), value(NQ - 1));
         else return 0.f;
     }
     template <bool OP>
-    __device__ __forceinline__ void store_any(__bf16 *tile) const
+    __device__ __forceinline__ void store_any(__bf16 *tile, int t = threadIdx.x) const
     {
 #pragma unroll
-        for (int k = 0; k < 2; ++k) {
-            __bf16 *dst = tile + (OP ? Tile<D>::op_quad(row(k), quad(k)) : Tile<D>::nat_quad(row(k), quad(k)));
+        for (int k = 0; k < NQ; ++k) {
+            __bf16 *dst = tile + (OP ? Tile<D>::op_quad(row(k, t), quad(k, t)) : Tile<D>::nat_quad(row(k, t), quad(k, t)));
             bf4v o[3];
             split4_any(value(k), o);
 #pragma unroll
@@ -442,18 +455,20 @@ __device__ __forceinline__ float dot4(f4v x, f4v y)
     return (x[0] * y[0] + x[1] * y[1]) + (x[2] * y[2] + x[3] * y[3]);
 }
 
-// Row normalisation of Sec. 3.3 on the two quads a thread holds; rows of zeros stay zeros.
+// Row normalisation of Sec. 3.3 on the quads a thread holds; rows of zeros stay zeros.
 // inv_out (if given) receives 1 / |row|.
 template <typename CH>
-__device__ __forceinline__ void normalise_quads(f4v (&x)[2], float *inv_out)
+__device__ __forceinline__ void normalise_quads(f4v (&x)[CH::NQ], float *inv_out, int t = threadIdx.x)
 {
-    float s[2] = {dot4(x[0], x[0]), dot4(x[1], x[1])};
+    float s[CH::NQ];
+#pragma unroll
+    for (int k = 0; k < CH::NQ; ++k) s[k] = dot4(x[k], x[k]);
     CH::row_totals(s);
 #pragma unroll
-    for (int k = 0; k < 2; ++k) {
+    for (int k = 0; k < CH::NQ; ++k) {
         const float inv = s[k] > 0.f ? 1.f / sqrtf(s[k]) : 0.f;
         x[k] *= inv;
-        if (inv_out && CH::leader()) inv_out[CH::row(k)] = inv;
+        if (inv_out && CH::leader(t)) inv_out[CH::row(k, t)] = inv;
     }
 }
 
@@ -518,6 +533,24 @@ __device__ __forceinline__ void state_product(f4v (&hi)[2], f4v (&lo)[2], const 
         mma_pair<LS, LY, SWAP>(hi, lo, x[cur], f[cur]);
         if (kt + 1 < NK) step_schedule<2 * LY, NM, (20 * LS - 16 + NM - 1) / NM + 1>();
         else __builtin_amdgcn_sched_barrier(0);
+    }
+}
+// The same over the state blocks of contraction steps kt0 .. kt0 + NK - 1 (st[0] is block 2 kt0), one
+// step at a time: for four waves a SIMD, which hide each other's latencies and have half the
+// registers each.
+template <int D, int NK, int LS, int LY, bool SWAP, typename LN>
+__device__ __forceinline__ void state_steps(f4v (&hi)[2], f4v (&lo)[2], const Blk (&st)[2 * NK],
+                                            const __bf16 *y, int kt0, const LN &ln)
+{
+    const int row = LN::local(ln.row);
+#pragma unroll
+    for (int kt = 0; kt < NK; ++kt) {
+        bf8v f[2][LY], x[LS];
+        load_rows<D, LY>(f[0], y, row, 0, kt0 + kt);
+        load_rows<D, LY>(f[1], y, row, 1, kt0 + kt);
+        split_frag<LS>(st[2 * kt].v, st[2 * kt + 1].v, x);
+        mma_pair<LS, LY, SWAP>(hi, lo, x, f);
+        __builtin_amdgcn_sched_barrier(0);
     }
 }
 // The same with a state that stays as it is, split once: the first LS of its LL planes.
@@ -626,6 +659,31 @@ __device__ __forceinline__ void rank_update(Blk (&st)[D / 16], const __bf16 *at,
     st[2 * NS - 1].v += t[(NS - 1) & 1][1];
 }
 
+// The same for state blocks rb0 .. rb0 + NR - 1, two blocks at a time (four with single planes), for four
+// waves a SIMD.
+template <int D, int NR, int LA, int LB, typename LN>
+__device__ __forceinline__ void rank_steps(Blk (&st)[NR], const __bf16 *at, int rb0, const bf8v (&b)[LB],
+                                           const LN &ln)
+{
+    const int col = LN::local(ln.col);
+    constexpr int AT = LA * LB == 1 && NR >= 4 ? 4 : 2;
+#pragma unroll
+    for (int r = 0; r < NR; r += AT) {
+        bf8v a[AT][LA];
+#pragma unroll
+        for (int i = 0; i < AT; ++i) load_cols<D, LA>(a[i], at, col, rb0 + r + i);
+        if constexpr (LA * LB == 1) {
+#pragma unroll
+            for (int i = 0; i < AT; ++i) st[r + i].v = mfma(a[i][0], b[0], st[r + i].v);
+        } else {
+            f4v t[2];
+            step_pair<LA, LB>(t, a, b);
+            st[r].v += t[0];
+            st[r + 1].v += t[1];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    }
+}
 // The same for two tiles of single planes, b0 and b1: one addition to the state for both.  The matrix
 // pipe cuts an accumulator off where the vector ALU rounds, so long sums gain from fewer, rounded
 // additions (bf16 D = 128, S over 8192 rows against 64 bits: 1.9e-7 with one instruction a tile onto

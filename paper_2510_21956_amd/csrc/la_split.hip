@@ -39,7 +39,7 @@
 // 63 / 85 / 105 us against 65 / 97 / 100 on kernels with chunks of 64 rows and two tiles a tensor;
 // D = 64, 36 slices of 5003 rows, with two workgroups a CU instead of one, 28 / 33 / 39 against
 // 41 / 51 / 56.  bf16 with normalised rows: 104 / 151 / 192 against 221 / 316 / 402 on fp32 tiles.
-#include "la_planes.h"
+#include "la_wave32.h"
 
 namespace la {
 namespace {
@@ -134,8 +134,8 @@ __device__ __forceinline__ void store_grad(TIO *out, float *part, bool add, int 
         store_grad_block<D, LD>(out, part, add, w * 16, rows_valid, l, x[0], x[1], x[2], x[3]);
 }
 // Backward of the row normalisation on the two output blocks; xhat = scale * the tile's rows.
-template <bool SWAP, bool OP, int D, int LQ>
-__device__ __forceinline__ void project_chunk(f4v (&x)[2], const __bf16 *tile, const Lanes<D, (D >= 128)> &ln,
+template <bool SWAP, bool OP, int D, int LQ, typename LN>
+__device__ __forceinline__ void project_chunk(f4v (&x)[2], const __bf16 *tile, const LN &ln,
                                               const float *scale, float *dots, const float *inv, int w,
                                               int c, int g)
 {
@@ -192,26 +192,34 @@ __device__ __forceinline__ void factor_frag(bf8v (&o)[3], const float *r, int g)
                   *reinterpret_cast<const f4v *>(r + 16 + 4 * g), o);
 }
 
+// The waves that form weight blocks are the last to reach the barrier behind them: between the two calls
+// their instructions go first.  fp32, D = 64, 64 slices of 4096 rows, forward / ascending / descending sweep
+// 68.6 / 92.0 / 95.0 us without, 67.1 / 90.0 / 93.9 with; without the mask, 64 of 16384, where no blocks are
+// formed but the waves of a SIMD drift apart, ascending 234.7 and 227.4; bf16 within 1 %.
+__device__ __forceinline__ void go_first(bool on)
+{
+    if (on) __builtin_amdgcn_s_setprio(2);
+}
+__device__ __forceinline__ void go_in_turn() { __builtin_amdgcn_s_setprio(0); }
+
 // One tensor's chunk into its tile: normalised (NORM, fp32) and times scale[row], if given, on
 // the way.  1 / |row| goes to inv_out.
 template <bool NORM, bool OP, int L, typename CH>
 __device__ __forceinline__ void stage(const CH &ch, __bf16 *tile, float *inv_out = nullptr,
-                                      const float *scale = nullptr)
+                                      const float *scale = nullptr, int t = threadIdx.x)
 {
+    f4v x[CH::NQ];
+    ch.values(x);
     if constexpr (L == 1) {  // bf16 as it stands; NORM: 1 / |row| to inv_out
-        if constexpr (NORM) {
-            f4v x[2] = {ch.value(0), ch.value(1)};
-            normalise_quads<CH>(x, inv_out);
-        }
-        ch.template store<OP, L>(tile);
+        if constexpr (NORM) normalise_quads<CH>(x, inv_out, t);
+        ch.template store<OP, L>(tile, t);
     } else {
-        f4v x[2] = {ch.value(0), ch.value(1)};
-        if constexpr (NORM) normalise_quads<CH>(x, inv_out);
+        if constexpr (NORM) normalise_quads<CH>(x, inv_out, t);
         if (scale) {
 #pragma unroll
-            for (int k = 0; k < 2; ++k) x[k] *= scale[CH::row(k)];
+            for (int k = 0; k < CH::NQ; ++k) x[k] *= scale[CH::row(k, t)];
         }
-        CH::template store_values<OP, L>(tile, x);
+        CH::template store_values<OP, L>(tile, x, t);
     }
 }
 
@@ -441,6 +449,7 @@ __global__ __launch_bounds__(4 * D, 2) void ks_fwd_apply(
         const long cn = min(c0 + MD::DEPTH * CR, c_last);
         cur.q.load(Qp, cn, N);
 
+        go_first(w < 3);
         // ---- phase A: weight blocks P = tril(a + b Q K^T), rows n, columns i ----
 #pragma unroll 1
         for (int pidx = w; pidx < 3; pidx += NW) {
@@ -467,6 +476,7 @@ __global__ __launch_bounds__(4 * D, 2) void ks_fwd_apply(
         cur.v.load(Vp, cn, N);
         block_sync();
 
+        go_in_turn();
         // ---- phase B: denominators; V^T P^T on top, divide, store ----
         if (l < CR) {
             const float ps = psum[0][l] + (l >= 16 ? psum[1][l] : 0.f);
@@ -535,7 +545,6 @@ __global__ __launch_bounds__(4 * D, 2) void ks_fwd_apply(
 // The rows are cut as fills the chip best, rows_wg a workgroup, whatever the segments were; the
 // state is split into planes once.  Bound by memory and by what a workgroup needs before its first
 // row (the 4 D^2 bytes of the state, out of L2).  bf16 stages 64 rows between its two barriers.
-// FIGURES
 // LD > D, xflags, Gin and Fraw as above.
 // ---------------------------------------------------------------------------
 template <int MODE, int D, int LD>
@@ -790,6 +799,7 @@ __global__ __launch_bounds__(4 * D, 2) void ks_bwd_dq(
         cur.o.load(Op, cn, N);
         if constexpr (!CAUSAL) cur.q.load(Qp, cn, N);
 
+        go_first(w < 3);
         // ---- phase A: weight blocks Cm' (rows n, columns i) ----
         if constexpr (CAUSAL) {
 #pragma unroll 1
@@ -817,6 +827,7 @@ __global__ __launch_bounds__(4 * D, 2) void ks_bwd_dq(
             block_sync();
         }
 
+        go_in_turn();
         // ---- phase B: K^T Cm'^T on top, scale, store ----
         f4v x[2];
 #pragma unroll
@@ -892,15 +903,279 @@ __global__ __launch_bounds__(4 * D, 2) void ks_bwd_dq(
 }
 
 // ---------------------------------------------------------------------------
-// Backward, descending sweep: dK and dV (Eq. back1 / back2).
+// Backward, ascending sweep, masked: dQ (Eq. back1), dprime, and the segment's reverse sums.
+//   Cm'_in = dO_i . v_n - dprime_i,  dprime_i = o_i . dO_i
+//   dQ_c = diag(b / g) (tril(Cm') K_c + dO_c S^T - dprime z^T);  then S += K_c^T V_c, z += sum k
+//   R += (Q/g)_c^T dO_c,  u += sum dprime (q/g),  w += sum dO / g
+// Half the waves make dQ and hold the state transposed (rows j, columns r: the product contracts over j);
+// the others form the weight blocks and hold R.  Only at D = 32 (and 16), where a chunk's latencies are
+// most of its time: one slice of 256 rows, D = 16, 14.7 -> 11.6 us.  Beyond, waves that hold both states are
+// as fast or faster: fp32, 64 slices of 4096 rows, D = 64 88 us against 92 in halves; bf16, 36 of 5003 33.2
+// against 35.2, 128 of 2048, D = 128 86 against 94.
+// ---------------------------------------------------------------------------
+template <int MODE, int D, int LD>
+__global__ __launch_bounds__(8 * D, 4) void ks_bwd_dq_halves(
+    const typename Mode<MODE>::TIO *__restrict__ Q, const typename Mode<MODE>::TIO *__restrict__ K,
+    const typename Mode<MODE>::TIO *__restrict__ V, const typename Mode<MODE>::TIO *__restrict__ O,
+    const float *__restrict__ G, const typename Mode<MODE>::TIO *__restrict__ dO,
+    typename Mode<MODE>::TIO *__restrict__ dQ, float *ws, const float *sinit, size_t sinit_floats,
+    float *__restrict__ dprime, int N, int nseg, SegMap sm, size_t slot_floats, float b, int xflags,
+    float *__restrict__ Pq)
+{
+    typedef Mode<MODE> MD;
+    typedef typename MD::TIO TIO;
+    constexpr int L = MD::LQ, LX = MD::LX;
+    constexpr bool SWAP = MD::SWAP, QT = MD::QT, PROJ = MD::NORM, F32 = sizeof(TIO) == 4;
+    static_assert(D == 32 && LD <= D, "the larger head sizes have a kernel of their own");
+    constexpr bool TIGHT = PROJ;
+    constexpr int DEPTH = MD::DEPTH;
+    constexpr int NW = D / 16, NRB = D / 16, PL = Tile<D>::PLANE, WPL = Tile<32>::PLANE;
+    typedef Chunk<TIO, D, LD, true> CH;
+    typedef BwdSlot<D> SL;
+    __shared__ __align__(16) __bf16 lds[4 * L * PL + LX * WPL];
+    __shared__ __align__(16) __bf16 frs[2][3 * CR], fdl[3 * CR];  // 1/g, dprime as operands
+    __shared__ __align__(16) float rsb[2][CR], gb[2][CR], dl[CR];
+    __shared__ __align__(16) float qinv[PROJ ? CR : 4], dots[PROJ ? NW * CR : 4];  // 1 / |q|
+    __shared__ __align__(16) float ik[MD::RN ? CR : 4];                            // 1 / |k|
+    __bf16 *dOt = lds;  // operand-ordered; the others natural
+    __bf16 *Qt = dOt + L * PL, *Vt = Qt + L * PL, *Kt = Vt + L * PL, *Ct = Kt + L * PL;
+
+    const int bh = blockIdx.x / nseg, seg = blockIdx.x % nseg;
+    const size_t base = (size_t)bh * N * LD;
+    const TIO *Qp = Q + base, *Kp = K + base, *Vp = V + base, *Op = O + base, *dOp = dO + base;
+    TIO *dQp = dQ + base;
+    const float *Gp = G + (size_t)bh * N;
+    float *dp = dprime + (size_t)bh * N;
+    const long row0 = seg_row(sm, seg, nseg, N), row1 = seg_row(sm, seg + 1, nseg, N);
+    const int t = threadIdx.x, l = t % 64, c = l % 16, g = l / 16;
+    const int wv = __builtin_amdgcn_readfirstlane(t / 64);
+    const int half = wv / NW, w = wv % NW;  // half 0: dQ; half 1: R; columns 16 w ..
+    const Lanes<D, TIGHT> ln(c, g);
+    const bf8v one[1] = {ones_frag()};
+    const bool need_R = seg > 0;  // segment 0's sums start no one
+    const bool need_Q = need_R || PROJ;
+
+    const float *slot = sinit + ((size_t)bh * nseg + seg) * sinit_floats;
+    Blk st[NRB];  // half 0: S^T, rows j, columns r = 16w + c;  half 1: R, rows r, columns j
+    Sum<SWAP> vec, vec2;  // z; u, w
+#pragma unroll
+    for (int jb = 0; jb < NRB; ++jb) st[jb].zero();
+    if (seg > 0 && half == 0) {
+#pragma unroll
+        for (int jb = 0; jb < NRB; ++jb)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                st[jb].set(i, slot[SL::ST + (jb * 16 + 4 * g + i) * D + w * 16 + c]);
+        vec.load(slot + SL::Z, w, c, g);
+    }
+    if (t < 64) store_weights<LX>(Ct, c, 1, g, f4v{0.f, 0.f, 0.f, 0.f});
+
+    // fp32: all five tensors in every thread (dO, O, Q, V, K); bf16: dO, O and Q in half 0, V and K in
+    // half 1
+    struct Set {
+        CH x[F32 ? 5 : 3];
+        float g;  // g of row t % 32 (first wave)
+    } sets[DEPTH];
+    const long c_last = row0 + (row1 - row0 - 1) / CR * CR;
+    auto request = [&](Set &s, long c0, bool first, bool second) __attribute__((always_inline)) {
+        const int th = ln.local(t);
+        if (first) {
+            if (F32 || half == 0) {
+                s.x[0].load(dOp, c0, N, th);
+                s.x[1].load(Op, c0, N, th);
+            } else {
+                s.x[0].load(Vp, c0, N, th);
+                s.x[1].load(Kp, c0, N, th);
+            }
+        }
+        if (second) {
+            if (need_Q && (F32 || half == 0)) s.x[2].load(Qp, c0, N, th);
+            if constexpr (F32) {
+                s.x[3].load(Vp, c0, N, th);
+                s.x[4].load(Kp, c0, N, th);
+            }
+            if (wv == 0) s.g = load_row_float(Gp, c0, N, th % CR);
+        }
+    };
+    // 1/g of the chunk starting at c0, whose g is gn, into buffer `par`
+    auto post_factors = [&](long c0, float gn, int par) {
+        const int th = ln.local(t);
+        if (th < CR) {
+            const bool ok = th < (int)(row1 - c0);
+            const float r = ok ? __builtin_amdgcn_rcpf(gn) : 0.f;
+            rsb[par][th] = r;
+            gb[par][th] = ok ? gn : 0.f;
+            store_factor<3>(frs[par], th, r);
+        }
+    };
+#pragma unroll
+    for (int i = 0; i < DEPTH; ++i) request(sets[i], min(row0 + i * CR, c_last), true, true);
+    post_factors(row0, sets[0].g, 0);
+    // nxt: the set that holds the chunk after this one
+    auto chunk = [&](long c0, Set &cur, Set &nxt, int par) __attribute__((always_inline)) {
+        block_sync();
+        const int th = ln.local(t), l = th % 64, c = l % 16, g = l / 16;
+        const Lanes<32> lw(c, g);
+        const float *rs = rsb[par];
+        const bool lo_on = c0 < sm.lo_rows;  // second plane of the intermediates: early rows
+        if (F32 || half == 0) {
+            if (need_Q) stage<MD::NORM, false, L>(cur.x[2], Qt, PROJ ? qinv : nullptr, QT ? rs : nullptr, th);
+            f4v d[CH::NQ], o[CH::NQ];
+            cur.x[0].values(d);
+            cur.x[1].values(o);
+            float s[CH::NQ];
+#pragma unroll
+            for (int k = 0; k < CH::NQ; ++k) s[k] = dot4(d[k], o[k]);
+            CH::row_totals(s);
+            if (CH::leader(th)) {
+                const int r = CH::row(0, th);
+                dl[r] = s[0];
+                // the row's weight in u: the staged rows are q/g (QT), or q (times 1/|q|;
+                // this lane wrote that factor)
+                float wu = QT ? s[0] : s[0] * rs[r];
+                if constexpr (MD::RN) wu *= qinv[r];
+                store_factor<3>(fdl, r, wu);
+                if (r < (int)(row1 - c0)) (dp + c0)[r] = s[0];
+            }
+            cur.x[0].template store<true, L>(dOt, th);
+        }
+        if (F32 || half == 1) {
+            constexpr int I = F32 ? 3 : 0;
+            cur.x[I].template store<false, L>(Vt, th);
+            stage<MD::NORM, false, L>(cur.x[I + 1], Kt, MD::RN ? ik : nullptr, nullptr, th);
+            if constexpr (F32) {
+                if (__builtin_expect(max(cur.x[0].top(), cur.x[I].top()) > kLargestBf16, 0)) {
+                    cur.x[0].template store_any<true>(dOt, th);
+                    cur.x[I].template store_any<false>(Vt, th);
+                }
+            }
+        }
+        block_sync();
+        const long cn = min(c0 + DEPTH * CR, c_last);
+        request(cur, cn, true, false);
+
+        if (half) {
+            // ---- phase A: weight blocks Cm' (rows n, columns i) ----
+#pragma unroll 1
+            for (int pidx = w; pidx < 3; pidx += NW) {
+                const int ib = pidx ? 1 : 0, nb = pidx == 2 ? 1 : 0;
+                const f4v pa = block_product<D, L, L>(Vt, nb, dOt, ib, ln);
+                const float di = dl[ib * 16 + c];
+                const int last = nb == ib ? c : 15;  // last row n at or before row i
+                f4v x;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) x[e] = 4 * g + e > last ? 0.f : pa[e] - di;
+                if constexpr (MD::RN) x *= *reinterpret_cast<const f4v *>(ik + nb * 16 + 4 * g);
+                with_planes<LX>(lo_on, [&](auto n) { store_weights<n.value>(Ct, ib * 16 + c, nb, g, x); });
+            }
+            block_sync();
+            bf8v df[L];
+            if (need_R) {
+                load_cols_op<D, L>(df, dOt, ln.local(ln.ocol), w);
+                {
+                    bf8v fr[3];
+                    load_factor<3>(fr, frs[par], g);
+                    vec2.add(df, fr);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+                bf8v qf[L], fd[3];
+                load_cols<D, L>(qf, Qt, ln.local(ln.col), w);
+                load_factor<3>(fd, fdl, g);
+                vec.add(qf, fd);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            request(cur, cn, false, true);
+            if (need_R) {
+                if constexpr (QT) {
+                    rank_steps<D, NRB, L, L>(st, Qt, 0, df, ln);
+                } else {
+                    with_planes<LX>(lo_on, [&](auto n) {
+                        bf8v oh[n.value];
+                        scale_frag<n.value>(oh, df, rs, g, MD::RN ? qinv : nullptr);
+                        rank_steps<D, NRB, L, n.value>(st, Qt, 0, oh, ln);
+                    });
+                }
+            }
+            if constexpr (PROJ) block_sync();  // the one inside project_chunk
+        } else {
+            f4v fh[2], fl[2];  // rows i, columns r (SWAP), or rows r, columns i
+#pragma unroll
+            for (int m = 0; m < 2; ++m) fh[m] = fl[m] = f4v{0.f, 0.f, 0.f, 0.f};
+            with_planes<LX>(lo_on, [&](auto n) { state_steps<D, D / 32, n.value, L, SWAP>(fh, fl, st, dOt, 0, ln); });
+            bf8v kf[L];
+            load_cols<D, L>(kf, Kt, ln.local(ln.col), w);
+            block_sync();
+
+            // ---- phase B: K^T Cm'^T on top, scale, store ----
+            f4v x[2];
+#pragma unroll
+            for (int m = 0; m < 2; ++m) {
+                f4v f = fh[m] + fl[m];
+                with_planes<LX>(lo_on, [&](auto n) {
+                    bf8v pf[n.value];
+                    load_rows<32, n.value>(pf, Ct, lw.row, m, 0);
+                    f += own_product<SWAP, L, n.value>(kf, pf);
+                });
+                x[m] = (b * row_factor<SWAP>(rs, m, c, g)) * (f - vec.v * row_factor<SWAP>(dl, m, c, g));
+            }
+            if constexpr (PROJ)  // qhat = g (q/g), or q / |q|
+                project_chunk<SWAP, false, D, L>(x, Qt, ln, QT ? gb[par] : qinv, dots, qinv, w, c, g);
+#pragma unroll
+            for (int m = 0; m < 2; ++m)
+                store_grad<SWAP, D, LD>(dQp + (size_t)(c0 + m * 16) * LD,
+                                        Pq + ((size_t)bh * N + c0 + m * 16) * D, xflags & 1, w,
+                                        (int)(row1 - c0) - m * 16, l, x[m]);
+            request(cur, cn, false, true);
+            if constexpr (MD::RN) {
+                bf8v fk[3], kh[3];
+                factor_frag(fk, ik, g);
+                vec.add(kf, fk);
+                scale_frag<3>(kh, kf, ik, g);
+                rank_steps<D, NRB, L, 3>(st, Vt, 0, kh, ln);
+            } else {
+                vec.add(kf, one);
+                rank_steps<D, NRB, L, L>(st, Vt, 0, kf, ln);
+            }
+            post_factors(min(c0 + CR, row1), nxt.g, par ^ 1);
+        }
+    };
+    if constexpr (DEPTH == 2) {
+        for (long c0 = row0; c0 < row1; c0 += 2 * CR) {
+            chunk(c0, sets[0], sets[DEPTH - 1], 0);
+            if (c0 + CR < row1) chunk(c0 + CR, sets[DEPTH - 1], sets[0], 1);
+        }
+    } else {
+        int par = 0;
+        for (long c0 = row0; c0 < row1; c0 += CR, par ^= 1) chunk(c0, sets[0], sets[0], par);
+    }
+    if (need_R && half) {
+        float *out = ws + ((size_t)bh * nseg + seg - 1) * slot_floats;
+#pragma unroll
+        for (int rb = 0; rb < NRB; ++rb)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) out[SL::R + (rb * 16 + 4 * g + i) * D + w * 16 + c] = st[rb].get(i);
+        vec2.store(out + SL::W, w, c, g);
+        vec.store(out + SL::U, w, c, g);
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Backward, descending sweep, masked: dK and dV (Eq. back1 / back2).
 //   dK_c = b (tril(Cm')^T (Q/g)_c + V_c R^T - 1 u^T),   Cm'_in = dO_i . v_n - dprime_i
 //   dV_c = tril(W)^T dO_c + a 1 w^T + b K_c R,          W_in = a / g_i + b (q_i/g_i) . k_n
 //   then R += (Q/g)_c^T dO_c, u += sum dprime (q/g), w += sum dO / g.
-// R is held twice: rows r x columns j for dV, rows j x columns r for dK.
+// R is held twice.  2 D/16 waves: half make dK and hold R^T (rows j, columns r) and u, the others make dV
+// and hold R (rows r, columns j) and w; both run the same code on exchanged tiles, 16 columns a wave.
+// Four waves a SIMD instead of two that hold both states: a SIMD issues a wave's instructions one every
+// five clocks, two waves' 2.9 and four waves' closer still, and the kernel is bound by what its waves
+// issue and wait for in turn (vector ALU 41 %, LDS 42 %, matrix pipe 35 % of the clocks, fp32 D = 64).
+// Half the registers a wave have to do (TIGHT).  Descending sweep, us, before and now: fp32, 64 slices of 4096
+// rows, D = 64 104 -> 94; of 1000 rows, D = 128 70 -> 67; bf16, 36 of 5003, D = 64 38.6 -> 30.0; normalised, 128 of
+// 2048, D = 128 190 -> 182; one slice of 256 rows, D = 16 17.7 -> 13.3.
 // LD > D: xflags & 2 (dK), & 4 (dV) mark the second of the two launches that build them up.
 // ---------------------------------------------------------------------------
-template <int MODE, int D, bool CAUSAL, int LD>
-__global__ __launch_bounds__(4 * D, 2) void ks_bwd_dkv(
+template <int MODE, int D, int LD>
+__global__ __launch_bounds__(8 * D, 4) void ks_bwd_dkv(
     const typename Mode<MODE>::TIO *__restrict__ Q, const typename Mode<MODE>::TIO *__restrict__ K,
     const typename Mode<MODE>::TIO *__restrict__ V, const float *__restrict__ G,
     const typename Mode<MODE>::TIO *__restrict__ dO, typename Mode<MODE>::TIO *__restrict__ dK,
@@ -910,86 +1185,99 @@ __global__ __launch_bounds__(4 * D, 2) void ks_bwd_dkv(
 {
     typedef Mode<MODE> MD;
     typedef typename MD::TIO TIO;
-    constexpr int LQ = MD::LQ, LV = MD::LV, LX = MD::LX;
-    constexpr bool SWAP = MD::SWAP, QT = MD::QT, PROJ = MD::NORM;
+    constexpr int L = MD::LQ, LX = MD::LX;  // planes of a tile, of intermediates
+    constexpr bool SWAP = MD::SWAP, QT = MD::QT, PROJ = MD::NORM, F32 = sizeof(TIO) == 4;
+    constexpr bool TIGHT = D == 128 || (D == 64 && PROJ);  // registers are short
+    constexpr int DEPTH = D == 128 ? 1 : MD::DEPTH;
     constexpr int NW = D / 16, NRB = D / 16, PL = Tile<D>::PLANE, WPL = Tile<32>::PLANE;
-    constexpr int TS = CAUSAL ? 1 : 0;
-    typedef Chunk<TIO, D, LD> CH;
+    typedef Chunk<TIO, D, LD, true> CH;
     typedef BwdSlot<D> SL;
-    __shared__ __align__(16) __bf16 lds[LQ * PL + LV * PL + TS * (LQ * PL + LV * PL + 2 * LX * WPL)];
+    __shared__ __align__(16) __bf16 lds[4 * L * PL + 2 * LX * WPL];
     __shared__ __align__(16) __bf16 frs[2][3 * CR], fdl[2][3 * CR];  // 1/g, dprime as operands
     __shared__ __align__(16) float rsb[2][CR], dlb[2][CR];
     __shared__ __align__(16) float kinv[PROJ ? CR : 4], dots[PROJ ? NW * CR : 4];  // 1 / |k|
     __shared__ __align__(16) float iq[MD::RN ? CR : 4];                            // 1 / |q|
-    __bf16 *Kt = lds, *Vt = Kt + LQ * PL;  // operand-ordered; Q/g and dO natural
-    __bf16 *Qt = Vt + LV * PL, *dOt = Qt + TS * LQ * PL, *Ct = dOt + TS * LV * PL,
-           *Wt = Ct + TS * LX * WPL;
+    __bf16 *Kt = lds, *Vt = Kt + L * PL;  // operand-ordered; Q/g and dO natural
+    __bf16 *Qt = Vt + L * PL, *dOt = Qt + L * PL, *Ct = dOt + L * PL, *Wt = Ct + LX * WPL;
 
     const int bh = blockIdx.x / nseg, seg = blockIdx.x % nseg;
     const size_t base = (size_t)bh * N * LD;
     const TIO *Qp = Q + base, *Kp = K + base, *Vp = V + base, *dOp = dO + base;
-    TIO *dKp = dK + base, *dVp = dV + base;
     const float *Gp = G + (size_t)bh * N, *dp = dprime + (size_t)bh * N;
     const long row0 = seg_row(sm, seg, nseg, N), row1 = seg_row(sm, seg + 1, nseg, N);
     const int t = threadIdx.x, l = t % 64, c = l % 16, g = l / 16;
-    const int w = __builtin_amdgcn_readfirstlane(t / 64);
-    const Lanes<D, (D >= 128)> ln(c, g);
-    const Lanes<32> lw(c, g);
+    const int wv = __builtin_amdgcn_readfirstlane(t / 64);
+    const int half = wv / NW, w = wv % NW;  // half 0: dK; half 1: dV; columns 16 w ..
+    const Lanes<D, TIGHT> ln(c, g);
 
-    const bool zero_init = CAUSAL && seg == nseg - 1;
-    const float *slot = ws + ((size_t)bh * nseg + (CAUSAL ? seg : 0)) * slot_floats;
-    Blk Ra[NRB], Rb[NRB];  // R: rows r, columns j = 16w + c;  R^T: rows j, columns r = 16w + c
+    // the half's tiles: of the state product, of the own columns, of the update; its weights
+    const __bf16 *Yt = half ? Kt : Vt, *Et = half ? dOt : Qt, *At = half ? Qt : dOt,
+                 *Xt = half ? Wt : Ct;
+    Blk st[NRB];
+    Sum<SWAP> vec;  // u or w
 #pragma unroll
-    for (int rb = 0; rb < NRB; ++rb) {
-        Ra[rb].zero();
-        Rb[rb].zero();
-    }
-    Sum<SWAP> uacc, wacc;  // u, w
-    if (!zero_init) {
+    for (int rb = 0; rb < NRB; ++rb) st[rb].zero();
+    if (seg < nseg - 1) {
+        const float *slot = ws + ((size_t)bh * nseg + seg) * slot_floats;
+        if (half) {
 #pragma unroll
-        for (int rb = 0; rb < NRB; ++rb) {
+            for (int rb = 0; rb < NRB; ++rb)
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
-                Ra[rb].set(i, slot[SL::R + (rb * 16 + 4 * g + i) * D + w * 16 + c]);
-            Rb[rb].v = *reinterpret_cast<const f4v *>(slot + SL::R + (w * 16 + c) * D + rb * 16 + 4 * g);
+                for (int i = 0; i < 4; ++i)
+                    st[rb].set(i, slot[SL::R + (rb * 16 + 4 * g + i) * D + w * 16 + c]);
+        } else {
+#pragma unroll
+            for (int rb = 0; rb < NRB; ++rb)
+                st[rb].v = *reinterpret_cast<const f4v *>(slot + SL::R + (w * 16 + c) * D + rb * 16 + 4 * g);
         }
-        uacc.load(slot + SL::U, w, c, g);
-        wacc.load(slot + SL::W, w, c, g);
+        vec.load(slot + (half ? SL::W : SL::U), w, c, g);
     }
-    if constexpr (CAUSAL) {
-        if (t < 64) {
-            store_weights<LX>(Ct, 16 + c, 0, g, f4v{0.f, 0.f, 0.f, 0.f});
-            store_weights<LX>(Wt, 16 + c, 0, g, f4v{0.f, 0.f, 0.f, 0.f});
-        }
+    if (t < 64) {
+        store_weights<LX>(Ct, 16 + c, 0, g, f4v{0.f, 0.f, 0.f, 0.f});
+        store_weights<LX>(Wt, 16 + c, 0, g, f4v{0.f, 0.f, 0.f, 0.f});
     }
 
     const long nchunks = (row1 - row0 + CR - 1) / CR;
+    // fp32: all four tensors in every thread; bf16: K and Q in half 0, V and dO in half 1
     struct Set {
-        CH k, v, q, d;
-        float g, dp;  // g, dprime of row t % 32
-    } sets[MD::DEPTH];
-    auto post_factors = [&](long c0, const Set &x, int par) {
-        if (CAUSAL && t < CR) {
-            const bool ok = t < (int)(row1 - c0);
-            const float r = ok ? __builtin_amdgcn_rcpf(x.g) : 0.f, d = ok ? x.dp : 0.f;
-            rsb[par][t] = r;
-            dlb[par][t] = d;
-            store_factor<3>(frs[par], t, r);
-            store_factor<3>(fdl[par], t, QT ? d : d * r);
+        CH x[F32 ? 4 : 2];
+        float gd;  // first wave: g of row l (l < 32), dprime of row l - 32
+    } sets[DEPTH];
+    // in two parts: registers are short while the state product runs
+    auto request = [&](Set &s, long c0, bool first, bool second) __attribute__((always_inline)) {
+        const int th = ln.local(t);
+        if (first) {
+            if constexpr (F32) {
+                s.x[0].load(Kp, c0, N, th);
+                s.x[1].load(Vp, c0, N, th);
+            } else {
+                s.x[0].load(half ? Vp : Kp, c0, N, th);
+            }
+        }
+        if (second) {
+            if constexpr (F32) {
+                s.x[2].load(Qp, c0, N, th);
+                s.x[3].load(dOp, c0, N, th);
+            } else {
+                s.x[1].load(half ? dOp : Qp, c0, N, th);
+            }
+            if (wv == 0) s.gd = (th < CR ? Gp : dp)[min((unsigned)c0 + th % CR, (unsigned)N - 1)];
         }
     };
-#pragma unroll
-    for (int i = 0; i < MD::DEPTH; ++i) {
-        const long cl = row0 + max(nchunks - 1 - i, 0L) * CR;
-        sets[i].k.load(Kp, cl, N);
-        sets[i].v.load(Vp, cl, N);
-        if constexpr (CAUSAL) {
-            sets[i].g = load_row_float(Gp, cl, N, t % CR);
-            sets[i].dp = load_row_float(dp, cl, N, t % CR);
-            sets[i].q.load(Qp, cl, N);
-            sets[i].d.load(dOp, cl, N);
+    // 1/g and dprime of the chunk starting at c0 into buffer `par`
+    auto post_factors = [&](long c0, const Set &x, int par) {
+        if (wv != 0) return;
+        const int th = ln.local(t), r = th % CR;
+        float y = r < (int)(row1 - c0) ? (th < CR ? __builtin_amdgcn_rcpf(x.gd) : x.gd) : 0.f;
+        (th < CR ? rsb : dlb)[par][r] = y;
+        if constexpr (!QT) {  // dprime / g
+            const float inv = __shfl(y, r);
+            if (th >= CR) y *= inv;
         }
-    }
+        store_factor<3>((th < CR ? frs : fdl)[par], r, y);
+    };
+#pragma unroll
+    for (int i = 0; i < DEPTH; ++i) request(sets[i], row0 + max(nchunks - 1 - i, 0L) * CR, true, true);
     post_factors(row0 + (nchunks - 1) * CR, sets[0], 0);
     // nxt: the set that holds the chunk after this one
     auto chunk = [&](long ci, Set &cur, Set &nxt, int par) __attribute__((always_inline)) {
@@ -997,78 +1285,351 @@ __global__ __launch_bounds__(4 * D, 2) void ks_bwd_dkv(
         const float *rs = rsb[par], *dl = dlb[par];
         const bool lo_on = c0 < sm.lo_rows;  // second plane of the intermediates: early rows
         block_sync();
+        const int th = ln.local(t), l = th % 64, c = l % 16, g = l / 16;
+        const Lanes<32> lw(c, g);
+        if constexpr (F32) {
+            stage<MD::NORM, true, L>(cur.x[0], Kt, PROJ ? kinv : nullptr, nullptr, th);
+            cur.x[1].template store<true, L>(Vt, th);
+            stage<MD::NORM, false, L>(cur.x[2], Qt, nullptr, rs, th);
+            cur.x[3].template store<false, L>(dOt, th);
+            if (__builtin_expect(max(cur.x[1].top(), cur.x[3].top()) > kLargestBf16, 0)) {
+                cur.x[1].template store_any<true>(Vt, th);
+                cur.x[3].template store_any<false>(dOt, th);
+            }
+        } else {
+            if (MD::RN && half == 0) {
+                f4v x[2];
+                cur.x[0].values(x);
+                normalise_quads<CH>(x, kinv, th);
+                cur.x[1].values(x);
+                normalise_quads<CH>(x, iq, th);
+                // the weights in u take the factor this lane just wrote
+                const int r = CH::row(0, th);
+                if (CH::leader(th)) store_factor<3>(fdl[par], r, dl[r] * rs[r] * iq[r]);
+            }
+            if constexpr (L == 1) {
+                cur.x[0].template store_raw<true>(half ? Vt : Kt, th);
+                cur.x[1].template store_raw<false>(half ? dOt : Qt, th);
+            }
+        }
+        block_sync();
+        const long cn = row0 + max(ci - DEPTH, 0L) * CR;
+        request(cur, cn, true, false);
+
+        go_first(wv < 6);
+        // ---- phase A: weight blocks Cm' and W (rows i, columns n) ----
+#pragma unroll 1
+        for (int pidx = wv; pidx < 6; pidx += 2 * NW) {
+            const int q = pidx >= 3 ? pidx - 3 : pidx, ib = q ? 1 : 0, nb = q == 2 ? 1 : 0;
+            const bool cm = pidx < 3;
+            const f4v r4 = *reinterpret_cast<const f4v *>(rs + ib * 16 + 4 * g);
+            f4v x = block_product<D, L, L>(cm ? dOt : Qt, ib, cm ? Vt : Kt, nb, ln);
+            f4v iq4 = {1.f, 1.f, 1.f, 1.f};
+            if constexpr (MD::RN) iq4 = *reinterpret_cast<const f4v *>(iq + ib * 16 + 4 * g);
+            if (cm) {
+                x -= *reinterpret_cast<const f4v *>(dl + ib * 16 + 4 * g);
+                if constexpr (!QT) x *= r4;
+                if constexpr (MD::RN) x *= iq4;
+            } else {
+                if constexpr (MD::RN) x = (x * kinv[nb * 16 + c]) * iq4;
+                if constexpr (QT) x = a * r4 + b * x;
+                else x = (a + b * x) * r4;
+            }
+            const int first = nb == ib ? c : 0;  // first row i that sees column n
+#pragma unroll
+            for (int e = 0; e < 4; ++e) x[e] = 4 * g + e < first ? 0.f : x[e];
+            with_planes<LX>(lo_on, [&](auto n) { store_weights<n.value>(cm ? Ct : Wt, nb * 16 + c, ib, g, x); });
+        }
+        f4v fh[2], fl[2];  // rows n, the wave's columns (SWAP), or the other way round
+#pragma unroll
+        for (int m = 0; m < 2; ++m) fh[m] = fl[m] = f4v{0.f, 0.f, 0.f, 0.f};
+        with_planes<LX>(lo_on, [&](auto n) { state_steps<D, D / 32, n.value, L, SWAP>(fh, fl, st, Yt, 0, ln); });
+        bf8v own[L];
+        load_cols<D, L>(own, Et, ln.local(ln.col), w);
+        request(cur, cn, false, true);
+        block_sync();
+
+        go_in_turn();
+        // ---- phase B ----
+        f4v x[2];
+#pragma unroll
+        for (int m = 0; m < 2; ++m) {
+            f4v f = fh[m] + fl[m], y = {0.f, 0.f, 0.f, 0.f};
+            with_planes<LX>(lo_on, [&](auto n) {
+                bf8v pf[n.value];
+                load_rows<32, n.value>(pf, Xt, lw.row, m, 0);
+                y = own_product<SWAP, L, n.value>(own, pf);
+            });
+            if (half) x[m] = (a * vec.v + (MD::RN ? b * kinv[m * 16 + c] : b) * f) + y;
+            else x[m] = b * ((f + y) - vec.v);
+        }
+        if constexpr (PROJ) {
+            if (half)
+                block_sync();  // the one inside project_chunk
+            else
+                project_chunk<SWAP, true, D, L>(x, Kt, ln, QT ? nullptr : kinv, dots, kinv, w, c, g);
+        }
+        TIO *out = (half ? dV : dK) + base + (size_t)c0 * LD;
+        float *part = (half ? Pv : Pk) + ((size_t)bh * N + c0) * D;
+#pragma unroll
+        for (int m = 0; m < 2; ++m)
+            store_grad<SWAP, D, LD>(out + (size_t)(m * 16) * LD, part + m * 16 * D, xflags & (half ? 4 : 2), w,
+                                    (int)(row1 - c0) - m * 16, l, x[m]);
+        bf8v fac[3];
+        load_factor<3>(fac, half ? frs[par] : fdl[par], g);
+        vec.add(own, fac);
+        if constexpr (QT) {
+            rank_steps<D, NRB, L, L>(st, At, 0, own, ln);
+        } else {
+            with_planes<LX>(lo_on, [&](auto n) {
+                bf8v og[n.value];
+                scale_frag<n.value>(og, own, rs, g, MD::RN ? iq : nullptr);
+                rank_steps<D, NRB, L, n.value>(st, At, 0, og, ln);
+            });
+        }
+        post_factors(row0 + max(ci - 1, 0L) * CR, nxt, par ^ 1);
+    };
+    if constexpr (DEPTH == 2) {
+        for (long ci = nchunks - 1; ci >= 0; ci -= 2) {
+            chunk(ci, sets[0], sets[DEPTH - 1], 0);
+            if (ci > 0) chunk(ci - 1, sets[DEPTH - 1], sets[0], 1);
+        }
+    } else {
+        int par = 0;
+        for (long ci = nchunks - 1; ci >= 0; --ci, par ^= 1) chunk(ci, sets[0], sets[0], par);
+    }
+}
+
+// ---------------------------------------------------------------------------
+// The same for bf16 at D = 128: waves of 32 columns (la_wave32.h), half of them for dK, half for dV, on
+// natural tiles; two chunks requested ahead.
+// ---------------------------------------------------------------------------
+template <int D, int LD>
+__global__ __launch_bounds__(4 * D, 2) void ks_bwd_dkv_wide(
+    const __bf16 *__restrict__ Q, const __bf16 *__restrict__ K, const __bf16 *__restrict__ V,
+    const float *__restrict__ G, const __bf16 *__restrict__ dO, __bf16 *__restrict__ dK, __bf16 *__restrict__ dV,
+    const float *__restrict__ ws, const float *__restrict__ dprime, int N, int nseg, SegMap sm,
+    size_t slot_floats, float a, float b, int xflags, float *__restrict__ Pk, float *__restrict__ Pv)
+{
+    constexpr int LX = Mode<P16>::LX, NW = D / 16, NC = D / 32, PL = NTile<D>::PLANE, WPL = NTile<32>::PLANE;
+    typedef Chunk<__bf16, D, LD> CH;
+    typedef BwdSlot<D> SL;
+    __shared__ __align__(16) __bf16 lds[4 * PL + 2 * LX * WPL];
+    __shared__ __align__(16) __bf16 frs[2][3 * CR], fdl[2][3 * CR];  // 1/g, dprime/g as operands
+    __shared__ __align__(16) float rsb[2][CR], dlb[2][CR], vecs[2 * D];  // 1/g, dprime; u and w
+    __bf16 *Kt = lds, *Vt = Kt + PL, *Qt = Vt + PL, *dOt = Qt + PL, *Ct = dOt + PL, *Wt = Ct + LX * WPL;
+
+    const int bh = blockIdx.x / nseg, seg = blockIdx.x % nseg;
+    const size_t base = (size_t)bh * N * LD;
+    const __bf16 *Qp = Q + base, *Kp = K + base, *Vp = V + base, *dOp = dO + base;
+    const float *Gp = G + (size_t)bh * N, *dp = dprime + (size_t)bh * N;
+    const long row0 = seg_row(sm, seg, nseg, N), row1 = seg_row(sm, seg + 1, nseg, N);
+    const int t = threadIdx.x, l = t % 64, c = l % 32, h = l / 32;
+    const int wv = __builtin_amdgcn_readfirstlane(t / 64);
+    const int half = wv / NC, w = wv % NC;  // half 0: dK; half 1: dV; columns 32 w ..
+    const Lanes32<D> ln(l);
+    const int wrow = Lanes32<32>(l).row;
+
+    // the half's tiles: of the state product, of the own columns, of the update; its weights
+    const __bf16 *Yt = half ? Kt : Vt, *Et = half ? dOt : Qt, *At = half ? Qt : dOt, *Xt = half ? Wt : Ct;
+    f16v st[NC];  // half 0: R^T, rows j, columns r;  half 1: R, rows r, columns j
+    float vec = 0.f;  // u or w, column c
+#pragma unroll
+    for (int rb = 0; rb < NC; ++rb) st[rb] = zero16();
+    if (seg < nseg - 1) {
+        const float *slot = ws + ((size_t)bh * nseg + seg) * slot_floats, *R = slot + SL::R;
+#pragma unroll
+        for (int rb = 0; rb < NC; ++rb)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const int r = 32 * rb + 16 * (k / 2) + 8 * h + 4 * (k % 2);
+                if (half) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) st[rb][4 * k + e] = R[(r + e) * D + 32 * w + c];
+                } else {
+                    const f4v x = *reinterpret_cast<const f4v *>(R + (32 * w + c) * D + r);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) st[rb][4 * k + e] = x[e];
+                }
+            }
+        vec = slot[(half ? SL::W : SL::U) + 32 * w + c];
+    }
+    vecs[half * D + 32 * w + c] = vec;
+    if (t < 64) {  // weight blocks that stay zero: rows n 16 .., columns i 0 .. 15
+        put_weights<LX>(Ct, 16 + l % 16, 0, l / 16, f4v{0.f, 0.f, 0.f, 0.f});
+        put_weights<LX>(Wt, 16 + l % 16, 0, l / 16, f4v{0.f, 0.f, 0.f, 0.f});
+    }
+
+    const long nchunks = (row1 - row0 + CR - 1) / CR;
+    struct Set {
+        CH k, v, q, d;
+    } sets[2];
+    float gd = 0.f;  // first wave: g of row l (l < 32), dprime of row l - 32 of the next chunk
+    auto request_gd = [&](long c0) __attribute__((always_inline)) {
+        if (wv == 0) gd = (t < CR ? Gp : dp)[min((unsigned)c0 + t % CR, (unsigned)N - 1)];
+    };
+    // 1/g and dprime of the chunk starting at c0 into buffer `par`
+    auto post_factors = [&](long c0, int par) {
+        if (wv != 0) return;
+        const int r = t % CR;
+        float y = r < (int)(row1 - c0) ? (t < CR ? __builtin_amdgcn_rcpf(gd) : gd) : 0.f;
+        (t < CR ? rsb : dlb)[par][r] = y;
+        const float inv = __shfl(y, r);
+        if (t >= CR) y *= inv;
+        store_row_factor<3>((t < CR ? frs : fdl)[par], r, y);
+    };
+    auto put = [&](const CH &x, __bf16 *tile) __attribute__((always_inline)) {
+        *reinterpret_cast<u4v *>(tile + NTile<D>::quad(CH::row(0), CH::quad(0))) = x.raw[0];
+    };
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const long cl = row0 + max(nchunks - 1 - i, 0L) * CR;
+        sets[i].k.load(Kp, cl, N);
+        sets[i].v.load(Vp, cl, N);
+        sets[i].q.load(Qp, cl, N);
+        sets[i].d.load(dOp, cl, N);
+    }
+    request_gd(row0 + (nchunks - 1) * CR);
+    post_factors(row0 + (nchunks - 1) * CR, 0);
+    auto chunk = [&](long ci, Set &cur, int par) __attribute__((always_inline)) {
+        const long c0 = row0 + ci * CR;
+        const float *rs = rsb[par], *dl = dlb[par];
+        const bool lo_on = c0 < sm.lo_rows;  // second plane of the intermediates: early rows
+        block_sync();
+        put(cur.k, Kt);
+        put(cur.v, Vt);
+        put(cur.q, Qt);
+        put(cur.d, dOt);
+        block_sync();
+        const long cn = row0 + max(ci - 2, 0L) * CR;
+        cur.k.load(Kp, cn, N);
+        cur.v.load(Vp, cn, N);
+        request_gd(row0 + max(ci - 1, 0L) * CR);
+        go_first(wv < 6);
+        // ---- phase A: weight blocks Cm' and W (rows i, columns n) ----
+#pragma unroll 1
+        for (int pidx = wv; pidx < 6; pidx += NW) {
+            const int q = pidx >= 3 ? pidx - 3 : pidx, ib = q ? 1 : 0, nb = q == 2 ? 1 : 0;
+            const int n = l % 16, g = l / 16;
+            const bool cm = pidx < 3;
+            f4v x = block16<D>(cm ? dOt : Qt, ib, cm ? Vt : Kt, nb, ln.row16);
+            if (cm) x -= *reinterpret_cast<const f4v *>(dl + ib * 16 + 4 * g);
+            else x = a + b * x;
+            x *= *reinterpret_cast<const f4v *>(rs + ib * 16 + 4 * g);
+            const int first = nb == ib ? n : 0;  // first row i that sees column n
+#pragma unroll
+            for (int e = 0; e < 4; ++e) x[e] = 4 * g + e < first ? 0.f : x[e];
+            with_planes<LX>(lo_on, [&](auto np) { put_weights<np.value>(cm ? Ct : Wt, nb * 16 + n, ib, g, x); });
+        }
+        f16v f;  // rows = the wave's columns, columns n
+        with_planes<LX>(lo_on, [&](auto np) { f = state_rows<D, np.value>(st, Yt, ln.row); });
+        bf8v own[2][1];
+#pragma unroll
+        for (int kr = 0; kr < 2; ++kr) own[kr][0] = load_col_frag<D>(Et, ln.own, w, kr);
+        cur.q.load(Qp, cn, N);
+        cur.d.load(dOp, cn, N);
+        block_sync();
+        go_in_turn();
+        // ---- phase B ----
+        f16v y;
+        with_planes<LX>(lo_on, [&](auto np) { y = weight_product<np.value>(own, Xt, wrow); });
+        // dK: b (f + y - u);  dV: b f + y + a w
+        const float ys = half ? 1.f : b, vs = half ? a : -b;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const f4v vq = *reinterpret_cast<const f4v *>(vecs + half * D + 32 * w + 8 * q + 4 * h);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) f[4 * q + e] = b * f[4 * q + e] + (ys * y[4 * q + e] + vs * vq[e]);
+        }
+        store_grad32<D, LD>((half ? dV : dK) + base + (size_t)c0 * LD, (half ? Pv : Pk) + ((size_t)bh * N + c0) * D,
+                            xflags & (half ? 4 : 2), 32 * w, (int)(row1 - c0), l, f);
+        vec += weighted_sum(own, half ? frs[par] : fdl[par], h);
+        vecs[half * D + 32 * w + c] = vec;
+        with_planes<LX>(lo_on, [&](auto np) {
+            bf8v og[2][np.value];
+            scale_own<np.value>(og, own, rs, h);
+            update_rows<D, np.value>(st, At, ln.upd, og);
+        });
+        post_factors(row0 + max(ci - 1, 0L) * CR, par ^ 1);
+    };
+    for (long ci = nchunks - 1; ci >= 0; ci -= 2) {
+        chunk(ci, sets[0], 0);
+        if (ci > 0) chunk(ci - 1, sets[1], 1);
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Backward without the mask: dK_c = b (V_c R^T - 1 u^T), dV_c = a 1 w^T + b K_c R, R, u, w the sums
+// over the whole sequence.
+// LD > D: xflags as above.
+// ---------------------------------------------------------------------------
+template <int MODE, int D, int LD>
+__global__ __launch_bounds__(4 * D, 2) void ks_bwd_dkv_read(
+    const typename Mode<MODE>::TIO *__restrict__ K, const typename Mode<MODE>::TIO *__restrict__ V,
+    typename Mode<MODE>::TIO *__restrict__ dK, typename Mode<MODE>::TIO *__restrict__ dV,
+    const float *__restrict__ ws, int N, int nseg, SegMap sm, size_t slot_floats, float a, float b,
+    int xflags, float *__restrict__ Pk, float *__restrict__ Pv)
+{
+    typedef Mode<MODE> MD;
+    typedef typename MD::TIO TIO;
+    constexpr int LQ = MD::LQ, LV = MD::LV, LX = MD::LX;
+    constexpr bool SWAP = MD::SWAP, QT = MD::QT, PROJ = MD::NORM;
+    constexpr int NW = D / 16, NRB = D / 16, PL = Tile<D>::PLANE;
+    typedef Chunk<TIO, D, LD> CH;
+    typedef BwdSlot<D> SL;
+    __shared__ __align__(16) __bf16 lds[LQ * PL + LV * PL];
+    __shared__ __align__(16) float kinv[PROJ ? CR : 4], dots[PROJ ? NW * CR : 4];  // 1 / |k|
+    __bf16 *Kt = lds, *Vt = Kt + LQ * PL;  // operand-ordered
+
+    const int bh = blockIdx.x / nseg, seg = blockIdx.x % nseg;
+    const size_t base = (size_t)bh * N * LD;
+    const TIO *Kp = K + base, *Vp = V + base;
+    TIO *dKp = dK + base, *dVp = dV + base;
+    const long row0 = seg_row(sm, seg, nseg, N), row1 = seg_row(sm, seg + 1, nseg, N);
+    const int t = threadIdx.x, l = t % 64, c = l % 16, g = l / 16;
+    const int w = __builtin_amdgcn_readfirstlane(t / 64);
+    const Lanes<D, (D >= 128)> ln(c, g);
+
+    const float *slot = ws + (size_t)bh * nseg * slot_floats;
+    Blk Ra[NRB], Rb[NRB];  // R: rows r, columns j = 16w + c;  R^T: rows j, columns r = 16w + c
+#pragma unroll
+    for (int rb = 0; rb < NRB; ++rb) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) Ra[rb].set(i, slot[SL::R + (rb * 16 + 4 * g + i) * D + w * 16 + c]);
+        Rb[rb].v = *reinterpret_cast<const f4v *>(slot + SL::R + (w * 16 + c) * D + rb * 16 + 4 * g);
+    }
+    Sum<SWAP> uacc, wacc;  // u, w
+    uacc.load(slot + SL::U, w, c, g);
+    wacc.load(slot + SL::W, w, c, g);
+
+    const long nchunks = (row1 - row0 + CR - 1) / CR;
+    struct Set {
+        CH k, v;
+    } sets[MD::DEPTH];
+#pragma unroll
+    for (int i = 0; i < MD::DEPTH; ++i) {
+        const long cl = row0 + max(nchunks - 1 - i, 0L) * CR;
+        sets[i].k.load(Kp, cl, N);
+        sets[i].v.load(Vp, cl, N);
+    }
+    auto chunk = [&](long ci, Set &cur) __attribute__((always_inline)) {
+        const long c0 = row0 + ci * CR;
+        const bool lo_on = c0 < sm.lo_rows;  // second plane of the intermediates: early rows
+        block_sync();
         stage<MD::NORM, true, LQ>(cur.k, Kt, PROJ ? kinv : nullptr);
         cur.v.template store<true, LV>(Vt);
-        if constexpr (CAUSAL) {
-            stage<MD::NORM, false, LQ>(cur.q, Qt, MD::RN ? iq : nullptr, QT ? rs : nullptr);
-            if constexpr (MD::RN) {  // the weights in u take the factor this lane just wrote
-                const int r = CH::row(0);
-                if (CH::leader()) store_factor<3>(fdl[par], r, dl[r] * rs[r] * iq[r]);
-            }
-            cur.d.template store<false, LV>(dOt);
-        }
-        if (__builtin_expect(max(cur.v.top(), CAUSAL ? cur.d.top() : 0.f) > kLargestBf16, 0)) {
-            cur.v.template store_any<true>(Vt);
-            if constexpr (CAUSAL) cur.d.template store_any<false>(dOt);
-        }
+        if (__builtin_expect(cur.v.top() > kLargestBf16, 0)) cur.v.template store_any<true>(Vt);
         block_sync();
         const long cn = row0 + max(ci - MD::DEPTH, 0L) * CR;
         cur.k.load(Kp, cn, N);
         cur.v.load(Vp, cn, N);
-        if constexpr (CAUSAL) {
-            cur.g = load_row_float(Gp, cn, N, t % CR);
-            cur.dp = load_row_float(dp, cn, N, t % CR);
-            // ---- phase A: weight blocks Cm' and W (rows i, columns n) ----
-#pragma unroll 1
-            for (int pidx = w; pidx < 6; pidx += NW) {
-                const int q = pidx >= 3 ? pidx - 3 : pidx, ib = q ? 1 : 0, nb = q == 2 ? 1 : 0;
-                f4v x;
-                if (pidx < 3) {
-                    const f4v pc = block_product<D, LV, LV>(dOt, ib, Vt, nb, ln);
-                    x = pc - *reinterpret_cast<const f4v *>(dl + ib * 16 + 4 * g);
-                    if constexpr (!QT) x *= *reinterpret_cast<const f4v *>(rs + ib * 16 + 4 * g);
-                    if constexpr (MD::RN) x *= *reinterpret_cast<const f4v *>(iq + ib * 16 + 4 * g);
-                } else {
-                    f4v pw = block_product<D, LQ, LQ>(Qt, ib, Kt, nb, ln);
-                    if constexpr (MD::RN)
-                        pw = (pw * kinv[nb * 16 + c]) * *reinterpret_cast<const f4v *>(iq + ib * 16 + 4 * g);
-                    const f4v r4 = *reinterpret_cast<const f4v *>(rs + ib * 16 + 4 * g);
-                    if constexpr (QT) x = a * r4 + b * pw;
-                    else x = (a + b * pw) * r4;
-                }
-                const int first = nb == ib ? c : 0;  // first row i that sees column n
-#pragma unroll
-                for (int e = 0; e < 4; ++e) x[e] = 4 * g + e < first ? 0.f : x[e];
-                with_planes<LX>(lo_on, [&](auto n) {
-                    store_weights<n.value>(pidx < 3 ? Ct : Wt, nb * 16 + c, ib, g, x);
-                });
-            }
-        }
         f4v kh[2], kl[2];  // rows n, columns r (SWAP), or rows r, columns n
 #pragma unroll
         for (int m = 0; m < 2; ++m) kh[m] = kl[m] = f4v{0.f, 0.f, 0.f, 0.f};
         with_planes<LX>(lo_on, [&](auto n) { state_product<D, n.value, LV, SWAP>(kh, kl, Rb, Vt, ln); });
-        if constexpr (CAUSAL) {
-            cur.q.load(Qp, cn, N);
-            block_sync();
-        }
-
-        // ---- phase B ----
-        bf8v qf[LQ], df[LV];
-        if constexpr (CAUSAL) load_cols<D, LQ>(qf, Qt, ln.local(ln.col), w);
         f4v x[2];
 #pragma unroll
-        for (int m = 0; m < 2; ++m) {
-            f4v f = kh[m] + kl[m];
-            if constexpr (CAUSAL) {
-                with_planes<LX>(lo_on, [&](auto n) {
-                    bf8v pf[n.value];
-                    load_rows<32, n.value>(pf, Ct, lw.row, m, 0);
-                    f += own_product<SWAP, LQ, n.value>(qf, pf);
-                });
-            }
-            x[m] = b * (f - uacc.v);
-        }
+        for (int m = 0; m < 2; ++m) x[m] = b * (kh[m] + kl[m] - uacc.v);
         if constexpr (PROJ)
             project_chunk<SWAP, true, D, LQ>(x, Kt, ln, QT ? nullptr : kinv, dots, kinv, w, c, g);
 #pragma unroll
@@ -1076,55 +1637,21 @@ __global__ __launch_bounds__(4 * D, 2) void ks_bwd_dkv(
             store_grad<SWAP, D, LD>(dKp + (size_t)(c0 + m * 16) * LD,
                                     Pk + ((size_t)bh * N + c0 + m * 16) * D, xflags & 2, w,
                                     (int)(row1 - c0) - m * 16, l, x[m]);
-        if constexpr (CAUSAL) cur.d.load(dOp, cn, N);
         f4v vh[2], vl[2];  // rows n, columns j (SWAP), or rows j, columns n
 #pragma unroll
         for (int m = 0; m < 2; ++m) vh[m] = vl[m] = f4v{0.f, 0.f, 0.f, 0.f};
         with_planes<LX>(lo_on, [&](auto n) { state_product<D, n.value, LQ, SWAP>(vh, vl, Ra, Kt, ln); });
-        if constexpr (CAUSAL) load_cols<D, LV>(df, dOt, ln.local(ln.col), w);
 #pragma unroll
         for (int m = 0; m < 2; ++m) {
-            f4v f = a * wacc.v + (MD::RN ? b * kinv[m * 16 + c] : b) * (vh[m] + vl[m]);
-            if constexpr (CAUSAL) {
-                with_planes<LX>(lo_on, [&](auto n) {
-                    bf8v pf[n.value];
-                    load_rows<32, n.value>(pf, Wt, lw.row, m, 0);
-                    f += own_product<SWAP, LV, n.value>(df, pf);
-                });
-            }
+            const f4v f = a * wacc.v + (MD::RN ? b * kinv[m * 16 + c] : b) * (vh[m] + vl[m]);
             store_grad<SWAP, D, LD>(dVp + (size_t)(c0 + m * 16) * LD,
                                     Pv + ((size_t)bh * N + c0 + m * 16) * D, xflags & 4, w,
                                     (int)(row1 - c0) - m * 16, l, f);
         }
-        if constexpr (CAUSAL) {
-            bf8v fr[3], fd[3];
-            load_factor<3>(fr, frs[par], g);
-            load_factor<3>(fd, fdl[par], g);
-            wacc.add(df, fr);
-            uacc.add(qf, fd);
-            if constexpr (QT) {
-                rank_update<D, LQ, LV>(Ra, Qt, df, ln);
-                rank_update<D, LV, LQ>(Rb, dOt, qf, ln);
-            } else {
-                with_planes<LX>(lo_on, [&](auto n) {
-                    bf8v oh[n.value], qg[n.value];
-                    scale_frag<n.value>(oh, df, rs, g, MD::RN ? iq : nullptr);
-                    scale_frag<n.value>(qg, qf, rs, g, MD::RN ? iq : nullptr);
-                    rank_update<D, LQ, n.value>(Ra, Qt, oh, ln);
-                    rank_update<D, LV, n.value>(Rb, dOt, qg, ln);
-                });
-            }
-            post_factors(row0 + max(ci - 1, 0L) * CR, nxt, par ^ 1);
-        }
     };
-    if constexpr (MD::DEPTH == 2) {
-        for (long ci = nchunks - 1; ci >= 0; ci -= 2) {
-            chunk(ci, sets[0], sets[MD::DEPTH - 1], 0);
-            if (ci > 0) chunk(ci - 1, sets[MD::DEPTH - 1], sets[0], 1);
-        }
-    } else {
-        int par = 0;
-        for (long ci = nchunks - 1; ci >= 0; --ci, par ^= 1) chunk(ci, sets[0], sets[0], par);
+    for (long ci = nchunks - 1; ci >= 0; ci -= MD::DEPTH) {
+        chunk(ci, sets[0]);
+        if (MD::DEPTH == 2 && ci > 0) chunk(ci - 1, sets[MD::DEPTH - 1]);
     }
 }
 
@@ -1174,6 +1701,25 @@ la_status run_forward(const Problem &pr, const Plan &pl, const void *Qv, const v
     return launch_status();
 }
 
+// The ascending masked sweep: two halves of a workgroup at D = 32, one kind of waves beyond.
+template <int MODE, int D, int LD>
+constexpr auto ks_bwd_dq_masked()
+{
+    if constexpr (D == 32) return ks_bwd_dq_halves<MODE, D, LD>;
+    else return ks_bwd_dq<MODE, D, true, LD>;
+}
+
+// The descending masked sweep: 32 columns a wave for bf16 at D = 128, whose tiles and states leave room for
+// it (us, three runs each: 94 to 98 against 105 to 107 with 16 columns and four waves a SIMD, 128 slices of
+// 2048 rows).  fp32 at D = 128 is within 2 % either way; at D = 64 the four waves are faster (bf16, 36 slices
+// of 5003 rows 30.0 against 34.2).
+template <int MODE, int D, int LD>
+constexpr auto ks_bwd_dkv_masked()
+{
+    if constexpr (MODE == P16 && D == 128) return ks_bwd_dkv_wide<D, LD>;
+    else return ks_bwd_dkv<MODE, D, LD>;
+}
+
 // dK == nullptr: the ascending sweep alone (dQ and the per-row o . dO).
 template <int MODE, int D, int LD>
 la_status run_backward(const Problem &pr, const Plan &pl, const void *Qv, const void *Kv,
@@ -1188,7 +1734,7 @@ la_status run_backward(const Problem &pr, const Plan &pl, const void *Qv, const 
     TIO *dQ = (TIO *)dQv, *dK = (TIO *)dKv, *dV = (TIO *)dVv;
     const int nseg = pl.nseg, nrun = pr.causal ? nseg - 1 : nseg;
     float *dprime = ws + pl.delta_offset_floats;
-    const dim3 grid(pr.BH * nseg), block(4 * D);
+    const dim3 grid(pr.BH * nseg), block(4 * D), block2(8 * D);
     // forward-running sums before every segment: handed over by the forward pass, or
     // per-segment sums (none needed from a masked pass's last segment) and a scan here
     if (!saved && nrun > 0) {
@@ -1202,8 +1748,8 @@ la_status run_backward(const Problem &pr, const Plan &pl, const void *Qv, const 
     }
     const float *sinit = saved ? saved : ws;
     const size_t sinit_floats = saved ? pl.saved_floats : pl.slot_floats;
-    auto *dq = pr.causal ? ks_bwd_dq<MODE, D, true, LD> : ks_bwd_dq<MODE, D, false, LD>;
-    dq<<<grid, block, 0, st>>>(Q, K, V, O, G, dO, dQ, ws, sinit, sinit_floats, dprime, pr.N, nseg,
+    auto *dq = !pr.causal ? ks_bwd_dq<MODE, D, false, LD> : ks_bwd_dq_masked<MODE, D, LD>();
+    dq<<<grid, pr.causal && D == 32 ? block2 : block, 0, st>>>(Q, K, V, O, G, dO, dQ, ws, sinit, sinit_floats, dprime, pr.N, nseg,
                                pl.map, pl.slot_floats, pr.b, bp.xflags, bp.Pq);
     tc.mark("bwd_dq");
     if (!dK) return launch_status();
@@ -1213,9 +1759,15 @@ la_status run_backward(const Problem &pr, const Plan &pl, const void *Qv, const 
                           pr.causal ? nseg - 2 : nseg - 1, st);
         tc.mark("scan_slots_rev");
     }
-    auto *dkv = pr.causal ? ks_bwd_dkv<MODE, D, true, LD> : ks_bwd_dkv<MODE, D, false, LD>;
-    dkv<<<grid, block, 0, st>>>(Q, K, V, G, dO, dK, dV, ws, dprime, pr.N, nseg, pl.map, pl.slot_floats,
-                                pr.a, pr.b, bp.xflags, bp.Pk, bp.Pv);
+    if (pr.causal) {
+        auto *dkv = ks_bwd_dkv_masked<MODE, D, LD>();
+        dkv<<<grid, MODE == P16 && D == 128 ? block : block2, 0, st>>>(
+            Q, K, V, G, dO, dK, dV, ws, dprime, pr.N, nseg, pl.map, pl.slot_floats, pr.a, pr.b, bp.xflags, bp.Pk,
+            bp.Pv);
+    } else {
+        ks_bwd_dkv_read<MODE, D, LD><<<grid, block, 0, st>>>(K, V, dK, dV, ws, pr.N, nseg, pl.map, pl.slot_floats,
+                                                             pr.a, pr.b, bp.xflags, bp.Pk, bp.Pv);
+    }
     tc.mark("bwd_dkv");
     return launch_status();
 }

@@ -70,6 +70,29 @@ def test_edges_against_plain_alu(la, D, dtype, N):
                 assert e <= 1.0, (D, dtype, N, causal, fwd.__name__, name, e)
 
 
+# segments of an even and an odd number of chunks, the last chunk of 1 and of 31 rows; the rows with a
+# second plane (132, 137, 260 of them) end inside a chunk
+@pytest.mark.parametrize("N", [1057, 1103, 2080])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("D", [32, 64, 128])
+def test_sweeps_over_many_chunks(la, D, dtype, N):
+    """The sweeps of the backward pass on the kernels' own cuts, both handed-over and own sums, against the
+    plain-ALU kernels on the same O and g; tolerance as above."""
+    dev, _ = upload_case(1, 3, N, D, dtype, 5100 + D + N, [0])
+    O, G, saved = gpu_forward_save(la, dev, 1.0, 0.5, True)
+    got = (gpu_backward(la, dev, O, G, 1.0, 0.5, True),
+           gpu_backward_saved(la, dev, O, G, saved, 1.0, 0.5, True))
+    try:
+        la.la_debug_override(0, 1)
+        want = gpu_backward(la, dev, O, G, 1.0, 0.5, True)
+    finally:
+        la.la_debug_override(0, 0)
+    for grads in got:
+        for name, x, y in zip(("dQ", "dK", "dV"), grads, want):
+            e = excess(to_f64(x), to_f64(y), 2 * TOL[dtype])
+            assert e <= 1.0, (D, dtype, N, name, e)
+
+
 @pytest.mark.parametrize("D", [64, 128])
 def test_fp32_is_fp32(la, oracle_mod, D):
     """Six bf16 products a float product keep 24 bits: the 2-norm error against 64 bits stays at
