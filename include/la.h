@@ -293,8 +293,8 @@ LA_API void la_debug_override(int seg_len, int force_generic);
  * floats, small next to the tensors.
  *
  *   la_saved_state_bytes: size of the `saved` buffer for this problem (0 for
- *       invalid arguments, and 0 when the library would not use one -- D = 16
- *       and D = 256; a zero-size buffer may be NULL).
+ *       invalid arguments, and 0 when the library would not use one -- D = 16;
+ *       a zero-size buffer may be NULL).
  *   la_forward_save:   la_forward, and additionally fills `saved` (device
  *       memory, 256-byte aligned, at least la_saved_state_bytes bytes).
  *   la_backward_saved: la_backward, reading `saved` as written by
@@ -303,7 +303,9 @@ LA_API void la_debug_override(int seg_len, int force_generic);
  * `saved` is caller-owned like every other buffer; its layout is private to
  * the library and to this library version.  `trace` is the timing hook
  * described below and may be NULL.  Error behaviour as for la_forward /
- * la_backward; a missing, misaligned or short `saved` is LA_ERR_WORKSPACE.
+ * la_backward; a missing, misaligned or short `saved` is LA_ERR_WORKSPACE, except
+ * at D = 256, where the hand-over is optional: such a buffer is left unused by both
+ * calls (callers that pass NULL there need not change).
  */
 LA_API size_t la_saved_state_bytes(int B, int H, int N, int D, la_dtype dt, int causal);
 

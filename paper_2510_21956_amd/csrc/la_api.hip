@@ -92,6 +92,7 @@ Plan make_plan(int B, int H, int N, int D, la_dtype dt, int causal, int is_backw
         const size_t need =
             split_scratch(h, (size_t)BH * N, dt, is_backward).total_floats * sizeof(float);
         if (need > p.total_bytes) p.total_bytes = need;
+        p.saved_bytes = 4 * h.saved_bytes;
     }
     return p;
 }
@@ -99,23 +100,23 @@ Plan make_plan(int B, int H, int N, int D, la_dtype dt, int causal, int is_backw
 // Forward and backward pass at D = 256: column block by column block on the matrix-core
 // kernels of D = 128, or (test hook) on the token-serial kernels.  dK == nullptr: dQ only.
 static la_status forward_256(const Problem &pr, const Plan &pl, int B, int H, const void *Q,
-                             const void *K, const void *V, void *O, float *G, float *ws,
+                             const void *K, const void *V, void *O, float *G, float *ws, float *saved,
                              hipStream_t st, Tracer &tc)
 {
     if (g_force_generic.load(std::memory_order_relaxed))
         return wide_forward(pr, pl, Q, K, V, O, G, ws, st, tc);
     const Plan h = make_plan(B, H, pr.N, 128, pr.dt, pr.causal, 0);
-    return split_forward(pr, h, Q, K, V, O, G, ws, st, tc);
+    return split_forward(pr, h, Q, K, V, O, G, ws, saved, st, tc);
 }
 static la_status backward_256(const Problem &pr, const Plan &pl, int B, int H, const void *Q,
                               const void *K, const void *V, const void *O, const float *G,
                               const void *dO, void *dQ, void *dK, void *dV, float *ws,
-                              hipStream_t st, Tracer &tc)
+                              const float *saved, hipStream_t st, Tracer &tc)
 {
     if (g_force_generic.load(std::memory_order_relaxed))
         return wide_backward(pr, pl, Q, K, V, O, G, dO, dQ, dK, dV, ws, st, tc);
     const Plan h = make_plan(B, H, pr.N, 128, pr.dt, pr.causal, 1);
-    return split_backward(pr, h, Q, K, V, O, G, dO, dQ, dK, dV, ws, st, tc);
+    return split_backward(pr, h, Q, K, V, O, G, dO, dQ, dK, dV, ws, saved, st, tc);
 }
 
 static la_status check_shape(int B, int H, int N, int D, la_dtype dt)
@@ -172,6 +173,16 @@ static bool use_fast(const Problem &pr)
     return (pr.D == 32 || pr.D == 64 || pr.D == 128) && !g_force_generic.load(std::memory_order_relaxed);
 }
 
+// Head size 256 on passes of the D = 128 kernels.  The hand-over buffer is optional there: calls were
+// made without one when there was none, so a missing, misaligned or short buffer is left unused.
+static bool use_split(const Problem &pr)
+{
+    return pr.D == 256 && !g_force_generic.load(std::memory_order_relaxed);
+}
+static bool good_saved(const void *saved, size_t bytes, const Plan &pl)
+{
+    return saved && bytes >= pl.saved_bytes && (((uintptr_t)saved) & 255u) == 0;
+}
 
 // Extra workspace of a backward pass that recomputes O and g (either handed in as NULL):
 // the forward pass's own workspace, then O, then g, each rounded up to 256 bytes.
@@ -254,7 +265,7 @@ size_t la_saved_state_bytes(int B, int H, int N, int D, la_dtype dt, int causal)
 {
     if (la::check_shape(B, H, N, D, dt) != LA_OK) return 0;
     la::Problem pr{B * H, N, D, 1.f, 0.f, causal ? 1 : 0, dt};
-    if (!la::use_fast(pr)) return 0;
+    if (!la::use_fast(pr) && !la::use_split(pr)) return 0;
     return la::make_plan(B, H, N, D, dt, causal, 0).saved_bytes;
 }
 
@@ -282,10 +293,10 @@ static la_status forward_impl(const void *Q, const void *K, const void *V, void 
     if (!fast) pl.map.cost_seg = 0;  // the plain-ALU kernels cut uniformly (same segment count)
     float *sv = nullptr;
     if (save && fast) {
-        if (!saved || saved_bytes < pl.saved_bytes || (((uintptr_t)saved) & 255u))
-            return LA_ERR_WORKSPACE;
+        if (!la::good_saved(saved, saved_bytes, pl)) return LA_ERR_WORKSPACE;
         sv = (float *)saved;
     }
+    if (save && la::use_split(pr) && la::good_saved(saved, saved_bytes, pl)) sv = (float *)saved;
     if (trace && (!trace->events || trace->capacity < 1)) return LA_ERR_NULL;
     {
         const size_t T = (size_t)B * H * N, tb = T * D * (dt == LA_F32 ? 4 : 2);
@@ -300,7 +311,7 @@ static la_status forward_impl(const void *Q, const void *K, const void *V, void 
         return la::planes_forward(pr, pl, D, Q, K, V, O, G, (float *)workspace, sv,
                                   (hipStream_t)hip_stream, tc);
     if (D == 256)
-        return la::forward_256(pr, pl, B, H, Q, K, V, O, G, (float *)workspace,
+        return la::forward_256(pr, pl, B, H, Q, K, V, O, G, (float *)workspace, sv,
                                (hipStream_t)hip_stream, tc);
     return la::generic_forward(pr, pl, Q, K, V, O, G, (float *)workspace,
                                (hipStream_t)hip_stream, tc);
@@ -339,10 +350,11 @@ static la_status backward_impl(const void *Q, const void *K, const void *V, cons
     }
     const float *sv = nullptr;
     if (use_saved && fast) {
-        if (!saved || saved_bytes < pl.saved_bytes || (((uintptr_t)saved) & 255u))
-            return LA_ERR_WORKSPACE;
+        if (!la::good_saved(saved, saved_bytes, pl)) return LA_ERR_WORKSPACE;
         sv = (const float *)saved;
     }
+    if (use_saved && la::use_split(pr) && la::good_saved(saved, saved_bytes, pl))
+        sv = (const float *)saved;
     if (trace && (!trace->events || trace->capacity < 1)) return LA_ERR_NULL;
     {
         const size_t tb = T * D * (dt == LA_F32 ? 4 : 2);
@@ -362,8 +374,8 @@ static la_status backward_impl(const void *Q, const void *K, const void *V, cons
         s = planes ? la::planes_forward(pr, pf, D, Q, K, V, o2, g2, (float *)(wsb + rc.fwd_ws_off),
                                         nullptr, st, tc)
             : D == 256
-                ? la::forward_256(pr, pf, B, H, Q, K, V, o2, g2, (float *)(wsb + rc.fwd_ws_off), st,
-                                  tc)
+                ? la::forward_256(pr, pf, B, H, Q, K, V, o2, g2, (float *)(wsb + rc.fwd_ws_off), nullptr,
+                                  st, tc)
                 : la::generic_forward(pr, pf, Q, K, V, o2, g2, (float *)(wsb + rc.fwd_ws_off), st,
                                       tc);
         if (s != LA_OK) return s;
@@ -373,7 +385,7 @@ static la_status backward_impl(const void *Q, const void *K, const void *V, cons
     s = planes ? la::planes_backward(pr, pl, D, Q, K, V, O, G, dO, dQ, dK, dV, (float *)workspace, sv,
                                      st, tc)
         : D == 256
-            ? la::backward_256(pr, pl, B, H, Q, K, V, O, G, dO, dQ, dK, dV, (float *)workspace, st,
+            ? la::backward_256(pr, pl, B, H, Q, K, V, O, G, dO, dQ, dK, dV, (float *)workspace, sv, st,
                                tc)
             : la::generic_backward(pr, pl, Q, K, V, O, G, dO, dQ, dK, dV, (float *)workspace, st,
                                    tc);
@@ -468,7 +480,7 @@ la_status la_backward_ab(const void *Q, const void *K, const void *V, const void
                                 nullptr, st, tc);
     } else if (D == 256) {
         s = la::backward_256(pr, pl, B, H, Q, K, V, O, G, dO, dq1, nullptr, nullptr,
-                             (float *)workspace, st, tc);
+                             (float *)workspace, nullptr, st, tc);
     } else {
         s = la::generic_backward(pr, pl, Q, K, V, O, G, dO, dq1, wsb + lay.dk_off,
                                  wsb + lay.dv_off, (float *)workspace, st, tc);

@@ -224,11 +224,13 @@ inline SplitScratch split_scratch(const Plan &pl128, size_t T, la_dtype dt, int 
 // of the D = 128 sums kernels, each followed by state_block_from_totals.
 la_status split_prefill(const Problem &pr, const Plan &pl, const void *K, const void *V, float *ws,
                         float *state, int accumulate, hipStream_t st);
+// saved (may be null): the hand-over buffers of the four passes one after another, pl.saved_bytes each.
 la_status split_forward(const Problem &pr, const Plan &pl, const void *Q, const void *K,
-                        const void *V, void *O, float *G, float *ws, hipStream_t st, Tracer &tc);
+                        const void *V, void *O, float *G, float *ws, float *saved, hipStream_t st,
+                        Tracer &tc);
 la_status split_backward(const Problem &pr, const Plan &pl, const void *Q, const void *K,
                          const void *V, const void *O, const float *G, const void *dO, void *dQ,
-                         void *dK, void *dV, float *ws, hipStream_t st, Tracer &tc);
+                         void *dK, void *dV, float *ws, const float *saved, hipStream_t st, Tracer &tc);
 // Head size 256 (la_wide.hip): token-serial kernels with the state in registers, behind the
 // test hook.  wide_backward with dK == nullptr runs the ascending sweep (dQ) only.
 la_status wide_forward(const Problem &pr, const Plan &pl, const void *Q, const void *K,

@@ -15,7 +15,10 @@ namespace la {
 // blocks of the 256-wide rows, each adding to what the previous ones left in the outputs.
 // `pl` is the plan of the D = 128 problem; behind that plan's workspace the forward pass keeps
 // the first pass's share of g and, for bf16, its undivided numerator in fp32, and the backward
-// pass, for bf16, the first share of every gradient block in fp32 (split_scratch).
+// pass, for bf16, the first share of every gradient block in fp32 (split_scratch).  With `saved` every
+// forward pass hands its sums at the segment boundaries to the backward pass on the same blocks, which
+// then runs no sums kernel and no scan (64 slices of 4096 rows, a step without and with: fp32 3390 and 3125 us,
+// bf16 1700 and 1556; 8 of 8000, bf16 650 and 580).
 static const void *col_block(const void *p, int j, la_dtype dt)
 {
     return (const char *)p + (size_t)128 * j * (dt == LA_F32 ? 4 : 2);
@@ -41,8 +44,15 @@ la_status split_prefill(const Problem &pr, const Plan &pl, const void *K, const 
     return LA_OK;
 }
 
+// Hand-over of pass (i, j) inside the buffer of all four.
+static float *saved_block(float *saved, const Plan &pl, int i, int j)
+{
+    return saved ? saved + (size_t)(2 * i + j) * (pl.saved_bytes / sizeof(float)) : nullptr;
+}
+
 la_status split_forward(const Problem &pr, const Plan &pl, const void *Q, const void *K,
-                        const void *V, void *O, float *G, float *ws, hipStream_t st, Tracer &tc)
+                        const void *V, void *O, float *G, float *ws, float *saved, hipStream_t st,
+                        Tracer &tc)
 {
     const SplitScratch sc = split_scratch(pl, (size_t)pr.BH * pr.N, pr.dt, 0);
     float *gpart = ws + sc.g_off, *fraw = ws + sc.f_off;
@@ -55,8 +65,8 @@ la_status split_forward(const Problem &pr, const Plan &pl, const void *Q, const 
         for (int i = 0; i < 2; ++i) {
             p.a = i == 0 ? pr.a : 0.f;
             const la_status s = planes_forward(p, pl, 256, col_block(Q, i, pr.dt), col_block(K, i, pr.dt),
-                                               Vj, Oj, i == 0 ? gpart : (j == 1 ? G : nullptr), ws, nullptr,
-                                               st, quiet, i == 0 ? XF_RAW : XF_ACC,
+                                               Vj, Oj, i == 0 ? gpart : (j == 1 ? G : nullptr), ws,
+                                               saved_block(saved, pl, i, j), st, quiet, i == 0 ? XF_RAW : XF_ACC,
                                                i == 0 ? nullptr : gpart, fraw);
             if (s != LA_OK) return s;
             tc.mark("fwd_block_pass");
@@ -68,7 +78,7 @@ la_status split_forward(const Problem &pr, const Plan &pl, const void *Q, const 
 // dK == nullptr: the ascending sweeps only (dQ).
 la_status split_backward(const Problem &pr, const Plan &pl, const void *Q, const void *K,
                          const void *V, const void *O, const float *G, const void *dO, void *dQ,
-                         void *dK, void *dV, float *ws, hipStream_t st, Tracer &tc)
+                         void *dK, void *dV, float *ws, const float *saved, hipStream_t st, Tracer &tc)
 {
     const SplitScratch sc = split_scratch(pl, (size_t)pr.BH * pr.N, pr.dt, 1);
     Problem p = pr;
@@ -87,7 +97,7 @@ la_status split_backward(const Problem &pr, const Plan &pl, const void *Q, const
                 p, pl, 256, col_block(Q, i, pr.dt), col_block(K, i, pr.dt), col_block(V, j, pr.dt),
                 col_block(O, j, pr.dt), G, col_block(dO, j, pr.dt), col_block(dQ, i, pr.dt),
                 dK ? col_block(dK, i, pr.dt) : nullptr, dK ? col_block(dV, j, pr.dt) : nullptr, ws,
-                nullptr, st, quiet, bp);
+                saved_block(const_cast<float *>(saved), pl, i, j), st, quiet, bp);
             if (s != LA_OK) return s;
             tc.mark("bwd_block_pass");
         }

@@ -93,6 +93,30 @@ def test_sweeps_over_many_chunks(la, D, dtype, N):
             assert e <= 1.0, (D, dtype, N, name, e)
 
 
+@pytest.mark.parametrize("N", [33, 700])  # one segment, three
+@pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_hand_over_at_head_size_256(la, dtype, causal, N):
+    """The four passes' sums handed over: O, G as without, gradients within the parity tolerance of those on
+    the backward pass's own sums (twice, as both may use it up).  Without a buffer, or with a short one,
+    the pair is la_forward and la_backward to the bit."""
+    dev, _ = upload_case(1, 3, N, 256, dtype, 6400 + N, [0])
+    O, G, saved = gpu_forward_save(la, dev, 1.0, 0.5, causal)
+    assert saved is not None
+    O2, G2 = gpu_forward(la, dev, 1.0, 0.5, causal)
+    assert torch.equal(O, O2) and torch.equal(G, G2)
+    want = gpu_backward(la, dev, O, G, 1.0, 0.5, causal)
+    for name, x, y in zip(("dQ", "dK", "dV"), gpu_backward_saved(la, dev, O, G, saved, 1.0, 0.5, causal), want):
+        e = excess(to_f64(x), to_f64(y), 2 * TOL[dtype])
+        assert e <= 1.0, (dtype, causal, N, name, e)
+    for none in (None, saved[:256]):
+        wf = scratch(la.la_workspace_bytes(1, 3, N, 256, la.LA_F32 if dtype == "f32" else la.LA_BF16, causal, 0),
+                     "cuda")
+        la.la_forward_save(dev["Q"], dev["K"], dev["V"], O2, G2, 1.0, 0.5, causal, wf, none)
+        got = gpu_backward_saved(la, dev, O2, G2, none, 1.0, 0.5, causal)
+        assert torch.equal(O, O2) and all(torch.equal(x, y) for x, y in zip(got, want))
+
+
 @pytest.mark.parametrize("D", [64, 128])
 def test_fp32_is_fp32(la, oracle_mod, D):
     """Six bf16 products a float product keep 24 bits: the 2-norm error against 64 bits stays at
