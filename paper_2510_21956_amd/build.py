@@ -1,12 +1,15 @@
-"""Compile the HIP sources under csrc/ into libla.so (gfx950 only), in-tree."""
+"""Compile the HIP sources under csrc/ into libla.so (gfx950 only) and the native part of the Python
+binding into _marshal.so, in-tree."""
 import glob
 import os
 import subprocess
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(os.path.dirname(HERE), "include")
 LIB = os.path.join(HERE, "libla.so")
+MARSHAL = os.path.join(HERE, "_marshal.so")
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
@@ -30,5 +33,21 @@ def build_library(verbose=False, extra_flags=(), out=LIB):
     return out
 
 
+def build_marshal(verbose=False, out=MARSHAL):
+    """The argument marshalling of binding.py (host code, against torch's headers)."""
+    import torch
+    from torch.utils.cpp_extension import include_paths, library_paths
+    cmd = ["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-fvisibility=hidden",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI, "-I", INCLUDE]
+    cmd += ["-isystem%s" % p for p in include_paths() + [sysconfig.get_paths()["include"]]]
+    cmd += [os.path.join(CSRC, "la_bind.cpp")]
+    cmd += ["-L%s" % p for p in library_paths()] + ["-ltorch_python", "-ltorch_cpu", "-lc10", "-o", out]
+    if verbose:
+        print(" ".join(cmd))
+    subprocess.run(cmd, check=True)
+    return out
+
+
 if __name__ == "__main__":
     print(build_library(verbose=True))
+    print(build_marshal(verbose=True))

@@ -146,3 +146,62 @@ def test_prefill_adds_any_number_of_slots(la, D, nseg):
                            np.full((B * H, 1), float(N))], axis=1)
     assert excess(once, want, TOL["f32"]) <= 1.0
     assert np.array_equal(twice, 2.0 * once)
+
+
+def _outcome(call):
+    try:
+        call()
+    except Exception as e:  # noqa: BLE001 -- the type and the text are what is compared
+        return type(e), str(e)
+    return None
+
+
+def test_native_marshalling_refuses_what_python_refuses(la, monkeypatch):
+    """Every form of a bad argument, through the native functions and through the Python ones: the same
+    exception with the same text; and the good calls give the same bits."""
+    from paper_2510_21956_amd import binding
+    assert binding._native is not None, "_marshal.so is not built"
+    B, H, N, D = 2, 3, 40, 32
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(11)
+    x = [torch.randn((B, H, N, D), device="cuda", generator=gen) for _ in range(9)]
+    G = torch.empty((B, H, N), device="cuda")
+    ws = torch.empty(1 << 22, dtype=torch.uint8, device="cuda")
+    st = torch.zeros(la.la_decode_state_bytes(B, H, D) // 4, device="cuda")
+    good = {"f": [x[0], x[1], x[2], x[3], G, 1.0, 0.5, True, ws, None],
+            "b": [x[0], x[1], x[2], x[3], G, x[4], x[5], x[6], x[7], 1, 0.5, 1, ws, None],
+            "d": [x[0], x[1], x[2], x[3], G, st, 1.0, 0.5], "p": [x[0], x[1], st, 0, ws]}
+    funcs = {"f": [la.la_forward_save, la.la_forward_qknorm_save,
+                   lambda *a: la.la_forward(*a[:-1]), lambda *a: la.la_forward_qknorm(*a[:-1])],
+             "b": [la.la_backward_saved, la.la_backward_qknorm_saved,
+                   lambda *a: la.la_backward(*a[:-1]), lambda *a: la.la_backward_qknorm(*a[:-1])],
+             "d": [la.la_decode_step], "p": [la.la_decode_prefill]}
+    bad = [None, x[0].transpose(1, 2), x[0][0], x[0].cpu(), x[0].half(), x[0].to(torch.bfloat16),
+           x[0][:, :, :20].contiguous(), x[0].double(), "text", 3, G.double(), ws[:256], ws[8:]]
+    for key, args in good.items():
+        n = len(args)
+        calls = [args] + [args[:i] + [v] + args[i + 1:] for i in range(n) for v in bad]
+        # a short, host or misaligned buffer may be taken where a tensor is optional; only the outcome counts
+        for fn in funcs[key]:
+            for c in calls:
+                native = _outcome(lambda: fn(*c))
+                with monkeypatch.context() as m:
+                    m.setattr(binding, "_native", None)
+                    assert _outcome(lambda: fn(*c)) == native, (key, [type(v) for v in c])
+    torch.cuda.synchronize()
+    saved = torch.empty(la.la_saved_state_bytes(B, H, N, D, la.LA_F32, True), dtype=torch.uint8, device="cuda")
+    out = []
+    for native in (binding._native, None):
+        with monkeypatch.context() as m:
+            m.setattr(binding, "_native", native)
+            O, dQ, dK, dV = (torch.full_like(x[0], float("nan")) for _ in range(4))
+            s2 = torch.zeros_like(st)
+            g = torch.full_like(G, float("nan"))
+            la.la_forward_save(x[0], x[1], x[2], O, g, 1.0, 0.05, True, ws, saved)
+            la.la_backward_saved(x[0], x[1], x[2], O, g, x[4], dQ, dK, dV, 1.0, 0.05, True, ws, saved)
+            la.la_decode_prefill(x[1], x[2], s2, 0, ws)
+            o1, g1 = torch.empty((B, H, 1, D), device="cuda"), torch.empty((B, H, 1), device="cuda")
+            q1 = [t[:, :, :1].contiguous() for t in x[:3]]
+            la.la_decode_step(*q1, o1, g1, s2, 1.0, 0.05, stream=torch.cuda.current_stream())
+            out.append([O, g, dQ, dK, dV, s2, o1, g1])
+    assert all(torch.equal(a, b) for a, b in zip(*out))
