@@ -22,8 +22,8 @@ static bool supported_d(int D) { return D == 16 || D == 32 || D == 64 || D == 12
 // x segments is about 256 x the workgroups that a compute unit holds at once: every compute
 // unit then gets the same number of equally long segments in a single round.  The sweeps of
 // the backward pass set that number (registers and LDS): one at D = 128 and two at D = 64
-// (measured at D = 64, bf16, 36 slices of 5003 rows: 159 us a step for one, 117 for two, 127
-// for three; fp32, 64 slices of 4096: 377, 305, 361), four at D = 32.  The same without the mask
+// (measured at D = 64, bf16, 36 slices of 5003 rows: 127 us a step for one, 108 for two, 123
+// for three; fp32, 64 slices of 4096: 336, 290, 349), four at D = 32.  The same without the mask
 // (us a step for one, two, three: D = 128, fp32, 4 slices of 10^5 rows 676, 714, 745; bf16, 32 of
 // 8192 225, 244, 247, and the forward pass alone 69, 76, 80, the sums for a prompt alone 17, 19, 19
 // (32 of 3001); D = 64, bf16, 64 of 16384 412, 362, 371, 80 of 3000 120, 105, 121; D = 32, bf16,

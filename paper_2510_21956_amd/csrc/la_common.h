@@ -59,8 +59,8 @@ __device__ __forceinline__ void store_elem(bf16_t *p, size_t i, float x) { p[i] 
 // sequence carry second bf16 planes of the intermediates and cost kLoCost units a row against
 // kHiCost for the others; segments are cut at equal cost, cost_seg units each, rounded to a
 // multiple of 64 rows, so that the workgroups of a launch, one segment each, finish together.
-// us a step with 1:1, 9:8, 5:4 and 4:3: bf16, D = 128, 16 slices of 131072 rows 2394, 2256, 2188, 2189,
-// 32 of 8192 310, 303, 290, 293; D = 64, 36 of 5003 111, 106, 108, 108, 80 of 3000 131, 128, 128, 135.
+// us a step with 9:8, 5:4 and 4:3: bf16, D = 128, 16 slices of 131072 rows 2214, 2153, 2140, 32 of 8192
+// 304, 291, 290; D = 64, 36 of 5003 105, 107, 107, 80 of 3000 124, 124, 129.
 constexpr int kLoCost = 5, kHiCost = 4;
 struct SegMap {
     int seg_len;

@@ -535,19 +535,18 @@ __device__ __forceinline__ void state_product(f4v (&hi)[2], f4v (&lo)[2], const 
         else __builtin_amdgcn_sched_barrier(0);
     }
 }
-// The same over the state blocks of contraction steps kt0 .. kt0 + NK - 1 (st[0] is block 2 kt0), one
-// step at a time: for four waves a SIMD, which hide each other's latencies and have half the
-// registers each.
-template <int D, int NK, int LS, int LY, bool SWAP, typename LN>
-__device__ __forceinline__ void state_steps(f4v (&hi)[2], f4v (&lo)[2], const Blk (&st)[2 * NK],
-                                            const __bf16 *y, int kt0, const LN &ln)
+// The same one step at a time: for four waves a SIMD, which hide each other's latencies and have half
+// the registers each.
+template <int D, int LS, int LY, bool SWAP, typename LN>
+__device__ __forceinline__ void state_steps(f4v (&hi)[2], f4v (&lo)[2], const Blk (&st)[D / 16],
+                                            const __bf16 *y, const LN &ln)
 {
     const int row = LN::local(ln.row);
 #pragma unroll
-    for (int kt = 0; kt < NK; ++kt) {
+    for (int kt = 0; kt < D / 32; ++kt) {
         bf8v f[2][LY], x[LS];
-        load_rows<D, LY>(f[0], y, row, 0, kt0 + kt);
-        load_rows<D, LY>(f[1], y, row, 1, kt0 + kt);
+        load_rows<D, LY>(f[0], y, row, 0, kt);
+        load_rows<D, LY>(f[1], y, row, 1, kt);
         split_frag<LS>(st[2 * kt].v, st[2 * kt + 1].v, x);
         mma_pair<LS, LY, SWAP>(hi, lo, x, f);
         __builtin_amdgcn_sched_barrier(0);
@@ -659,19 +658,18 @@ __device__ __forceinline__ void rank_update(Blk (&st)[D / 16], const __bf16 *at,
     st[2 * NS - 1].v += t[(NS - 1) & 1][1];
 }
 
-// The same for state blocks rb0 .. rb0 + NR - 1, two blocks at a time (four with single planes), for four
-// waves a SIMD.
-template <int D, int NR, int LA, int LB, typename LN>
-__device__ __forceinline__ void rank_steps(Blk (&st)[NR], const __bf16 *at, int rb0, const bf8v (&b)[LB],
-                                           const LN &ln)
+// The same two blocks at a time (four with single planes), for four waves a SIMD.
+template <int D, int LA, int LB, typename LN>
+__device__ __forceinline__ void rank_steps(Blk (&st)[D / 16], const __bf16 *at, const bf8v (&b)[LB], const LN &ln)
 {
     const int col = LN::local(ln.col);
+    constexpr int NR = D / 16;
     constexpr int AT = LA * LB == 1 && NR >= 4 ? 4 : 2;
 #pragma unroll
     for (int r = 0; r < NR; r += AT) {
         bf8v a[AT][LA];
 #pragma unroll
-        for (int i = 0; i < AT; ++i) load_cols<D, LA>(a[i], at, col, rb0 + r + i);
+        for (int i = 0; i < AT; ++i) load_cols<D, LA>(a[i], at, col, r + i);
         if constexpr (LA * LB == 1) {
 #pragma unroll
             for (int i = 0; i < AT; ++i) st[r + i].v = mfma(a[i][0], b[0], st[r + i].v);

@@ -14,11 +14,13 @@
 // step, and the rounding of a single plane does not average out over 16 columns (dK without the
 // mask: 2.8e-3 against 64 bits with one plane, 1.7e-3, the rounding of the output, with three).
 //
-// A workgroup of D/16 waves handles one (slice, segment) in chunks of 32 rows; wave w owns
-// columns [16w, 16w+16) of the D x D running state, which stays in its accumulators for the
-// whole segment.  Output blocks are computed transposed (accumulator rows = output columns): a
-// lane then holds four columns of a row, which an exchange between lanes turns into whole
-// runs of a row (store_block).  The backward sweeps of fp32, which have no registers to spare,
+// A workgroup handles one (slice, segment) in chunks of 32 rows.  Of its waves, one for every 16 columns
+// of the D x D running state (wave w: [16w, 16w+16)) keeps them in its accumulators for the whole
+// segment; the descending sweep (ks_bwd_dkv) and, up to D = 32, the ascending one (ks_bwd_dq_halves)
+// have twice as many, one half for each of their two products with a state; bf16 at D = 128 descends
+// with 32 columns a wave (ks_bwd_dkv_wide).  Output blocks are computed transposed (accumulator rows =
+// output columns): a lane then holds four columns of a row, which an exchange between lanes turns into
+// whole runs of a row (store_block).  The backward sweeps of fp32, which have no registers to spare,
 // compute them the other way round, store single floats and need no exchange (SWAP).
 //
 // The descending sums weight row i by 1/g_i.  With split rows of Q (QT) the kernels stage
@@ -29,16 +31,19 @@
 // exact, the weight blocks carry the 1/g, and the wave's own 32 x 16 operand of R's update is
 // scaled in registers.
 //
-// What bounds them (counters of the masked kernels).  fp32: the matrix pipe, the vector ALU
-// (splitting inputs and states) and LDS reads take 30 to 45 % of the clocks each and overlap
-// only in part, two waves a SIMD: 64 slices of 10^4 rows, D = 128, forward / ascending /
-// descending sweep 411 / 543 / 719 us against 489 / 646 / 863 us on the fp32 matrix pipe; D = 64,
-// 64 slices of 4096 rows, 70 / 91 / 113 against 79 / 98 / 110.  bf16, D = 128: waiting, 38 to 44 % of a
-// wave's life, at the barriers between a chunk's phases and for memory with 40 KB in flight per CU
-// (vector ALU and LDS 33 % each in the descending sweep, matrix pipe 19 %): 128 slices of 2048 rows
-// 63 / 85 / 105 us against 65 / 97 / 100 on kernels with chunks of 64 rows and two tiles a tensor;
-// D = 64, 36 slices of 5003 rows, with two workgroups a CU instead of one, 28 / 33 / 39 against
-// 41 / 51 / 56.  bf16 with normalised rows: 104 / 151 / 192 against 221 / 316 / 402 on fp32 tiles.
+// What bounds them (counters of the masked kernels): issue.  A wave issues one instruction every 5.3
+// clocks, two waves of a SIMD together one vector instruction every 2.9; with two waves a SIMD and a
+// chunk's phases in turn between barriers, the matrix pipe, the vector ALU (splitting inputs and states)
+// and LDS reads take 30 to 45 % of the clocks each in fp32, 14 to 35 % in bf16, where waits make up the
+// rest (barriers, and memory with 40 KB in flight per CU).  Four waves a SIMD in the descending sweep,
+// wider columns for bf16 at D = 128, and issue order (go_first) are what moved them.  Forward /
+// ascending / descending sweep, us, before and now:
+//   fp32, D = 64, 64 slices of 4096 rows         70 / 92 / 112 -> 70 / 94 / 99
+//   fp32, D = 128, 64 slices of 1000             47 / 60 / 74  -> 47 / 60 / 70
+//   bf16, D = 64, 36 slices of 5003              28 / 33 / 38  -> 28 / 33 / 30
+//   bf16, D = 128, 128 slices of 2048            65 / 88 / 110 -> 65 / 88 / 98
+//   bf16 normalised, the same                    105 / 152 / 195 -> 104 / 150 / 185
+//   fp32, D = 16, one slice of 256               12.6 / 14.7 / 17.6 -> 12.6 / 11.5 / 13.2
 #include "la_wave32.h"
 
 namespace la {
@@ -1087,12 +1092,12 @@ __global__ __launch_bounds__(8 * D, 4) void ks_bwd_dq_halves(
             request(cur, cn, false, true);
             if (need_R) {
                 if constexpr (QT) {
-                    rank_steps<D, NRB, L, L>(st, Qt, 0, df, ln);
+                    rank_steps<D, L, L>(st, Qt, df, ln);
                 } else {
                     with_planes<LX>(lo_on, [&](auto n) {
                         bf8v oh[n.value];
                         scale_frag<n.value>(oh, df, rs, g, MD::RN ? qinv : nullptr);
-                        rank_steps<D, NRB, L, n.value>(st, Qt, 0, oh, ln);
+                        rank_steps<D, L, n.value>(st, Qt, oh, ln);
                     });
                 }
             }
@@ -1101,7 +1106,7 @@ __global__ __launch_bounds__(8 * D, 4) void ks_bwd_dq_halves(
             f4v fh[2], fl[2];  // rows i, columns r (SWAP), or rows r, columns i
 #pragma unroll
             for (int m = 0; m < 2; ++m) fh[m] = fl[m] = f4v{0.f, 0.f, 0.f, 0.f};
-            with_planes<LX>(lo_on, [&](auto n) { state_steps<D, D / 32, n.value, L, SWAP>(fh, fl, st, dOt, 0, ln); });
+            with_planes<LX>(lo_on, [&](auto n) { state_steps<D, n.value, L, SWAP>(fh, fl, st, dOt, ln); });
             bf8v kf[L];
             load_cols<D, L>(kf, Kt, ln.local(ln.col), w);
             block_sync();
@@ -1131,10 +1136,10 @@ __global__ __launch_bounds__(8 * D, 4) void ks_bwd_dq_halves(
                 factor_frag(fk, ik, g);
                 vec.add(kf, fk);
                 scale_frag<3>(kh, kf, ik, g);
-                rank_steps<D, NRB, L, 3>(st, Vt, 0, kh, ln);
+                rank_steps<D, L, 3>(st, Vt, kh, ln);
             } else {
                 vec.add(kf, one);
-                rank_steps<D, NRB, L, L>(st, Vt, 0, kf, ln);
+                rank_steps<D, L, L>(st, Vt, kf, ln);
             }
             post_factors(min(c0 + CR, row1), nxt.g, par ^ 1);
         }
@@ -1168,7 +1173,7 @@ __global__ __launch_bounds__(8 * D, 4) void ks_bwd_dq_halves(
 // and hold R (rows r, columns j) and w; both run the same code on exchanged tiles, 16 columns a wave.
 // Four waves a SIMD instead of two that hold both states: a SIMD issues a wave's instructions one every
 // five clocks, two waves' 2.9 and four waves' closer still, and the kernel is bound by what its waves
-// issue and wait for in turn (vector ALU 41 %, LDS 42 %, matrix pipe 35 % of the clocks, fp32 D = 64).
+// issue and wait for in turn (vector ALU 30 -> 37 %, LDS 38 -> 46 %, matrix pipe 31 -> 38 % of the clocks, fp32 D = 64).
 // Half the registers a wave have to do (TIGHT).  Descending sweep, us, before and now: fp32, 64 slices of 4096
 // rows, D = 64 104 -> 94; of 1000 rows, D = 128 70 -> 67; bf16, 36 of 5003, D = 64 38.6 -> 30.0; normalised, 128 of
 // 2048, D = 128 190 -> 182; one slice of 256 rows, D = 16 17.7 -> 13.3.
@@ -1343,7 +1348,7 @@ __global__ __launch_bounds__(8 * D, 4) void ks_bwd_dkv(
         f4v fh[2], fl[2];  // rows n, the wave's columns (SWAP), or the other way round
 #pragma unroll
         for (int m = 0; m < 2; ++m) fh[m] = fl[m] = f4v{0.f, 0.f, 0.f, 0.f};
-        with_planes<LX>(lo_on, [&](auto n) { state_steps<D, D / 32, n.value, L, SWAP>(fh, fl, st, Yt, 0, ln); });
+        with_planes<LX>(lo_on, [&](auto n) { state_steps<D, n.value, L, SWAP>(fh, fl, st, Yt, ln); });
         bf8v own[L];
         load_cols<D, L>(own, Et, ln.local(ln.col), w);
         request(cur, cn, false, true);
@@ -1379,12 +1384,12 @@ __global__ __launch_bounds__(8 * D, 4) void ks_bwd_dkv(
         load_factor<3>(fac, half ? frs[par] : fdl[par], g);
         vec.add(own, fac);
         if constexpr (QT) {
-            rank_steps<D, NRB, L, L>(st, At, 0, own, ln);
+            rank_steps<D, L, L>(st, At, own, ln);
         } else {
             with_planes<LX>(lo_on, [&](auto n) {
                 bf8v og[n.value];
                 scale_frag<n.value>(og, own, rs, g, MD::RN ? iq : nullptr);
-                rank_steps<D, NRB, L, n.value>(st, At, 0, og, ln);
+                rank_steps<D, L, n.value>(st, At, og, ln);
             });
         }
         post_factors(row0 + max(ci - 1, 0L) * CR, nxt, par ^ 1);
@@ -1402,7 +1407,8 @@ __global__ __launch_bounds__(8 * D, 4) void ks_bwd_dkv(
 
 // ---------------------------------------------------------------------------
 // The same for bf16 at D = 128: waves of 32 columns (la_wave32.h), half of them for dK, half for dV, on
-// natural tiles; two chunks requested ahead.
+// natural tiles; two chunks requested ahead.  Half the LDS reads of 16 columns a wave (LDS 33 -> 26 % of the
+// clocks); waits are what is left (43 % of a wave's life).  110 -> 98 us, 128 slices of 2048 rows.
 // ---------------------------------------------------------------------------
 template <int D, int LD>
 __global__ __launch_bounds__(4 * D, 2) void ks_bwd_dkv_wide(
