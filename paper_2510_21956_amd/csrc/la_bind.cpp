@@ -1,6 +1,6 @@
 // Argument marshalling of the small, frequent calls (binding.py) in native code: the checks, addresses
 // and conversions that the Python functions of the same names make, one tensor at a time, took most
-// of a decode step's 7 us.  Takes tensors only, without a trace; everything else stays with the Python
+// of a decode step's 7 us.  Takes plain tensors only, without a trace; everything else stays with the Python
 // functions, which are also what a build without this file runs.
 //
 // Refuses what they refuse, with the same exceptions.  C++ exceptions (a tensor without storage, a
@@ -32,7 +32,10 @@ struct PythonError {};  // a Python exception is set
 }
 
 bool is_none(PyObject *o) { return o == Py_None; }
-bool tensor_or_none(PyObject *o) { return is_none(o) || THPVariable_Check(o); }
+// Tensors and parameters; a subclass may answer is_contiguous, data_ptr and the rest in its own way, which
+// the Python functions ask it for.
+bool plain(PyObject *o) { return THPVariable_CheckExact(o); }
+bool plain_or_none(PyObject *o) { return is_none(o) || plain(o); }
 const at::Tensor &tensor(PyObject *o) { return THPVariable_Unpack(o); }
 void *address(PyObject *o) { return is_none(o) ? nullptr : tensor(o).data_ptr(); }
 size_t bytes(const at::Tensor &t) { return (size_t)t.numel() * t.element_size(); }
@@ -116,9 +119,9 @@ PyObject *status(Call call)
 }
 bool ours(PyObject *const *a, int first, int last)
 {
-    if (!THPVariable_Check(a[first])) return false;
+    if (!plain(a[first])) return false;
     for (int i = first + 1; i <= last; ++i)
-        if (!tensor_or_none(a[i])) return false;
+        if (!plain_or_none(a[i])) return false;
     return true;
 }
 
@@ -127,7 +130,7 @@ PyObject *forward(PyObject *, PyObject *const *x, Py_ssize_t n)
 {
     return guarded([&]() -> PyObject * {
         if (n != 12) refuse(PyExc_TypeError, "forward takes 12 arguments");
-        if (!ours(x, 1, 5) || !THPVariable_Check(x[9]) || !tensor_or_none(x[10]) || is_none(x[2]) ||
+        if (!ours(x, 1, 5) || !plain(x[9]) || !plain_or_none(x[10]) || is_none(x[2]) ||
             is_none(x[3]) || is_none(x[4]))
             Py_RETURN_NONE;
         const long kind = PyLong_AsLong(x[0]);
@@ -164,7 +167,7 @@ PyObject *backward(PyObject *, PyObject *const *x, Py_ssize_t n)
 {
     return guarded([&]() -> PyObject * {
         if (n != 16) refuse(PyExc_TypeError, "backward takes 16 arguments");
-        if (!ours(x, 1, 9) || !THPVariable_Check(x[13]) || !tensor_or_none(x[14])) Py_RETURN_NONE;
+        if (!ours(x, 1, 9) || !plain(x[13]) || !plain_or_none(x[14])) Py_RETURN_NONE;
         for (int i : {2, 3, 6, 7, 8, 9})
             if (is_none(x[i])) Py_RETURN_NONE;
         const long kind = PyLong_AsLong(x[0]);
@@ -230,7 +233,7 @@ PyObject *decode_prefill(PyObject *, PyObject *const *x, Py_ssize_t n)
     return guarded([&]() -> PyObject * {
         if (n != 6) refuse(PyExc_TypeError, "decode_prefill takes 6 arguments");
         for (int i : {0, 1, 2, 4})
-            if (!THPVariable_Check(x[i])) Py_RETURN_NONE;
+            if (!plain(x[i])) Py_RETURN_NONE;
         const at::Tensor &K = tensor(x[0]), &V = tensor(x[1]), &state = tensor(x[2]), &ws = tensor(x[4]);
         if (K.dim() != 4) refuse(PyExc_ValueError, "K must be [B, H, N, D]");
         check_packed({x[0], x[1], x[2], x[4]});

@@ -176,7 +176,12 @@ def test_native_marshalling_refuses_what_python_refuses(la, monkeypatch):
              "b": [la.la_backward_saved, la.la_backward_qknorm_saved,
                    lambda *a: la.la_backward(*a[:-1]), lambda *a: la.la_backward_qknorm(*a[:-1])],
              "d": [la.la_decode_step], "p": [la.la_decode_prefill]}
-    bad = [None, x[0].transpose(1, 2), x[0][0], x[0].cpu(), x[0].half(), x[0].to(torch.bfloat16),
+
+    class Scattered(torch.Tensor):  # a subclass answers for itself
+        def is_contiguous(self, *args, **kwargs):
+            return False
+
+    bad = [None, x[0].as_subclass(Scattered), x[0].transpose(1, 2), x[0][0], x[0].cpu(), x[0].half(), x[0].to(torch.bfloat16),
            x[0][:, :, :20].contiguous(), x[0].double(), "text", 3, G.double(), ws[:256], ws[8:]]
     for key, args in good.items():
         n = len(args)
