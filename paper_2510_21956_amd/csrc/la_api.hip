@@ -90,9 +90,9 @@ Plan make_plan(int B, int H, int N, int D, la_dtype dt, int causal, int is_backw
     if (D == 256) {
         const Plan h = make_plan(B, H, N, 128, dt, causal, is_backward);
         const size_t need =
-            split_scratch(h, (size_t)BH * N, dt, is_backward).total_floats * sizeof(float);
+            split_scratch(h, (int)BH, N, dt, is_backward).total_floats * sizeof(float);
         if (need > p.total_bytes) p.total_bytes = need;
-        p.saved_bytes = 4 * h.saved_bytes;
+        p.saved_bytes = split_saved_bytes(h, (int)BH);
     }
     return p;
 }

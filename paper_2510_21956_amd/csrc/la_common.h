@@ -143,8 +143,9 @@ struct Tracer {
 // element-wise over floats [off, off+len) of each slot, over slots lo..hi.
 //   mode 0: slot[s] += slot[s-1], s = lo+1..hi;  mode 1: slot[s] += slot[s+1], s = hi-1..lo;
 //   mode 2: slot[0] = sum of slots lo..hi.
+// skip (may be null), one int a slice on the device: slices with a nonzero one are left out.
 void launch_scan_slots(float *ws, int BH, int nseg, size_t slot_floats, int off, int len, int mode,
-                       int lo, int hi, hipStream_t st);
+                       int lo, int hi, hipStream_t st, const int *skip = nullptr);
 
 // Matrix-core kernels (la_split.hip): D = 16 (on the tiles of 32), 32, 64, 128 (ld == D), or 128
 // columns of rows ld = 256 wide, one of several launches that build the results up (without
@@ -154,9 +155,12 @@ void launch_scan_slots(float *ws, int BH, int nseg, size_t slot_floats, int off,
 // planes_totals: the per-segment sums over the whole sequence, S = sum k v^T, z = sum k, p = sum v,
 // in the slots of every slice as [S | z | p] (forward plan without the mask); state_from_totals adds
 // the slots up.
+// `handed` (one int a slice on the device; null: `saved` holds whenever it is given): the slices whose sums
+// in `saved` hold; the sums of the others are formed in the workspace, as without `saved`.
 struct BlockPass {
     int xflags = 0;
     float *Pq = nullptr, *Pk = nullptr, *Pv = nullptr;
+    const int *handed = nullptr;
 };
 la_status planes_forward(const Problem &pr, const Plan &pl, int ld, const void *Q, const void *K,
                          const void *V, void *O, float *G, float *ws, float *saved, hipStream_t st,
@@ -200,13 +204,15 @@ la_status state_from_totals(const float *ws, float *state, int BH, int D, int ns
 // What split_forward / split_backward keep behind the D = 128 plan's workspace (offsets and
 // total in floats, T = token-heads).  Forward: one float per token-head (g_off) and, for bf16
 // tensors, 128 (f_off).  Backward, bf16 tensors only: 128 each for the dQ and dK block in
-// progress (q_off, k_off) and 2 x 128 for the two dV blocks (v_off).
+// progress (q_off, k_off) and 2 x 128 for the two dV blocks (v_off); behind them one int a slice
+// (flag_off, BlockPass::handed).
 struct SplitScratch {
-    size_t g_off, f_off, q_off, k_off, v_off, total_floats;
+    size_t g_off, f_off, q_off, k_off, v_off, flag_off, total_floats;
 };
-inline SplitScratch split_scratch(const Plan &pl128, size_t T, la_dtype dt, int is_backward)
+inline SplitScratch split_scratch(const Plan &pl128, int BH, int N, la_dtype dt, int is_backward)
 {
     SplitScratch s{};
+    const size_t T = (size_t)BH * N;
     const size_t base = pl128.total_bytes / sizeof(float), wide = dt == LA_BF16 ? T * 128 : 0;
     if (!is_backward) {
         s.g_off = base;
@@ -216,7 +222,8 @@ inline SplitScratch split_scratch(const Plan &pl128, size_t T, la_dtype dt, int 
         s.q_off = base;
         s.k_off = s.q_off + wide;
         s.v_off = s.k_off + wide;
-        s.total_floats = s.v_off + 2 * wide;
+        s.flag_off = s.v_off + 2 * wide;
+        s.total_floats = s.flag_off + BH;
     }
     return s;
 }
@@ -224,7 +231,13 @@ inline SplitScratch split_scratch(const Plan &pl128, size_t T, la_dtype dt, int 
 // of the D = 128 sums kernels, each followed by state_block_from_totals.
 la_status split_prefill(const Problem &pr, const Plan &pl, const void *K, const void *V, float *ws,
                         float *state, int accumulate, hipStream_t st);
-// saved (may be null): the hand-over buffers of the four passes one after another, pl.saved_bytes each.
+// saved (may be null): the hand-over buffers of the four passes one after another, pl.saved_bytes each, and
+// behind them kWitnessWords words a slice that tell the backward pass whose sums they are.
+constexpr int kWitnessWords = 256;
+inline size_t split_saved_bytes(const Plan &pl128, int BH)
+{
+    return 4 * pl128.saved_bytes + (size_t)BH * kWitnessWords * 4;
+}
 la_status split_forward(const Problem &pr, const Plan &pl, const void *Q, const void *K,
                         const void *V, void *O, float *G, float *ws, float *saved, hipStream_t st,
                         Tracer &tc);

@@ -17,8 +17,50 @@ namespace la {
 // the first pass's share of g and, for bf16, its undivided numerator in fp32, and the backward
 // pass, for bf16, the first share of every gradient block in fp32 (split_scratch).  With `saved` every
 // forward pass hands its sums at the segment boundaries to the backward pass on the same blocks, which
-// then runs no sums kernel and no scan (64 slices of 4096 rows, a step without and with: fp32 3390 and 3125 us,
-// bf16 1700 and 1556; 8 of 8000, bf16 650 and 580).
+// then forms none (64 slices of 4096 rows, a step without and with: fp32 3390 and 3145 us, bf16 1700 and 1576).
+//
+// Whether a hand-over buffer holds this problem's sums is for the backward pass to find out: the buffer is
+// optional, and a forward call that was given none (or one it could not use) succeeds all the same.  So the
+// forward pass leaves the last row of every slice's O in it, under a key of the problem, and the backward pass
+// compares that with the O it is given: sums of other inputs, or memory that no forward pass wrote, are passed
+// over, slice by slice.  The sums kernels are launched either way and return at once where the sums hold (20 us
+// a step, witness included).
+namespace {
+
+// What the segments and the layout of the sums depend on.
+uint32_t problem_key(const Problem &pr, const Plan &pl)
+{
+    uint32_t k = 0x9e3779b9u;
+    for (uint32_t x : {(uint32_t)pr.BH, (uint32_t)pr.N, (uint32_t)pr.causal, (uint32_t)pr.dt, (uint32_t)pl.nseg,
+                       (uint32_t)pl.seg_len, (uint32_t)(pl.map.cost_seg > 0)}) {
+        k = (k ^ x) * 0x85ebca6bu;
+        k ^= k >> 15;
+    }
+    return k;
+}
+// One wave a slice; a row of O is `words` (128 or 256) words.
+__global__ __launch_bounds__(64) void k_leave_witness(const uint32_t *__restrict__ O, uint32_t *__restrict__ wit,
+                                                      int N, int words, uint32_t key)
+{
+    const uint32_t *row = O + ((size_t)blockIdx.x * N + N - 1) * words;
+    uint32_t *w = wit + (size_t)blockIdx.x * kWitnessWords;
+    for (int i = threadIdx.x; i < words; i += 64) w[i] = row[i] ^ key;
+}
+__global__ __launch_bounds__(64) void k_check_witness(const uint32_t *__restrict__ O,
+                                                      const uint32_t *__restrict__ wit, int *__restrict__ handed,
+                                                      int N, int words, uint32_t key)
+{
+    const uint32_t *row = O + ((size_t)blockIdx.x * N + N - 1) * words;
+    const uint32_t *w = wit + (size_t)blockIdx.x * kWitnessWords;
+    uint32_t diff = 0;
+    for (int i = threadIdx.x; i < words; i += 64) diff |= w[i] ^ row[i] ^ key;
+    const int same = __all(diff == 0);
+    if (threadIdx.x == 0) handed[blockIdx.x] = same;
+}
+int row_words(la_dtype dt) { return dt == LA_F32 ? 256 : 128; }
+
+}  // namespace
+
 static const void *col_block(const void *p, int j, la_dtype dt)
 {
     return (const char *)p + (size_t)128 * j * (dt == LA_F32 ? 4 : 2);
@@ -44,17 +86,18 @@ la_status split_prefill(const Problem &pr, const Plan &pl, const void *K, const 
     return LA_OK;
 }
 
-// Hand-over of pass (i, j) inside the buffer of all four.
-static float *saved_block(float *saved, const Plan &pl, int i, int j)
+// Hand-over of pass (i, j) inside the buffer of all four; block 4 is the witness.
+template <typename F>
+static F *saved_block(F *saved, const Plan &pl, int block)
 {
-    return saved ? saved + (size_t)(2 * i + j) * (pl.saved_bytes / sizeof(float)) : nullptr;
+    return saved ? saved + (size_t)block * (pl.saved_bytes / sizeof(float)) : nullptr;
 }
 
 la_status split_forward(const Problem &pr, const Plan &pl, const void *Q, const void *K,
                         const void *V, void *O, float *G, float *ws, float *saved, hipStream_t st,
                         Tracer &tc)
 {
-    const SplitScratch sc = split_scratch(pl, (size_t)pr.BH * pr.N, pr.dt, 0);
+    const SplitScratch sc = split_scratch(pl, pr.BH, pr.N, pr.dt, 0);
     float *gpart = ws + sc.g_off, *fraw = ws + sc.f_off;
     Problem p = pr;
     p.D = 128;
@@ -66,13 +109,16 @@ la_status split_forward(const Problem &pr, const Plan &pl, const void *Q, const 
             p.a = i == 0 ? pr.a : 0.f;
             const la_status s = planes_forward(p, pl, 256, col_block(Q, i, pr.dt), col_block(K, i, pr.dt),
                                                Vj, Oj, i == 0 ? gpart : (j == 1 ? G : nullptr), ws,
-                                               saved_block(saved, pl, i, j), st, quiet, i == 0 ? XF_RAW : XF_ACC,
+                                               saved_block(saved, pl, 2 * i + j), st, quiet, i == 0 ? XF_RAW : XF_ACC,
                                                i == 0 ? nullptr : gpart, fraw);
             if (s != LA_OK) return s;
             tc.mark("fwd_block_pass");
         }
     }
-    return LA_OK;
+    if (!saved) return LA_OK;
+    k_leave_witness<<<dim3(pr.BH), dim3(64), 0, st>>>((const uint32_t *)O, (uint32_t *)saved_block(saved, pl, 4),
+                                                      pr.N, row_words(pr.dt), problem_key(pr, pl));
+    return launch_status();
 }
 
 // dK == nullptr: the ascending sweeps only (dQ).
@@ -80,10 +126,15 @@ la_status split_backward(const Problem &pr, const Plan &pl, const void *Q, const
                          const void *V, const void *O, const float *G, const void *dO, void *dQ,
                          void *dK, void *dV, float *ws, const float *saved, hipStream_t st, Tracer &tc)
 {
-    const SplitScratch sc = split_scratch(pl, (size_t)pr.BH * pr.N, pr.dt, 1);
+    const SplitScratch sc = split_scratch(pl, pr.BH, pr.N, pr.dt, 1);
     Problem p = pr;
     p.D = 128;
     Tracer quiet(nullptr, st);  // the caller's trace gets one mark per pass, not per kernel
+    int *handed = saved ? (int *)(ws + sc.flag_off) : nullptr;
+    if (saved)
+        k_check_witness<<<dim3(pr.BH), dim3(64), 0, st>>>(
+            (const uint32_t *)O, (const uint32_t *)saved_block(saved, pl, 4), handed, pr.N, row_words(pr.dt),
+            problem_key(pr, pl));
     for (int i = 0; i < 2; ++i)
         for (int j = 0; j < 2; ++j) {
             p.a = i == 0 ? pr.a : 0.f;
@@ -93,11 +144,12 @@ la_status split_backward(const Problem &pr, const Plan &pl, const void *Q, const
             bp.Pq = ws + sc.q_off;
             bp.Pk = ws + sc.k_off;
             bp.Pv = ws + sc.v_off + (size_t)j * pr.BH * pr.N * 128;
+            bp.handed = handed;
             const la_status s = planes_backward(
                 p, pl, 256, col_block(Q, i, pr.dt), col_block(K, i, pr.dt), col_block(V, j, pr.dt),
                 col_block(O, j, pr.dt), G, col_block(dO, j, pr.dt), col_block(dQ, i, pr.dt),
                 dK ? col_block(dK, i, pr.dt) : nullptr, dK ? col_block(dV, j, pr.dt) : nullptr, ws,
-                saved_block(const_cast<float *>(saved), pl, i, j), st, quiet, bp);
+                saved_block(saved, pl, 2 * i + j), st, quiet, bp);
             if (s != LA_OK) return s;
             tc.mark("bwd_block_pass");
         }

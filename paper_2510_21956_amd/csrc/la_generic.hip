@@ -225,14 +225,15 @@ __global__ __launch_bounds__(NT) void k_bwd_state(const T *__restrict__ Q, const
 //   mode 1: slot[s] += slot[s+1] for s = hi-1..lo   (running sum, descending)
 //   mode 2: slot[0] = sum of slots lo..hi           (no mask: every row sees every row), with
 //           what the additions lose: some hundred slots of one long slice add up
+// Slices with skip[slice] != 0 (skip may be null) stay as they are.
 // ---------------------------------------------------------------------------
 template <int BATCH>
 __global__ __launch_bounds__(NT) void k_scan_slots(float *__restrict__ ws, int nseg,
                                                    size_t slot_floats, int off, int len, int mode,
-                                                   int lo, int hi)
+                                                   int lo, int hi, const int *__restrict__ skip)
 {
     int e = blockIdx.y * NT + threadIdx.x;
-    if (e >= len || hi < lo) return;
+    if (e >= len || hi < lo || (skip && skip[blockIdx.x])) return;
     float *p = ws + (size_t)blockIdx.x * nseg * slot_floats + off + e;
     // The slots are read BATCH at a time before anything is added or written back: one memory
     // round trip per BATCH slots instead of one per slot (the sums are formed in the same order
@@ -537,7 +538,7 @@ la_status fwd_impl(const Problem &pr, const Plan &pl, const T *Q, const T *K, co
         tc.mark("generic_fwd_state");
         const int len = D * D + 2 * D;
         k_scan_slots<16><<<dim3(pr.BH, (len + NT - 1) / NT), dim3(NT), 0, st>>>(
-            ws, nseg, pl.slot_floats, 0, len, pr.causal ? 0 : 2, pr.causal ? 1 : 0, nseg - 1);
+            ws, nseg, pl.slot_floats, 0, len, pr.causal ? 0 : 2, pr.causal ? 1 : 0, nseg - 1, nullptr);
         tc.mark("scan_slots");
     }
     k_fwd_apply<T, D><<<dim3(pr.BH * nseg), dim3(NT), 0, st>>>(
@@ -561,13 +562,13 @@ la_status bwd_impl(const Problem &pr, const Plan &pl, const T *Q, const T *K, co
     const int lenS = D * D + D, lenR = D * D + 2 * D;
     if (pr.causal) {
         k_scan_slots<16><<<dim3(pr.BH, (lenS + NT - 1) / NT), dim3(NT), 0, st>>>(
-            ws, nseg, pl.slot_floats, 0, lenS, 0, 1, nseg - 1);
+            ws, nseg, pl.slot_floats, 0, lenS, 0, 1, nseg - 1, nullptr);
         k_scan_slots<16><<<dim3(pr.BH, (lenR + NT - 1) / NT), dim3(NT), 0, st>>>(
-            ws, nseg, pl.slot_floats, lenS, lenR, 1, 0, nseg - 2);
+            ws, nseg, pl.slot_floats, lenS, lenR, 1, 0, nseg - 2, nullptr);
         tc.mark("scan_slots");
     } else {
         k_scan_slots<16><<<dim3(pr.BH, (lenS + lenR + NT - 1) / NT), dim3(NT), 0, st>>>(
-            ws, nseg, pl.slot_floats, 0, lenS + lenR, 2, 0, nseg - 1);
+            ws, nseg, pl.slot_floats, 0, lenS + lenR, 2, 0, nseg - 1, nullptr);
         tc.mark("scan_slots");
     }
     k_bwd_apply<T, D><<<dim3(pr.BH * nseg), dim3(NT), 0, st>>>(
@@ -612,13 +613,13 @@ la_status bwd_by_d(const Problem &pr, const Plan &pl, const void *Q, const void 
 }  // namespace
 
 void launch_scan_slots(float *ws, int BH, int nseg, size_t slot_floats, int off, int len, int mode,
-                       int lo, int hi, hipStream_t st)
+                       int lo, int hi, hipStream_t st, const int *skip)
 {
     // a running sum over a single slot changes nothing; the total of a single slot 0 neither
     if (hi < lo || (hi == lo && (mode != 2 || lo == 0))) return;
     auto *kernel = hi - lo < 8 ? k_scan_slots<8> : k_scan_slots<16>;
     kernel<<<dim3(BH, (len + NT - 1) / NT), dim3(NT), 0, st>>>(ws, nseg, slot_floats, off, len, mode,
-                                                               lo, hi);
+                                                               lo, hi, skip);
 }
 
 namespace {

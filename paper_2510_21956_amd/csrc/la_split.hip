@@ -237,7 +237,8 @@ __device__ __forceinline__ void stage(const CH &ch, __bf16 *tile, float *inv_out
 template <int MODE, int D, bool TRANSPOSED, int LD, bool LONG>
 __global__ __launch_bounds__(4 * D, 2) void ks_kv_state(
     const typename Mode<MODE>::TIO *__restrict__ K, const typename Mode<MODE>::TIO *__restrict__ V,
-    float *__restrict__ ws, int N, int nseg, int nseg_run, SegMap sm, size_t slot_floats, int slot_shift)
+    float *__restrict__ ws, int N, int nseg, int nseg_run, SegMap sm, size_t slot_floats, int slot_shift,
+    const int *__restrict__ skip)
 {
     typedef Mode<MODE> MD;
     typedef typename MD::TIO TIO;
@@ -247,6 +248,9 @@ __global__ __launch_bounds__(4 * D, 2) void ks_kv_state(
     __shared__ __align__(16) __bf16 lds[NT * TP];
     __shared__ __align__(16) float ikb[MD::RN ? NT * CR : 4];  // 1 / |k|
     const int bh = blockIdx.x / nseg_run, seg = blockIdx.x % nseg_run;
+    if constexpr (LD > D) {  // slices whose sums were handed over
+        if (skip && skip[bh]) return;
+    }
     const TIO *Kp = K + (size_t)bh * N * LD, *Vp = V + (size_t)bh * N * LD;
     const long row0 = seg_row(sm, seg, nseg, N), row1 = seg_row(sm, seg + 1, nseg, N);
     const int t = threadIdx.x, l = t % 64, c = l % 16, g = l / 16;
@@ -671,7 +675,7 @@ __global__ __launch_bounds__(4 * D, 2) void ks_fwd_read(
 //   dQ_c = diag(b / g) (tril(Cm') K_c + dO_c S^T - dprime z^T);  then S += K_c^T V_c, z += sum k
 //   R += (Q/g)_c^T dO_c,  u += sum dprime (q/g),  w += sum dO / g
 // The state is held transposed (rows j, columns r): the product contracts over j.
-// LD > D: xflags & 1 marks the second of the two launches that build dQ up.
+// LD > D: xflags & 1 marks the second of the two launches that build dQ up; handed as in BlockPass.
 // fp32 at D = 128 without the mask holds S^T, R and two chunks in 256 registers but for 6 to 10, which
 // go to scratch once a chunk (a state in its accumulators less would cost a pass over Q and dO).
 // ---------------------------------------------------------------------------
@@ -682,7 +686,7 @@ __global__ __launch_bounds__(4 * D, 2) void ks_bwd_dq(
     const float *__restrict__ G, const typename Mode<MODE>::TIO *__restrict__ dO,
     typename Mode<MODE>::TIO *__restrict__ dQ, float *ws, const float *sinit, size_t sinit_floats,
     float *__restrict__ dprime, int N, int nseg, SegMap sm, size_t slot_floats, float b, int xflags,
-    float *__restrict__ Pq)
+    float *__restrict__ Pq, const int *__restrict__ handed)
 {
     typedef Mode<MODE> MD;
     typedef typename MD::TIO TIO;
@@ -717,6 +721,9 @@ __global__ __launch_bounds__(4 * D, 2) void ks_bwd_dq(
 
     const bool zero_init = CAUSAL && seg == 0;
     const float *slot = sinit + ((size_t)bh * nseg + (CAUSAL ? seg : 0)) * sinit_floats;
+    if constexpr (LD > D) {
+        if (handed && !handed[bh]) slot = ws + ((size_t)bh * nseg + (CAUSAL ? seg : 0)) * slot_floats;
+    }
     Blk st[NRB], accR[NRB];  // S^T: rows j, columns r = 16w + c;  R: rows r, columns j
 #pragma unroll
     for (int jb = 0; jb < NRB; ++jb) {
@@ -925,7 +932,7 @@ __global__ __launch_bounds__(8 * D, 4) void ks_bwd_dq_halves(
     const float *__restrict__ G, const typename Mode<MODE>::TIO *__restrict__ dO,
     typename Mode<MODE>::TIO *__restrict__ dQ, float *ws, const float *sinit, size_t sinit_floats,
     float *__restrict__ dprime, int N, int nseg, SegMap sm, size_t slot_floats, float b, int xflags,
-    float *__restrict__ Pq)
+    float *__restrict__ Pq, const int *)
 {
     typedef Mode<MODE> MD;
     typedef typename MD::TIO TIO;
@@ -1687,7 +1694,7 @@ la_status run_forward(const Problem &pr, const Plan &pl, const void *Qv, const v
     if (nrun > 0) {
         (pr.causal ? ks_kv_state<MODE, D, false, LD, false> : ks_kv_state<MODE, D, false, LD, true>)<<<
             dim3(pr.BH * nrun), block, 0, st>>>(
-            K, V, ws, pr.N, nseg, nrun, pl.map, pl.slot_floats, pr.causal ? 1 : 0);
+            K, V, ws, pr.N, nseg, nrun, pl.map, pl.slot_floats, pr.causal ? 1 : 0, nullptr);
         tc.mark("fwd_state");
         launch_scan_slots(ws, pr.BH, nseg, pl.slot_floats, 0, D * D + 2 * D, pr.causal ? 0 : 2,
                           pr.causal ? 1 : 0, nseg - 1, st);
@@ -1743,20 +1750,21 @@ la_status run_backward(const Problem &pr, const Plan &pl, const void *Qv, const 
     const dim3 grid(pr.BH * nseg), block(4 * D), block2(8 * D);
     // forward-running sums before every segment: handed over by the forward pass, or
     // per-segment sums (none needed from a masked pass's last segment) and a scan here
-    if (!saved && nrun > 0) {
+    if ((!saved || bp.handed) && nrun > 0) {
         (pr.causal ? ks_kv_state<MODE, D, true, LD, false> : ks_kv_state<MODE, D, true, LD, true>)<<<
             dim3(pr.BH * nrun), block, 0, st>>>(
-            K, V, ws, pr.N, nseg, nrun, pl.map, pl.slot_floats, pr.causal ? 1 : 0);
+            K, V, ws, pr.N, nseg, nrun, pl.map, pl.slot_floats, pr.causal ? 1 : 0, bp.handed);
         tc.mark("bwd_state");
         launch_scan_slots(ws, pr.BH, nseg, pl.slot_floats, SL::ST, SL::R - SL::ST, pr.causal ? 0 : 2,
-                          pr.causal ? 1 : 0, nseg - 1, st);
+                          pr.causal ? 1 : 0, nseg - 1, st, bp.handed);
         tc.mark("scan_slots");
     }
     const float *sinit = saved ? saved : ws;
     const size_t sinit_floats = saved ? pl.saved_floats : pl.slot_floats;
     auto *dq = !pr.causal ? ks_bwd_dq<MODE, D, false, LD> : ks_bwd_dq_masked<MODE, D, LD>();
-    dq<<<grid, pr.causal && D == 32 ? block2 : block, 0, st>>>(Q, K, V, O, G, dO, dQ, ws, sinit, sinit_floats, dprime, pr.N, nseg,
-                               pl.map, pl.slot_floats, pr.b, bp.xflags, bp.Pq);
+    dq<<<grid, pr.causal && D == 32 ? block2 : block, 0, st>>>(
+        Q, K, V, O, G, dO, dQ, ws, sinit, sinit_floats, dprime, pr.N, nseg, pl.map, pl.slot_floats, pr.b, bp.xflags,
+        bp.Pq, bp.handed);
     tc.mark("bwd_dq");
     if (!dK) return launch_status();
     // reverse-running sums left by the ascending sweep
@@ -1784,7 +1792,7 @@ la_status run_totals(const Problem &pr, const Plan &pl, const void *K, const voi
 {
     typedef typename Mode<MODE>::TIO TIO;
     ks_kv_state<MODE, D, false, LD, true><<<dim3(pr.BH * pl.nseg), dim3(4 * D), 0, st>>>(
-        (const TIO *)K, (const TIO *)V, ws, pr.N, pl.nseg, pl.nseg, pl.map, pl.slot_floats, 0);
+        (const TIO *)K, (const TIO *)V, ws, pr.N, pl.nseg, pl.nseg, pl.map, pl.slot_floats, 0, nullptr);
     return launch_status();
 }
 

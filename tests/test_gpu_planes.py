@@ -117,6 +117,41 @@ def test_hand_over_at_head_size_256(la, dtype, causal, N):
         assert torch.equal(O, O2) and all(torch.equal(x, y) for x, y in zip(got, want))
 
 
+@pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_sums_at_head_size_256_are_used_only_where_they_were_written(la, dtype, causal):
+    """The forward call succeeds without a hand-over buffer, so the backward call may be given one that holds
+    something else: memory no forward pass wrote, sums of other inputs, of the other mask.  Gradients are
+    then those of la_backward to the bit, slice by slice; a buffer that does hold is read."""
+    B, H, N, D = 1, 3, 700, 256
+    code = la.LA_F32 if dtype == "f32" else la.LA_BF16
+    dev, _ = upload_case(B, H, N, D, dtype, 6600, [0])
+    other, _ = upload_case(B, H, N, D, dtype, 6601, [0])
+    _, _, foreign = gpu_forward_save(la, other, 1.0, 0.5, causal)
+    _, _, masked_otherwise = gpu_forward_save(la, dev, 1.0, 0.5, not causal)
+    O, G = (torch.full_like(x, float("nan")) for x in gpu_forward(la, dev, 1.0, 0.5, causal))
+    wf = scratch(la.la_workspace_bytes(B, H, N, D, code, causal, 0), "cuda")
+    la.la_forward_save(dev["Q"], dev["K"], dev["V"], O, G, 1.0, 0.5, causal, wf, None)
+    want = gpu_backward(la, dev, O, G, 1.0, 0.5, causal)
+    for saved in (torch.zeros_like(foreign), torch.full_like(foreign, 0xFF), foreign, masked_otherwise):
+        got = gpu_backward_saved(la, dev, O, G, saved, 1.0, 0.5, causal)
+        assert all(torch.equal(x, y) for x, y in zip(got, want)), (dtype, causal)
+    # one slice's inputs changed since: that slice as without, the others on the sums
+    _, _, saved = gpu_forward_save(la, dev, 1.0, 0.5, causal)
+    kept = gpu_backward_saved(la, dev, O, G, saved, 1.0, 0.5, causal)
+    for n in ("Q", "K", "V"):
+        dev[n][0, 1].copy_(other[n][0, 1])
+    O, G = gpu_forward(la, dev, 1.0, 0.5, causal)
+    want = gpu_backward(la, dev, O, G, 1.0, 0.5, causal)
+    got = gpu_backward_saved(la, dev, O, G, saved, 1.0, 0.5, causal)
+    for x, y, z in zip(got, want, kept):
+        assert torch.equal(x[0, 1], y[0, 1]) and torch.equal(x[0, 0], z[0, 0]) and torch.equal(x[0, 2], z[0, 2])
+    # the sums are read: poisoned ones show (the first slice's of the first of the four passes: three segments)
+    saved[:3 * (128 * 128 + 128) * 4] = 0xFF
+    got = gpu_backward_saved(la, dev, O, G, saved, 1.0, 0.5, causal)
+    assert torch.isnan(got[0][0, 0].float()).any()
+
+
 @pytest.mark.parametrize("D", [64, 128])
 def test_fp32_is_fp32(la, oracle_mod, D):
     """Six bf16 products a float product keep 24 bits: the 2-norm error against 64 bits stays at
