@@ -304,11 +304,11 @@ LA_API void la_debug_override(int seg_len, int force_generic);
  * the library and to this library version.  `trace` is the timing hook
  * described below and may be NULL.  Error behaviour as for la_forward /
  * la_backward; a missing, misaligned or short `saved` is LA_ERR_WORKSPACE, except
- * at D = 256, where the hand-over is optional: such a buffer is left unused by both
- * calls (callers that pass NULL there need not change), and la_backward_saved finds
- * out whether the sums in the one it is given are those of its inputs (by the last
- * row of every slice of O, which la_forward_save leaves in the buffer); where they
- * are not, it forms its own.
+ * at D = 256, where the hand-over is optional: such a buffer, or one that overlaps
+ * another buffer of the call, is left unused by both calls (callers that pass NULL
+ * there need not change), and la_backward_saved finds out whether the sums in the
+ * one it is given are those of its inputs (by the last row of every slice of O,
+ * which la_forward_save leaves in the buffer); where they are not, it forms its own.
  */
 LA_API size_t la_saved_state_bytes(int B, int H, int N, int D, la_dtype dt, int causal);
 

@@ -174,7 +174,8 @@ static bool use_fast(const Problem &pr)
 }
 
 // Head size 256 on passes of the D = 128 kernels.  The hand-over buffer is optional there: calls were
-// made without one when there was none, so a missing, misaligned or short buffer is left unused.
+// made without one when there was none, so a missing, misaligned or short buffer, or one that overlaps
+// another of the call, is left unused.
 static bool use_split(const Problem &pr)
 {
     return pr.D == 256 && !g_force_generic.load(std::memory_order_relaxed);
@@ -296,10 +297,14 @@ static la_status forward_impl(const void *Q, const void *K, const void *V, void 
         if (!la::good_saved(saved, saved_bytes, pl)) return LA_ERR_WORKSPACE;
         sv = (float *)saved;
     }
-    if (save && la::use_split(pr) && la::good_saved(saved, saved_bytes, pl)) sv = (float *)saved;
+    const size_t T = (size_t)B * H * N, tb = T * D * (dt == LA_F32 ? 4 : 2);
+    if (save && la::use_split(pr) && la::good_saved(saved, saved_bytes, pl)) {
+        const la::Range others[] = {{Q, tb}, {K, tb}, {V, tb}, {O, tb}, {G, T * 4}, {workspace, pl.total_bytes}};
+        const la::Range own[] = {{saved, pl.saved_bytes}};
+        if (!la::any_alias(others, 6, own, 1)) sv = (float *)saved;
+    }
     if (trace && (!trace->events || trace->capacity < 1)) return LA_ERR_NULL;
     {
-        const size_t T = (size_t)B * H * N, tb = T * D * (dt == LA_F32 ? 4 : 2);
         const la::Range ins[] = {{Q, tb}, {K, tb}, {V, tb}};
         const la::Range outs[] = {{O, tb}, {G, T * 4}, {workspace, pl.total_bytes},
                                   {sv, sv ? pl.saved_bytes : 0}};
@@ -353,11 +358,14 @@ static la_status backward_impl(const void *Q, const void *K, const void *V, cons
         if (!la::good_saved(saved, saved_bytes, pl)) return LA_ERR_WORKSPACE;
         sv = (const float *)saved;
     }
-    if (use_saved && la::use_split(pr) && la::good_saved(saved, saved_bytes, pl))
-        sv = (const float *)saved;
+    const size_t tb = T * D * (dt == LA_F32 ? 4 : 2);
+    if (use_saved && la::use_split(pr) && la::good_saved(saved, saved_bytes, pl)) {
+        const la::Range others[] = {{dQ, tb}, {dK, tb}, {dV, tb}, {workspace, need}};
+        const la::Range own[] = {{saved, pl.saved_bytes}};
+        if (!la::any_alias(others, 4, own, 1)) sv = (const float *)saved;
+    }
     if (trace && (!trace->events || trace->capacity < 1)) return LA_ERR_NULL;
     {
-        const size_t tb = T * D * (dt == LA_F32 ? 4 : 2);
         const la::Range ins[] = {{Q, tb}, {K, tb}, {V, tb}, {O, tb}, {G, T * 4}, {dO, tb},
                                  {sv, sv ? pl.saved_bytes : 0}};
         const la::Range outs[] = {{dQ, tb}, {dK, tb}, {dV, tb}, {workspace, need}};

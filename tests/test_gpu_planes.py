@@ -152,6 +152,25 @@ def test_sums_at_head_size_256_are_used_only_where_they_were_written(la, dtype, 
     assert torch.isnan(got[0][0, 0].float()).any()
 
 
+def test_hand_over_buffer_that_overlaps_another_at_head_size_256(la):
+    """Left unused by both calls, as any buffer was before there was a hand-over at this head size."""
+    B, H, N, D = 1, 2, 700, 256
+    dev, _ = upload_case(B, H, N, D, "f32", 6700, [0])
+    args = dev["Q"], dev["K"], dev["V"]
+    ns = la.la_saved_state_bytes(B, H, N, D, la.LA_F32, True)
+    nb = [la.la_workspace_bytes(B, H, N, D, la.LA_F32, True, w) for w in (0, 1)]
+    ws = scratch(max(nb) + ns, "cuda")
+    O, G = gpu_forward(la, dev, 1.0, 0.5, True)
+    want = gpu_backward(la, dev, O, G, 1.0, 0.5, True)
+    O2, G2 = torch.empty_like(O), torch.empty_like(G)
+    grads = [torch.empty_like(O) for _ in range(3)]
+    for at in (0, nb[1] // 2 // 256 * 256):  # at the workspace's start and inside it
+        la.la_forward_save(*args, O2, G2, 1.0, 0.5, True, ws[:nb[0]], ws[at:at + ns])
+        la.la_backward_saved(*args, O2, G2, dev["dO"], *grads, 1.0, 0.5, True, ws[:nb[1]], ws[at:at + ns])
+        assert torch.equal(O, O2) and torch.equal(G, G2)
+        assert all(torch.equal(x, y) for x, y in zip(grads, want))
+
+
 @pytest.mark.parametrize("D", [64, 128])
 def test_fp32_is_fp32(la, oracle_mod, D):
     """Six bf16 products a float product keep 24 bits: the 2-norm error against 64 bits stays at
