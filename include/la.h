@@ -290,10 +290,13 @@ LA_API void la_debug_override(int seg_len, int force_generic);
  * la_forward_save write them out at the segment boundaries and hand them to
  * la_backward_saved, which then skips that recomputation.  This is an
  * addition to the set {Q,K,V,O,g} that Sec. 3.2 keeps: O(B*H*(N/segment)*D^2)
- * floats, small next to the tensors.
+ * floats, small next to the tensors where these are large (8 to 17 MB at D = 64
+ * and 128 where the segments just fill the GPU, 68 MB at D = 256), but larger than
+ * a tensor where sequences are short.
  *
  *   la_saved_state_bytes: size of the `saved` buffer for this problem (0 for
- *       invalid arguments, and 0 when the library would not use one -- D = 16;
+ *       invalid arguments, and 0 when the library would not use one -- D = 16,
+ *       and D = 256 where it would exceed both 96 MB and one tensor's bytes;
  *       a zero-size buffer may be NULL).
  *   la_forward_save:   la_forward, and additionally fills `saved` (device
  *       memory, 256-byte aligned, at least la_saved_state_bytes bytes).

@@ -92,7 +92,13 @@ Plan make_plan(int B, int H, int N, int D, la_dtype dt, int causal, int is_backw
         const size_t need =
             split_scratch(h, (int)BH, N, dt, is_backward).total_floats * sizeof(float);
         if (need > p.total_bytes) p.total_bytes = need;
-        p.saved_bytes = split_saved_bytes(h, (int)BH);
+        // The hand-over, 264 KB a segment, is optional here.  One segment with the mask hands nothing over: 256
+        // bytes that stay unused.  Slices cut into several segments have 340 in all at most, 90 MB.  What
+        // takes more than kSplitSavedMost, hundreds or thousands of short slices, is handed over only where it is
+        // no larger than one of the tensors (8000 slices of 40 rows without the mask, bf16: 2.1 GB of sums
+        // next to tensors of 164 MB).
+        const size_t tensor = (size_t)BH * N * D * (dt == LA_F32 ? 4 : 2), bytes = split_saved_bytes(h, (int)BH);
+        p.saved_bytes = causal && h.nseg == 1 ? 256 : bytes <= kSplitSavedMost || bytes <= tensor ? bytes : 0;
     }
     return p;
 }
@@ -180,9 +186,13 @@ static bool use_split(const Problem &pr)
 {
     return pr.D == 256 && !g_force_generic.load(std::memory_order_relaxed);
 }
+static bool split_hands_over(const Problem &pr, const Plan &pl)
+{
+    return use_split(pr) && pl.saved_bytes > 256;
+}
 static bool good_saved(const void *saved, size_t bytes, const Plan &pl)
 {
-    return saved && bytes >= pl.saved_bytes && (((uintptr_t)saved) & 255u) == 0;
+    return saved && pl.saved_bytes && bytes >= pl.saved_bytes && (((uintptr_t)saved) & 255u) == 0;
 }
 
 // Extra workspace of a backward pass that recomputes O and g (either handed in as NULL):
@@ -298,7 +308,7 @@ static la_status forward_impl(const void *Q, const void *K, const void *V, void 
         sv = (float *)saved;
     }
     const size_t T = (size_t)B * H * N, tb = T * D * (dt == LA_F32 ? 4 : 2);
-    if (save && la::use_split(pr) && la::good_saved(saved, saved_bytes, pl)) {
+    if (save && la::split_hands_over(pr, pl) && la::good_saved(saved, saved_bytes, pl)) {
         const la::Range others[] = {{Q, tb}, {K, tb}, {V, tb}, {O, tb}, {G, T * 4}, {workspace, pl.total_bytes}};
         const la::Range own[] = {{saved, pl.saved_bytes}};
         if (!la::any_alias(others, 6, own, 1)) sv = (float *)saved;
@@ -359,7 +369,7 @@ static la_status backward_impl(const void *Q, const void *K, const void *V, cons
         sv = (const float *)saved;
     }
     const size_t tb = T * D * (dt == LA_F32 ? 4 : 2);
-    if (use_saved && la::use_split(pr) && la::good_saved(saved, saved_bytes, pl)) {
+    if (use_saved && la::split_hands_over(pr, pl) && la::good_saved(saved, saved_bytes, pl)) {
         const la::Range others[] = {{dQ, tb}, {dK, tb}, {dV, tb}, {workspace, need}};
         const la::Range own[] = {{saved, pl.saved_bytes}};
         if (!la::any_alias(others, 4, own, 1)) sv = (const float *)saved;

@@ -76,6 +76,18 @@ def test_workspace_bytes(lib):
     assert la.la_saved_state_bytes(4, 16, 4096, 48, la.LA_F32, 1) == 0
 
 
+@pytest.mark.parametrize("B,H,N,e,causal,want", [
+    (4, 16, 4096, 4, 1, "sums"), (1, 8, 8000, 2, 1, "sums"), (1, 1, 200000, 2, 0, "sums"), (10, 17, 400, 2, 1, "sums"),
+    (10, 50, 200, 4, 1, "unused"), (8, 1000, 40, 2, 1, "unused"),  # one segment with the mask
+    (8, 1000, 40, 2, 0, "none"), (10, 50, 200, 4, 0, "none"), (8, 1000, 300, 4, 0, "sums")])
+def test_hand_over_size_at_head_size_256(lib, B, H, N, e, causal, want):
+    """Bounded by 96 MiB or one tensor, and no room for sums where none are handed over."""
+    import paper_2510_21956_amd as la
+    n = la.la_saved_state_bytes(B, H, N, 256, la.LA_F32 if e == 4 else la.LA_BF16, causal)
+    assert n <= max(96 << 20, B * H * N * 256 * e)
+    assert n == {"unused": 256, "none": 0}.get(want, n) and (want != "sums" or n >= 4 * B * H * 128 * 129 * 4)
+
+
 def test_argument_checks_precede_any_launch(lib):
     """Bad arguments are rejected on the host: these calls must return an error
     code without a GPU being present."""
