@@ -161,23 +161,29 @@ __device__ __forceinline__ f16v state_rows(const f16v (&st)[D / 32], const __bf1
     return hi + lo;
 }
 // st[k] += A^T B over the chunk rows: A = columns 32 k of tile `at`, B the wave's own columns (b[kr], LB
-// planes).
+// planes).  The products meet on an accumulator of their own and are added once, rounded: an instruction
+// that adds onto a long sum cuts off what lies below its last bit, and there are two a chunk.  A block's
+// addition runs under the next block's instructions (descending sweep, us, chained onto the state / added after
+// each block / this: 128 slices of 2048 rows 101.4, 109.0, 105.5, 16 of 131072 795, 806, 788).
 template <int D, int LB>
 __device__ __forceinline__ void update_rows(f16v (&st)[D / 32], const __bf16 *at, int upd, const bf8v (&b)[2][LB])
 {
+    f16v t[2];
+    asm volatile("" : "+v"(upd));  // addresses worked out here, not kept across the chunk loop
 #pragma unroll
-    for (int k = 0; k < D / 32; ++k) {
-        const bf8v a0 = load_col_frag<D>(at, upd, k, 0), a1 = load_col_frag<D>(at, upd, k, 1);
-        if constexpr (LB == 1) {
-            st[k] = mfma32(a1, b[1][0], mfma32(a0, b[0][0], st[k]));
-        } else {
-            f16v t = zero16();
+    for (int k = 0; k <= D / 32; ++k) {
+        if (k < D / 32) {
+            const bf8v a0 = load_col_frag<D>(at, upd, k, 0), a1 = load_col_frag<D>(at, upd, k, 1);
+            t[k % 2] = zero16();
 #pragma unroll
-            for (int p = LB - 1; p >= 0; --p) t = mfma32(a1, b[1][p], mfma32(a0, b[0][p], t));
-            st[k] += t;
-            // here and not where the next chunk wants it: all blocks' products would stay in registers
-            asm volatile("" : "+v"(st[k]));
+            for (int p = LB - 1; p >= 0; --p) t[k % 2] = mfma32(a1, b[1][p], mfma32(a0, b[0][p], t[k % 2]));
         }
+        if (k > 0) {
+            st[k - 1] += t[(k - 1) % 2];
+            // here and not where the next chunk wants it: all blocks' products would stay in registers
+            asm volatile("" : "+v"(st[k - 1]));
+        }
+        __builtin_amdgcn_sched_barrier(0);
     }
 }
 // Own columns x weight tile of LW planes, over the 32 rows of the chunk, smallest products first.

@@ -171,6 +171,30 @@ def test_hand_over_buffer_that_overlaps_another_at_head_size_256(la):
         assert all(torch.equal(x, y) for x, y in zip(grads, want))
 
 
+def test_descending_sums_lose_no_small_products(la):
+    """bf16, D = 128, one segment: R starts at 2^23 with the last row, and every 16 rows add a product of 1/2,
+    which an instruction that adds onto R cuts off and 32 rows on an accumulator of their own keep.  dK and
+    dV of the first rows are the difference of two entries of R, one of them without the additions: exact but
+    for the rounding of R's second plane and of the result, 2^-9 each."""
+    N, D = 8192, 128
+    big, i = 2.0 ** 12, torch.arange(0, N, 16, device="cuda")
+    Q, K, V, dO = (torch.zeros((1, 1, N, D), device="cuda", dtype=torch.bfloat16) for _ in range(4))
+    Q[0, 0, i, 0], dO[0, 0, i, 0] = 1.0, 0.5       # into R[0, 0] alone
+    Q[0, 0, -1, :2], dO[0, 0, -1, :2] = big, big / 2   # 2^23 into R[0..1, 0..1]
+    V[..., 0], V[..., 1] = 1.0, -1.0               # dK[:, 0] reads R[0, 0] - R[0, 1]
+    K[..., 0], K[..., 1] = 1.0, -1.0               # dV[:, 0] reads R[0, 0] - R[1, 0]
+    O, G = torch.zeros_like(Q), torch.ones((1, 1, N), device="cuda")
+    try:
+        la.la_debug_override(N, 0)
+        dQ, dK, dV = gpu_backward(la, {"Q": Q, "K": K, "V": V, "dO": dO}, O, G, 0.0, 1.0, True)
+    finally:
+        la.la_debug_override(0, 0)
+    want = 0.5 * torch.flip(torch.cumsum(torch.flip((torch.arange(N) % 16 == 0).double(), [0]), 0), [0])[:64]
+    for name, x in (("dK", dK), ("dV", dV)):
+        got = x[0, 0, :64, 0].double().cpu()
+        assert (got - want).abs().max() <= want.max() * 2.0 ** -8, (name, got[0].item(), want[0].item())
+
+
 @pytest.mark.parametrize("D", [64, 128])
 def test_fp32_is_fp32(la, oracle_mod, D):
     """Six bf16 products a float product keep 24 bits: the 2-norm error against 64 bits stays at
