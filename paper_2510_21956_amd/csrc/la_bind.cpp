@@ -3,12 +3,10 @@
 // of a decode step's 7 us.  Takes plain tensors only, without a trace; everything else stays with the Python
 // functions, which are also what a build without this file runs.
 //
-// Refuses what they refuse, with the same exceptions.  C++ exceptions (a tensor without storage, a
-// functorch wrapper) become RuntimeError.  The library is called without the interpreter lock, as ctypes
-// does.
+// Refuses nothing itself: what does not pass the checks (a tensor without storage or a functorch wrapper, whose
+// C++ exception ends up here, included) goes back to the Python functions, which refuse or take it.  The library
+// is called without the interpreter lock, as ctypes does.
 #include <torch/csrc/autograd/python_variable.h>
-
-#include <string>
 
 #include "la.h"
 
@@ -24,11 +22,10 @@ decltype(&la_backward_saved) bwd_saved, bwd_qknorm_saved;
 decltype(&la_decode_step) dec_step;
 decltype(&la_decode_prefill) dec_prefill;
 
-struct PythonError {};  // a Python exception is set
-[[noreturn]] void refuse(PyObject *type, const char *text)
+struct Decline {};  // the Python function takes over; a Python exception may be set
+void require(bool ok)
 {
-    PyErr_SetString(type, text);
-    throw PythonError();
+    if (!ok) throw Decline();
 }
 
 bool is_none(PyObject *o) { return o == Py_None; }
@@ -47,35 +44,30 @@ void check_packed(std::initializer_list<PyObject *> ts)
     for (PyObject *o : ts) {
         if (is_none(o)) continue;
         const at::Tensor &t = tensor(o);
-        if (!t.is_cuda() || !t.is_contiguous()) refuse(PyExc_ValueError, "tensors must be contiguous device tensors");
-        if (t.get_device() != ref.get_device()) refuse(PyExc_ValueError, "tensors must live on one device");
+        require(t.is_cuda() && t.is_contiguous() && t.get_device() == ref.get_device());
     }
 }
 void check_like(const at::Tensor &ref, std::initializer_list<PyObject *> ts)
 {
     for (PyObject *o : ts)
-        if (!is_none(o) && tensor(o).sizes() != ref.sizes()) refuse(PyExc_ValueError, "shape mismatch");
-    for (PyObject *o : ts)
-        if (!is_none(o) && tensor(o).scalar_type() != ref.scalar_type()) refuse(PyExc_TypeError, "dtype mismatch");
+        require(is_none(o) || (tensor(o).sizes() == ref.sizes() && tensor(o).scalar_type() == ref.scalar_type()));
 }
-void check_rows(const at::Tensor &ref, PyObject *g, const char *text)
+void check_rows(const at::Tensor &ref, PyObject *g)
 {
     if (is_none(g)) return;
     const at::Tensor &t = tensor(g);
-    if (t.sizes() != ref.sizes().slice(0, 3) || t.scalar_type() != at::kFloat) refuse(PyExc_ValueError, text);
+    require(t.sizes() == ref.sizes().slice(0, 3) && t.scalar_type() == at::kFloat);
 }
 la_dtype dtype_code(const at::Tensor &t)
 {
-    if (t.scalar_type() == at::kFloat) return LA_F32;
-    if (t.scalar_type() == at::kBFloat16) return LA_BF16;
-    PyErr_Format(PyExc_TypeError, "Q/K/V must be float32 or bfloat16, got torch.%s", c10::toString(t.scalar_type()));
-    throw PythonError();
+    require(t.scalar_type() == at::kFloat || t.scalar_type() == at::kBFloat16);
+    return t.scalar_type() == at::kFloat ? LA_F32 : LA_BF16;
 }
 float number(PyObject *o)
 {
     if (PyFloat_CheckExact(o)) return (float)PyFloat_AS_DOUBLE(o);
     PyObject *f = PyNumber_Float(o);  // what float(o) gives
-    if (!f) throw PythonError();
+    require(f);
     const double x = PyFloat_AS_DOUBLE(f);
     Py_DECREF(f);
     return (float)x;
@@ -83,32 +75,33 @@ float number(PyObject *o)
 int truth(PyObject *o)
 {
     const int x = PyObject_IsTrue(o);
-    if (x < 0) throw PythonError();
+    require(x >= 0);
     return x;
 }
 void *stream_of(PyObject *stream, const at::Tensor &ref)
 {
     PyObject *h = is_none(stream) ? PyObject_CallFunction(raw_stream, "i", (int)ref.get_device())
                                   : PyObject_GetAttrString(stream, "cuda_stream");
-    if (!h) throw PythonError();
+    require(h);
     void *p = PyLong_AsVoidPtr(h);
     Py_DECREF(h);
-    if (!p && PyErr_Occurred()) throw PythonError();
+    require(p || !PyErr_Occurred());
     return p;
 }
 
-// Runs body, which returns the library's status, or nothing where a tensor is expected and something
-// else was given (None is returned: the Python function takes over).
+// Runs body, which returns the library's status, on n arguments.  None: the Python function takes over.
 template <typename Body>
-PyObject *guarded(Body body)
+PyObject *guarded(Py_ssize_t given, Py_ssize_t n, Body body)
 {
+    if (given != n) return PyErr_Format(PyExc_TypeError, "%zd arguments expected", n);
     try {
         return body();
-    } catch (const PythonError &) {
-    } catch (const std::exception &e) {
-        PyErr_SetString(PyExc_RuntimeError, e.what());
+    } catch (const Decline &) {
+    } catch (const std::exception &) {
     }
-    return nullptr;
+    if (PyErr_Occurred() && !PyErr_ExceptionMatches(PyExc_Exception)) return nullptr;  // an interrupt
+    PyErr_Clear();
+    Py_RETURN_NONE;
 }
 template <typename Call>
 PyObject *status(Call call)
@@ -128,17 +121,16 @@ bool ours(PyObject *const *a, int first, int last)
 // kind (0 plain, 1 save, 2 qknorm, 3 qknorm_save), Q, K, V, O, G, a, b, causal, workspace, saved, stream
 PyObject *forward(PyObject *, PyObject *const *x, Py_ssize_t n)
 {
-    return guarded([&]() -> PyObject * {
-        if (n != 12) refuse(PyExc_TypeError, "forward takes 12 arguments");
+    return guarded(n, 12, [&]() -> PyObject * {
         if (!ours(x, 1, 5) || !plain(x[9]) || !plain_or_none(x[10]) || is_none(x[2]) ||
             is_none(x[3]) || is_none(x[4]))
             Py_RETURN_NONE;
         const long kind = PyLong_AsLong(x[0]);
         const at::Tensor &Q = tensor(x[1]), &ws = tensor(x[9]);
-        if (Q.dim() != 4) refuse(PyExc_ValueError, "Q must be [B, H, N, D]");
+        require(Q.dim() == 4);
         check_packed({x[1], x[2], x[3], x[4], x[5], x[9]});
         check_like(Q, {x[2], x[3], x[4]});
-        check_rows(Q, x[5], "G must be [B, H, N] float32 (or None)");
+        check_rows(Q, x[5]);
         const float a = number(x[6]), b = number(x[7]);
         const int causal = truth(x[8]), B = Q.size(0), H = Q.size(1), N = Q.size(2), D = Q.size(3);
         const la_dtype dt = dtype_code(Q);
@@ -165,17 +157,16 @@ PyObject *forward(PyObject *, PyObject *const *x, Py_ssize_t n)
 // kind, Q, K, V, O, G, dO, dQ, dK, dV, a, b, causal, workspace, saved, stream
 PyObject *backward(PyObject *, PyObject *const *x, Py_ssize_t n)
 {
-    return guarded([&]() -> PyObject * {
-        if (n != 16) refuse(PyExc_TypeError, "backward takes 16 arguments");
+    return guarded(n, 16, [&]() -> PyObject * {
         if (!ours(x, 1, 9) || !plain(x[13]) || !plain_or_none(x[14])) Py_RETURN_NONE;
         for (int i : {2, 3, 6, 7, 8, 9})
             if (is_none(x[i])) Py_RETURN_NONE;
         const long kind = PyLong_AsLong(x[0]);
         const at::Tensor &Q = tensor(x[1]), &ws = tensor(x[13]);
-        if (Q.dim() != 4) refuse(PyExc_ValueError, "Q must be [B, H, N, D]");
+        require(Q.dim() == 4);
         check_packed({x[1], x[2], x[3], x[4], x[5], x[6], x[7], x[8], x[9], x[13]});
-        for (int i : {2, 3, 4, 6, 7, 8, 9}) check_like(Q, {x[i]});
-        check_rows(Q, x[5], "G must be [B, H, N] float32 (or None)");
+        check_like(Q, {x[2], x[3], x[4], x[6], x[7], x[8], x[9]});
+        check_rows(Q, x[5]);
         const float a = number(x[10]), b = number(x[11]);
         const int causal = truth(x[12]), B = Q.size(0), H = Q.size(1), N = Q.size(2), D = Q.size(3);
         const la_dtype dt = dtype_code(Q);
@@ -204,17 +195,16 @@ PyObject *backward(PyObject *, PyObject *const *x, Py_ssize_t n)
 // q, k, v, o, g, state, a, b, stream
 PyObject *decode_step(PyObject *, PyObject *const *x, Py_ssize_t n)
 {
-    return guarded([&]() -> PyObject * {
-        if (n != 9) refuse(PyExc_TypeError, "decode_step takes 9 arguments");
+    return guarded(n, 9, [&]() -> PyObject * {
         if (!ours(x, 0, 5)) Py_RETURN_NONE;
         for (int i : {1, 2, 3, 5})
             if (is_none(x[i])) Py_RETURN_NONE;
         const at::Tensor &q = tensor(x[0]), &state = tensor(x[5]);
-        if (q.dim() != 4) refuse(PyExc_ValueError, "q must be [B, H, T, D]");
+        require(q.dim() == 4);
         check_packed({x[0], x[1], x[2], x[3], x[4], x[5]});
         check_like(q, {x[1], x[2], x[3]});
-        if (state.scalar_type() != at::kFloat) refuse(PyExc_TypeError, "dtype mismatch");
-        check_rows(q, x[4], "g must be [B, H, T] float32 (or None)");
+        require(state.scalar_type() == at::kFloat);
+        check_rows(q, x[4]);
         const float a = number(x[6]), b = number(x[7]);
         const int B = q.size(0), H = q.size(1), T = q.size(2), D = q.size(3);
         const la_dtype dt = dtype_code(q);
@@ -230,15 +220,14 @@ PyObject *decode_step(PyObject *, PyObject *const *x, Py_ssize_t n)
 // K, V, state, accumulate, workspace, stream
 PyObject *decode_prefill(PyObject *, PyObject *const *x, Py_ssize_t n)
 {
-    return guarded([&]() -> PyObject * {
-        if (n != 6) refuse(PyExc_TypeError, "decode_prefill takes 6 arguments");
+    return guarded(n, 6, [&]() -> PyObject * {
         for (int i : {0, 1, 2, 4})
             if (!plain(x[i])) Py_RETURN_NONE;
         const at::Tensor &K = tensor(x[0]), &V = tensor(x[1]), &state = tensor(x[2]), &ws = tensor(x[4]);
-        if (K.dim() != 4) refuse(PyExc_ValueError, "K must be [B, H, N, D]");
+        require(K.dim() == 4);
         check_packed({x[0], x[1], x[2], x[4]});
-        if (V.sizes() != K.sizes() || V.scalar_type() != K.scalar_type() || state.scalar_type() != at::kFloat)
-            refuse(PyExc_ValueError, "shape or dtype mismatch");
+        check_like(K, {x[1]});
+        require(state.scalar_type() == at::kFloat);
         const int B = K.size(0), H = K.size(1), N = K.size(2), D = K.size(3), add = truth(x[3]);
         const la_dtype dt = dtype_code(K);
         void *st = stream_of(x[5], K), *k = address(x[0]), *v = address(x[1]), *s = address(x[2]), *w = address(x[4]);

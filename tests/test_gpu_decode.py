@@ -210,3 +210,35 @@ def test_native_marshalling_refuses_what_python_refuses(la, monkeypatch):
             la.la_decode_step(*q1, o1, g1, s2, 1.0, 0.05, stream=torch.cuda.current_stream())
             out.append([O, g, dQ, dK, dV, s2, o1, g1])
     assert all(torch.equal(a, b) for a, b in zip(*out))
+
+
+@pytest.mark.parametrize("dtype", [torch.float16, torch.float64, torch.int32])
+def test_calls_in_another_type_are_refused_in_the_same_words(la, monkeypatch, dtype):
+    """Every tensor of the call in a type the library does not take: nothing stops the checks before the type
+    itself is refused."""
+    from paper_2510_21956_amd import binding
+    assert binding._native is not None, "_marshal.so is not built"
+    x = torch.zeros((1, 2, 8, 16), device="cuda", dtype=dtype)
+    G, st = torch.zeros((1, 2, 8), device="cuda"), torch.zeros(1 << 12, device="cuda")
+    ws = torch.zeros(1 << 16, dtype=torch.uint8, device="cuda")
+    for call in (lambda: la.la_forward(x, x, x, x, G, 1.0, 0.5, True, ws),
+                 lambda: la.la_backward(x, x, x, x, G, x, x, x, x, 1.0, 0.5, True, ws),
+                 lambda: la.la_decode_step(x, x, x, x, G, st, 1.0, 0.5),
+                 lambda: la.la_decode_prefill(x, x, st, 0, ws)):
+        native = _outcome(call)
+        with monkeypatch.context() as m:
+            m.setattr(binding, "_native", None)
+            assert native == _outcome(call) == (TypeError, "Q/K/V must be float32 or bfloat16, got %s" % dtype)
+
+
+def test_stream_handles_are_taken_as_ctypes_takes_them(la):
+    """A stream object may hold its handle as a number, as a ctypes pointer or, for the default stream, as None."""
+    import ctypes
+    q = [torch.randn((1, 2, 1, 16), device="cuda") for _ in range(3)]
+    out = []
+    for handle in (0, None, ctypes.c_void_p(0), ctypes.c_void_p(torch.cuda.default_stream().cuda_stream)):
+        o, st = torch.zeros_like(q[0]), torch.zeros(la.la_decode_state_bytes(1, 2, 16) // 4, device="cuda")
+        la.la_decode_step(*q, o, None, st, 1.0, 0.5, stream=type("Stream", (), {"cuda_stream": handle})())
+        torch.cuda.synchronize()
+        out.append(o)
+    assert out[0].abs().sum() > 0 and all(torch.equal(out[0], o) for o in out)
