@@ -7,6 +7,8 @@ built, loading fails with an error that says how to build it.
 import ctypes
 import importlib.util
 import os
+import sys
+import warnings
 
 import torch
 
@@ -105,17 +107,31 @@ def load_library():
 
 
 def _load_native(lib):
+    """The native marshalling, if there is one that fits; a file that does not load, or that was built for
+    another torch or Python (whose tensors it would misread), is reported and left out: the Python functions
+    below do all of it."""
     global _native
     if not os.path.exists(_MARSHAL_PATH):
-        return  # the Python functions below do all of it
+        return
+    try:
+        _native = _open_native(lib)
+    except Exception as e:
+        warnings.warn("%s is not used, calls take a few microseconds longer: %s" % (_MARSHAL_PATH, e),
+                      RuntimeWarning, stacklevel=3)
+
+
+def _open_native(lib):
     spec = importlib.util.spec_from_file_location("_marshal", _MARSHAL_PATH)
     module = importlib.util.module_from_spec(spec)
     spec.loader.exec_module(module)
+    here = "torch %s, Python %d.%d" % (torch.__version__, *sys.version_info[:2])
+    if getattr(module, "built_for", None) != here:
+        raise ImportError("built for %s, not for %s" % (getattr(module, "built_for", "another version"), here))
     module.init(_device_stream, *(ctypes.cast(f, ctypes.c_void_p).value for f in (
         lib.la_forward_traced, lib.la_forward_qknorm, lib.la_forward_save, lib.la_forward_qknorm_save,
         lib.la_backward_traced, lib.la_backward_qknorm, lib.la_backward_saved,
         lib.la_backward_qknorm_saved, lib.la_decode_step, lib.la_decode_prefill)))
-    _native = module
+    return module
 
 
 def la_version():

@@ -3,6 +3,7 @@ binding into _marshal.so, in-tree."""
 import glob
 import os
 import subprocess
+import sys
 import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -38,7 +39,8 @@ def build_marshal(verbose=False, out=MARSHAL):
     import torch
     from torch.utils.cpp_extension import include_paths, library_paths
     cmd = ["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-fvisibility=hidden",
-           "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI, "-I", INCLUDE]
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI,
+           '-DLA_BUILT_FOR="torch %s, Python %d.%d"' % (torch.__version__, *sys.version_info[:2]), "-I", INCLUDE]
     cmd += ["-isystem%s" % p for p in include_paths() + [sysconfig.get_paths()["include"]]]
     cmd += [os.path.join(CSRC, "la_bind.cpp")]
     cmd += ["-L%s" % p for p in library_paths()] + ["-ltorch_python", "-ltorch_cpu", "-lc10", "-o", out]

@@ -1,4 +1,8 @@
 """Host-only checks of the Python binding: what it refuses before it calls the library."""
+import os
+import shutil
+import warnings
+
 import pytest
 import torch
 
@@ -67,3 +71,29 @@ def test_packed_first_tensor_reaches_the_library(monkeypatch):
     for call in _calls(DeviceTensor(torch.zeros(2, 3, 8, 16))):
         with pytest.raises(Reached):
             call()
+
+
+@pytest.mark.parametrize("form", ["fits", "absent", "not a library", "a header alone", "another torch"])
+def test_marshalling_that_does_not_load_is_left_out(monkeypatch, tmp_path, form):
+    """The library loads at the first call and at every later one, on the Python functions if need be, with one
+    warning where a file is there and not used."""
+    path = tmp_path / "_marshal.so"
+    la.load_library()
+    if not os.path.exists(binding._MARSHAL_PATH):
+        pytest.skip("_marshal.so is not built")
+    if form in ("fits", "another torch"):
+        shutil.copy(binding._MARSHAL_PATH, path)
+    elif form == "a header alone":
+        path.write_bytes(open(binding._MARSHAL_PATH, "rb").read()[:64])
+    elif form == "not a library":
+        path.write_text("text")
+    if form == "another torch":
+        monkeypatch.setattr(torch, "__version__", "1.0.0")
+    for name, value in (("_MARSHAL_PATH", str(path)), ("_lib", None), ("_native", None)):
+        monkeypatch.setattr(binding, name, value)
+    with warnings.catch_warnings(record=True) as seen:
+        warnings.simplefilter("always")
+        lib = la.load_library()
+        assert la.load_library() is lib and la.la_version() >= 100
+    assert (binding._native is not None) == (form == "fits")
+    assert [w.category for w in seen] == ([] if form in ("fits", "absent") else [RuntimeWarning])
