@@ -5,6 +5,7 @@ import os
 import subprocess
 import sys
 import sysconfig
+import warnings
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
@@ -12,6 +13,7 @@ INCLUDE = os.path.join(os.path.dirname(HERE), "include")
 LIB = os.path.join(HERE, "libla.so")
 MARSHAL = os.path.join(HERE, "_marshal.so")
 
+CXX = "g++"
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
     "-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-shared",
@@ -35,10 +37,21 @@ def build_library(verbose=False, extra_flags=(), out=LIB):
 
 
 def build_marshal(verbose=False, out=MARSHAL):
-    """The argument marshalling of binding.py (host code, against torch's headers)."""
+    """The argument marshalling of binding.py (host code, against torch's headers).  binding.py works without
+    it: where it cannot be built, a warning says why, None is returned and no older file stays."""
+    if os.path.exists(out):
+        os.remove(out)
+    try:
+        return _compile_marshal(verbose, out)
+    except (ImportError, OSError, subprocess.CalledProcessError) as e:
+        warnings.warn("%s is not built, calls take a few microseconds longer: %s" % (out, e), RuntimeWarning,
+                      stacklevel=2)
+
+
+def _compile_marshal(verbose, out):
     import torch
     from torch.utils.cpp_extension import include_paths, library_paths
-    cmd = ["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-fvisibility=hidden",
+    cmd = [CXX, "-O2", "-std=c++17", "-shared", "-fPIC", "-fvisibility=hidden",
            "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI,
            '-DLA_BUILT_FOR="torch %s, Python %d.%d"' % (torch.__version__, *sys.version_info[:2]), "-I", INCLUDE]
     cmd += ["-isystem%s" % p for p in include_paths() + [sysconfig.get_paths()["include"]]]

@@ -97,3 +97,17 @@ def test_marshalling_that_does_not_load_is_left_out(monkeypatch, tmp_path, form)
         assert la.load_library() is lib and la.la_version() >= 100
     assert (binding._native is not None) == (form == "fits")
     assert [w.category for w in seen] == ([] if form in ("fits", "absent") else [RuntimeWarning])
+
+
+@pytest.mark.parametrize("compiler", ["/nonexistent/c++", "false"])
+def test_build_goes_on_without_the_marshalling(monkeypatch, tmp_path, compiler):
+    """No host compiler, or one that fails (torch's headers missing): a warning, and no stale file."""
+    from paper_2510_21956_amd import build
+    stale = tmp_path / "_marshal.so"
+    stale.write_text("of an older library")
+    monkeypatch.setattr(build, "CXX", compiler, raising=False)
+    real = build.subprocess.run
+    monkeypatch.setattr(build.subprocess, "run", lambda cmd, **k: real([compiler] + cmd[1:], **k))
+    with pytest.warns(RuntimeWarning, match="not built"):
+        assert build.build_marshal(out=str(stale)) is None
+    assert not stale.exists()
