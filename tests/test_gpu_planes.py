@@ -93,6 +93,26 @@ def test_sweeps_over_many_chunks(la, D, dtype, N):
             assert e <= 1.0, (D, dtype, N, name, e)
 
 
+@pytest.mark.parametrize("D,norm", [(16, False), (16, True), (32, True), (64, True), (128, True)])
+@pytest.mark.parametrize("N", [1057, 1103])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_normalising_and_padded_sweeps_over_many_chunks(la, dtype, N, D, norm):
+    """The same for the forms with factors per row and for head size 16: rows requested two chunks ahead and
+    factors posted by one half of a workgroup come round several times a segment."""
+    dev, _ = upload_case(1, 3, N, D, dtype, 5700 + D + N, [0], normalise=not norm)
+    fwd, bwd = (_qknorm_forward, _qknorm_backward) if norm else (gpu_forward, gpu_backward)
+    O, G = fwd(la, dev, 1.0, 0.5, True)
+    got = bwd(la, dev, O, G, 1.0, 0.5, True)
+    try:
+        la.la_debug_override(0, 1)
+        want = fwd(la, dev, 1.0, 0.5, True) + tuple(bwd(la, dev, O, G, 1.0, 0.5, True))
+    finally:
+        la.la_debug_override(0, 0)
+    for name, x, y in zip(("O", "G", "dQ", "dK", "dV"), (O, G) + tuple(got), want):
+        e = excess(to_f64(x), to_f64(y), 2 * (TOL["f32"] if name == "G" else TOL[dtype]))
+        assert e <= 1.0, (D, dtype, N, norm, name, e)
+
+
 @pytest.mark.parametrize("N", [33, 700])  # one segment, three
 @pytest.mark.parametrize("causal", [True, False])
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
