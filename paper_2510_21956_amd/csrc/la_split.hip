@@ -198,14 +198,20 @@ __device__ __forceinline__ void factor_frag(bf8v (&o)[3], const float *r, int g)
 }
 
 // The waves that form weight blocks are the last to reach the barrier behind them: between the two calls
-// their instructions go first.  fp32, D = 64, 64 slices of 4096 rows, forward / ascending / descending sweep
-// 68.6 / 92.0 / 95.0 us without, 67.1 / 90.0 / 93.9 with; without the mask, 64 of 16384, where no blocks are
-// formed but the waves of a SIMD drift apart, ascending 234.7 and 227.4; bf16 within 1 %.
+// their instructions go first.  Forward / ascending / descending sweep, us, without and with: fp32, D = 64, 64
+// slices of 4096 rows 68.5 / 91.2 / 95.0, 67.2 / 90.8 / 94.2; bf16, 36 of 5003 27.9 / 33.2 / 30.6, 27.6 / 32.8 /
+// 29.9; normalised 39.4 / 54.3 / 62.7, 38.1 / 53.2 / 61.4.  At D = 128 it moves nothing (fp32, 64 of 1000 47.0 /
+// 59.9 / 68.6, 47.1 / 60.2 / 69.2; bf16, 128 of 2048 65.1 / 87.0 / 102.1, 65.1 / 86.9 / 101.8).
+template <int D>
 __device__ __forceinline__ void go_first(bool on)
 {
-    if (on) __builtin_amdgcn_s_setprio(2);
+    if (D <= 64 && on) __builtin_amdgcn_s_setprio(2);
 }
-__device__ __forceinline__ void go_in_turn() { __builtin_amdgcn_s_setprio(0); }
+template <int D>
+__device__ __forceinline__ void go_in_turn()
+{
+    if (D <= 64) __builtin_amdgcn_s_setprio(0);
+}
 
 // One tensor's chunk into its tile: normalised (NORM, fp32) and times scale[row], if given, on
 // the way.  1 / |row| goes to inv_out.
@@ -458,7 +464,7 @@ __global__ __launch_bounds__(4 * D, 2) void ks_fwd_apply(
         const long cn = min(c0 + MD::DEPTH * CR, c_last);
         cur.q.load(Qp, cn, N);
 
-        go_first(w < 3);
+        go_first<D>(w < 3);
         // ---- phase A: weight blocks P = tril(a + b Q K^T), rows n, columns i ----
 #pragma unroll 1
         for (int pidx = w; pidx < 3; pidx += NW) {
@@ -485,7 +491,7 @@ __global__ __launch_bounds__(4 * D, 2) void ks_fwd_apply(
         cur.v.load(Vp, cn, N);
         block_sync();
 
-        go_in_turn();
+        go_in_turn<D>();
         // ---- phase B: denominators; V^T P^T on top, divide, store ----
         if (l < CR) {
             const float ps = psum[0][l] + (l >= 16 ? psum[1][l] : 0.f);
@@ -691,7 +697,7 @@ __global__ __launch_bounds__(4 * D, 2) void ks_bwd_dq(
     typedef Mode<MODE> MD;
     typedef typename MD::TIO TIO;
     constexpr int LQ = MD::LQ, LV = MD::LV, LX = MD::LX;
-    constexpr bool SWAP = MD::SWAP, QT = MD::QT, PROJ = MD::NORM;
+    constexpr bool SWAP = MD::SWAP, QT = MD::QT, PROJ = MD::NORM, F32 = sizeof(TIO) == 4;
     constexpr int NW = D / 16, NRB = D / 16, PL = Tile<D>::PLANE, WPL = Tile<32>::PLANE;
     constexpr int TS = CAUSAL ? 1 : 0;
     typedef Chunk<TIO, D, LD> CH;
@@ -806,12 +812,16 @@ __global__ __launch_bounds__(4 * D, 2) void ks_bwd_dq(
         }
         block_sync();
         const long cn = min(c0 + MD::DEPTH * CR, c_last);
-        cur.g = load_row_float(Gp, cn, N, t % CR);
+        // Under a branch the load stays here; as a plain load the compiler moves it into post_factors, behind this
+        // chunk's stores, where the first wave waits for both.  Ascending sweep, us, plain and under a branch: fp32
+        // without the mask, D = 64 (64 x 16384) 236.3, 228.8, D = 32 (64 x 8192) 55.2, 50.8; bf16 with it, D = 64
+        // (36 x 5003) 32.8, 32.3; bf16 without, two chunks ahead, D = 64 (64 x 16384) 108.8, 112.5.
+        if ((!F32 && !CAUSAL) || w == 0) cur.g = load_row_float(Gp, cn, N, t % CR);
         cur.d.load(dOp, cn, N);
         cur.o.load(Op, cn, N);
         if constexpr (!CAUSAL) cur.q.load(Qp, cn, N);
 
-        go_first(w < 3);
+        if constexpr (CAUSAL) go_first<D>(w < 3);
         // ---- phase A: weight blocks Cm' (rows n, columns i) ----
         if constexpr (CAUSAL) {
 #pragma unroll 1
@@ -839,7 +849,7 @@ __global__ __launch_bounds__(4 * D, 2) void ks_bwd_dq(
             block_sync();
         }
 
-        go_in_turn();
+        if constexpr (CAUSAL) go_in_turn<D>();
         // ---- phase B: K^T Cm'^T on top, scale, store ----
         f4v x[2];
 #pragma unroll
@@ -1328,7 +1338,7 @@ __global__ __launch_bounds__(8 * D, 4) void ks_bwd_dkv(
         const long cn = row0 + max(ci - DEPTH, 0L) * CR;
         request(cur, cn, true, false);
 
-        go_first(wv < 6);
+        go_first<D>(wv < 6);
         // ---- phase A: weight blocks Cm' and W (rows i, columns n) ----
 #pragma unroll 1
         for (int pidx = wv; pidx < 6; pidx += 2 * NW) {
@@ -1361,7 +1371,7 @@ __global__ __launch_bounds__(8 * D, 4) void ks_bwd_dkv(
         request(cur, cn, false, true);
         block_sync();
 
-        go_in_turn();
+        go_in_turn<D>();
         // ---- phase B ----
         f4v x[2];
 #pragma unroll
@@ -1518,7 +1528,6 @@ __global__ __launch_bounds__(4 * D, 2) void ks_bwd_dkv_wide(
         cur.k.load(Kp, cn, N);
         cur.v.load(Vp, cn, N);
         request_gd(row0 + max(ci - 1, 0L) * CR);
-        go_first(wv < 6);
         // ---- phase A: weight blocks Cm' and W (rows i, columns n) ----
 #pragma unroll 1
         for (int pidx = wv; pidx < 6; pidx += NW) {
@@ -1542,7 +1551,6 @@ __global__ __launch_bounds__(4 * D, 2) void ks_bwd_dkv_wide(
         cur.q.load(Qp, cn, N);
         cur.d.load(dOp, cn, N);
         block_sync();
-        go_in_turn();
         // ---- phase B ----
         f16v y;
         with_planes<LX>(lo_on, [&](auto np) { y = weight_product<np.value>(own, Xt, wrow); });
