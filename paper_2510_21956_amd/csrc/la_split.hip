@@ -213,6 +213,74 @@ __device__ __forceinline__ void go_in_turn()
     if (D <= 64) __builtin_amdgcn_s_setprio(0);
 }
 
+// Of the ascending sweeps: 1/g and g of a chunk of `rows` rows, of which thread t < 32 holds row t's g.
+__device__ __forceinline__ void post_ascending(float *rs, float *gb, __bf16 *fr, int t, int rows, float gn)
+{
+    if (t < CR) {
+        const bool ok = t < rows;
+        const float r = ok ? __builtin_amdgcn_rcpf(gn) : 0.f;
+        rs[t] = r;
+        gb[t] = ok ? gn : 0.f;
+        store_factor<3>(fr, t, r);
+    }
+}
+// Their weight blocks Cm' (rows n, columns i) on or below the diagonal, one a wave w of D / 16.
+template <int MODE, int D, typename LN>
+__device__ __forceinline__ void ascending_weights(__bf16 *Ct, const __bf16 *Vt, const __bf16 *dOt, const float *dl,
+                                                  const float *ik, int w, bool lo_on, const LN &ln, int c, int g)
+{
+    typedef Mode<MODE> MD;
+#pragma unroll 1
+    for (int pidx = w; pidx < 3; pidx += D / 16) {
+        const int ib = pidx ? 1 : 0, nb = pidx == 2 ? 1 : 0;
+        const f4v pa = block_product<D, MD::LV, MD::LV>(Vt, nb, dOt, ib, ln);
+        const float di = dl[ib * 16 + c];
+        const int last = nb == ib ? c : 15;  // last row n at or before row i
+        f4v x;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) x[e] = 4 * g + e > last ? 0.f : pa[e] - di;
+        if constexpr (MD::RN) x *= *reinterpret_cast<const f4v *>(ik + nb * 16 + 4 * g);
+        with_planes<MD::LX>(lo_on, [&](auto n) { store_weights<n.value>(Ct, ib * 16 + c, nb, g, x); });
+    }
+}
+// Of the descending sweeps: thread t < 32 holds row t's g, thread 32 + r dprime of row r.  Returns the row's factor
+// in w (1/g) or u (dprime, over g where the staged rows are not).
+template <bool QT>
+__device__ __forceinline__ float post_descending(float *rs, float *dl, int t, int rows, float gd)
+{
+    const int r = t % CR;
+    float y = r < rows ? (t < CR ? __builtin_amdgcn_rcpf(gd) : gd) : 0.f;
+    (t < CR ? rs : dl)[r] = y;
+    if constexpr (!QT) {
+        const float inv = __shfl(y, r);
+        if (t >= CR) y *= inv;
+    }
+    return y;
+}
+// Weights of block (ib, nb) from its products x (rows i = 4 g + e, column n): of Cm' (cm) or W.
+template <bool QT, bool RN>
+__device__ __forceinline__ f4v descending_weight(f4v x, bool cm, int ib, int nb, const float *rs, const float *dl,
+                                                 const float *iq, const float *kinv, float a, float b, int n, int g)
+{
+    const int row = ib * 16 + 4 * g;
+    const f4v r4 = *reinterpret_cast<const f4v *>(rs + row);
+    f4v iq4 = {1.f, 1.f, 1.f, 1.f};
+    if constexpr (RN) iq4 = *reinterpret_cast<const f4v *>(iq + row);
+    if (cm) {
+        x -= *reinterpret_cast<const f4v *>(dl + row);
+        if constexpr (!QT) x *= r4;
+        if constexpr (RN) x *= iq4;
+    } else {
+        if constexpr (RN) x = (x * kinv[nb * 16 + n]) * iq4;
+        if constexpr (QT) x = a * r4 + b * x;
+        else x = (a + b * x) * r4;
+    }
+    const int first = nb == ib ? n : 0;  // first row i that sees column n
+#pragma unroll
+    for (int e = 0; e < 4; ++e) x[e] = 4 * g + e < first ? 0.f : x[e];
+    return x;
+}
+
 // One tensor's chunk into its tile: normalised (NORM, fp32) and times scale[row], if given, on
 // the way.  1 / |row| goes to inv_out.
 template <bool NORM, bool OP, int L, typename CH>
@@ -757,13 +825,7 @@ __global__ __launch_bounds__(4 * D, 2) void ks_bwd_dq(
     const long c_last = row0 + (row1 - row0 - 1) / CR * CR;
     // 1/g of the chunk starting at c0, whose g is gn, into buffer `par`
     auto post_factors = [&](long c0, float gn, int par) {
-        if (t < CR) {
-            const bool ok = t < (int)(row1 - c0);
-            const float r = ok ? __builtin_amdgcn_rcpf(gn) : 0.f;
-            rsb[par][t] = r;
-            gb[par][t] = ok ? gn : 0.f;
-            store_factor<3>(frs[par], t, r);
-        }
+        post_ascending(rsb[par], gb[par], frs[par], t, (int)(row1 - c0), gn);
     };
 #pragma unroll
     for (int i = 0; i < MD::DEPTH; ++i) {
@@ -824,18 +886,7 @@ __global__ __launch_bounds__(4 * D, 2) void ks_bwd_dq(
         if constexpr (CAUSAL) go_first<D>(w < 3);
         // ---- phase A: weight blocks Cm' (rows n, columns i) ----
         if constexpr (CAUSAL) {
-#pragma unroll 1
-            for (int pidx = w; pidx < 3; pidx += NW) {
-                const int ib = pidx ? 1 : 0, nb = pidx == 2 ? 1 : 0;
-                const f4v pa = block_product<D, LV, LV>(Vt, nb, dOt, ib, ln);
-                const float di = dl[ib * 16 + c];
-                const int last = nb == ib ? c : 15;  // last row n at or before row i
-                f4v x;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) x[e] = 4 * g + e > last ? 0.f : pa[e] - di;
-                if constexpr (MD::RN) x *= *reinterpret_cast<const f4v *>(ik + nb * 16 + 4 * g);
-                with_planes<LX>(lo_on, [&](auto n) { store_weights<n.value>(Ct, ib * 16 + c, nb, g, x); });
-            }
+            ascending_weights<MODE, D>(Ct, Vt, dOt, dl, ik, w, lo_on, ln, c, g);
             cur.v.load(Vp, cn, N);
         }
         f4v fh[2], fl[2];  // rows i, columns r (SWAP), or rows r, columns i
@@ -1021,14 +1072,7 @@ __global__ __launch_bounds__(8 * D, 4) void ks_bwd_dq_halves(
     };
     // 1/g of the chunk starting at c0, whose g is gn, into buffer `par`
     auto post_factors = [&](long c0, float gn, int par) {
-        const int th = ln.local(t);
-        if (th < CR) {
-            const bool ok = th < (int)(row1 - c0);
-            const float r = ok ? __builtin_amdgcn_rcpf(gn) : 0.f;
-            rsb[par][th] = r;
-            gb[par][th] = ok ? gn : 0.f;
-            store_factor<3>(frs[par], th, r);
-        }
+        post_ascending(rsb[par], gb[par], frs[par], ln.local(t), (int)(row1 - c0), gn);
     };
 #pragma unroll
     for (int i = 0; i < DEPTH; ++i) request(sets[i], min(row0 + i * CR, c_last), true, true);
@@ -1078,18 +1122,7 @@ __global__ __launch_bounds__(8 * D, 4) void ks_bwd_dq_halves(
 
         if (half) {
             // ---- phase A: weight blocks Cm' (rows n, columns i) ----
-#pragma unroll 1
-            for (int pidx = w; pidx < 3; pidx += NW) {
-                const int ib = pidx ? 1 : 0, nb = pidx == 2 ? 1 : 0;
-                const f4v pa = block_product<D, L, L>(Vt, nb, dOt, ib, ln);
-                const float di = dl[ib * 16 + c];
-                const int last = nb == ib ? c : 15;  // last row n at or before row i
-                f4v x;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) x[e] = 4 * g + e > last ? 0.f : pa[e] - di;
-                if constexpr (MD::RN) x *= *reinterpret_cast<const f4v *>(ik + nb * 16 + 4 * g);
-                with_planes<LX>(lo_on, [&](auto n) { store_weights<n.value>(Ct, ib * 16 + c, nb, g, x); });
-            }
+            ascending_weights<MODE, D>(Ct, Vt, dOt, dl, ik, w, lo_on, ln, c, g);
             block_sync();
             bf8v df[L];
             if (need_R) {
@@ -1290,12 +1323,7 @@ __global__ __launch_bounds__(8 * D, 4) void ks_bwd_dkv(
     auto post_factors = [&](long c0, const Set &x, int par) {
         if (wv != 0) return;
         const int th = ln.local(t), r = th % CR;
-        float y = r < (int)(row1 - c0) ? (th < CR ? __builtin_amdgcn_rcpf(x.gd) : x.gd) : 0.f;
-        (th < CR ? rsb : dlb)[par][r] = y;
-        if constexpr (!QT) {  // dprime / g
-            const float inv = __shfl(y, r);
-            if (th >= CR) y *= inv;
-        }
+        const float y = post_descending<QT>(rsb[par], dlb[par], th, (int)(row1 - c0), x.gd);
         store_factor<3>((th < CR ? frs : fdl)[par], r, y);
     };
 #pragma unroll
@@ -1344,22 +1372,8 @@ __global__ __launch_bounds__(8 * D, 4) void ks_bwd_dkv(
         for (int pidx = wv; pidx < 6; pidx += 2 * NW) {
             const int q = pidx >= 3 ? pidx - 3 : pidx, ib = q ? 1 : 0, nb = q == 2 ? 1 : 0;
             const bool cm = pidx < 3;
-            const f4v r4 = *reinterpret_cast<const f4v *>(rs + ib * 16 + 4 * g);
             f4v x = block_product<D, L, L>(cm ? dOt : Qt, ib, cm ? Vt : Kt, nb, ln);
-            f4v iq4 = {1.f, 1.f, 1.f, 1.f};
-            if constexpr (MD::RN) iq4 = *reinterpret_cast<const f4v *>(iq + ib * 16 + 4 * g);
-            if (cm) {
-                x -= *reinterpret_cast<const f4v *>(dl + ib * 16 + 4 * g);
-                if constexpr (!QT) x *= r4;
-                if constexpr (MD::RN) x *= iq4;
-            } else {
-                if constexpr (MD::RN) x = (x * kinv[nb * 16 + c]) * iq4;
-                if constexpr (QT) x = a * r4 + b * x;
-                else x = (a + b * x) * r4;
-            }
-            const int first = nb == ib ? c : 0;  // first row i that sees column n
-#pragma unroll
-            for (int e = 0; e < 4; ++e) x[e] = 4 * g + e < first ? 0.f : x[e];
+            x = descending_weight<QT, MD::RN>(x, cm, ib, nb, rs, dl, iq, kinv, a, b, c, g);
             with_planes<LX>(lo_on, [&](auto n) { store_weights<n.value>(cm ? Ct : Wt, nb * 16 + c, ib, g, x); });
         }
         f4v fh[2], fl[2];  // rows n, the wave's columns (SWAP), or the other way round
@@ -1494,12 +1508,8 @@ __global__ __launch_bounds__(4 * D, 2) void ks_bwd_dkv_wide(
     // 1/g and dprime of the chunk starting at c0 into buffer `par`
     auto post_factors = [&](long c0, int par) {
         if (wv != 0) return;
-        const int r = t % CR;
-        float y = r < (int)(row1 - c0) ? (t < CR ? __builtin_amdgcn_rcpf(gd) : gd) : 0.f;
-        (t < CR ? rsb : dlb)[par][r] = y;
-        const float inv = __shfl(y, r);
-        if (t >= CR) y *= inv;
-        store_row_factor<3>((t < CR ? frs : fdl)[par], r, y);
+        const float y = post_descending<false>(rsb[par], dlb[par], t, (int)(row1 - c0), gd);
+        store_row_factor<3>((t < CR ? frs : fdl)[par], t % CR, y);
     };
     auto put = [&](const CH &x, __bf16 *tile) __attribute__((always_inline)) {
         *reinterpret_cast<u4v *>(tile + NTile<D>::quad(CH::row(0), CH::quad(0))) = x.raw[0];
@@ -1535,12 +1545,7 @@ __global__ __launch_bounds__(4 * D, 2) void ks_bwd_dkv_wide(
             const int n = l % 16, g = l / 16;
             const bool cm = pidx < 3;
             f4v x = block16<D>(cm ? dOt : Qt, ib, cm ? Vt : Kt, nb, ln.row16);
-            if (cm) x -= *reinterpret_cast<const f4v *>(dl + ib * 16 + 4 * g);
-            else x = a + b * x;
-            x *= *reinterpret_cast<const f4v *>(rs + ib * 16 + 4 * g);
-            const int first = nb == ib ? n : 0;  // first row i that sees column n
-#pragma unroll
-            for (int e = 0; e < 4; ++e) x[e] = 4 * g + e < first ? 0.f : x[e];
+            x = descending_weight<false, false>(x, cm, ib, nb, rs, dl, nullptr, nullptr, a, b, n, g);
             with_planes<LX>(lo_on, [&](auto np) { put_weights<np.value>(cm ? Ct : Wt, nb * 16 + n, ib, g, x); });
         }
         f16v f;  // rows = the wave's columns, columns n
