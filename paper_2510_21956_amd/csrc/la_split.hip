@@ -31,19 +31,22 @@
 // exact, the weight blocks carry the 1/g, and the wave's own 32 x 16 operand of R's update is
 // scaled in registers.
 //
-// What bounds them (counters of the masked kernels): issue.  A wave issues one instruction every 5.3
-// clocks, two waves of a SIMD together one vector instruction every 2.9; with two waves a SIMD and a
+// What bounds them (counters of the masked kernels): issue and traffic.  A wave issues one instruction every
+// 5.3 clocks, two waves of a SIMD together one vector instruction every 2.9; with two waves a SIMD and a
 // chunk's phases in turn between barriers, the matrix pipe, the vector ALU (splitting inputs and states)
-// and LDS reads take 30 to 45 % of the clocks each in fp32, 14 to 35 % in bf16, where waits make up the
-// rest (barriers, and memory with 40 KB in flight per CU).  Four waves a SIMD in the descending sweep,
-// wider columns for bf16 at D = 128, and issue order (go_first) are what moved them.  Forward /
-// ascending / descending sweep, us, before and now:
-//   fp32, D = 64, 64 slices of 4096 rows         70 / 92 / 112 -> 70 / 94 / 99
-//   fp32, D = 128, 64 slices of 1000             47 / 60 / 74  -> 47 / 60 / 70
-//   bf16, D = 64, 36 slices of 5003              28 / 33 / 38  -> 28 / 33 / 30
-//   bf16, D = 128, 128 slices of 2048            65 / 88 / 110 -> 65 / 88 / 98
-//   bf16 normalised, the same                    105 / 152 / 195 -> 104 / 150 / 185
-//   fp32, D = 16, one slice of 256               12.6 / 14.7 / 17.6 -> 12.6 / 11.5 / 13.2
+// and LDS reads take 25 to 45 % of the clocks each in fp32, 14 to 38 % in bf16, where waits make up the
+// rest (barriers, and memory with 40 KB in flight per CU); at D = 64 in fp32 and in bf16 the sweeps move their own
+// traffic at 4.2 to 5.0 TB/s, where a copy reaches 5.0.  Four waves a SIMD in the descending sweep and wider
+// columns for bf16 at D = 128 are what moved them.  Forward / ascending / descending sweep, us, on waves that
+// hold both states of a sweep and now (one card, medians of five runs each; cards differ by up to 8 %):
+//   fp32, D = 64, 64 slices of 4096 rows         72 / 95 / 117 -> 74 / 95 / 104
+//   fp32, D = 128, 64 slices of 1000             51 / 64 / 80 -> 50 / 64 / 74
+//   bf16, D = 64, 36 slices of 5003              28 / 34 / 39 -> 28 / 33 / 31
+//   bf16, D = 128, 128 slices of 2048            66 / 89 / 112 -> 66 / 88 / 104
+//   bf16, D = 128, 16 slices of 131072           498 / 683 / 918 -> 504 / 690 / 843
+//   bf16 normalised, D = 128, 128 of 2048        106 / 153 / 196 -> 108 / 156 / 194
+//   fp32, D = 16, one slice of 256               12.6 / 14.6 / 17.5 -> 12.5 / 11.4 / 13.0
+//   fp32 without the mask, D = 64, 64 of 16384   96 / 242 / 205 -> 96 / 232 / 205
 #include "la_wave32.h"
 
 namespace la {
@@ -198,10 +201,9 @@ __device__ __forceinline__ void factor_frag(bf8v (&o)[3], const float *r, int g)
 }
 
 // The waves that form weight blocks are the last to reach the barrier behind them: between the two calls
-// their instructions go first.  Forward / ascending / descending sweep, us, without and with: fp32, D = 64, 64
-// slices of 4096 rows 68.5 / 91.2 / 95.0, 67.2 / 90.8 / 94.2; bf16, 36 of 5003 27.9 / 33.2 / 30.6, 27.6 / 32.8 /
-// 29.9; normalised 39.4 / 54.3 / 62.7, 38.1 / 53.2 / 61.4.  At D = 128 it moves nothing (fp32, 64 of 1000 47.0 /
-// 59.9 / 68.6, 47.1 / 60.2 / 69.2; bf16, 128 of 2048 65.1 / 87.0 / 102.1, 65.1 / 86.9 / 101.8).
+// their instructions go first.  Time of the forward / ascending / descending sweep with it: fp32, D = 64 (64 slices
+// of 4096 rows) - 2 / - 0.5 / - 1 %; bf16 (36 of 5003) - 1 / - 1 / - 2 %; normalised - 3 / - 2 / - 2 %; D = 32, bf16 (64 of
+// 4096), descending - 5 %.  At D = 128 it moves nothing (fp32, 64 of 1000 0 / + 0.5 / + 1 %; bf16, 128 of 2048 0 / 0 / 0).
 template <int D>
 __device__ __forceinline__ void go_first(bool on)
 {
@@ -875,10 +877,11 @@ __global__ __launch_bounds__(4 * D, 2) void ks_bwd_dq(
         block_sync();
         const long cn = min(c0 + MD::DEPTH * CR, c_last);
         // Under a branch the load stays here; as a plain load the compiler moves it into post_factors, behind this
-        // chunk's stores, where the first wave waits for both.  Ascending sweep, us, plain and under a branch: fp32
-        // without the mask, D = 64 (64 x 16384) 236.3, 228.8, D = 32 (64 x 8192) 55.2, 50.8; bf16 with it, D = 64
-        // (36 x 5003) 32.8, 32.3; bf16 without, two chunks ahead, D = 64 (64 x 16384) 108.8, 112.5.
-        if ((!F32 && !CAUSAL) || w == 0) cur.g = load_row_float(Gp, cn, N, t % CR);
+        // chunk's stores, where the first wave waits for both.  Time of the sweep under a branch: fp32 without the
+        // mask - 3 % (D = 64, 64 x 16384) and - 8 % (D = 32, 64 x 8192), bf16 with it - 1.5 % (D = 64, 36 x 5003); bf16
+        // without, which requests two chunks ahead, + 3 % (64 x 16384); fp32 with it, where the load stays put
+        // either way, no less, and at D = 128 normalised a register goes to scratch.
+        if (F32 == CAUSAL || w == 0) cur.g = load_row_float(Gp, cn, N, t % CR);
         cur.d.load(dOp, cn, N);
         cur.o.load(Op, cn, N);
         if constexpr (!CAUSAL) cur.q.load(Qp, cn, N);
@@ -982,7 +985,7 @@ __global__ __launch_bounds__(4 * D, 2) void ks_bwd_dq(
 //   R += (Q/g)_c^T dO_c,  u += sum dprime (q/g),  w += sum dO / g
 // Half the waves make dQ and hold the state transposed (rows j, columns r: the product contracts over j);
 // the others form the weight blocks and hold R.  Only at D = 32 (and 16), where a chunk's latencies are
-// most of its time: one slice of 256 rows, D = 16, 14.7 -> 11.6 us.  Beyond, waves that hold both states are
+// most of its time: one slice of 256 rows, D = 16, 14.6 -> 11.4 us.  Beyond, waves that hold both states are
 // as fast or faster: fp32, 64 slices of 4096 rows, D = 64 88 us against 92 in halves; bf16, 36 of 5003 33.2
 // against 35.2, 128 of 2048, D = 128 86 against 94.
 // ---------------------------------------------------------------------------
@@ -1221,12 +1224,9 @@ __global__ __launch_bounds__(8 * D, 4) void ks_bwd_dq_halves(
 //   then R += (Q/g)_c^T dO_c, u += sum dprime (q/g), w += sum dO / g.
 // R is held twice.  2 D/16 waves: half make dK and hold R^T (rows j, columns r) and u, the others make dV
 // and hold R (rows r, columns j) and w; both run the same code on exchanged tiles, 16 columns a wave.
-// Four waves a SIMD instead of two that hold both states: a SIMD issues a wave's instructions one every
-// five clocks, two waves' 2.9 and four waves' closer still, and the kernel is bound by what its waves
-// issue and wait for in turn (vector ALU 30 -> 37 %, LDS 38 -> 46 %, matrix pipe 31 -> 38 % of the clocks, fp32 D = 64).
-// Half the registers a wave have to do (TIGHT).  Descending sweep, us, before and now: fp32, 64 slices of 4096
-// rows, D = 64 104 -> 94; of 1000 rows, D = 128 70 -> 67; bf16, 36 of 5003, D = 64 38.6 -> 30.0; normalised, 128 of
-// 2048, D = 128 190 -> 182; one slice of 256 rows, D = 16 17.7 -> 13.3.
+// Four waves a SIMD instead of two that hold both states: more of what the waves issue and wait for in turn
+// overlaps (fp32, D = 64: vector ALU 30 -> 38 %, LDS 38 -> 46 %, matrix pipe 31 -> 38 % of the clocks; times at the
+// top).  Half the registers a wave have to do (TIGHT).
 // LD > D: xflags & 2 (dK), & 4 (dV) mark the second of the two launches that build them up.
 // ---------------------------------------------------------------------------
 template <int MODE, int D, int LD>
@@ -1438,8 +1438,8 @@ __global__ __launch_bounds__(8 * D, 4) void ks_bwd_dkv(
 
 // ---------------------------------------------------------------------------
 // The same for bf16 at D = 128: waves of 32 columns (la_wave32.h), half of them for dK, half for dV, on
-// natural tiles; two chunks requested ahead.  Half the LDS reads of 16 columns a wave (LDS 33 -> 26 % of the
-// clocks); waits are what is left (43 % of a wave's life).  110 -> 98 us, 128 slices of 2048 rows.
+// natural tiles; two chunks requested ahead.  Half the LDS reads of 16 columns a wave (LDS 33 -> 25 % of the
+// clocks); waits are what is left (43 % of a wave's life).
 // ---------------------------------------------------------------------------
 template <int D, int LD>
 __global__ __launch_bounds__(4 * D, 2) void ks_bwd_dkv_wide(
@@ -1736,8 +1736,8 @@ constexpr auto ks_bwd_dq_masked()
 }
 
 // The descending masked sweep: 32 columns a wave for bf16 at D = 128, whose tiles and states leave room for
-// it (us, three runs each: 94 to 98 against 105 to 107 with 16 columns and four waves a SIMD, 128 slices of
-// 2048 rows).  fp32 at D = 128 is within 2 % either way; at D = 64 the four waves are faster (bf16, 36 slices
+// it (us, 32 columns and 16 with four waves a SIMD, medians of six runs: 128 slices of 2048 rows 109 and 118, 16
+// of 131072 825 and 911, 64 of 500 31.0 and 32.5; a step at head size 256, 64 of 4096, 1596 and 1609).  fp32 at D = 128 is within 2 % either way; at D = 64 the four waves are faster (bf16, 36 slices
 // of 5003 rows 30.0 against 34.2).
 template <int MODE, int D, int LD>
 constexpr auto ks_bwd_dkv_masked()

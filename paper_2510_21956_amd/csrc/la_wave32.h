@@ -163,8 +163,8 @@ __device__ __forceinline__ f16v state_rows(const f16v (&st)[D / 32], const __bf1
 // st[k] += A^T B over the chunk rows: A = columns 32 k of tile `at`, B the wave's own columns (b[kr], LB
 // planes).  The products meet on an accumulator of their own and are added once, rounded: an instruction
 // that adds onto a long sum cuts off what lies below its last bit, and there are two a chunk.  A block's
-// addition runs under the next block's instructions (descending sweep, us, chained onto the state / added after
-// each block / this: 128 slices of 2048 rows 101.4, 109.0, 105.5, 16 of 131072 795, 806, 788).
+// addition runs under the next block's instructions: + 4 % of the descending sweep (128 slices of 2048 rows) and
+// - 1 % (16 of 131072) against instructions chained onto the state, + 8 % and + 1 % where each block waits for its own.
 template <int D, int LB>
 __device__ __forceinline__ void update_rows(f16v (&st)[D / 32], const __bf16 *at, int upd, const bf8v (&b)[2][LB])
 {
