@@ -234,6 +234,7 @@ la_status split_prefill(const Problem &pr, const Plan &pl, const void *K, const 
 // saved (may be null): the hand-over buffers of the four passes one after another, pl.saved_bytes each, and
 // behind them kWitnessWords words a slice that tell the backward pass whose sums they are.
 constexpr int kWitnessWords = 256;
+// Where more is handed over only as far as it is no larger than a tensor (make_plan).
 constexpr size_t kSplitSavedMost = (size_t)96 << 20;
 inline size_t split_saved_bytes(const Plan &pl128, int BH)
 {

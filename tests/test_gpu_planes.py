@@ -172,6 +172,43 @@ def test_sums_at_head_size_256_are_used_only_where_they_were_written(la, dtype, 
     assert torch.isnan(got[0][0, 0].float()).any()
 
 
+@pytest.mark.parametrize("causal", [True, False])
+def test_hand_over_at_head_size_256_in_a_graph(la, causal):
+    """The pair captured once: every replay, on new inputs and with eager calls in between, gives the eager
+    pair's bits; a replay of the backward pass alone on new inputs forms its own sums."""
+    B, H, N, D = 1, 2, 700, 256
+    draws = [upload_case(B, H, N, D, "bf16", 6800 + k, [0])[0] for k in range(3)]
+    dev = {n: x.clone() for n, x in draws[0].items()}
+    O, G, saved = gpu_forward_save(la, dev, 1.0, 0.5, causal)
+    ws = [scratch(la.la_workspace_bytes(B, H, N, D, la.LA_BF16, causal, w), "cuda") for w in (0, 1)]
+    grads = [torch.empty_like(O) for _ in range(3)]
+
+    def forward():
+        la.la_forward_save(dev["Q"], dev["K"], dev["V"], O, G, 1.0, 0.5, causal, ws[0], saved)
+
+    def backward():
+        la.la_backward_saved(dev["Q"], dev["K"], dev["V"], O, G, dev["dO"], *grads, 1.0, 0.5, causal, ws[1], saved)
+    fwd, bwd = torch.cuda.CUDAGraph(), torch.cuda.CUDAGraph()
+    for graph, call in ((fwd, forward), (bwd, backward)):
+        with torch.cuda.graph(graph):
+            call()
+    for k in (1, 2, 0, 1):
+        for n in dev:
+            dev[n].copy_(draws[k][n])
+        Oe, Ge, se = gpu_forward_save(la, dev, 1.0, 0.5, causal)
+        own = gpu_backward(la, dev, Oe, Ge, 1.0, 0.5, causal)
+        want = gpu_backward_saved(la, dev, Oe, Ge, se, 1.0, 0.5, causal)
+        O.copy_(Oe)
+        G.copy_(Ge)
+        bwd.replay()
+        assert all(torch.equal(x, y) for x, y in zip(grads, own)), (causal, k)
+        O.zero_()
+        fwd.replay()
+        bwd.replay()
+        assert torch.equal(O, Oe) and torch.equal(G, Ge)
+        assert all(torch.equal(x, y) for x, y in zip(grads, want)), (causal, k)
+
+
 def test_hand_over_buffer_that_overlaps_another_at_head_size_256(la):
     """Left unused by both calls, as any buffer was before there was a hand-over at this head size."""
     B, H, N, D = 1, 2, 700, 256
