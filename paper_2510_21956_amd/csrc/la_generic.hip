@@ -263,6 +263,69 @@ __global__ __launch_bounds__(NT) void k_scan_slots(float *__restrict__ ws, int n
     if (mode == 2) p[0] = __builtin_isfinite(run) ? run + lost : run;
 }
 
+// The same for many slots: PARTS groups of 32 lanes take RUN slots each, all of one read at once, and add what the
+// groups before them hold.  One memory round trip per PARTS * RUN slots instead of one per 16: a step on one slice
+// of 30000 rows, bf16, D = 64, in 469 segments 135 -> 46 us, in 235 91 -> 48; fp32, D = 128, in 235 180 -> 136.
+template <int PARTS>
+__global__ __launch_bounds__(32 * PARTS) void k_scan_parts(float *__restrict__ ws, int nseg, size_t slot_floats,
+                                                           int off, int len, int mode, int lo, int hi,
+                                                           const int *__restrict__ skip)
+{
+    constexpr int RUN = 16;
+    __shared__ float sums[PARTS][32], rest[PARTS][32];
+    if (skip && skip[blockIdx.x]) return;
+    const int l = threadIdx.x % 32, part = threadIdx.x / 32, e = blockIdx.y * 32 + l;
+    const bool on = e < len;
+    float *p = ws + (size_t)blockIdx.x * nseg * slot_floats + off + (on ? e : 0);
+    const int n = hi - lo + 1;
+    float before = 0.f, lost = 0.f;  // the slots before this round; what mode 2 lost
+    const auto add = [&](float &run, float &less, float x) __attribute__((always_inline)) {
+        const float sum = run + x, y = sum - run;
+        less += (run - (sum - y)) + (x - y);
+        run = sum;
+    };
+    for (int i0 = 0; i0 < n; i0 += PARTS * RUN) {
+        const int first = i0 + part * RUN;
+        float x[RUN];
+#pragma unroll
+        for (int i = 0; i < RUN; ++i) {
+            const int k = first + i;
+            x[i] = on && k < n ? p[(size_t)(mode == 1 ? hi - k : lo + k) * slot_floats] : 0.f;
+        }
+        float run = 0.f, less = 0.f;
+        if (mode == 2) {
+#pragma unroll
+            for (int i = 0; i < RUN; ++i) add(run, less, x[i]);
+            rest[part][l] = less;
+        } else {
+#pragma unroll
+            for (int i = 0; i < RUN; ++i) x[i] = run += x[i];
+        }
+        sums[part][l] = run;
+        block_sync();
+        float base = before;
+#pragma unroll
+        for (int q = 0; q < PARTS; ++q) {
+            if (q == part) base = before;
+            if (mode == 2) {
+                add(before, lost, sums[q][l]);
+                lost += rest[q][l];
+            } else {
+                before += sums[q][l];
+            }
+        }
+        if (mode != 2) {
+#pragma unroll
+            for (int i = 0; i < RUN; ++i) {
+                const int k = first + i;
+                if (on && k < n && k > 0) p[(size_t)(mode == 1 ? hi - k : lo + k) * slot_floats] = base + x[i];
+            }
+        }
+        block_sync();
+    }
+    if (mode == 2 && part == 0 && on) p[0] = __builtin_isfinite(before) ? before + lost : before;
+}
+
 // ---------------------------------------------------------------------------
 // Phase 3 (forward): Eq. fglast / div chunk by chunk.
 //   f = tril(a + b Q_c K_c^T) V_c + a 1 p^T + b Q_c S ;  g = rowsum(tril) + a n + b Q_c z
@@ -617,9 +680,15 @@ void launch_scan_slots(float *ws, int BH, int nseg, size_t slot_floats, int off,
 {
     // a running sum over a single slot changes nothing; the total of a single slot 0 neither
     if (hi < lo || (hi == lo && (mode != 2 || lo == 0))) return;
-    auto *kernel = hi - lo < 8 ? k_scan_slots<8> : k_scan_slots<16>;
-    kernel<<<dim3(BH, (len + NT - 1) / NT), dim3(NT), 0, st>>>(ws, nseg, slot_floats, off, len, mode,
-                                                               lo, hi, skip);
+    const int n = hi - lo + 1;
+    if (n <= 16) {
+        (n <= 8 ? k_scan_slots<8> : k_scan_slots<16>)<<<dim3(BH, (len + NT - 1) / NT), dim3(NT), 0, st>>>(
+            ws, nseg, slot_floats, off, len, mode, lo, hi, skip);
+    } else {
+        const dim3 grid(BH, (len + 31) / 32);
+        if (n <= 128) k_scan_parts<8><<<grid, dim3(256), 0, st>>>(ws, nseg, slot_floats, off, len, mode, lo, hi, skip);
+        else k_scan_parts<32><<<grid, dim3(1024), 0, st>>>(ws, nseg, slot_floats, off, len, mode, lo, hi, skip);
+    }
 }
 
 namespace {
