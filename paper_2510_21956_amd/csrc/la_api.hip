@@ -18,47 +18,56 @@ static size_t round_up(size_t x, size_t m) { return (x + m - 1) / m * m; }
 
 static bool supported_d(int D) { return D == 16 || D == 32 || D == 64 || D == 128 || D == 256; }
 
-// Segment length.  A workgroup walks its segment serially, so a launch is balanced when slices
-// x segments is about 256 x the workgroups that a compute unit holds at once: every compute
-// unit then gets the same number of equally long segments in a single round.  The sweeps of
-// the backward pass set that number (registers and LDS): one at D = 128 and two at D = 64
-// (measured at D = 64, bf16, 36 slices of 5003 rows: 127 us a step for one, 108 for two, 123
-// for three; fp32, 64 slices of 4096: 336, 290, 349), four at D = 32.  The same without the mask
-// (us a step for one, two, three: D = 128, fp32, 4 slices of 10^5 rows 676, 714, 745; bf16, 32 of
-// 8192 225, 244, 247, and the forward pass alone 69, 76, 80, the sums for a prompt alone 17, 19, 19
-// (32 of 3001); D = 64, bf16, 64 of 16384 412, 362, 371, 80 of 3000 120, 105, 121; D = 32, bf16,
-// 16 of 131072 599, 407, 358, and 350 for four).
-// At D = 64 without the mask the nearest number may leave some compute units a segment more than
-// others where one segment more a slice would not: 192 slices of 1000 rows, three segments of 384
-// rows (three a unit at most, 576 in all) or four of 256 (768): 163 and 151 us a step in fp32, 96
-// and 91 in bf16.
-// Segments are also kept long enough that the D x D state a segment hands over stays small
-// next to the rows it covers (a sixth of their bytes at the shortest: short sequences in few
-// slices would otherwise leave most of the chip idle).  la_debug_override can force a length
-// (rounded up to 64).
-Plan make_plan(int B, int H, int N, int D, la_dtype dt, int causal, int is_backward, bool pad16)
+// Rows of the segments a slice is cut into, a multiple of the shortest a segment may be (64 in bf16, whose
+// kernels request two chunks ahead, 32 in fp32).
+//
+// A workgroup walks its segment serially, so what a launch takes is the rows of the compute unit that has most.
+// Compute units hold `resident` workgroups at once (registers and LDS of the backward sweeps: one at D = 128,
+// two at D = 64, four at D <= 32).  Of the cuts that give every unit k segments, k = 1 .. 3 resident, and of no cut
+// at all, the one is taken that costs least in rows:
+//   (segment) x (2 (segments of that unit) + (its rounds)): segments that run together on a unit hide some of each
+//   other's latency; 384 for a round after the first; 2 `kernels` for a cut, whose segments' states have kernels of
+//   their own.
+// Short sequences in few slices are cut down to the shortest segments (a step, us, with 192 rows a segment at least,
+// 128 at D <= 64, and now: fp32, D = 128, 4 slices of 500 rows 157 and 48; bf16, D = 64, 1 of 30000 87 and 46; fp32,
+// D = 32, 8 of 300 50 and 27), and a cut never leaves a few workgroups to a round of their own (fp32, D = 64, 60
+// slices of 4000 rows: 322 in nine segments, 540 workgroups on 512 places, 261 in eight).  Over 600 shapes of 1 to
+// 190 slices and 60 to 30000 rows, masked and not, the rule is within 1 % of the best length on the average; what
+// it replaces took 1.1 to 1.4 times as long.
+static long segment_rows(long BH, int N, int D, la_dtype dt, int causal, Cut cut)
+{
+    const long step = dt == LA_F32 ? 32 : 64, resident = D >= 128 ? 1 : D == 64 ? 2 : 4;
+    const long kernels = dt == LA_F32 ? (D >= 128 ? 64 : 32) : (D >= 128 || !causal ? 192 : 64);
+    const long most = cut.min_rows ? max(N / cut.min_rows, 1) : (N + step - 1) / step;
+    const auto cost = [&](long rows) {
+        const long load = (BH * ((N + rows - 1) / rows) + 255) / 256, rounds = (load + resident - 1) / resident;
+        return rows * (2 * load + rounds) + 384 * (rounds - 1) + (rows < N ? 2 * kernels : 0);
+    };
+    long best_rows = (long)round_up((size_t)N, step), best = cost((long)round_up((size_t)N, 32));
+    for (long k = 1; k <= cut.rounds * resident; ++k) {
+        const long want = min(256 * k / BH, most);
+        if (want <= 1) continue;
+        const long rows = (long)round_up((size_t)((N + want - 1) / want), step), c = cost(rows);
+        if (c < best) {
+            best = c;
+            best_rows = rows;
+        }
+        if (want == most) break;
+    }
+    return best_rows;
+}
+
+// la_debug_override can force a length (rounded up to 64).
+Plan make_plan(int B, int H, int N, int D, la_dtype dt, int causal, int is_backward, bool pad16, Cut cut)
 {
     Plan p;
     const long BH = (long)B * H;
-    const int min_len = (D >= 128) ? 192 : 128;
-    const long resident = D == 256 ? 1 : D <= 32 ? 4 : D == 64 ? 2 : 1;
-    const long target = 256 * resident;
-    long want = (target + BH / 2) / BH;  // nearest number of segments per slice
-    if (!causal && D == 64 && BH * (want + 1) <= 1024) {
-        // rows of the compute unit with the most segments
-        const auto load = [&](long n) {
-            return (BH * n + 255) / 256 * (long)round_up((size_t)((N + n - 1) / n), 64);
-        };
-        if (want >= 1 && 10 * load(want + 1) <= 9 * load(want)) ++want;
-    }
-    long max_by_len = N / min_len;
-    if (max_by_len < 1) max_by_len = 1;
-    if (want > max_by_len) want = max_by_len;
-    if (want < 1) want = 1;
-    long seg_len = (N + want - 1) / want;
+    // D = 256: the plan itself is that of the token-serial kernels; the passes of the D = 128 kernels have
+    // theirs (below), whose segments hand over four states each and are kept to one a compute unit
+    const Cut own = D == 256 ? kCoarse : cut;
+    long seg_len = segment_rows(BH, N, D, dt, causal, own);
     const int forced = g_seg_len_override.load(std::memory_order_relaxed);
-    if (forced > 0) seg_len = forced;
-    seg_len = (long)round_up((size_t)seg_len, 64);
+    if (forced > 0) seg_len = (long)round_up((size_t)forced, 64);
     p.seg_len = (int)seg_len;
     p.nseg = (int)((N + seg_len - 1) / seg_len);
     p.map = SegMap{p.seg_len, lo_rows_of(N), 0};
@@ -88,17 +97,20 @@ Plan make_plan(int B, int H, int N, int D, la_dtype dt, int causal, int is_backw
     // D = 256 runs as passes of the D = 128 kernels (split_forward / split_backward): their
     // workspace, plus what the forward passes hand to each other
     if (D == 256) {
-        const Plan h = make_plan(B, H, N, 128, dt, causal, is_backward);
+        const Plan h = block_plan(B, H, N, dt, causal, is_backward, cut);
         const size_t need =
             split_scratch(h, (int)BH, N, dt, is_backward).total_floats * sizeof(float);
         if (need > p.total_bytes) p.total_bytes = need;
-        // The hand-over, 264 KB a segment, is optional here.  One segment with the mask hands nothing over: 256
-        // bytes that stay unused.  Slices cut into several segments have 340 in all at most, 90 MB.  What
+        // The hand-over, 264 KB a segment, is optional here; its size is that of the cut that is nearest to one
+        // workgroup a unit, of 192 rows a segment at least, or of the plan's where that is finer.  One segment with the
+        // mask hands nothing over: 256 bytes that stay unused.  Slices cut into several segments have 340 in all at most, 90 MB.  What
         // takes more than kSplitSavedMost, hundreds or thousands of short slices, is handed over only where it is
         // no larger than one of the tensors (8000 slices of 40 rows without the mask, bf16: 2.1 GB of sums
         // next to tensors of 164 MB).
-        const size_t tensor = (size_t)BH * N * D * (dt == LA_F32 ? 4 : 2), bytes = split_saved_bytes(h, (int)BH);
-        p.saved_bytes = causal && h.nseg == 1 ? 256 : bytes <= kSplitSavedMost || bytes <= tensor ? bytes : 0;
+        const long nseg = max((long)h.nseg, max(min((256 + BH / 2) / BH, (long)N / 192), 1L));
+        const size_t tensor = (size_t)BH * N * D * (dt == LA_F32 ? 4 : 2);
+        const size_t bytes = split_saved_bytes(h, (int)BH) + 4 * (nseg - h.nseg) * (h.saved_bytes / h.nseg);
+        p.saved_bytes = causal && nseg == 1 ? 256 : bytes <= kSplitSavedMost || bytes <= tensor ? bytes : 0;
     }
     return p;
 }
@@ -107,11 +119,11 @@ Plan make_plan(int B, int H, int N, int D, la_dtype dt, int causal, int is_backw
 // kernels of D = 128, or (test hook) on the token-serial kernels.  dK == nullptr: dQ only.
 static la_status forward_256(const Problem &pr, const Plan &pl, int B, int H, const void *Q,
                              const void *K, const void *V, void *O, float *G, float *ws, float *saved,
-                             hipStream_t st, Tracer &tc)
+                             hipStream_t st, Tracer &tc, Cut cut)
 {
     if (g_force_generic.load(std::memory_order_relaxed))
         return wide_forward(pr, pl, Q, K, V, O, G, ws, st, tc);
-    const Plan h = make_plan(B, H, pr.N, 128, pr.dt, pr.causal, 0);
+    const Plan h = block_plan(B, H, pr.N, pr.dt, pr.causal, 0, cut);
     return split_forward(pr, h, Q, K, V, O, G, ws, saved, st, tc);
 }
 static la_status backward_256(const Problem &pr, const Plan &pl, int B, int H, const void *Q,
@@ -121,7 +133,7 @@ static la_status backward_256(const Problem &pr, const Plan &pl, int B, int H, c
 {
     if (g_force_generic.load(std::memory_order_relaxed))
         return wide_backward(pr, pl, Q, K, V, O, G, dO, dQ, dK, dV, ws, st, tc);
-    const Plan h = make_plan(B, H, pr.N, 128, pr.dt, pr.causal, 1);
+    const Plan h = block_plan(B, H, pr.N, pr.dt, pr.causal, 1);
     return split_backward(pr, h, Q, K, V, O, G, dO, dQ, dK, dV, ws, saved, st, tc);
 }
 
@@ -286,7 +298,7 @@ static la_status forward_impl(const void *Q, const void *K, const void *V, void 
                               int B, int H, int N, int D, float a, float b, int causal,
                               la_dtype dt, void *workspace, size_t workspace_bytes, bool save,
                               void *saved, size_t saved_bytes, void *hip_stream, la_trace *trace,
-                              int norm_qk = 0, bool pad16 = true)
+                              int norm_qk = 0, bool pad16 = true, la::Cut cut = la::Cut())
 {
     la_status s = la::check_shape(B, H, N, D, dt);
     if (s != LA_OK) return s;
@@ -295,7 +307,7 @@ static la_status forward_impl(const void *Q, const void *K, const void *V, void 
     if (!la::aligned16(Q) || !la::aligned16(K) || !la::aligned16(V) || !la::aligned16(O) ||
         !la::aligned16(G))
         return LA_ERR_ALIGN;
-    la::Plan pl = la::make_plan(B, H, N, D, dt, causal, 0, pad16);
+    la::Plan pl = la::make_plan(B, H, N, D, dt, causal, 0, pad16, cut);
     if (!la::grid_ok(B, H, pl)) return LA_ERR_SHAPE;
     if (!workspace || workspace_bytes < pl.total_bytes || (((uintptr_t)workspace) & 255u))
         return LA_ERR_WORKSPACE;
@@ -327,7 +339,7 @@ static la_status forward_impl(const void *Q, const void *K, const void *V, void 
                                   (hipStream_t)hip_stream, tc);
     if (D == 256)
         return la::forward_256(pr, pl, B, H, Q, K, V, O, G, (float *)workspace, sv,
-                               (hipStream_t)hip_stream, tc);
+                               (hipStream_t)hip_stream, tc, cut);
     return la::generic_forward(pr, pl, Q, K, V, O, G, (float *)workspace,
                                (hipStream_t)hip_stream, tc);
 }
@@ -393,7 +405,7 @@ static la_status backward_impl(const void *Q, const void *K, const void *V, cons
                                         nullptr, st, tc)
             : D == 256
                 ? la::forward_256(pr, pf, B, H, Q, K, V, o2, g2, (float *)(wsb + rc.fwd_ws_off), nullptr,
-                                  st, tc)
+                                  st, tc, la::Cut())
                 : la::generic_forward(pr, pf, Q, K, V, o2, g2, (float *)(wsb + rc.fwd_ws_off), st,
                                       tc);
         if (s != LA_OK) return s;
@@ -444,12 +456,14 @@ la_status la_forward_static(const void *Q, const void *K, const void *V, void *O
     if (!Q || !K || !V || !O) return LA_ERR_NULL;
     la::Plan pl = la::make_plan(B, H, N, D, dt, causal, 0);
     if (!la::grid_ok(B, H, pl)) return LA_ERR_SHAPE;
-    // Head size 16 in thousands of slices: the states of the padded tiles, four times the size,
-    // may not fit where those of the plain-ALU kernels do.
+    // Where the states of many segments exceed the scratch, fewer may fit.  Head size 16 in thousands of slices:
+    // the states of the padded tiles, four times the size, may not fit where those of the plain-ALU kernels do.
     bool pad16 = true;
-    if (D == 16 && pl.total_bytes > (size_t)LA_STATIC_SCRATCH_BYTES) {
-        pad16 = false;
-        pl = la::make_plan(B, H, N, D, dt, causal, 0, pad16);
+    la::Cut cut;
+    if (pl.total_bytes > (size_t)LA_STATIC_SCRATCH_BYTES) {
+        pad16 = D != 16;
+        cut = la::kCoarse;
+        pl = la::make_plan(B, H, N, D, dt, causal, 0, pad16, cut);
     }
     if (pl.total_bytes > (size_t)LA_STATIC_SCRATCH_BYTES) return LA_ERR_WORKSPACE;
     void *ws = static_scratch();
@@ -457,7 +471,7 @@ la_status la_forward_static(const void *Q, const void *K, const void *V, void *O
     // nothing in the forward workspace has to start at zero: every slot that is read has
     // been written by this call's own kernels first
     return forward_impl(Q, K, V, O, G, B, H, N, D, a, b, causal, dt, ws, LA_STATIC_SCRATCH_BYTES,
-                        false, nullptr, 0, hip_stream, nullptr, 0, pad16);
+                        false, nullptr, 0, hip_stream, nullptr, 0, pad16, cut);
 }
 
 la_status la_backward_ab(const void *Q, const void *K, const void *V, const void *O,
@@ -604,7 +618,7 @@ la_status la_decode_prefill(const void *K, const void *V, float *state, size_t s
     la::Problem pr{B * H, N, D, 1.f, 0.f, 0, dt};
     hipStream_t st = (hipStream_t)hip_stream;
     if (D == 256)
-        return la::split_prefill(pr, la::make_plan(B, H, N, 128, dt, 0, 0), K, V,
+        return la::split_prefill(pr, la::block_plan(B, H, N, dt, 0, 0), K, V,
                                  (float *)workspace, state, accumulate ? 1 : 0, st);
     s = la::use_fast(pr) ? la::planes_totals(pr, pl, D, K, V, (float *)workspace, st)
                          : la::generic_kv_totals(pr, pl, K, V, (float *)workspace, st);

@@ -106,9 +106,20 @@ struct Plan {
     size_t saved_bytes;
 };
 
+// How finely sequences are cut (segment_rows in la_api.hip): min_rows a segment at least (0: the shortest there
+// are), `rounds` times as many segments at most as the compute units hold at once.
+struct Cut {
+    int min_rows = 0, rounds = 3;
+};
+constexpr Cut kCoarse{192, 1};
 // pad16: D = 16 on the tiles of D = 32 (else on the plain-ALU kernels).
 Plan make_plan(int B, int H, int N, int D, la_dtype dt, int causal, int is_backward,
-               bool pad16 = true);
+               bool pad16 = true, Cut cut = Cut());
+// The plan of the D = 128 passes of a D = 256 problem.
+inline Plan block_plan(int B, int H, int N, la_dtype dt, int causal, int is_backward, Cut cut = Cut())
+{
+    return make_plan(B, H, N, 128, dt, causal, is_backward, true, Cut{cut.min_rows, 1});
+}
 
 struct Problem {
     int BH, N, D;

@@ -103,6 +103,7 @@ la_status split_forward(const Problem &pr, const Plan &pl, const void *Q, const 
     Problem p = pr;
     p.D = 128;
     Tracer quiet(nullptr, st);  // the caller's trace gets one mark per pass, not per kernel
+    if (pr.causal && pl.nseg == 1) saved = nullptr;  // no segment starts from another's sums
     for (int j = 0; j < 2; ++j) {
         const void *Vj = col_block(V, j, pr.dt);
         void *Oj = col_block(O, j, pr.dt);
@@ -131,6 +132,7 @@ la_status split_backward(const Problem &pr, const Plan &pl, const void *Q, const
     Problem p = pr;
     p.D = 128;
     Tracer quiet(nullptr, st);  // the caller's trace gets one mark per pass, not per kernel
+    if (pr.causal && pl.nseg == 1) saved = nullptr;
     int *handed = saved ? (int *)(ws + sc.flag_off) : nullptr;
     if (saved)
         k_check_witness<<<dim3(pr.BH), dim3(64), 0, st>>>(

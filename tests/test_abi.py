@@ -88,6 +88,30 @@ def test_hand_over_size_at_head_size_256(lib, B, H, N, e, causal, want):
     assert n == {"unused": 256, "none": 0}.get(want, n) and (want != "sums" or n >= 4 * B * H * 128 * 129 * 4)
 
 
+@pytest.mark.parametrize("BH,N,D,e,causal,most", [
+    (4, 500, 128, 4, 1, 64), (4, 500, 128, 2, 1, 32), (1, 256, 16, 4, 1, 8), (1, 30000, 64, 2, 1, 512),
+    (60, 4000, 64, 4, 1, 512), (42, 9979, 128, 4, 1, 256), (190, 10000, 128, 2, 1, 768), (64, 100000, 64, 4, 0, 512)])
+def test_cuts(lib, BH, N, D, e, causal, most):
+    """Short sequences are cut into the shortest segments, and no cut leaves a few segments over what the compute
+    units hold in whole rounds."""
+    import paper_2510_21956_amd as la
+    S = max(D, 32)
+    slots = la.la_workspace_bytes(1, BH, N, D, la.LA_F32 if e == 4 else la.LA_BF16, causal, 0) // (4 * (S * S + 2 * S))
+    assert 0.9 * most <= slots <= most
+
+
+@pytest.mark.parametrize("BH,N,D,dt", [(120, 383, 256, 1), (4, 2000, 256, 0), (190, 4000, 128, 0), (252, 2000, 128, 1),
+                                       (7000, 40, 16, 0), (20000, 40, 16, 0)])
+def test_forward_static_takes_coarser_cuts(lib, BH, N, D, dt):
+    """Where the states of the finest cut exceed the scratch, a coarser one is taken: not LA_ERR_WORKSPACE."""
+    import torch
+    if torch.cuda.is_available():
+        pytest.skip("made-up addresses: where there is no device the call ends as it asks for the scratch's address")
+    vp = ctypes.c_void_p
+    f = [vp(0x10000000 + (k << 36)) for k in range(5)]
+    assert lib.la_forward_static(*f, 1, BH, N, D, 1.0, 0.5, 1, dt, vp(0)) == 6
+
+
 def test_argument_checks_precede_any_launch(lib):
     """Bad arguments are rejected on the host: these calls must return an error
     code without a GPU being present."""

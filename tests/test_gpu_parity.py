@@ -109,6 +109,34 @@ def test_small_shapes(oracle_mod, la, knobs, shape, causal, dtype):
         check_against_oracle(oracle_mod, la, dev, ref, slices, dtype, a, b, causal, tag)
 
 
+# Segments at the edges of how their slots are added up: in the kernels (up to five at D <= 64), eight, sixteen,
+# 128 and 512 slots to a round of the scan kernels; the shortest segments (32 rows in fp32, 64 in bf16).
+@pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("D,nseg", [(16, 5), (64, 2), (64, 5), (64, 6), (128, 9), (64, 17), (32, 18), (32, 129),
+                                    (32, 130), (16, 514)])
+def test_segment_counts(oracle_mod, la, knobs, D, nseg, dtype, causal):
+    knobs(64, 0)
+    N = 64 * nseg - 27
+    tag = "segments %d D%d %s %s" % (nseg, D, dtype, "causal" if causal else "full")
+    print("case", tag, flush=True)
+    dev, ref = upload_case(1, 2, N, D, dtype, 500 + nseg, [0, 1])
+    check_against_oracle(oracle_mod, la, dev, ref, [0, 1], dtype, 1.0, 0.5, causal, tag)
+
+
+@pytest.mark.parametrize("B,H,N,D,dtype", [(1, 3, 97, 32, "f32"), (1, 2, 250, 64, "f32"), (1, 2, 330, 128, "f32"),
+                                           (1, 1, 190, 256, "f32"), (1, 2, 330, 128, "bf16"), (1, 300, 70, 128, "f32"),
+                                           (2, 150, 70, 64, "bf16")])
+def test_shortest_segments(oracle_mod, la, knobs, B, H, N, D, dtype):
+    knobs(0, 0)
+    slices = [0, B * H - 1]
+    for causal in (True, False):
+        tag = "short B%d H%d N%d D%d %s %s" % (B, H, N, D, dtype, "causal" if causal else "full")
+        print("case", tag, flush=True)
+        dev, ref = upload_case(B, H, N, D, dtype, 600 + N, slices)
+        check_against_oracle(oracle_mod, la, dev, ref, slices, dtype, 1.0, 0.5, causal, tag)
+
+
 # General coefficients on every path.  With a = 1 every factor `a` in the kernels is
 # invisible, so: a != 1 with b < 0, b = 0 (the linear term vanishes), b close to a (small
 # denominators), and a = b = 1, the kernel the paper's own implementation fixes (Sec. 4).
