@@ -81,10 +81,11 @@ struct Sum {
         v = T{};
         run = LongSum<T>{};
     }
+    // where the lane's share is in an array of D
+    static __device__ __forceinline__ int at(int w, int c, int g) { return w * 16 + (SWAP ? c : 4 * g); }
     __device__ __forceinline__ void load(const float *p, int w, int c, int g)
     {
-        if constexpr (SWAP) v = p[w * 16 + c];
-        else v = *reinterpret_cast<const f4v *>(p + w * 16 + 4 * g);
+        v = *reinterpret_cast<const T *>(p + at(w, c, g));
     }
     __device__ __forceinline__ void store(float *p, int w, int c, int g) const
     {
@@ -198,6 +199,47 @@ __device__ __forceinline__ void factor_frag(bf8v (&o)[3], const float *r, int g)
 {
     split_frag<3>(*reinterpret_cast<const f4v *>(r + 4 * g),
                   *reinterpret_cast<const f4v *>(r + 16 + 4 * g), o);
+}
+
+// The state a workgroup starts from: the sum of `n` slots, `step` floats from one to the next, in that order,
+// as four rows of one column a lane (COLS; rows 16 rb + 4 g .., column 16 w + c of the D x D block p) or its
+// transpose, and NV vectors (the lane's share at v[k], a float or four).  n = 1 reads a slot that
+// launch_scan_slots has summed up.
+template <int D, bool COLS, int NV, typename T>
+__device__ __forceinline__ void add_slots(Blk (&st)[D / 16], const float *p, T (&sum)[NV],
+                                          const float *const (&v)[NV], ptrdiff_t step, int n, int w, int c, int g)
+{
+    constexpr int NRB = D / 16, BATCH = 2;
+    const float *q = COLS ? p + 4 * g * D + w * 16 + c : p + (w * 16 + c) * D + 4 * g;
+    const auto read = [&](ptrdiff_t at, Blk (&x)[NRB], T (&y)[NV]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int rb = 0; rb < NRB; ++rb) {
+            if constexpr (COLS) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) x[rb].set(e, q[at + (rb * 16 + e) * D]);
+            } else {
+                x[rb].v = *reinterpret_cast<const f4v *>(q + at + rb * 16);
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < NV; ++k) y[k] = *reinterpret_cast<const T *>(v[k] + at);
+    };
+    if (n > 0) read(0, st, sum);
+    if constexpr (D > 64) return;
+    for (int i0 = 1; i0 < n; i0 += BATCH) {
+        Blk x[BATCH][NRB];
+        T y[BATCH][NV];
+#pragma unroll
+        for (int i = 0; i < BATCH; ++i) read(min(i0 + i, n - 1) * step, x[i], y[i]);
+#pragma unroll
+        for (int i = 0; i < BATCH; ++i)
+            if (i0 + i < n) {
+#pragma unroll
+                for (int rb = 0; rb < NRB; ++rb) st[rb].v += x[i][rb].v;
+#pragma unroll
+                for (int k = 0; k < NV; ++k) sum[k] += y[i][k];
+            }
+    }
 }
 
 // The waves that form weight blocks are the last to reach the barrier behind them: between the two calls
@@ -453,8 +495,9 @@ template <int MODE, int D, int LD>
 __global__ __launch_bounds__(4 * D, 2) void ks_fwd_apply(
     const typename Mode<MODE>::TIO *__restrict__ Q, const typename Mode<MODE>::TIO *__restrict__ K,
     const typename Mode<MODE>::TIO *__restrict__ V, typename Mode<MODE>::TIO *__restrict__ O,
-    float *__restrict__ G, const float *__restrict__ ws, float *__restrict__ saved, int N, int nseg, SegMap sm, size_t slot_floats, size_t saved_floats,
-    float a, float b, int xflags, const float *__restrict__ Gin, float *__restrict__ Fraw)
+    float *__restrict__ G, const float *__restrict__ ws, float *__restrict__ saved, int N, int nseg,
+    SegMap sm, size_t slot_floats, int fold, size_t saved_floats, float a, float b, int xflags,
+    const float *__restrict__ Gin, float *__restrict__ Fraw)
 {
     typedef Mode<MODE> MD;
     typedef typename MD::TIO TIO;
@@ -480,20 +523,16 @@ __global__ __launch_bounds__(4 * D, 2) void ks_fwd_apply(
     const Lanes<32> lw(c, g);
     const bf8v one[1] = {ones_frag()};
 
-    // initial state from the scanned slot: S[r][j], j = 16w + c
-    const float *slot = ws + ((size_t)bh * nseg + seg) * slot_floats;
+    // initial state: S[r][j], j = 16w + c
+    const int nsum = fold ? seg : min(seg, 1);
+    const float *slot = ws + ((size_t)bh * nseg + seg - max(nsum - 1, 0)) * slot_floats;
     Blk st[NRB];
 #pragma unroll
     for (int rb = 0; rb < NRB; ++rb) st[rb].zero();
-    f4v pacc = {0.f, 0.f, 0.f, 0.f}, zacc = pacc;  // p, z [16w + 4g + e]
-    if (seg > 0) {
-#pragma unroll
-        for (int rb = 0; rb < NRB; ++rb)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) st[rb].set(i, slot[(rb * 16 + 4 * g + i) * D + w * 16 + c]);
-        pacc = *reinterpret_cast<const f4v *>(slot + D * D + D + w * 16 + 4 * g);
-        zacc = *reinterpret_cast<const f4v *>(slot + D * D + w * 16 + 4 * g);
-    }
+    f4v vec[2] = {};  // p, z [16w + 4g + e]
+    const float *const vp[2] = {slot + D * D + D + w * 16 + 4 * g, slot + D * D + w * 16 + 4 * g};
+    add_slots<D, true>(st, slot, vec, vp, slot_floats, nsum, w, c, g);
+    f4v pacc = vec[0], zacc = vec[1];
     if (c == 0) *reinterpret_cast<f4v *>(zs + w * 16 + 4 * g) = zacc;
     // the block above the diagonal stays zero
     if (t < 64) store_weights<LX>(Pt, c, 1, g, f4v{0.f, 0.f, 0.f, 0.f});
@@ -761,7 +800,7 @@ __global__ __launch_bounds__(4 * D, 2) void ks_bwd_dq(
     const typename Mode<MODE>::TIO *__restrict__ V, const typename Mode<MODE>::TIO *__restrict__ O,
     const float *__restrict__ G, const typename Mode<MODE>::TIO *__restrict__ dO,
     typename Mode<MODE>::TIO *__restrict__ dQ, float *ws, const float *sinit, size_t sinit_floats,
-    float *__restrict__ dprime, int N, int nseg, SegMap sm, size_t slot_floats, float b, int xflags,
+    float *__restrict__ dprime, int N, int nseg, SegMap sm, size_t slot_floats, int fold, float b, int xflags,
     float *__restrict__ Pq, const int *__restrict__ handed)
 {
     typedef Mode<MODE> MD;
@@ -809,12 +848,12 @@ __global__ __launch_bounds__(4 * D, 2) void ks_bwd_dq(
     Sum<SWAP> zacc, uacc;      // z, u
     Sum<SWAP, !CAUSAL && QT> wacc;  // w: without the mask, most of dV (fp32: bf16 rounds it anyway)
     if (!zero_init) {
-#pragma unroll
-        for (int jb = 0; jb < NRB; ++jb)
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-                st[jb].set(i, slot[SL::ST + (jb * 16 + 4 * g + i) * D + w * 16 + c]);
-        zacc.load(slot + SL::Z, w, c, g);
+        const int nsum = CAUSAL && fold ? seg : 1;
+        slot -= (nsum - 1) * sinit_floats;
+        typename Sum<SWAP>::T x[1] = {};
+        const float *const vp[1] = {slot + SL::Z + Sum<SWAP>::at(w, c, g)};
+        add_slots<D, true>(st, slot + SL::ST, x, vp, sinit_floats, nsum, w, c, g);
+        zacc.v = x[0];
     }
     if constexpr (CAUSAL) {
         if (t < 64) store_weights<LX>(Ct, c, 1, g, f4v{0.f, 0.f, 0.f, 0.f});
@@ -995,7 +1034,7 @@ __global__ __launch_bounds__(8 * D, 4) void ks_bwd_dq_halves(
     const typename Mode<MODE>::TIO *__restrict__ V, const typename Mode<MODE>::TIO *__restrict__ O,
     const float *__restrict__ G, const typename Mode<MODE>::TIO *__restrict__ dO,
     typename Mode<MODE>::TIO *__restrict__ dQ, float *ws, const float *sinit, size_t sinit_floats,
-    float *__restrict__ dprime, int N, int nseg, SegMap sm, size_t slot_floats, float b, int xflags,
+    float *__restrict__ dprime, int N, int nseg, SegMap sm, size_t slot_floats, int fold, float b, int xflags,
     float *__restrict__ Pq, const int *)
 {
     typedef Mode<MODE> MD;
@@ -1037,12 +1076,12 @@ __global__ __launch_bounds__(8 * D, 4) void ks_bwd_dq_halves(
 #pragma unroll
     for (int jb = 0; jb < NRB; ++jb) st[jb].zero();
     if (seg > 0 && half == 0) {
-#pragma unroll
-        for (int jb = 0; jb < NRB; ++jb)
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-                st[jb].set(i, slot[SL::ST + (jb * 16 + 4 * g + i) * D + w * 16 + c]);
-        vec.load(slot + SL::Z, w, c, g);
+        const int nsum = fold ? seg : 1;
+        slot -= (nsum - 1) * sinit_floats;
+        typename Sum<SWAP>::T x[1] = {};
+        const float *const vp[1] = {slot + SL::Z + Sum<SWAP>::at(w, c, g)};
+        add_slots<D, true>(st, slot + SL::ST, x, vp, sinit_floats, nsum, w, c, g);
+        vec.v = x[0];
     }
     if (t < 64) store_weights<LX>(Ct, c, 1, g, f4v{0.f, 0.f, 0.f, 0.f});
 
@@ -1235,7 +1274,7 @@ __global__ __launch_bounds__(8 * D, 4) void ks_bwd_dkv(
     const typename Mode<MODE>::TIO *__restrict__ V, const float *__restrict__ G,
     const typename Mode<MODE>::TIO *__restrict__ dO, typename Mode<MODE>::TIO *__restrict__ dK,
     typename Mode<MODE>::TIO *__restrict__ dV, const float *__restrict__ ws, const float *__restrict__ dprime, int N,
-    int nseg, SegMap sm, size_t slot_floats, float a, float b, int xflags,
+    int nseg, SegMap sm, size_t slot_floats, int fold, float a, float b, int xflags,
     float *__restrict__ Pk, float *__restrict__ Pv)
 {
     typedef Mode<MODE> MD;
@@ -1273,19 +1312,14 @@ __global__ __launch_bounds__(8 * D, 4) void ks_bwd_dkv(
 #pragma unroll
     for (int rb = 0; rb < NRB; ++rb) st[rb].zero();
     if (seg < nseg - 1) {
-        const float *slot = ws + ((size_t)bh * nseg + seg) * slot_floats;
-        if (half) {
-#pragma unroll
-            for (int rb = 0; rb < NRB; ++rb)
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    st[rb].set(i, slot[SL::R + (rb * 16 + 4 * g + i) * D + w * 16 + c]);
-        } else {
-#pragma unroll
-            for (int rb = 0; rb < NRB; ++rb)
-                st[rb].v = *reinterpret_cast<const f4v *>(slot + SL::R + (w * 16 + c) * D + rb * 16 + 4 * g);
-        }
-        vec.load(slot + (half ? SL::W : SL::U), w, c, g);
+        const int nsum = fold ? nseg - 1 - seg : 1;
+        const ptrdiff_t step = -(ptrdiff_t)slot_floats;
+        const float *slot = ws + ((size_t)bh * nseg + seg + nsum - 1) * slot_floats;
+        typename Sum<SWAP>::T x[1] = {};
+        const float *const vp[1] = {slot + (half ? SL::W : SL::U) + Sum<SWAP>::at(w, c, g)};
+        if (half) add_slots<D, true>(st, slot + SL::R, x, vp, step, nsum, w, c, g);
+        else add_slots<D, false>(st, slot + SL::R, x, vp, step, nsum, w, c, g);
+        vec.v = x[0];
     }
     if (t < 64) {
         store_weights<LX>(Ct, 16 + c, 0, g, f4v{0.f, 0.f, 0.f, 0.f});
@@ -1446,7 +1480,7 @@ __global__ __launch_bounds__(4 * D, 2) void ks_bwd_dkv_wide(
     const __bf16 *__restrict__ Q, const __bf16 *__restrict__ K, const __bf16 *__restrict__ V,
     const float *__restrict__ G, const __bf16 *__restrict__ dO, __bf16 *__restrict__ dK, __bf16 *__restrict__ dV,
     const float *__restrict__ ws, const float *__restrict__ dprime, int N, int nseg, SegMap sm,
-    size_t slot_floats, float a, float b, int xflags, float *__restrict__ Pk, float *__restrict__ Pv)
+    size_t slot_floats, int, float a, float b, int xflags, float *__restrict__ Pk, float *__restrict__ Pv)
 {
     constexpr int LX = Mode<P16>::LX, NW = D / 16, NC = D / 32, PL = NTile<D>::PLANE, WPL = NTile<32>::PLANE;
     typedef Chunk<__bf16, D, LD> CH;
@@ -1694,6 +1728,18 @@ int read_rows(int BH, int N, int D)
     }
 }
 
+// Whether the masked apply kernels add the segments' slots up themselves (add_slots) instead of a scan between
+// the kernels: up to five segments at D = 64, where a workgroup reads four slots of 16 KB at most, up to nine below
+// (4 KB a slot).  A step, us, scan / in the kernels: D = 64, bf16, 128 slices of 600 rows (four segments) 64.1 / 59.8,
+// 120 of 1000 73.7 / 69.8, fp32, 128 of 600 108.4 / 103.4; D = 32, fp32, 8 of 300 (five) 28.4 / 26.6; eight segments,
+// fp32, D = 64, 64 of 4096 280 / 282, fourteen, bf16, 36 of 5003 98 / 113; sixteen, bf16, D = 32, 64 of 4096 81 / 90.  At
+// D = 128, 64 KB a slot, it is no faster with four (fp32, 64 of 1000 201 / 199) and slower with eight (16 of 1000
+// 103 / 117).
+bool folds_scan(const Problem &pr, int nseg)
+{
+    return pr.causal && nseg <= (pr.D <= 32 ? 9 : pr.D == 64 ? 5 : 1);
+}
+
 template <int MODE, int D, int LD>
 la_status run_forward(const Problem &pr, const Plan &pl, const void *Qv, const void *Kv,
                       const void *Vv, void *Ov, float *G, float *ws, float *saved, hipStream_t st,
@@ -1704,18 +1750,21 @@ la_status run_forward(const Problem &pr, const Plan &pl, const void *Qv, const v
     TIO *O = (TIO *)Ov;
     const int nseg = pl.nseg, nrun = pr.causal ? nseg - 1 : nseg;
     const dim3 block(4 * D);
+    const bool fold = folds_scan(pr, nseg);
     if (nrun > 0) {
         (pr.causal ? ks_kv_state<MODE, D, false, LD, false> : ks_kv_state<MODE, D, false, LD, true>)<<<
             dim3(pr.BH * nrun), block, 0, st>>>(
             K, V, ws, pr.N, nseg, nrun, pl.map, pl.slot_floats, pr.causal ? 1 : 0, nullptr);
         tc.mark("fwd_state");
-        launch_scan_slots(ws, pr.BH, nseg, pl.slot_floats, 0, D * D + 2 * D, pr.causal ? 0 : 2,
-                          pr.causal ? 1 : 0, nseg - 1, st);
-        tc.mark("scan_slots");
+        if (!fold) {
+            launch_scan_slots(ws, pr.BH, nseg, pl.slot_floats, 0, D * D + 2 * D, pr.causal ? 0 : 2,
+                              pr.causal ? 1 : 0, nseg - 1, st);
+            tc.mark("scan_slots");
+        }
     }
     if (pr.causal) {
         ks_fwd_apply<MODE, D, LD><<<dim3(pr.BH * nseg), block, 0, st>>>(
-            Q, K, V, O, G, ws, saved, pr.N, nseg, pl.map, pl.slot_floats, pl.saved_floats, pr.a, pr.b,
+            Q, K, V, O, G, ws, saved, pr.N, nseg, pl.map, pl.slot_floats, fold, pl.saved_floats, pr.a, pr.b,
             xflags, Gin, Fraw);
     } else {
         const int rows_wg = read_rows(pr.BH, pr.N, D), nwg = (pr.N + rows_wg - 1) / rows_wg;
@@ -1760,6 +1809,7 @@ la_status run_backward(const Problem &pr, const Plan &pl, const void *Qv, const 
     TIO *dQ = (TIO *)dQv, *dK = (TIO *)dKv, *dV = (TIO *)dVv;
     const int nseg = pl.nseg, nrun = pr.causal ? nseg - 1 : nseg;
     float *dprime = ws + pl.delta_offset_floats;
+    const bool fold = folds_scan(pr, nseg);
     const dim3 grid(pr.BH * nseg), block(4 * D), block2(8 * D);
     // forward-running sums before every segment: handed over by the forward pass, or
     // per-segment sums (none needed from a masked pass's last segment) and a scan here
@@ -1768,20 +1818,22 @@ la_status run_backward(const Problem &pr, const Plan &pl, const void *Qv, const 
             dim3(pr.BH * nrun), block, 0, st>>>(
             K, V, ws, pr.N, nseg, nrun, pl.map, pl.slot_floats, pr.causal ? 1 : 0, bp.handed);
         tc.mark("bwd_state");
-        launch_scan_slots(ws, pr.BH, nseg, pl.slot_floats, SL::ST, SL::R - SL::ST, pr.causal ? 0 : 2,
-                          pr.causal ? 1 : 0, nseg - 1, st, bp.handed);
-        tc.mark("scan_slots");
+        if (saved || !fold) {
+            launch_scan_slots(ws, pr.BH, nseg, pl.slot_floats, SL::ST, SL::R - SL::ST, pr.causal ? 0 : 2,
+                              pr.causal ? 1 : 0, nseg - 1, st, bp.handed);
+            tc.mark("scan_slots");
+        }
     }
     const float *sinit = saved ? saved : ws;
     const size_t sinit_floats = saved ? pl.saved_floats : pl.slot_floats;
     auto *dq = !pr.causal ? ks_bwd_dq<MODE, D, false, LD> : ks_bwd_dq_masked<MODE, D, LD>();
     dq<<<grid, pr.causal && D == 32 ? block2 : block, 0, st>>>(
-        Q, K, V, O, G, dO, dQ, ws, sinit, sinit_floats, dprime, pr.N, nseg, pl.map, pl.slot_floats, pr.b, bp.xflags,
-        bp.Pq, bp.handed);
+        Q, K, V, O, G, dO, dQ, ws, sinit, sinit_floats, dprime, pr.N, nseg, pl.map, pl.slot_floats,
+        fold && !saved, pr.b, bp.xflags, bp.Pq, bp.handed);
     tc.mark("bwd_dq");
     if (!dK) return launch_status();
     // reverse-running sums left by the ascending sweep
-    if (!pr.causal || nseg > 1) {
+    if (!pr.causal || (nseg > 1 && !fold)) {
         launch_scan_slots(ws, pr.BH, nseg, pl.slot_floats, SL::R, SL::END - SL::R, pr.causal ? 1 : 2, 0,
                           pr.causal ? nseg - 2 : nseg - 1, st);
         tc.mark("scan_slots_rev");
@@ -1789,8 +1841,8 @@ la_status run_backward(const Problem &pr, const Plan &pl, const void *Qv, const 
     if (pr.causal) {
         auto *dkv = ks_bwd_dkv_masked<MODE, D, LD>();
         dkv<<<grid, MODE == P16 && D == 128 ? block : block2, 0, st>>>(
-            Q, K, V, G, dO, dK, dV, ws, dprime, pr.N, nseg, pl.map, pl.slot_floats, pr.a, pr.b, bp.xflags, bp.Pk,
-            bp.Pv);
+            Q, K, V, G, dO, dK, dV, ws, dprime, pr.N, nseg, pl.map, pl.slot_floats, fold, pr.a, pr.b, bp.xflags,
+            bp.Pk, bp.Pv);
     } else {
         ks_bwd_dkv_read<MODE, D, LD><<<grid, block, 0, st>>>(K, V, dK, dV, ws, pr.N, nseg, pl.map, pl.slot_floats,
                                                              pr.a, pr.b, bp.xflags, bp.Pk, bp.Pv);
