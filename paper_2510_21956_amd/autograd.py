@@ -3,7 +3,8 @@
 Plumbing only: it allocates the outputs, the workspaces and the hand-over buffer with
 torch, keeps the set {Q, K, V, O, g} of Sec. 3.2 (plus the forward pass's running sums at
 the segment boundaries) for the backward pass, and calls la_forward_save /
-la_backward_saved.  Every arithmetic step runs in the HIP library; there is no fallback.
+la_backward_saved; for plain tensors outside of modes, transforms and traces by a node of the same steps in
+native code (binding.attention).  Every arithmetic step runs in the HIP library; there is no fallback.
 Gradients are with respect to the Q, K, V handed in; with ``normalize_qk`` the rows of Q and
 K are scaled to unit length inside the kernels (Sec. 3.3) and the gradients are those for the
 raw rows.  a and b are constants.
@@ -43,18 +44,23 @@ class LinearAttentionFunction(torch.autograd.Function):
 
     @staticmethod
     def backward(ctx, dO):
-        Q, K, V, O, G = ctx.saved_tensors
-        a, b, causal, normalize_qk = ctx.la_args
-        B, H, N, D = Q.shape
-        dO = dO.contiguous()
-        dQ, dK, dV = torch.empty_like(Q), torch.empty_like(Q), torch.empty_like(Q)
-        ws = _bytes(_b.la_workspace_bytes(B, H, N, D, _code(Q), causal, 1), Q.device)
-        bwd = _b.la_backward_qknorm_saved if normalize_qk else _b.la_backward_saved
-        bwd(Q, K, V, O, G, dO, dQ, dK, dV, a, b, causal, ws, ctx.la_saved)
-        return dQ, dK, dV, None, None, None, None
+        return (*python_backward(*ctx.saved_tensors, dO, ctx.la_saved, *ctx.la_args), None, None, None, None)
+
+
+def python_backward(Q, K, V, O, G, dO, saved, a, b, causal, normalize_qk):
+    B, H, N, D = Q.shape
+    dO = dO.contiguous()
+    dQ, dK, dV = torch.empty_like(Q), torch.empty_like(Q), torch.empty_like(Q)
+    ws = _bytes(_b.la_workspace_bytes(B, H, N, D, _code(Q), causal, 1), Q.device)
+    bwd = _b.la_backward_qknorm_saved if normalize_qk else _b.la_backward_saved
+    bwd(Q, K, V, O, G, dO, dQ, dK, dV, a, b, causal, ws, saved)
+    return dQ, dK, dV
 
 
 def linear_attention(Q, K, V, a=1.0, b=0.5, causal=True, normalize_qk=False):
     """Differentiable linear attention on [B, H, N, D] float32 or bfloat16 device tensors;
     ``normalize_qk`` scales the rows of Q and K to unit length inside the kernels (D <= 128)."""
+    O = _b.attention(Q, K, V, a, b, causal, normalize_qk)
+    if O is not None:
+        return O
     return LinearAttentionFunction.apply(Q, K, V, a, b, causal, normalize_qk)

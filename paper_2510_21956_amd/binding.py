@@ -127,10 +127,12 @@ def _open_native(lib):
     here = "torch %s, Python %d.%d" % (torch.__version__, *sys.version_info[:2])
     if getattr(module, "built_for", None) != here:
         raise ImportError("built for %s, not for %s" % (getattr(module, "built_for", "another version"), here))
-    module.init(_device_stream, *(ctypes.cast(f, ctypes.c_void_p).value for f in (
+    from . import autograd  # imports this module; by the first call both are there
+    module.init(autograd.python_backward, _device_stream, *(ctypes.cast(f, ctypes.c_void_p).value for f in (
         lib.la_forward_traced, lib.la_forward_qknorm, lib.la_forward_save, lib.la_forward_qknorm_save,
         lib.la_backward_traced, lib.la_backward_qknorm, lib.la_backward_saved,
-        lib.la_backward_qknorm_saved, lib.la_decode_step, lib.la_decode_prefill)))
+        lib.la_backward_qknorm_saved, lib.la_decode_step, lib.la_decode_prefill, lib.la_workspace_bytes,
+        lib.la_saved_state_bytes)))
     return module
 
 
@@ -354,6 +356,19 @@ def _backward(Q, K, V, O, G, dO, dQ, dK, dV, a, b, causal, workspace, saved, str
         rc = lib.la_backward_traced(*head, _stream_ptr(stream, Q), tr)
     if rc != 0:
         raise LaError(rc, "la_backward_saved" if use_saved else "la_backward")
+
+
+def attention(Q, K, V, a, b, causal, normalize):
+    """O of linear_attention (autograd.py) through the autograd node in native code; None where that is left to
+    the Python one."""
+    if _native is None:
+        load_library()
+        if _native is None:
+            return None
+    O = _native.attention(Q, K, V, a, b, causal, normalize)
+    if type(O) is int:
+        raise LaError(O, "la_forward_save")
+    return O
 
 
 def la_decode_state_bytes(B, H, D):

@@ -14,6 +14,7 @@ LIB = os.path.join(HERE, "libla.so")
 MARSHAL = os.path.join(HERE, "_marshal.so")
 
 CXX = "g++"
+ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
     "-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-shared",
@@ -52,11 +53,11 @@ def _compile_marshal(verbose, out):
     import torch
     from torch.utils.cpp_extension import include_paths, library_paths
     cmd = [CXX, "-O2", "-std=c++17", "-shared", "-fPIC", "-fvisibility=hidden",
-           "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI,
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI, "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
            '-DLA_BUILT_FOR="torch %s, Python %d.%d"' % (torch.__version__, *sys.version_info[:2]), "-I", INCLUDE]
-    cmd += ["-isystem%s" % p for p in include_paths() + [sysconfig.get_paths()["include"]]]
+    cmd += ["-isystem%s" % p for p in include_paths() + [os.path.join(ROCM, "include"), sysconfig.get_paths()["include"]]]
     cmd += [os.path.join(CSRC, "la_bind.cpp")]
-    cmd += ["-L%s" % p for p in library_paths()] + ["-ltorch_python", "-ltorch_cpu", "-lc10", "-o", out]
+    cmd += ["-L%s" % p for p in library_paths()] + ["-ltorch_python", "-ltorch_cpu", "-lc10_hip", "-lc10", "-o", out]
     if verbose:
         print(" ".join(cmd))
     subprocess.run(cmd, check=True)

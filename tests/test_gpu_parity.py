@@ -374,6 +374,56 @@ def test_autograd_wrapper(oracle_mod, la, knobs, dtype, causal):
         assert e <= 1.0, "%s exceeds tolerance by factor %.3g" % (name, e)
 
 
+@pytest.mark.parametrize("norm,D,dtype", [(False, 16, "f32"), (False, 64, "bf16"), (True, 64, "f32"), (False, 256, "f32")])
+def test_autograd_nodes_native_and_python(la, knobs, monkeypatch, norm, D, dtype):
+    """The wrapper's node in native code and the Python one: the same bits, the same refusals; strided inputs,
+    saved-tensor hooks, a second backward pass, create_graph and a graph that is gone taken alike."""
+    from paper_2510_21956_amd import binding
+    knobs(0, 0)
+    dev, _ = upload_case(2, 3, 130, D, dtype, 77, [])
+    wide = torch.randn((2, 130, 3, D), device="cuda").to(dev["Q"].dtype)
+
+    def run(node):
+        Q, K, V = (dev[n].clone().requires_grad_(True) for n in ("Q", "K", "V"))
+        X = wide.clone().requires_grad_(True)
+        packed = []
+        with torch.autograd.graph.saved_tensors_hooks(lambda t: packed.append(t.shape) or t.clone(), lambda t: t):
+            O = la.linear_attention(Q, K, V, 1.0, 0.5, True, norm)
+            P = la.linear_attention(X.transpose(1, 2), K, V, 1, 0.25, False, norm)
+        assert ("LinearAttentionFunction" in O.grad_fn.name()) == (node == "python")
+        loss = O.float().sum() + (P.float() ** 2).sum()
+        got = [O, P, *torch.autograd.grad(loss, (Q, K, V, X), retain_graph=True)]
+        got += torch.autograd.grad(loss, (Q, K, V, X), create_graph=True)
+        got += torch.autograd.grad(P, (X,), torch.ones((), device="cuda", dtype=P.dtype).expand(P.shape))
+        with torch.no_grad():
+            got.append(la.linear_attention(Q, K, V))
+        assert not got[-1].requires_grad and all(not t.requires_grad for t in got[2:6])
+        refused = []
+
+        def refuse(f):
+            with pytest.raises(Exception) as e:
+                f()
+            refused.append((type(e.value), str(e.value) if "backward" not in str(e.value) else ""))
+        for args in ((Q, K[:, :, :7], V), (Q, K.double(), V), (Q[..., :5], K[..., :5], V[..., :5]), (Q[0], K[0], V[0]),
+                     (Q.half(), K.half(), V.half()), (Q.cpu(), K.cpu(), V.cpu()), (Q[:0], K[:0], V[:0])):
+            refuse(lambda: la.linear_attention(*args))
+        refuse(lambda: torch.autograd.grad(P, (X,), P.detach()))  # its graph is gone
+        O2 = la.linear_attention(Q * 1, K, V)
+        refuse(lambda: torch.func.grad(lambda q: la.linear_attention(q, K, V).sum())(Q))
+        with torch.no_grad():
+            K.add_(1)
+        refuse(lambda: O2.sum().backward())  # K is not what was saved
+        return [t.detach() for t in got], refused, packed
+
+    assert binding._native is not None
+    native = run("native")
+    monkeypatch.setattr(binding, "attention", lambda *a: None)
+    python = run("python")
+    assert native[1:] == python[1:]
+    for x, y in zip(native[0], python[0]):
+        assert torch.equal(x, y)
+
+
 def test_run_to_run_determinism(la, knobs):
     knobs(0, 0)
     dev, _ = upload_case(2, 4, 1500, 64, "f32", 99, [])
