@@ -77,6 +77,10 @@ struct Blk {
     __device__ __forceinline__ void set(int i, float x) { v[i] = x; }
 };
 
+// Where a branch stays one: made a selection, what a launch without `add` never loads would be waited for all
+// the same.
+__device__ __forceinline__ void keep_branch() { asm volatile(""); }
+
 // Rows of a 16-row block that exist.  The clamp is a vector instruction whatever its operand; its
 // result is named uniform, or every store whose descriptor it goes into becomes a loop over
 // the lanes' descriptors.
@@ -93,15 +97,12 @@ __device__ __forceinline__ int valid_rows(int n)
 // descriptor that covers its first `rows_valid` rows (at most 16, possibly none): stores
 // to rows beyond them are dropped by the address check, without a branch, and the lane's
 // address is one 32-bit offset that does not change from block to block.
-// acc = 1 adds what the block holds already, acc = 2 adds it times old_scale[row]: the calls
-// that work on a block of columns of wider rows build their results up over several launches.
-// A bf16 block takes the values to add from an fp32 array instead (old32: rows old_ld floats
-// apart, the same columns), so that the result is rounded once.
+// With `add`, old (load_block) is added first, times old_scale[row] if given: the calls that work on a block of
+// columns of wider rows build their results up over several launches.
 template <typename T>
 __device__ __forceinline__ void store_block(T *base, int ld, int col0, int rows_valid, int l,
-                                            float x0, float x1, float x2, float x3, int acc = 0,
-                                            const float *old_scale = nullptr,
-                                            const float *old32 = nullptr, int old_ld = 0)
+                                            float x0, float x1, float x2, float x3, bool add = false,
+                                            f4v old = f4v{}, const float *old_scale = nullptr)
 {
     const int src = 16 * (l % 4) + l / 4;  // lane that holds (row l/4, column quad l%4)
     const int row = l / 4, cq = l % 4;
@@ -109,34 +110,36 @@ __device__ __forceinline__ void store_block(T *base, int ld, int col0, int rows_
     const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
         base, 0, nrows * ld * (int)sizeof(T), kBufferFlags);
     const int off = (row * ld + col0 + 4 * cq) * (int)sizeof(T);
-    if constexpr (sizeof(T) == 4) {
+    if (sizeof(T) == 4 || add) {
         f4v y = {__shfl(x0, src), __shfl(x1, src), __shfl(x2, src), __shfl(x3, src)};
-        if (acc) {
-            const u4v o = __builtin_amdgcn_raw_buffer_load_b128(rsrc, off, 0, 0);
-            const float sc = acc == 2 ? old_scale[row] : 1.f;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) y[e] += sc * __uint_as_float(o[e]);
+        if (add) {
+            keep_branch();
+            y += (old_scale ? old_scale[row] : 1.f) * old;
         }
-        const u4v v = {__float_as_uint(y[0]), __float_as_uint(y[1]), __float_as_uint(y[2]),
-                       __float_as_uint(y[3])};
-        __builtin_amdgcn_raw_buffer_store_b128(v, rsrc, off, 0, 0);
-    } else if (acc) {  // bf16: what is added comes from old32, see above
-        f4v y = {__shfl(x0, src), __shfl(x1, src), __shfl(x2, src), __shfl(x3, src)};
-        const float sc = acc == 2 ? old_scale[row] : 1.f;
-        const __amdgpu_buffer_rsrc_t r32 = __builtin_amdgcn_make_buffer_rsrc(
-            const_cast<float *>(old32), 0, nrows * old_ld * 4, kBufferFlags);
-        const u4v o =
-            __builtin_amdgcn_raw_buffer_load_b128(r32, (row * old_ld + col0 + 4 * cq) * 4, 0, 0);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) y[e] += sc * __uint_as_float(o[e]);
-        bf4v p = to_bf4(y);
-        __builtin_amdgcn_raw_buffer_store_b64(*reinterpret_cast<u2v *>(&p), rsrc, off, 0, 0);
+        if constexpr (sizeof(T) == 4) {
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4v, y), rsrc, off, 0, 0);
+        } else {
+            __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u2v, to_bf4(y)), rsrc, off, 0, 0);
+        }
     } else {
         bf4v p = to_bf4(f4v{x0, x1, x2, x3});
         u2v u = *reinterpret_cast<u2v *>(&p);
         const u2v v = {(unsigned)__shfl((int)u[0], src), (unsigned)__shfl((int)u[1], src)};
         __builtin_amdgcn_raw_buffer_store_b64(v, rsrc, off, 0, 0);
     }
+}
+// What an fp32 block holds, in the layout in which store_block adds it.  Asked for a phase ahead, before the next
+// chunk's rows (loads are waited for in order): read where it is added, every block of a launch that adds waited for
+// memory.  Head size 256, 64 slices of 4096 rows, a forward launch that adds 287 -> 266 us (fp32), 163 -> 136 (bf16), a
+// backward launch that adds to all gradients 572 -> 520 and 291 -> 275; a step 3177 -> 3062 and 1580 -> 1458, without
+// the mask 2133 -> 1980 and 1246 -> 1166.  Launches that do not add are kernels of their own: with both in one, they
+// took up to 3 % longer.
+__device__ __forceinline__ f4v load_block(const float *base, int ld, int col0, int rows_valid, int l)
+{
+    const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<float *>(base), 0, valid_rows(rows_valid) * ld * 4, kBufferFlags);
+    return __builtin_bit_cast(
+        f4v, __builtin_amdgcn_raw_buffer_load_b128(rsrc, (l / 4 * ld + col0 + 4 * (l % 4)) * 4, 0, 0));
 }
 
 // One 16-row block of a bf16 gradient.  With LD > D (a block of D columns of rows LD wide) the
@@ -145,15 +148,14 @@ __device__ __forceinline__ void store_block(T *base, int ld, int col0, int rows_
 // rounds once.  (fp32 gradients are stored by columns and added up in place.)
 template <int D, int LD>
 __device__ __forceinline__ void store_grad_block(__bf16 *out, float *part, bool add, int col0,
-                                                 int rows_valid, int l, float x0, float x1,
-                                                 float x2, float x3)
+                                                 int rows_valid, int l, f4v x, f4v old)
 {
     if constexpr (LD <= D)
-        store_block<__bf16>(out, LD, col0, rows_valid, l, x0, x1, x2, x3);
+        store_block<__bf16>(out, LD, col0, rows_valid, l, x[0], x[1], x[2], x[3]);
     else if (!add)
-        store_block<float>(part, D, col0, rows_valid, l, x0, x1, x2, x3);
+        store_block<float>(part, D, col0, rows_valid, l, x[0], x[1], x[2], x[3]);
     else
-        store_block<__bf16>(out, LD, col0, rows_valid, l, x0, x1, x2, x3, 1, nullptr, part, D);
+        store_block<__bf16>(out, LD, col0, rows_valid, l, x[0], x[1], x[2], x[3], true, old);
 }
 
 // Backward of the row normalisation (Sec. 3.3) on gradient blocks still in registers:

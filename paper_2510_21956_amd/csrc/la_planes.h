@@ -704,26 +704,27 @@ __device__ __forceinline__ void rank_update_two(Blk (&st)[D / 16], const __bf16 
 // Store a 16 x 16 fp32 block of which lane (c, g) holds rows 4g .. 4g+3 of column col0 + c: the 16
 // lanes of a group write one 64-byte run of a row.  The buffer descriptor covers the block's
 // first `rows_valid` rows (at most 16, possibly none): stores beyond them are dropped.
-// add: what the block holds already is added first.
 __device__ __forceinline__ void store_cols_block(float *base, int ld, int col0, int rows_valid, int c,
-                                                 int g, f4v x, bool add = false)
+                                                 int g, f4v x)
 {
-    const int nrows = valid_rows(rows_valid);
     const __amdgpu_buffer_rsrc_t rsrc =
-        __builtin_amdgcn_make_buffer_rsrc(base, 0, nrows * ld * 4, kBufferFlags);
+        __builtin_amdgcn_make_buffer_rsrc(base, 0, valid_rows(rows_valid) * ld * 4, kBufferFlags);
     const int off = (4 * g * ld + col0 + c) * 4;
-    if (add) {
-        float o[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-            o[e] = __builtin_bit_cast(
-                float, __builtin_amdgcn_raw_buffer_load_b32(rsrc, off + e * ld * 4, 0, 0));
-#pragma unroll
-        for (int e = 0; e < 4; ++e) x[e] += o[e];
-    }
 #pragma unroll
     for (int e = 0; e < 4; ++e)
         __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(x[e]), rsrc, off + e * ld * 4, 0, 0);
+}
+// What the block holds, in the same layout.
+__device__ __forceinline__ f4v load_cols_block(const float *base, int ld, int col0, int rows_valid, int c, int g)
+{
+    const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<float *>(base), 0, valid_rows(rows_valid) * ld * 4, kBufferFlags);
+    const int off = (4 * g * ld + col0 + c) * 4;
+    f4v x;
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+        x[e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rsrc, off + e * ld * 4, 0, 0));
+    return x;
 }
 
 // Backward of the row normalisation (Sec. 3.3) on gradient blocks still in registers:

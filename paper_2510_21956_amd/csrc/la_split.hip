@@ -131,16 +131,28 @@ __device__ __forceinline__ f4v own_product(const bf8v (&own)[LA], const bf8v (&p
     if constexpr (SWAP) return step_product<LB, LA>(p, own);
     else return step_product<LA, LB>(own, p);
 }
-// One 16-row block of a gradient; LD > D builds it up over two launches (store_grad_block).
+// One 16-row block of a gradient; LD > D builds it up over two launches (store_grad_block), of which the second
+// (`add`) asks for the share of the first ahead (load_grad).
+template <bool SWAP, int D, int LD, typename TIO>
+__device__ __forceinline__ f4v load_grad(const TIO *out, const float *part, int w, int rows_valid, int l)
+{
+    if constexpr (SWAP) return load_cols_block(out, LD, w * 16, rows_valid, l % 16, l / 16);
+    else return load_block(part, D, w * 16, rows_valid, l);
+}
 template <bool SWAP, int D, int LD, typename TIO>
 __device__ __forceinline__ void store_grad(TIO *out, float *part, bool add, int w, int rows_valid, int l,
-                                           f4v x)
+                                           f4v x, f4v old)
 {
     if (LD < D && w * 16 >= LD) return;  // columns that are not there
-    if constexpr (SWAP)
-        store_cols_block(out, LD, w * 16, rows_valid, l % 16, l / 16, x, LD > D && add);
-    else
-        store_grad_block<D, LD>(out, part, add, w * 16, rows_valid, l, x[0], x[1], x[2], x[3]);
+    if constexpr (SWAP) {
+        if (LD > D && add) {
+            keep_branch();
+            x += old;
+        }
+        store_cols_block(out, LD, w * 16, rows_valid, l % 16, l / 16, x);
+    } else {
+        store_grad_block<D, LD>(out, part, add, w * 16, rows_valid, l, x, old);
+    }
 }
 // Backward of the row normalisation on the two output blocks; xhat = scale * the tile's rows.
 template <bool SWAP, bool OP, int D, int LQ, typename LN>
@@ -487,16 +499,16 @@ __global__ __launch_bounds__(4 * D, 2) void ks_kv_state(
 //   f = tril(a + b Q_c K_c^T) V_c + a 1 p^T + b Q_c S ;  g = rowsum(tril) + a n + b Q_c z
 //   then S += K_c^T V_c, z += sum k, p += sum v
 // LD > D: the call works on D columns of rows LD wide and is one of several launches that
-// build O up: xflags & XF_RAW leaves the numerator undivided in O and the launch's share of g
-// in G; xflags & XF_ACC adds the numerator that O holds and the share of g in Gin first.  bf16
-// tensors keep the undivided numerator in Fraw instead (fp32, B*H*N rows of D): O is rounded once.
+// build O up: the first leaves the numerator undivided in O and its share of g in G; the second (ADD) adds
+// the numerator that O holds and the share of g in Gin first.  bf16 tensors keep the undivided numerator
+// in Fraw instead (fp32, B*H*N rows of D): O is rounded once.
 // ---------------------------------------------------------------------------
-template <int MODE, int D, int LD>
+template <int MODE, int D, int LD, bool ADD>
 __global__ __launch_bounds__(4 * D, 2) void ks_fwd_apply(
     const typename Mode<MODE>::TIO *__restrict__ Q, const typename Mode<MODE>::TIO *__restrict__ K,
     const typename Mode<MODE>::TIO *__restrict__ V, typename Mode<MODE>::TIO *__restrict__ O,
     float *__restrict__ G, const float *__restrict__ ws, float *__restrict__ saved, int N, int nseg,
-    SegMap sm, size_t slot_floats, int fold, size_t saved_floats, float a, float b, int xflags,
+    SegMap sm, size_t slot_floats, int fold, size_t saved_floats, float a, float b,
     const float *__restrict__ Gin, float *__restrict__ Fraw)
 {
     typedef Mode<MODE> MD;
@@ -571,6 +583,15 @@ __global__ __launch_bounds__(4 * D, 2) void ks_fwd_apply(
         if (__builtin_expect(cur.v.top() > kLargestBf16, 0)) cur.v.template store_any<false>(Vt);
         block_sync();
         const long cn = min(c0 + MD::DEPTH * CR, c_last);
+        f4v old[2] = {};  // numerators that the launch before left
+        if constexpr (ADD) {
+#pragma unroll
+            for (int m = 0; m < 2; ++m) {
+                const int nrows = (int)(row1 - c0) - m * 16;
+                if constexpr (RAW32) old[m] = load_block(Fraw + ((size_t)bh * N + c0 + m * 16) * D, D, w * 16, nrows, l);
+                else old[m] = load_block(Op + (size_t)(c0 + m * 16) * LD, LD, w * 16, nrows, l);
+            }
+        }
         cur.q.load(Qp, cn, N);
 
         go_first<D>(w < 3);
@@ -606,12 +627,10 @@ __global__ __launch_bounds__(4 * D, 2) void ks_fwd_apply(
             const float ps = psum[0][l] + (l >= 16 ? psum[1][l] : 0.f);
             float gv = b * qzs[l] + a * (float)c0 + ps;
             const bool valid = l < (int)(row1 - c0);
-            if constexpr (LD > D) {
-                if ((xflags & XF_ACC) && valid) gv += (Gin + (size_t)bh * N + c0)[l];
-                ginv[w][l] = (xflags & XF_RAW) ? 1.f : 1.f / gv;
-            } else {
-                ginv[w][l] = 1.f / gv;
+            if constexpr (ADD) {
+                if (valid) gv += (Gin + (size_t)bh * N + c0)[l];
             }
+            ginv[w][l] = LD > D && !ADD ? 1.f : 1.f / gv;
             if (w == 0 && G && valid) (Gp + c0)[l] = gv;
         }
         __builtin_amdgcn_wave_barrier();
@@ -627,11 +646,11 @@ __global__ __launch_bounds__(4 * D, 2) void ks_fwd_apply(
             if (LD < D && w * 16 >= LD) break;  // columns that are not there
             const int nrows = (int)(row1 - c0) - m * 16;
             float *fr = RAW32 ? Fraw + ((size_t)bh * N + c0 + m * 16) * D : nullptr;
-            if (RAW32 && (xflags & XF_RAW))
+            if (RAW32 && !ADD)
                 store_block<float>(fr, D, w * 16, nrows, l, y[0], y[1], y[2], y[3]);
             else
                 store_block<TIO>(Op + (size_t)(c0 + m * 16) * LD, LD, w * 16, nrows, l, y[0], y[1], y[2],
-                                 y[3], (LD > D && (xflags & XF_ACC)) ? 2 : 0, &ginv[w][m * 16], fr, D);
+                                 y[3], ADD, old[m], &ginv[w][m * 16]);
         }
         pacc += step_product<LV, 1>(vf, one);
         bf8v kf[LQ];
@@ -669,14 +688,14 @@ __global__ __launch_bounds__(4 * D, 2) void ks_fwd_apply(
 // The rows are cut as fills the chip best, rows_wg a workgroup, whatever the segments were; the
 // state is split into planes once.  Bound by memory and by what a workgroup needs before its first
 // row (the 4 D^2 bytes of the state, out of L2).  bf16 stages 64 rows between its two barriers.
-// LD > D, xflags, Gin and Fraw as above.
+// LD > D, ADD, Gin and Fraw as above.
 // ---------------------------------------------------------------------------
-template <int MODE, int D, int LD>
+template <int MODE, int D, int LD, bool ADD>
 __global__ __launch_bounds__(4 * D, 2) void ks_fwd_read(
     const typename Mode<MODE>::TIO *__restrict__ Q, typename Mode<MODE>::TIO *__restrict__ O,
     float *__restrict__ G, const float *__restrict__ ws, float *__restrict__ saved, int N, int nseg,
     int nwg, int rows_wg, int lo_rows, size_t slot_floats, size_t saved_floats, float a, float b,
-    int xflags, const float *__restrict__ Gin, float *__restrict__ Fraw)
+    const float *__restrict__ Gin, float *__restrict__ Fraw)
 {
     typedef Mode<MODE> MD;
     typedef typename MD::TIO TIO;
@@ -737,6 +756,18 @@ __global__ __launch_bounds__(4 * D, 2) void ks_fwd_read(
         if constexpr (LQ == 1) sets[i].template store<true, 1>(lds + i * PL);
         else CH::template store_values<true, LQ>(lds, x);
     };
+    f4v old[NT][2] = {};  // numerators that the launch before left
+    const auto request_old = [&](long c0) __attribute__((always_inline)) {
+        if constexpr (!ADD) return;
+#pragma unroll
+        for (int i = 0; i < NT; ++i)
+#pragma unroll
+            for (int m = 0; m < 2; ++m) {
+                const long r = c0 + i * CR + m * 16;
+                if constexpr (ADD && RAW32) old[i][m] = load_block(Fraw + ((size_t)bh * N + r) * D, D, w * 16, (int)(row1 - r), l);
+                else if constexpr (ADD) old[i][m] = load_block(Op + (size_t)r * LD, LD, w * 16, (int)(row1 - r), l);
+            }
+    };
     auto rows = [&](long c0, int i) __attribute__((always_inline)) {
         f4v fh[2], fl[2];  // rows j = 16w + 4g + e, columns i
 #pragma unroll
@@ -752,17 +783,18 @@ __global__ __launch_bounds__(4 * D, 2) void ks_fwd_read(
             if (LD < D && w * 16 >= LD) break;  // columns that are not there
             const int nrows = (int)(row1 - c0) - m * 16;
             float *fr = RAW32 ? Fraw + ((size_t)bh * N + c0 + m * 16) * D : nullptr;
-            if (RAW32 && (xflags & XF_RAW))
+            if (RAW32 && !ADD)
                 store_block<float>(fr, D, w * 16, nrows, l, y[0], y[1], y[2], y[3]);
             else
                 store_block<TIO>(Op + (size_t)(c0 + m * 16) * LD, LD, w * 16, nrows, l, y[0], y[1], y[2],
-                                 y[3], (LD > D && (xflags & XF_ACC)) ? 2 : 0, &ginv[w][r], fr, D);
+                                 y[3], ADD, old[i][m], &ginv[w][r]);
         }
     };
     for (long c0 = row0; c0 < row1; c0 += NT * CR) {
         const bool two = NT == 2 && c0 + CR < row1;
         block_sync();  // zs is written; every wave is done with the tiles, qzs and the factors
         put(0);
+        request_old(c0);  // ahead of the next rows: loads are waited for in order
         if (NT == 2) sets[0].load(Qp, min(c0 + 2 * CR, c_last), N);
         if (two) put(NT - 1);
         block_sync();
@@ -770,12 +802,10 @@ __global__ __launch_bounds__(4 * D, 2) void ks_fwd_read(
         if (l < (two ? 2 * CR : CR)) {
             float gv = b * qzs[l] + a * (float)N;
             const bool valid = l < (int)(row1 - c0);
-            if constexpr (LD > D) {
-                if ((xflags & XF_ACC) && valid) gv += (Gin + (size_t)bh * N + c0)[l];
-                ginv[w][l] = (xflags & XF_RAW) ? 1.f : 1.f / gv;
-            } else {
-                ginv[w][l] = 1.f / gv;
+            if constexpr (ADD) {
+                if (valid) gv += (Gin + (size_t)bh * N + c0)[l];
             }
+            ginv[w][l] = LD > D && !ADD ? 1.f : 1.f / gv;
             if (w == 0 && G && valid) (Gp + c0)[l] = gv;
         }
         __builtin_amdgcn_wave_barrier();
@@ -790,17 +820,17 @@ __global__ __launch_bounds__(4 * D, 2) void ks_fwd_read(
 //   dQ_c = diag(b / g) (tril(Cm') K_c + dO_c S^T - dprime z^T);  then S += K_c^T V_c, z += sum k
 //   R += (Q/g)_c^T dO_c,  u += sum dprime (q/g),  w += sum dO / g
 // The state is held transposed (rows j, columns r): the product contracts over j.
-// LD > D: xflags & 1 marks the second of the two launches that build dQ up; handed as in BlockPass.
+// LD > D: ADD marks the second of the two launches that build dQ up; handed as in BlockPass.
 // fp32 at D = 128 without the mask holds S^T, R and two chunks in 256 registers but for 6 to 10, which
 // go to scratch once a chunk (a state in its accumulators less would cost a pass over Q and dO).
 // ---------------------------------------------------------------------------
-template <int MODE, int D, bool CAUSAL, int LD>
+template <int MODE, int D, bool CAUSAL, int LD, bool ADD>
 __global__ __launch_bounds__(4 * D, 2) void ks_bwd_dq(
     const typename Mode<MODE>::TIO *__restrict__ Q, const typename Mode<MODE>::TIO *__restrict__ K,
     const typename Mode<MODE>::TIO *__restrict__ V, const typename Mode<MODE>::TIO *__restrict__ O,
     const float *__restrict__ G, const typename Mode<MODE>::TIO *__restrict__ dO,
     typename Mode<MODE>::TIO *__restrict__ dQ, float *ws, const float *sinit, size_t sinit_floats,
-    float *__restrict__ dprime, int N, int nseg, SegMap sm, size_t slot_floats, int fold, float b, int xflags,
+    float *__restrict__ dprime, int N, int nseg, SegMap sm, size_t slot_floats, int fold, float b,
     float *__restrict__ Pq, const int *__restrict__ handed)
 {
     typedef Mode<MODE> MD;
@@ -915,6 +945,13 @@ __global__ __launch_bounds__(4 * D, 2) void ks_bwd_dq(
         }
         block_sync();
         const long cn = min(c0 + MD::DEPTH * CR, c_last);
+        f4v old[2] = {};  // shares that the launch before left
+        if constexpr (ADD) {
+#pragma unroll
+            for (int m = 0; m < 2; ++m)
+                old[m] = load_grad<SWAP, D, LD>(dQp + (size_t)(c0 + m * 16) * LD, Pq + ((size_t)bh * N + c0 + m * 16) * D,
+                                                w, (int)(row1 - c0) - m * 16, l);
+        }
         // Under a branch the load stays here; as a plain load the compiler moves it into post_factors, behind this
         // chunk's stores, where the first wave waits for both.  Time of the sweep under a branch: fp32 without the
         // mask - 3 % (D = 64, 64 x 16384) and - 8 % (D = 32, 64 x 8192), bf16 with it - 1.5 % (D = 64, 36 x 5003); bf16
@@ -962,8 +999,8 @@ __global__ __launch_bounds__(4 * D, 2) void ks_bwd_dq(
 #pragma unroll
         for (int m = 0; m < 2; ++m)
             store_grad<SWAP, D, LD>(dQp + (size_t)(c0 + m * 16) * LD,
-                                    Pq + ((size_t)bh * N + c0 + m * 16) * D, xflags & 1, w,
-                                    (int)(row1 - c0) - m * 16, l, x[m]);
+                                    Pq + ((size_t)bh * N + c0 + m * 16) * D, ADD, w,
+                                    (int)(row1 - c0) - m * 16, l, x[m], old[m]);
         if constexpr (CAUSAL) {
             cur.q.load(Qp, cn, N);
             if constexpr (MD::RN) {
@@ -1034,7 +1071,7 @@ __global__ __launch_bounds__(8 * D, 4) void ks_bwd_dq_halves(
     const typename Mode<MODE>::TIO *__restrict__ V, const typename Mode<MODE>::TIO *__restrict__ O,
     const float *__restrict__ G, const typename Mode<MODE>::TIO *__restrict__ dO,
     typename Mode<MODE>::TIO *__restrict__ dQ, float *ws, const float *sinit, size_t sinit_floats,
-    float *__restrict__ dprime, int N, int nseg, SegMap sm, size_t slot_floats, int fold, float b, int xflags,
+    float *__restrict__ dprime, int N, int nseg, SegMap sm, size_t slot_floats, int fold, float b,
     float *__restrict__ Pq, const int *)
 {
     typedef Mode<MODE> MD;
@@ -1220,8 +1257,8 @@ __global__ __launch_bounds__(8 * D, 4) void ks_bwd_dq_halves(
 #pragma unroll
             for (int m = 0; m < 2; ++m)
                 store_grad<SWAP, D, LD>(dQp + (size_t)(c0 + m * 16) * LD,
-                                        Pq + ((size_t)bh * N + c0 + m * 16) * D, xflags & 1, w,
-                                        (int)(row1 - c0) - m * 16, l, x[m]);
+                                        Pq + ((size_t)bh * N + c0 + m * 16) * D, false, w,
+                                        (int)(row1 - c0) - m * 16, l, x[m], f4v{});
             request(cur, cn, false, true);
             if constexpr (MD::RN) {
                 bf8v fk[3], kh[3];
@@ -1266,9 +1303,9 @@ __global__ __launch_bounds__(8 * D, 4) void ks_bwd_dq_halves(
 // Four waves a SIMD instead of two that hold both states: more of what the waves issue and wait for in turn
 // overlaps (fp32, D = 64: vector ALU 30 -> 38 %, LDS 38 -> 46 %, matrix pipe 31 -> 38 % of the clocks; times at the
 // top).  Half the registers a wave have to do (TIGHT).
-// LD > D: xflags & 2 (dK), & 4 (dV) mark the second of the two launches that build them up.
+// LD > D: xflags & 2 (dK), & 4 (dV) mark the second of the two launches that build them up (ADD: either).
 // ---------------------------------------------------------------------------
-template <int MODE, int D, int LD>
+template <int MODE, int D, int LD, bool ADD>
 __global__ __launch_bounds__(8 * D, 4) void ks_bwd_dkv(
     const typename Mode<MODE>::TIO *__restrict__ Q, const typename Mode<MODE>::TIO *__restrict__ K,
     const typename Mode<MODE>::TIO *__restrict__ V, const float *__restrict__ G,
@@ -1398,6 +1435,17 @@ __global__ __launch_bounds__(8 * D, 4) void ks_bwd_dkv(
         }
         block_sync();
         const long cn = row0 + max(ci - DEPTH, 0L) * CR;
+        const auto out = [&] { return (half ? dV : dK) + base + (size_t)c0 * LD; };
+        const auto part = [&] { return (half ? Pv : Pk) + ((size_t)bh * N + c0) * D; };
+        f4v old[2] = {};  // shares that the launch before left
+        if constexpr (ADD) {
+            if (xflags & (half ? 4 : 2)) {
+#pragma unroll
+                for (int m = 0; m < 2; ++m)
+                    old[m] = load_grad<SWAP, D, LD>(out() + (size_t)(m * 16) * LD, part() + m * 16 * D, w,
+                                                    (int)(row1 - c0) - m * 16, l);
+            }
+        }
         request(cur, cn, true, false);
 
         go_first<D>(wv < 6);
@@ -1439,12 +1487,10 @@ __global__ __launch_bounds__(8 * D, 4) void ks_bwd_dkv(
             else
                 project_chunk<SWAP, true, D, L>(x, Kt, ln, QT ? nullptr : kinv, dots, kinv, w, c, g);
         }
-        TIO *out = (half ? dV : dK) + base + (size_t)c0 * LD;
-        float *part = (half ? Pv : Pk) + ((size_t)bh * N + c0) * D;
 #pragma unroll
         for (int m = 0; m < 2; ++m)
-            store_grad<SWAP, D, LD>(out + (size_t)(m * 16) * LD, part + m * 16 * D, xflags & (half ? 4 : 2), w,
-                                    (int)(row1 - c0) - m * 16, l, x[m]);
+            store_grad<SWAP, D, LD>(out() + (size_t)(m * 16) * LD, part() + m * 16 * D, ADD && (xflags & (half ? 4 : 2)), w,
+                                    (int)(row1 - c0) - m * 16, l, x[m], old[m]);
         bf8v fac[3];
         load_factor<3>(fac, half ? frs[par] : fdl[par], g);
         vec.add(own, fac);
@@ -1475,7 +1521,7 @@ __global__ __launch_bounds__(8 * D, 4) void ks_bwd_dkv(
 // natural tiles; two chunks requested ahead.  Half the LDS reads of 16 columns a wave (LDS 33 -> 25 % of the
 // clocks); waits are what is left (43 % of a wave's life).
 // ---------------------------------------------------------------------------
-template <int D, int LD>
+template <int D, int LD, bool ADD>
 __global__ __launch_bounds__(4 * D, 2) void ks_bwd_dkv_wide(
     const __bf16 *__restrict__ Q, const __bf16 *__restrict__ K, const __bf16 *__restrict__ V,
     const float *__restrict__ G, const __bf16 *__restrict__ dO, __bf16 *__restrict__ dK, __bf16 *__restrict__ dV,
@@ -1569,6 +1615,11 @@ __global__ __launch_bounds__(4 * D, 2) void ks_bwd_dkv_wide(
         put(cur.d, dOt);
         block_sync();
         const long cn = row0 + max(ci - 2, 0L) * CR;
+        f16v old = zero16();  // shares that the launch before left
+        if constexpr (ADD) {
+            if (xflags & (half ? 4 : 2))
+                old = load_cols32((half ? Pv : Pk) + ((size_t)bh * N + c0) * D, D, 32 * w, (int)(row1 - c0), l);
+        }
         cur.k.load(Kp, cn, N);
         cur.v.load(Vp, cn, N);
         request_gd(row0 + max(ci - 1, 0L) * CR);
@@ -1601,8 +1652,14 @@ __global__ __launch_bounds__(4 * D, 2) void ks_bwd_dkv_wide(
 #pragma unroll
             for (int e = 0; e < 4; ++e) f[4 * q + e] = b * f[4 * q + e] + (ys * y[4 * q + e] + vs * vq[e]);
         }
+        if constexpr (ADD) {
+            if (xflags & (half ? 4 : 2)) {
+                keep_branch();
+                f += old;
+            }
+        }
         store_grad32<D, LD>((half ? dV : dK) + base + (size_t)c0 * LD, (half ? Pv : Pk) + ((size_t)bh * N + c0) * D,
-                            xflags & (half ? 4 : 2), 32 * w, (int)(row1 - c0), l, f);
+                            ADD && (xflags & (half ? 4 : 2)), 32 * w, (int)(row1 - c0), l, f);
         vec += weighted_sum(own, half ? frs[par] : fdl[par], h);
         vecs[half * D + 32 * w + c] = vec;
         with_planes<LX>(lo_on, [&](auto np) {
@@ -1623,7 +1680,7 @@ __global__ __launch_bounds__(4 * D, 2) void ks_bwd_dkv_wide(
 // over the whole sequence.
 // LD > D: xflags as above.
 // ---------------------------------------------------------------------------
-template <int MODE, int D, int LD>
+template <int MODE, int D, int LD, bool ADD>
 __global__ __launch_bounds__(4 * D, 2) void ks_bwd_dkv_read(
     const typename Mode<MODE>::TIO *__restrict__ K, const typename Mode<MODE>::TIO *__restrict__ V,
     typename Mode<MODE>::TIO *__restrict__ dK, typename Mode<MODE>::TIO *__restrict__ dV,
@@ -1681,6 +1738,16 @@ __global__ __launch_bounds__(4 * D, 2) void ks_bwd_dkv_read(
         if (__builtin_expect(cur.v.top() > kLargestBf16, 0)) cur.v.template store_any<true>(Vt);
         block_sync();
         const long cn = row0 + max(ci - MD::DEPTH, 0L) * CR;
+        f4v oldk[2] = {}, oldv[2] = {};  // shares that the launch before left
+        if constexpr (ADD) {
+#pragma unroll
+            for (int m = 0; m < 2; ++m) {
+                const size_t at = (size_t)(c0 + m * 16) * LD, pat = ((size_t)bh * N + c0 + m * 16) * D;
+                const int nrows = (int)(row1 - c0) - m * 16;
+                if (xflags & 2) oldk[m] = load_grad<SWAP, D, LD>(dKp + at, Pk + pat, w, nrows, l);
+                if (xflags & 4) oldv[m] = load_grad<SWAP, D, LD>(dVp + at, Pv + pat, w, nrows, l);
+            }
+        }
         cur.k.load(Kp, cn, N);
         cur.v.load(Vp, cn, N);
         f4v kh[2], kl[2];  // rows n, columns r (SWAP), or rows r, columns n
@@ -1695,8 +1762,8 @@ __global__ __launch_bounds__(4 * D, 2) void ks_bwd_dkv_read(
 #pragma unroll
         for (int m = 0; m < 2; ++m)
             store_grad<SWAP, D, LD>(dKp + (size_t)(c0 + m * 16) * LD,
-                                    Pk + ((size_t)bh * N + c0 + m * 16) * D, xflags & 2, w,
-                                    (int)(row1 - c0) - m * 16, l, x[m]);
+                                    Pk + ((size_t)bh * N + c0 + m * 16) * D, ADD && (xflags & 2), w,
+                                    (int)(row1 - c0) - m * 16, l, x[m], oldk[m]);
         f4v vh[2], vl[2];  // rows n, columns j (SWAP), or rows j, columns n
 #pragma unroll
         for (int m = 0; m < 2; ++m) vh[m] = vl[m] = f4v{0.f, 0.f, 0.f, 0.f};
@@ -1705,8 +1772,8 @@ __global__ __launch_bounds__(4 * D, 2) void ks_bwd_dkv_read(
         for (int m = 0; m < 2; ++m) {
             const f4v f = a * wacc.v + (MD::RN ? b * kinv[m * 16 + c] : b) * (vh[m] + vl[m]);
             store_grad<SWAP, D, LD>(dVp + (size_t)(c0 + m * 16) * LD,
-                                    Pv + ((size_t)bh * N + c0 + m * 16) * D, xflags & 4, w,
-                                    (int)(row1 - c0) - m * 16, l, f);
+                                    Pv + ((size_t)bh * N + c0 + m * 16) * D, ADD && (xflags & 4), w,
+                                    (int)(row1 - c0) - m * 16, l, f, oldv[m]);
         }
     };
     for (long ci = nchunks - 1; ci >= 0; ci -= MD::DEPTH) {
@@ -1763,36 +1830,40 @@ la_status run_forward(const Problem &pr, const Plan &pl, const void *Qv, const v
         }
     }
     if (pr.causal) {
-        ks_fwd_apply<MODE, D, LD><<<dim3(pr.BH * nseg), block, 0, st>>>(
+        auto *apply = ks_fwd_apply<MODE, D, LD, false>;
+        if (LD > D && (xflags & XF_ACC)) apply = ks_fwd_apply<MODE, D, LD, (LD > D)>;
+        apply<<<dim3(pr.BH * nseg), block, 0, st>>>(
             Q, K, V, O, G, ws, saved, pr.N, nseg, pl.map, pl.slot_floats, fold, pl.saved_floats, pr.a, pr.b,
-            xflags, Gin, Fraw);
+            Gin, Fraw);
     } else {
         const int rows_wg = read_rows(pr.BH, pr.N, D), nwg = (pr.N + rows_wg - 1) / rows_wg;
-        ks_fwd_read<MODE, D, LD><<<dim3(pr.BH * nwg), block, 0, st>>>(
+        auto *read = ks_fwd_read<MODE, D, LD, false>;
+        if (LD > D && (xflags & XF_ACC)) read = ks_fwd_read<MODE, D, LD, (LD > D)>;
+        read<<<dim3(pr.BH * nwg), block, 0, st>>>(
             Q, O, G, ws, saved, pr.N, nseg, nwg, rows_wg, pl.map.lo_rows, pl.slot_floats,
-            pl.saved_floats, pr.a, pr.b, xflags, Gin, Fraw);
+            pl.saved_floats, pr.a, pr.b, Gin, Fraw);
     }
     tc.mark("fwd_apply");
     return launch_status();
 }
 
 // The ascending masked sweep: two halves of a workgroup at D = 32, one kind of waves beyond.
-template <int MODE, int D, int LD>
+template <int MODE, int D, int LD, bool ADD>
 constexpr auto ks_bwd_dq_masked()
 {
     if constexpr (D == 32) return ks_bwd_dq_halves<MODE, D, LD>;
-    else return ks_bwd_dq<MODE, D, true, LD>;
+    else return ks_bwd_dq<MODE, D, true, LD, ADD>;
 }
 
 // The descending masked sweep: 32 columns a wave for bf16 at D = 128, whose tiles and states leave room for
 // it (us, 32 columns and 16 with four waves a SIMD, medians of six runs: 128 slices of 2048 rows 109 and 118, 16
 // of 131072 825 and 911, 64 of 500 31.0 and 32.5; a step at head size 256, 64 of 4096, 1596 and 1609).  fp32 at D = 128 is within 2 % either way; at D = 64 the four waves are faster (bf16, 36 slices
 // of 5003 rows 30.0 against 34.2).
-template <int MODE, int D, int LD>
+template <int MODE, int D, int LD, bool ADD>
 constexpr auto ks_bwd_dkv_masked()
 {
-    if constexpr (MODE == P16 && D == 128) return ks_bwd_dkv_wide<D, LD>;
-    else return ks_bwd_dkv<MODE, D, LD>;
+    if constexpr (MODE == P16 && D == 128) return ks_bwd_dkv_wide<D, LD, ADD>;
+    else return ks_bwd_dkv<MODE, D, LD, ADD>;
 }
 
 // dK == nullptr: the ascending sweep alone (dQ and the per-row o . dO).
@@ -1826,10 +1897,13 @@ la_status run_backward(const Problem &pr, const Plan &pl, const void *Qv, const 
     }
     const float *sinit = saved ? saved : ws;
     const size_t sinit_floats = saved ? pl.saved_floats : pl.slot_floats;
-    auto *dq = !pr.causal ? ks_bwd_dq<MODE, D, false, LD> : ks_bwd_dq_masked<MODE, D, LD>();
+    constexpr bool ADDS = LD > D;  // some launches add to what others left
+    auto *dq = !pr.causal ? ks_bwd_dq<MODE, D, false, LD, false> : ks_bwd_dq_masked<MODE, D, LD, false>();
+    if (ADDS && (bp.xflags & 1))
+        dq = !pr.causal ? ks_bwd_dq<MODE, D, false, LD, ADDS> : ks_bwd_dq_masked<MODE, D, LD, ADDS>();
     dq<<<grid, pr.causal && D == 32 ? block2 : block, 0, st>>>(
         Q, K, V, O, G, dO, dQ, ws, sinit, sinit_floats, dprime, pr.N, nseg, pl.map, pl.slot_floats,
-        fold && !saved, pr.b, bp.xflags, bp.Pq, bp.handed);
+        fold && !saved, pr.b, bp.Pq, bp.handed);
     tc.mark("bwd_dq");
     if (!dK) return launch_status();
     // reverse-running sums left by the ascending sweep
@@ -1839,12 +1913,15 @@ la_status run_backward(const Problem &pr, const Plan &pl, const void *Qv, const 
         tc.mark("scan_slots_rev");
     }
     if (pr.causal) {
-        auto *dkv = ks_bwd_dkv_masked<MODE, D, LD>();
+        auto *dkv = ks_bwd_dkv_masked<MODE, D, LD, false>();
+        if (ADDS && (bp.xflags & 6)) dkv = ks_bwd_dkv_masked<MODE, D, LD, ADDS>();
         dkv<<<grid, MODE == P16 && D == 128 ? block : block2, 0, st>>>(
             Q, K, V, G, dO, dK, dV, ws, dprime, pr.N, nseg, pl.map, pl.slot_floats, fold, pr.a, pr.b, bp.xflags,
             bp.Pk, bp.Pv);
     } else {
-        ks_bwd_dkv_read<MODE, D, LD><<<grid, block, 0, st>>>(K, V, dK, dV, ws, pr.N, nseg, pl.map, pl.slot_floats,
+        auto *dkv = ks_bwd_dkv_read<MODE, D, LD, false>;
+        if (ADDS && (bp.xflags & 6)) dkv = ks_bwd_dkv_read<MODE, D, LD, ADDS>;
+        dkv<<<grid, block, 0, st>>>(K, V, dK, dV, ws, pr.N, nseg, pl.map, pl.slot_floats,
                                                              pr.a, pr.b, bp.xflags, bp.Pk, bp.Pv);
     }
     tc.mark("bwd_dkv");

@@ -232,24 +232,11 @@ __device__ __forceinline__ void scale_own(bf8v (&o)[2][L], const bf8v (&f)[2][1]
 
 // ---- outputs -----------------------------------------------------------------------------------
 // Accumulator rows = columns col0 .., columns = the chunk's rows, of which `rows` exist.  bf16: the
-// halves of the wave exchange quads so that a lane stores eight columns; `old` (fp32, rows of old_ld,
-// the same columns), if given, is added first, so that the sum is rounded once.
+// halves of the wave exchange quads so that a lane stores eight columns.
 __device__ __forceinline__ int chunk_rows(int n) { return __builtin_amdgcn_readfirstlane(n < 0 ? 0 : (n > CR ? CR : n)); }
-__device__ __forceinline__ void store_cols32(__bf16 *base, int ld, int col0, int rows, int l, f16v x,
-                                             const float *old = nullptr, int old_ld = 0)
+__device__ __forceinline__ void store_cols32(__bf16 *base, int ld, int col0, int rows, int l, const f16v &x)
 {
     const int n = chunk_rows(rows), c = l % 32, h = l / 32;
-    if (old) {
-        const __amdgpu_buffer_rsrc_t r32 =
-            __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(old), 0, n * old_ld * 4, kBufferFlags);
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const u4v o = __builtin_amdgcn_raw_buffer_load_b128(
-                r32, (c * old_ld + col0 + 4 * h + 8 * q) * 4, 0, 0);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) x[4 * q + e] += __uint_as_float(o[e]);
-        }
-    }
     const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(base, 0, n * ld * 2, kBufferFlags);
     const int off = (c * ld + col0 + 8 * h) * 2;
 #pragma unroll
@@ -271,15 +258,30 @@ __device__ __forceinline__ void store_cols32(float *base, int ld, int col0, int 
     for (int q = 0; q < 4; ++q)
         __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4v, quad_of(x, q)), rsrc, off + 32 * q, 0, 0);
 }
+// What they hold in fp32, in the same layout.
+__device__ __forceinline__ f16v load_cols32(const float *base, int ld, int col0, int rows, int l)
+{
+    const __amdgpu_buffer_rsrc_t rsrc =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(base), 0, chunk_rows(rows) * ld * 4, kBufferFlags);
+    const int off = (l % 32 * ld + col0 + 4 * (l / 32)) * 4;
+    f16v x;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const f4v o = __builtin_bit_cast(f4v, __builtin_amdgcn_raw_buffer_load_b128(rsrc, off + 32 * q, 0, 0));
+#pragma unroll
+        for (int e = 0; e < 4; ++e) x[4 * q + e] = o[e];
+    }
+    return x;
+}
 // One chunk of a gradient, 32 columns.  LD > D builds it up over two launches, the first of which leaves
-// its share in `part` (fp32, rows of D).
+// its share in `part` (fp32, rows of D); the second (`add`) has added it to x.
 template <int D, int LD>
 __device__ __forceinline__ void store_grad32(__bf16 *out, float *part, bool add, int col0, int rows, int l,
                                              const f16v &x)
 {
     if constexpr (LD <= D) store_cols32(out, LD, col0, rows, l, x);
     else if (!add) store_cols32(part, D, col0, rows, l, x);
-    else store_cols32(out, LD, col0, rows, l, x, part, D);
+    else store_cols32(out, LD, col0, rows, l, x);
 }
 
 }  // namespace
