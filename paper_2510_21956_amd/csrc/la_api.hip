@@ -38,6 +38,7 @@ static long segment_rows(long BH, int N, int D, la_dtype dt, int causal, Cut cut
 {
     const long step = dt == LA_F32 ? 32 : 64, resident = D >= 128 ? 1 : D == 64 ? 2 : 4;
     const long kernels = dt == LA_F32 ? (D >= 128 ? 64 : 32) : (D >= 128 || !causal ? 192 : 64);
+    BH *= cut.problems;
     const long most = cut.min_rows ? max(N / cut.min_rows, 1) : (N + step - 1) / step;
     const auto cost = [&](long rows) {
         const long load = (BH * ((N + rows - 1) / rows) + 255) / 256, rounds = (load + resident - 1) / resident;
@@ -148,10 +149,10 @@ static la_status check_shape(int B, int H, int N, int D, la_dtype dt)
     return LA_OK;
 }
 
-// The launch grid is slices x segments in one int.
+// The launch grid is slices x segments (x blocks at D = 256) in one int.
 static bool grid_ok(int B, int H, const Plan &pl)
 {
-    return (double)B * H * pl.nseg <= 2147483647.0;
+    return (double)B * H * pl.nseg * (pl.slot_floats >= 65536 ? 4 : 1) <= 2147483647.0;
 }
 
 static bool aligned16(const void *p) { return (((uintptr_t)p) & 15u) == 0; }

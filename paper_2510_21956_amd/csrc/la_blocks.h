@@ -195,9 +195,6 @@ struct BwdSlot {
                          END = 2 * D * D + 3 * D;
 };
 
-// Flags of the launches that build O up at head size 256 (see ks_fwd_apply).
-constexpr int XF_RAW = 1, XF_ACC = 2;
-
 inline la_status launch_status()
 {
     return hipGetLastError() == hipSuccess ? LA_OK : LA_ERR_LAUNCH;

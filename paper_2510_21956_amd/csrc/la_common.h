@@ -104,12 +104,14 @@ struct Plan {
     // whole sequence (without).
     size_t saved_floats;
     size_t saved_bytes;
+    bool together = true;  // D = 256: the four block problems share launches (split_scratch)
 };
 
 // How finely sequences are cut (segment_rows in la_api.hip): min_rows a segment at least (0: the shortest there
 // are), `rounds` times as many segments at most as the compute units hold at once.
 struct Cut {
     int min_rows = 0, rounds = 3;
+    int problems = 1;  // problems of this size that share a launch
 };
 constexpr Cut kCoarse{192, 1};
 // pad16: D = 16 on the tiles of D = 32 (else on the plain-ALU kernels).
@@ -118,7 +120,9 @@ Plan make_plan(int B, int H, int N, int D, la_dtype dt, int causal, int is_backw
 // The plan of the D = 128 passes of a D = 256 problem.
 inline Plan block_plan(int B, int H, int N, la_dtype dt, int causal, int is_backward, Cut cut = Cut())
 {
-    return make_plan(B, H, N, 128, dt, causal, is_backward, true, Cut{cut.min_rows, 1});
+    Plan p = make_plan(B, H, N, 128, dt, causal, is_backward, true, Cut{cut.min_rows, 1, cut.min_rows ? 1 : 2});
+    p.together = !cut.min_rows;
+    return p;
 }
 
 struct Problem {
@@ -154,32 +158,35 @@ struct Tracer {
 // element-wise over floats [off, off+len) of each slot, over slots lo..hi.
 //   mode 0: slot[s] += slot[s-1], s = lo+1..hi;  mode 1: slot[s] += slot[s+1], s = hi-1..lo;
 //   mode 2: slot[0] = sum of slots lo..hi.
-// skip (may be null), one int a slice on the device: slices with a nonzero one are left out.
+// skip (may be null), one int for each of skip_slices slices on the device, over and over: slices with a nonzero
+// one are left out.
 void launch_scan_slots(float *ws, int BH, int nseg, size_t slot_floats, int off, int len, int mode,
-                       int lo, int hi, hipStream_t st, const int *skip = nullptr);
+                       int lo, int hi, hipStream_t st, const int *skip = nullptr, int skip_slices = 1);
 
-// Matrix-core kernels (la_split.hip): D = 16 (on the tiles of 32), 32, 64, 128 (ld == D), or 128
-// columns of rows ld = 256 wide, one of several launches that build the results up (without
-// normalisation): xflags, Gin, Fraw and BlockPass as in split_forward / split_backward.
-// `saved` (may be null) is the forward-to-backward hand-over buffer described in Plan.
+// Matrix-core kernels (la_split.hip): D = 16 (on the tiles of 32), 32, 64, 128 (ld == D), or the four block
+// problems of 128 columns of rows ld = 256 wide (without normalisation; pr.D = 128), for which BlockScratch names
+// the scratch of split_scratch.
+// `saved` (may be null) is the forward-to-backward hand-over buffer described in Plan, ld = 256: those of the four
+// block problems one after another.
 // dK == nullptr: the ascending sweep alone, dQ for the coefficients in pr.
 // planes_totals: the per-segment sums over the whole sequence, S = sum k v^T, z = sum k, p = sum v,
-// in the slots of every slice as [S | z | p] (forward plan without the mask); state_from_totals adds
-// the slots up.
+// in the slots of every slice as [S | z | p] (forward plan without the mask), ld = 256: those of the four block
+// problems one after another; state_from_totals adds the slots up.
 // `handed` (one int a slice on the device; null: `saved` holds whenever it is given): the slices whose sums
 // in `saved` hold; the sums of the others are formed in the workspace, as without `saved`.
-struct BlockPass {
-    int xflags = 0;
-    float *Pq = nullptr, *Pk = nullptr, *Pv = nullptr;
+struct BlockScratch {
+    bool together = true;                 // every block problem has slots of its own
+    float *g = nullptr, *f = nullptr;     // forward
+    float *q = nullptr, *k = nullptr, *v = nullptr, *delta = nullptr;  // backward
     const int *handed = nullptr;
 };
 la_status planes_forward(const Problem &pr, const Plan &pl, int ld, const void *Q, const void *K,
                          const void *V, void *O, float *G, float *ws, float *saved, hipStream_t st,
-                         Tracer &tc, int xflags = 0, const float *Gin = nullptr, float *Fraw = nullptr);
+                         Tracer &tc, const BlockScratch &bs = BlockScratch());
 la_status planes_backward(const Problem &pr, const Plan &pl, int ld, const void *Q, const void *K,
                           const void *V, const void *O, const float *G, const void *dO, void *dQ,
                           void *dK, void *dV, float *ws, const float *saved, hipStream_t st,
-                          Tracer &tc, const BlockPass &bp = BlockPass());
+                          Tracer &tc, const BlockScratch &bs = BlockScratch());
 la_status planes_totals(const Problem &pr, const Plan &pl, int ld, const void *K, const void *V,
                         float *ws, hipStream_t st);
 
@@ -209,37 +216,40 @@ la_status state_block_from_totals(const float *ws, float *state, int BH, int nse
 la_status state_from_totals(const float *ws, float *state, int BH, int D, int nseg,
                             size_t slot_floats, int N, int accumulate, hipStream_t st);
 
-// Head size 256 as passes of the D = 128 matrix-core kernels over column blocks of the
-// 256-wide rows (la_fast.hip); `pl` is the plan of the D = 128 problem.  dK == nullptr runs
-// the ascending sweeps (dQ) only.
-// What split_forward / split_backward keep behind the D = 128 plan's workspace (offsets and
-// total in floats, T = token-heads).  Forward: one float per token-head (g_off) and, for bf16
-// tensors, 128 (f_off).  Backward, bf16 tensors only: 128 each for the dQ and dK block in
-// progress (q_off, k_off) and 2 x 128 for the two dV blocks (v_off); behind them one int a slice
-// (flag_off, BlockPass::handed).
+// Head size 256 on the D = 128 matrix-core kernels over column blocks of the 256-wide rows (la_fast.hip);
+// `pl` is the plan of the D = 128 problem.  dK == nullptr runs the ascending sweeps (dQ) only.
+// What split_forward / split_backward keep in the workspace (offsets and total in floats, T = token-heads): the
+// slots of the four block problems, one after another (of one, where the problems run one after another: not
+// `together`); forward, one float per token-head (g_off) and, for bf16 tensors, 128 for each column block of V
+// (f_off); backward, two floats per token-head (delta_off) and, for bf16 tensors, 128 for each column block of dQ
+// (q_off), dK (k_off) and dV (v_off); behind them one int a slice (flag_off, BlockScratch::handed).
 struct SplitScratch {
-    size_t g_off, f_off, q_off, k_off, v_off, flag_off, total_floats;
+    bool together;
+    size_t g_off, f_off, delta_off, q_off, k_off, v_off, flag_off, total_floats;
 };
+inline size_t split_slots(const Plan &pl128, int BH) { return (size_t)BH * pl128.nseg * pl128.slot_floats; }
 inline SplitScratch split_scratch(const Plan &pl128, int BH, int N, la_dtype dt, int is_backward)
 {
     SplitScratch s{};
-    const size_t T = (size_t)BH * N;
-    const size_t base = pl128.total_bytes / sizeof(float), wide = dt == LA_BF16 ? T * 128 : 0;
+    s.together = pl128.together;
+    const size_t T = (size_t)BH * N, wide = dt == LA_BF16 ? T * 128 : 0, rows = (T + 63) / 64 * 64;
+    const size_t base = split_slots(pl128, BH) * (s.together ? 4 : 1);  // slots are a multiple of 64 floats
     if (!is_backward) {
         s.g_off = base;
-        s.f_off = s.g_off + ((T + 63) / 64) * 64;
-        s.total_floats = s.f_off + wide;
+        s.f_off = s.g_off + rows;
+        s.total_floats = s.f_off + (s.together ? 2 : 1) * wide;
     } else {
-        s.q_off = base;
-        s.k_off = s.q_off + wide;
-        s.v_off = s.k_off + wide;
+        s.delta_off = base;
+        s.q_off = s.delta_off + 2 * rows;
+        s.k_off = s.q_off + 2 * wide;
+        s.v_off = s.k_off + 2 * wide;
         s.flag_off = s.v_off + 2 * wide;
         s.total_floats = s.flag_off + BH;
     }
     return s;
 }
-// The decode state of a D = 256 problem (+)= the sums over its N rows of K, V: four passes
-// of the D = 128 sums kernels, each followed by state_block_from_totals.
+// The decode state of a D = 256 problem (+)= the sums over its N rows of K, V: the D = 128 sums kernel on all four
+// blocks, then state_block_from_totals on each.
 la_status split_prefill(const Problem &pr, const Plan &pl, const void *K, const void *V, float *ws,
                         float *state, int accumulate, hipStream_t st);
 // saved (may be null): the hand-over buffers of the four passes one after another, pl.saved_bytes each, and

@@ -1,5 +1,5 @@
-// D = 256 as passes of the D = 128 matrix-core kernels (la_split.hip) over blocks of 128 columns
-// (split_forward, split_backward, split_prefill).
+// D = 256 on the D = 128 matrix-core kernels (la_split.hip), over blocks of 128 columns (split_forward,
+// split_backward, split_prefill).
 #include "la_blocks.h"
 
 namespace la {
@@ -11,21 +11,24 @@ namespace la {
 // and (0, b) for i = 2, g is the sum of their denominators, and likewise
 //   dq_i = sum_j dq(q_i, k_i, v_j; o_j, dO_j, g),   dk_i = sum_j dk(...),   dv_j = sum_i dv(...)
 // where the blocks (o_j, dO_j) and the full g stand for the stored set of the block problem
-// (delta = o . OmegaHat splits over j as well).  Four passes of the D = 128 kernels over column
-// blocks of the 256-wide rows, each adding to what the previous ones left in the outputs.
-// `pl` is the plan of the D = 128 problem; behind that plan's workspace the forward pass keeps
-// the first pass's share of g and, for bf16, its undivided numerator in fp32, and the backward
-// pass, for bf16, the first share of every gradient block in fp32 (split_scratch).  With `saved` every
-// forward pass hands its sums at the segment boundaries to the backward pass on the same blocks, which
-// then forms none (a step without and with, us: 64 slices of 4096 rows, fp32 3568 and 3328, bf16 1661 and 1584; 8 of
-// 8000, bf16 652 and 608).
+// (delta = o . OmegaHat splits over j as well).  The four block problems run on the D = 128 kernels over column
+// blocks of the 256-wide rows and build the outputs up in two launches each: all sums in one launch, all scans in
+// one, then the two block problems that begin the output blocks and the two that add to them (run_forward,
+// run_backward).  What two block problems of a launch read in common is then in the last-level cache, and half
+// the segments fill the chip.  One block problem after another, 12 launches forward and 20 backward, took, a step,
+// us, and take now: 64 slices of 4096 rows, fp32 3029 and 2790, bf16 1425 and 1200, without the mask 1925 and 1820,
+// 1109 and 968; 100 of 400, fp32 631 and 441, bf16 345 and 212; one of 300, bf16 165 and 80.
+// `pl` is the plan of the D = 128 problem; behind the slots the forward pass keeps the first share of g and, for
+// bf16, the undivided numerators in fp32, and the backward pass, for bf16, the first share of every gradient block
+// in fp32 (split_scratch).  la_forward_static, whose scratch may not hold four sets of slots, runs one block problem
+// after another where it does not.  With `saved` the forward pass hands its sums at the segment boundaries to the
+// backward pass, which then forms none.
 //
 // Whether a hand-over buffer holds this problem's sums is for the backward pass to find out: the buffer is
 // optional, and a forward call that was given none (or one it could not use) succeeds all the same.  So the
 // forward pass leaves the last row of every slice's O in it, under a key of the problem, and the backward pass
 // compares that with the O it is given: sums of other inputs, or memory that no forward pass wrote, are passed
-// over, slice by slice.  The sums kernels are launched either way and return at once where the sums hold (20 us
-// a step, witness included).
+// over, slice by slice.  The sums kernel is launched either way and returns at once where the sums hold.
 namespace {
 
 // What the segments and the layout of the sums depend on.
@@ -62,36 +65,23 @@ int row_words(la_dtype dt) { return dt == LA_F32 ? 256 : 128; }
 
 }  // namespace
 
-static const void *col_block(const void *p, int j, la_dtype dt)
-{
-    return (const char *)p + (size_t)128 * j * (dt == LA_F32 ? 4 : 2);
-}
-static void *col_block(void *p, int j, la_dtype dt)
-{
-    return (char *)p + (size_t)128 * j * (dt == LA_F32 ? 4 : 2);
-}
-
 la_status split_prefill(const Problem &pr, const Plan &pl, const void *K, const void *V, float *ws,
                         float *state, int accumulate, hipStream_t st)
 {
     Problem p = pr;
     p.D = 128;
-    for (int i = 0; i < 2; ++i)
-        for (int j = 0; j < 2; ++j) {
-            la_status s = planes_totals(p, pl, 256, col_block(K, i, pr.dt), col_block(V, j, pr.dt), ws, st);
-            if (s != LA_OK) return s;
-            s = state_block_from_totals(ws, state, pr.BH, pl.nseg, pl.slot_floats, i, j, pr.N,
-                                        accumulate, st);
-            if (s != LA_OK) return s;
-        }
-    return LA_OK;
+    la_status s = planes_totals(p, pl, 256, K, V, ws, st);
+    for (int b = 0; b < 4 && s == LA_OK; ++b)
+        s = state_block_from_totals(ws + b * split_slots(pl, pr.BH), state, pr.BH, pl.nseg, pl.slot_floats, b / 2,
+                                    b % 2, pr.N, accumulate, st);
+    return s;
 }
 
-// Hand-over of pass (i, j) inside the buffer of all four; block 4 is the witness.
+// The witness, behind the hand-over buffers of the four block problems.
 template <typename F>
-static F *saved_block(F *saved, const Plan &pl, int block)
+static uint32_t *witness(F *saved, const Plan &pl)
 {
-    return saved ? saved + (size_t)block * (pl.saved_bytes / sizeof(float)) : nullptr;
+    return (uint32_t *)(saved + 4 * (pl.saved_bytes / sizeof(float)));
 }
 
 la_status split_forward(const Problem &pr, const Plan &pl, const void *Q, const void *K,
@@ -99,27 +89,17 @@ la_status split_forward(const Problem &pr, const Plan &pl, const void *Q, const 
                         Tracer &tc)
 {
     const SplitScratch sc = split_scratch(pl, pr.BH, pr.N, pr.dt, 0);
-    float *gpart = ws + sc.g_off, *fraw = ws + sc.f_off;
     Problem p = pr;
     p.D = 128;
-    Tracer quiet(nullptr, st);  // the caller's trace gets one mark per pass, not per kernel
     if (pr.causal && pl.nseg == 1) saved = nullptr;  // no segment starts from another's sums
-    for (int j = 0; j < 2; ++j) {
-        const void *Vj = col_block(V, j, pr.dt);
-        void *Oj = col_block(O, j, pr.dt);
-        for (int i = 0; i < 2; ++i) {
-            p.a = i == 0 ? pr.a : 0.f;
-            const la_status s = planes_forward(p, pl, 256, col_block(Q, i, pr.dt), col_block(K, i, pr.dt),
-                                               Vj, Oj, i == 0 ? gpart : (j == 1 ? G : nullptr), ws,
-                                               saved_block(saved, pl, 2 * i + j), st, quiet, i == 0 ? XF_RAW : XF_ACC,
-                                               i == 0 ? nullptr : gpart, fraw);
-            if (s != LA_OK) return s;
-            tc.mark("fwd_block_pass");
-        }
-    }
-    if (!saved) return LA_OK;
-    k_leave_witness<<<dim3(pr.BH), dim3(64), 0, st>>>((const uint32_t *)O, (uint32_t *)saved_block(saved, pl, 4),
-                                                      pr.N, row_words(pr.dt), problem_key(pr, pl));
+    BlockScratch bs;
+    bs.together = sc.together;
+    bs.g = ws + sc.g_off;
+    bs.f = ws + sc.f_off;
+    const la_status s = planes_forward(p, pl, 256, Q, K, V, O, G, ws, saved, st, tc, bs);
+    if (s != LA_OK || !saved) return s;
+    k_leave_witness<<<dim3(pr.BH), dim3(64), 0, st>>>((const uint32_t *)O, witness(saved, pl), pr.N, row_words(pr.dt),
+                                                      problem_key(pr, pl));
     return launch_status();
 }
 
@@ -131,32 +111,19 @@ la_status split_backward(const Problem &pr, const Plan &pl, const void *Q, const
     const SplitScratch sc = split_scratch(pl, pr.BH, pr.N, pr.dt, 1);
     Problem p = pr;
     p.D = 128;
-    Tracer quiet(nullptr, st);  // the caller's trace gets one mark per pass, not per kernel
     if (pr.causal && pl.nseg == 1) saved = nullptr;
-    int *handed = saved ? (int *)(ws + sc.flag_off) : nullptr;
-    if (saved)
-        k_check_witness<<<dim3(pr.BH), dim3(64), 0, st>>>(
-            (const uint32_t *)O, (const uint32_t *)saved_block(saved, pl, 4), handed, pr.N, row_words(pr.dt),
-            problem_key(pr, pl));
-    for (int i = 0; i < 2; ++i)
-        for (int j = 0; j < 2; ++j) {
-            p.a = i == 0 ? pr.a : 0.f;
-            BlockPass bp;
-            // dQ_i and dK_i are complete after j = 1, dV_j after i = 1
-            bp.xflags = (j == 1 ? 1 | 2 : 0) | (i == 1 ? 4 : 0);
-            bp.Pq = ws + sc.q_off;
-            bp.Pk = ws + sc.k_off;
-            bp.Pv = ws + sc.v_off + (size_t)j * pr.BH * pr.N * 128;
-            bp.handed = handed;
-            const la_status s = planes_backward(
-                p, pl, 256, col_block(Q, i, pr.dt), col_block(K, i, pr.dt), col_block(V, j, pr.dt),
-                col_block(O, j, pr.dt), G, col_block(dO, j, pr.dt), col_block(dQ, i, pr.dt),
-                dK ? col_block(dK, i, pr.dt) : nullptr, dK ? col_block(dV, j, pr.dt) : nullptr, ws,
-                saved_block(saved, pl, 2 * i + j), st, quiet, bp);
-            if (s != LA_OK) return s;
-            tc.mark("bwd_block_pass");
-        }
-    return LA_OK;
+    BlockScratch bs;
+    bs.q = ws + sc.q_off;
+    bs.k = ws + sc.k_off;
+    bs.v = ws + sc.v_off;
+    bs.delta = ws + sc.delta_off;
+    if (saved) {
+        int *handed = (int *)(ws + sc.flag_off);
+        k_check_witness<<<dim3(pr.BH), dim3(64), 0, st>>>((const uint32_t *)O, witness((float *)saved, pl), handed,
+                                                          pr.N, row_words(pr.dt), problem_key(pr, pl));
+        bs.handed = handed;
+    }
+    return planes_backward(p, pl, 256, Q, K, V, O, G, dO, dQ, dK, dV, ws, saved, st, tc, bs);
 }
 
 }  // namespace la

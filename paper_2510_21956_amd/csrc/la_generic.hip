@@ -230,10 +230,10 @@ __global__ __launch_bounds__(NT) void k_bwd_state(const T *__restrict__ Q, const
 template <int BATCH>
 __global__ __launch_bounds__(NT) void k_scan_slots(float *__restrict__ ws, int nseg,
                                                    size_t slot_floats, int off, int len, int mode,
-                                                   int lo, int hi, const int *__restrict__ skip)
+                                                   int lo, int hi, const int *__restrict__ skip, int skip_slices)
 {
     int e = blockIdx.y * NT + threadIdx.x;
-    if (e >= len || hi < lo || (skip && skip[blockIdx.x])) return;
+    if (e >= len || hi < lo || (skip && skip[blockIdx.x % skip_slices])) return;
     float *p = ws + (size_t)blockIdx.x * nseg * slot_floats + off + e;
     // The slots are read BATCH at a time before anything is added or written back: one memory
     // round trip per BATCH slots instead of one per slot (the sums are formed in the same order
@@ -269,11 +269,11 @@ __global__ __launch_bounds__(NT) void k_scan_slots(float *__restrict__ ws, int n
 template <int PARTS>
 __global__ __launch_bounds__(32 * PARTS) void k_scan_parts(float *__restrict__ ws, int nseg, size_t slot_floats,
                                                            int off, int len, int mode, int lo, int hi,
-                                                           const int *__restrict__ skip)
+                                                           const int *__restrict__ skip, int skip_slices)
 {
     constexpr int RUN = 16;
     __shared__ float sums[PARTS][32], rest[PARTS][32];
-    if (skip && skip[blockIdx.x]) return;
+    if (skip && skip[blockIdx.x % skip_slices]) return;
     const int l = threadIdx.x % 32, part = threadIdx.x / 32, e = blockIdx.y * 32 + l;
     const bool on = e < len;
     float *p = ws + (size_t)blockIdx.x * nseg * slot_floats + off + (on ? e : 0);
@@ -601,7 +601,7 @@ la_status fwd_impl(const Problem &pr, const Plan &pl, const T *Q, const T *K, co
         tc.mark("generic_fwd_state");
         const int len = D * D + 2 * D;
         k_scan_slots<16><<<dim3(pr.BH, (len + NT - 1) / NT), dim3(NT), 0, st>>>(
-            ws, nseg, pl.slot_floats, 0, len, pr.causal ? 0 : 2, pr.causal ? 1 : 0, nseg - 1, nullptr);
+            ws, nseg, pl.slot_floats, 0, len, pr.causal ? 0 : 2, pr.causal ? 1 : 0, nseg - 1, nullptr, 1);
         tc.mark("scan_slots");
     }
     k_fwd_apply<T, D><<<dim3(pr.BH * nseg), dim3(NT), 0, st>>>(
@@ -625,13 +625,13 @@ la_status bwd_impl(const Problem &pr, const Plan &pl, const T *Q, const T *K, co
     const int lenS = D * D + D, lenR = D * D + 2 * D;
     if (pr.causal) {
         k_scan_slots<16><<<dim3(pr.BH, (lenS + NT - 1) / NT), dim3(NT), 0, st>>>(
-            ws, nseg, pl.slot_floats, 0, lenS, 0, 1, nseg - 1, nullptr);
+            ws, nseg, pl.slot_floats, 0, lenS, 0, 1, nseg - 1, nullptr, 1);
         k_scan_slots<16><<<dim3(pr.BH, (lenR + NT - 1) / NT), dim3(NT), 0, st>>>(
-            ws, nseg, pl.slot_floats, lenS, lenR, 1, 0, nseg - 2, nullptr);
+            ws, nseg, pl.slot_floats, lenS, lenR, 1, 0, nseg - 2, nullptr, 1);
         tc.mark("scan_slots");
     } else {
         k_scan_slots<16><<<dim3(pr.BH, (lenS + lenR + NT - 1) / NT), dim3(NT), 0, st>>>(
-            ws, nseg, pl.slot_floats, 0, lenS + lenR, 2, 0, nseg - 1, nullptr);
+            ws, nseg, pl.slot_floats, 0, lenS + lenR, 2, 0, nseg - 1, nullptr, 1);
         tc.mark("scan_slots");
     }
     k_bwd_apply<T, D><<<dim3(pr.BH * nseg), dim3(NT), 0, st>>>(
@@ -676,18 +676,18 @@ la_status bwd_by_d(const Problem &pr, const Plan &pl, const void *Q, const void 
 }  // namespace
 
 void launch_scan_slots(float *ws, int BH, int nseg, size_t slot_floats, int off, int len, int mode,
-                       int lo, int hi, hipStream_t st, const int *skip)
+                       int lo, int hi, hipStream_t st, const int *skip, int skip_slices)
 {
     // a running sum over a single slot changes nothing; the total of a single slot 0 neither
     if (hi < lo || (hi == lo && (mode != 2 || lo == 0))) return;
     const int n = hi - lo + 1;
     if (n <= 16) {
         (n <= 8 ? k_scan_slots<8> : k_scan_slots<16>)<<<dim3(BH, (len + NT - 1) / NT), dim3(NT), 0, st>>>(
-            ws, nseg, slot_floats, off, len, mode, lo, hi, skip);
+            ws, nseg, slot_floats, off, len, mode, lo, hi, skip, skip_slices);
     } else {
         const dim3 grid(BH, (len + 31) / 32);
-        if (n <= 128) k_scan_parts<8><<<grid, dim3(256), 0, st>>>(ws, nseg, slot_floats, off, len, mode, lo, hi, skip);
-        else k_scan_parts<32><<<grid, dim3(1024), 0, st>>>(ws, nseg, slot_floats, off, len, mode, lo, hi, skip);
+        if (n <= 128) k_scan_parts<8><<<grid, dim3(256), 0, st>>>(ws, nseg, slot_floats, off, len, mode, lo, hi, skip, skip_slices);
+        else k_scan_parts<32><<<grid, dim3(1024), 0, st>>>(ws, nseg, slot_floats, off, len, mode, lo, hi, skip, skip_slices);
     }
 }
 

@@ -337,6 +337,31 @@ __device__ __forceinline__ f4v descending_weight(f4v x, bool cm, int ib, int nb,
     return x;
 }
 
+// Head size 256 (LD > D): the block problems of one launch, 1 << lg of them, block problem 2 i + j on columns 128 i
+// .. of Q and K and 128 j .. of V.  Workgroups of the same rows follow one another, so that what they read in
+// common comes out of the last-level cache.  Strides between the block problems' slots, hand-over buffers (or
+// slots) and, between column blocks, of the fp32 shares and the token-heads.
+struct Blocks {
+    int lg = 0;
+    unsigned ids = 0;
+    size_t slots = 0, sinit = 0, part = 0, rows = 0;
+};
+struct Block {
+    int id = 0, i = 0, j = 0;
+};
+template <bool ON>
+__device__ __forceinline__ Block block_of(const Blocks &bl, int &wg)
+{
+    Block b;
+    if constexpr (ON) {
+        b.id = bl.ids >> 2 * (wg & ((1 << bl.lg) - 1)) & 3;
+        b.i = b.id >> 1;
+        b.j = b.id & 1;
+        wg >>= bl.lg;
+    }
+    return b;
+}
+
 // One tensor's chunk into its tile: normalised (NORM, fp32) and times scale[row], if given, on
 // the way.  1 / |row| goes to inv_out.
 template <bool NORM, bool OP, int L, typename CH>
@@ -368,7 +393,7 @@ template <int MODE, int D, bool TRANSPOSED, int LD, bool LONG>
 __global__ __launch_bounds__(4 * D, 2) void ks_kv_state(
     const typename Mode<MODE>::TIO *__restrict__ K, const typename Mode<MODE>::TIO *__restrict__ V,
     float *__restrict__ ws, int N, int nseg, int nseg_run, SegMap sm, size_t slot_floats, int slot_shift,
-    const int *__restrict__ skip)
+    const int *__restrict__ skip, Blocks bl)
 {
     typedef Mode<MODE> MD;
     typedef typename MD::TIO TIO;
@@ -377,9 +402,14 @@ __global__ __launch_bounds__(4 * D, 2) void ks_kv_state(
     typedef Chunk<TIO, D, LD> CH;
     __shared__ __align__(16) __bf16 lds[NT * TP];
     __shared__ __align__(16) float ikb[MD::RN ? NT * CR : 4];  // 1 / |k|
-    const int bh = blockIdx.x / nseg_run, seg = blockIdx.x % nseg_run;
+    int wg = blockIdx.x;
+    const Block at = block_of<(LD > D)>(bl, wg);
+    const int bh = wg / nseg_run, seg = wg % nseg_run;
     if constexpr (LD > D) {  // slices whose sums were handed over
         if (skip && skip[bh]) return;
+        K += D * at.i;
+        V += D * at.j;
+        ws += at.id * bl.slots;
     }
     const TIO *Kp = K + (size_t)bh * N * LD, *Vp = V + (size_t)bh * N * LD;
     const long row0 = seg_row(sm, seg, nseg, N), row1 = seg_row(sm, seg + 1, nseg, N);
@@ -509,7 +539,7 @@ __global__ __launch_bounds__(4 * D, 2) void ks_fwd_apply(
     const typename Mode<MODE>::TIO *__restrict__ V, typename Mode<MODE>::TIO *__restrict__ O,
     float *__restrict__ G, const float *__restrict__ ws, float *__restrict__ saved, int N, int nseg,
     SegMap sm, size_t slot_floats, int fold, size_t saved_floats, float a, float b,
-    const float *__restrict__ Gin, float *__restrict__ Fraw)
+    const float *__restrict__ Gin, float *__restrict__ Fraw, Blocks bl)
 {
     typedef Mode<MODE> MD;
     typedef typename MD::TIO TIO;
@@ -523,7 +553,20 @@ __global__ __launch_bounds__(4 * D, 2) void ks_fwd_apply(
     __bf16 *Qt = lds;  // operand-ordered; K and V natural
     __bf16 *Kt = Qt + LQ * PL, *Vt = Kt + LQ * PL, *Pt = Vt + LV * PL;
 
-    const int bh = blockIdx.x / nseg, seg = blockIdx.x % nseg;
+    int wg = blockIdx.x;
+    const Block at = block_of<(LD > D)>(bl, wg);
+    if constexpr (LD > D) {
+        Q += D * at.i;
+        K += D * at.i;
+        V += D * at.j;
+        O += D * at.j;
+        ws += at.id * bl.slots;
+        if (saved) saved += at.id * bl.sinit;
+        if (at.i) a = 0.f;
+        if (at.j) G = nullptr;  // both blocks have the same
+        Fraw += at.j * bl.part;
+    }
+    const int bh = wg / nseg, seg = wg % nseg;
     const size_t base = (size_t)bh * N * LD;
     const TIO *Qp = Q + base, *Kp = K + base, *Vp = V + base;
     TIO *Op = O + base;
@@ -695,7 +738,7 @@ __global__ __launch_bounds__(4 * D, 2) void ks_fwd_read(
     const typename Mode<MODE>::TIO *__restrict__ Q, typename Mode<MODE>::TIO *__restrict__ O,
     float *__restrict__ G, const float *__restrict__ ws, float *__restrict__ saved, int N, int nseg,
     int nwg, int rows_wg, int lo_rows, size_t slot_floats, size_t saved_floats, float a, float b,
-    const float *__restrict__ Gin, float *__restrict__ Fraw)
+    const float *__restrict__ Gin, float *__restrict__ Fraw, Blocks bl)
 {
     typedef Mode<MODE> MD;
     typedef typename MD::TIO TIO;
@@ -706,7 +749,18 @@ __global__ __launch_bounds__(4 * D, 2) void ks_fwd_read(
     __shared__ __align__(16) __bf16 lds[NT * LQ * PL];  // operand-ordered tiles of Q
     __shared__ __align__(16) float zs[D], qzs[NT * CR], ginv[NW][NT * CR], iqb[MD::RN ? NT * CR : 4];
 
-    const int bh = blockIdx.x / nwg, part = blockIdx.x % nwg;
+    int wg = blockIdx.x;
+    const Block at = block_of<(LD > D)>(bl, wg);
+    if constexpr (LD > D) {
+        Q += D * at.i;
+        O += D * at.j;
+        ws += at.id * bl.slots;
+        if (saved) saved += at.id * bl.sinit;
+        if (at.i) a = 0.f;
+        if (at.j) G = nullptr;  // both blocks have the same
+        Fraw += at.j * bl.part;
+    }
+    const int bh = wg / nwg, part = wg % nwg;
     const size_t base = (size_t)bh * N * LD;
     const TIO *Qp = Q + base;
     TIO *Op = O + base;
@@ -820,7 +874,7 @@ __global__ __launch_bounds__(4 * D, 2) void ks_fwd_read(
 //   dQ_c = diag(b / g) (tril(Cm') K_c + dO_c S^T - dprime z^T);  then S += K_c^T V_c, z += sum k
 //   R += (Q/g)_c^T dO_c,  u += sum dprime (q/g),  w += sum dO / g
 // The state is held transposed (rows j, columns r): the product contracts over j.
-// LD > D: ADD marks the second of the two launches that build dQ up; handed as in BlockPass.
+// LD > D: ADD marks the second of the two launches that build dQ up; handed as in BlockScratch.
 // fp32 at D = 128 without the mask holds S^T, R and two chunks in 256 registers but for 6 to 10, which
 // go to scratch once a chunk (a state in its accumulators less would cost a pass over Q and dO).
 // ---------------------------------------------------------------------------
@@ -831,7 +885,7 @@ __global__ __launch_bounds__(4 * D, 2) void ks_bwd_dq(
     const float *__restrict__ G, const typename Mode<MODE>::TIO *__restrict__ dO,
     typename Mode<MODE>::TIO *__restrict__ dQ, float *ws, const float *sinit, size_t sinit_floats,
     float *__restrict__ dprime, int N, int nseg, SegMap sm, size_t slot_floats, int fold, float b,
-    float *__restrict__ Pq, const int *__restrict__ handed)
+    float *__restrict__ Pq, const int *__restrict__ handed, Blocks bl)
 {
     typedef Mode<MODE> MD;
     typedef typename MD::TIO TIO;
@@ -849,7 +903,21 @@ __global__ __launch_bounds__(4 * D, 2) void ks_bwd_dq(
     __bf16 *dOt = lds;  // operand-ordered; the others natural
     __bf16 *Qt = dOt + LV * PL, *Vt = Qt + LQ * PL, *Kt = Vt + TS * LV * PL, *Ct = Kt + TS * LQ * PL;
 
-    const int bh = blockIdx.x / nseg, seg = blockIdx.x % nseg;
+    int wg = blockIdx.x;
+    const Block at = block_of<(LD > D)>(bl, wg);
+    if constexpr (LD > D) {
+        Q += D * at.i;
+        K += D * at.i;
+        dQ += D * at.i;
+        V += D * at.j;
+        O += D * at.j;
+        dO += D * at.j;
+        ws += at.id * bl.slots;
+        sinit += at.id * bl.sinit;
+        dprime += at.j * bl.rows;
+        Pq += at.i * bl.part;
+    }
+    const int bh = wg / nseg, seg = wg % nseg;
     const size_t base = (size_t)bh * N * LD;
     const TIO *Qp = Q + base, *Kp = K + base, *Vp = V + base, *Op = O + base, *dOp = dO + base;
     TIO *dQp = dQ + base;
@@ -930,7 +998,7 @@ __global__ __launch_bounds__(4 * D, 2) void ks_bwd_dq(
                     float wu = QT ? s[k] : s[k] * rs[r];
                     if constexpr (MD::RN) wu *= qinv[r];
                     store_factor<3>(fdl, r, wu);
-                    if (r < (int)(row1 - c0)) (dp + c0)[r] = s[k];
+                    if (r < (int)(row1 - c0) && at.i == 0) (dp + c0)[r] = s[k];
                 }
             }
             cur.d.template store<true, LV>(dOt);
@@ -1072,7 +1140,7 @@ __global__ __launch_bounds__(8 * D, 4) void ks_bwd_dq_halves(
     const float *__restrict__ G, const typename Mode<MODE>::TIO *__restrict__ dO,
     typename Mode<MODE>::TIO *__restrict__ dQ, float *ws, const float *sinit, size_t sinit_floats,
     float *__restrict__ dprime, int N, int nseg, SegMap sm, size_t slot_floats, int fold, float b,
-    float *__restrict__ Pq, const int *)
+    float *__restrict__ Pq, const int *, Blocks)
 {
     typedef Mode<MODE> MD;
     typedef typename MD::TIO TIO;
@@ -1303,7 +1371,7 @@ __global__ __launch_bounds__(8 * D, 4) void ks_bwd_dq_halves(
 // Four waves a SIMD instead of two that hold both states: more of what the waves issue and wait for in turn
 // overlaps (fp32, D = 64: vector ALU 30 -> 38 %, LDS 38 -> 46 %, matrix pipe 31 -> 38 % of the clocks; times at the
 // top).  Half the registers a wave have to do (TIGHT).
-// LD > D: xflags & 2 (dK), & 4 (dV) mark the second of the two launches that build them up (ADD: either).
+// LD > D: ADD marks the second of the two launches that build them up.
 // ---------------------------------------------------------------------------
 template <int MODE, int D, int LD, bool ADD>
 __global__ __launch_bounds__(8 * D, 4) void ks_bwd_dkv(
@@ -1311,8 +1379,8 @@ __global__ __launch_bounds__(8 * D, 4) void ks_bwd_dkv(
     const typename Mode<MODE>::TIO *__restrict__ V, const float *__restrict__ G,
     const typename Mode<MODE>::TIO *__restrict__ dO, typename Mode<MODE>::TIO *__restrict__ dK,
     typename Mode<MODE>::TIO *__restrict__ dV, const float *__restrict__ ws, const float *__restrict__ dprime, int N,
-    int nseg, SegMap sm, size_t slot_floats, int fold, float a, float b, int xflags,
-    float *__restrict__ Pk, float *__restrict__ Pv)
+    int nseg, SegMap sm, size_t slot_floats, int fold, float a, float b, float *__restrict__ Pk, float *__restrict__ Pv,
+    Blocks bl)
 {
     typedef Mode<MODE> MD;
     typedef typename MD::TIO TIO;
@@ -1331,7 +1399,22 @@ __global__ __launch_bounds__(8 * D, 4) void ks_bwd_dkv(
     __bf16 *Kt = lds, *Vt = Kt + L * PL;  // operand-ordered; Q/g and dO natural
     __bf16 *Qt = Vt + L * PL, *dOt = Qt + L * PL, *Ct = dOt + L * PL, *Wt = Ct + LX * WPL;
 
-    const int bh = blockIdx.x / nseg, seg = blockIdx.x % nseg;
+    int wg = blockIdx.x;
+    const Block at = block_of<(LD > D)>(bl, wg);
+    if constexpr (LD > D) {
+        Q += D * at.i;
+        K += D * at.i;
+        dK += D * at.i;
+        V += D * at.j;
+        dO += D * at.j;
+        dV += D * at.j;
+        ws += at.id * bl.slots;
+        dprime += at.j * bl.rows;
+        if (at.i) a = 0.f;
+        Pk += at.i * bl.part;
+        Pv += at.j * bl.part;
+    }
+    const int bh = wg / nseg, seg = wg % nseg;
     const size_t base = (size_t)bh * N * LD;
     const TIO *Qp = Q + base, *Kp = K + base, *Vp = V + base, *dOp = dO + base;
     const float *Gp = G + (size_t)bh * N, *dp = dprime + (size_t)bh * N;
@@ -1439,7 +1522,7 @@ __global__ __launch_bounds__(8 * D, 4) void ks_bwd_dkv(
         const auto part = [&] { return (half ? Pv : Pk) + ((size_t)bh * N + c0) * D; };
         f4v old[2] = {};  // shares that the launch before left
         if constexpr (ADD) {
-            if (xflags & (half ? 4 : 2)) {
+            {
 #pragma unroll
                 for (int m = 0; m < 2; ++m)
                     old[m] = load_grad<SWAP, D, LD>(out() + (size_t)(m * 16) * LD, part() + m * 16 * D, w,
@@ -1489,7 +1572,7 @@ __global__ __launch_bounds__(8 * D, 4) void ks_bwd_dkv(
         }
 #pragma unroll
         for (int m = 0; m < 2; ++m)
-            store_grad<SWAP, D, LD>(out() + (size_t)(m * 16) * LD, part() + m * 16 * D, ADD && (xflags & (half ? 4 : 2)), w,
+            store_grad<SWAP, D, LD>(out() + (size_t)(m * 16) * LD, part() + m * 16 * D, ADD, w,
                                     (int)(row1 - c0) - m * 16, l, x[m], old[m]);
         bf8v fac[3];
         load_factor<3>(fac, half ? frs[par] : fdl[par], g);
@@ -1526,7 +1609,8 @@ __global__ __launch_bounds__(4 * D, 2) void ks_bwd_dkv_wide(
     const __bf16 *__restrict__ Q, const __bf16 *__restrict__ K, const __bf16 *__restrict__ V,
     const float *__restrict__ G, const __bf16 *__restrict__ dO, __bf16 *__restrict__ dK, __bf16 *__restrict__ dV,
     const float *__restrict__ ws, const float *__restrict__ dprime, int N, int nseg, SegMap sm,
-    size_t slot_floats, int, float a, float b, int xflags, float *__restrict__ Pk, float *__restrict__ Pv)
+    size_t slot_floats, int, float a, float b, float *__restrict__ Pk, float *__restrict__ Pv,
+    Blocks bl)
 {
     constexpr int LX = Mode<P16>::LX, NW = D / 16, NC = D / 32, PL = NTile<D>::PLANE, WPL = NTile<32>::PLANE;
     typedef Chunk<__bf16, D, LD> CH;
@@ -1536,7 +1620,22 @@ __global__ __launch_bounds__(4 * D, 2) void ks_bwd_dkv_wide(
     __shared__ __align__(16) float rsb[2][CR], dlb[2][CR], vecs[2 * D];  // 1/g, dprime; u and w
     __bf16 *Kt = lds, *Vt = Kt + PL, *Qt = Vt + PL, *dOt = Qt + PL, *Ct = dOt + PL, *Wt = Ct + LX * WPL;
 
-    const int bh = blockIdx.x / nseg, seg = blockIdx.x % nseg;
+    int wg = blockIdx.x;
+    const Block at = block_of<(LD > D)>(bl, wg);
+    if constexpr (LD > D) {
+        Q += D * at.i;
+        K += D * at.i;
+        dK += D * at.i;
+        V += D * at.j;
+        dO += D * at.j;
+        dV += D * at.j;
+        ws += at.id * bl.slots;
+        dprime += at.j * bl.rows;
+        if (at.i) a = 0.f;
+        Pk += at.i * bl.part;
+        Pv += at.j * bl.part;
+    }
+    const int bh = wg / nseg, seg = wg % nseg;
     const size_t base = (size_t)bh * N * LD;
     const __bf16 *Qp = Q + base, *Kp = K + base, *Vp = V + base, *dOp = dO + base;
     const float *Gp = G + (size_t)bh * N, *dp = dprime + (size_t)bh * N;
@@ -1617,8 +1716,7 @@ __global__ __launch_bounds__(4 * D, 2) void ks_bwd_dkv_wide(
         const long cn = row0 + max(ci - 2, 0L) * CR;
         f16v old = zero16();  // shares that the launch before left
         if constexpr (ADD) {
-            if (xflags & (half ? 4 : 2))
-                old = load_cols32((half ? Pv : Pk) + ((size_t)bh * N + c0) * D, D, 32 * w, (int)(row1 - c0), l);
+            old = load_cols32((half ? Pv : Pk) + ((size_t)bh * N + c0) * D, D, 32 * w, (int)(row1 - c0), l);
         }
         cur.k.load(Kp, cn, N);
         cur.v.load(Vp, cn, N);
@@ -1653,13 +1751,10 @@ __global__ __launch_bounds__(4 * D, 2) void ks_bwd_dkv_wide(
             for (int e = 0; e < 4; ++e) f[4 * q + e] = b * f[4 * q + e] + (ys * y[4 * q + e] + vs * vq[e]);
         }
         if constexpr (ADD) {
-            if (xflags & (half ? 4 : 2)) {
-                keep_branch();
-                f += old;
-            }
+            f += old;
         }
         store_grad32<D, LD>((half ? dV : dK) + base + (size_t)c0 * LD, (half ? Pv : Pk) + ((size_t)bh * N + c0) * D,
-                            ADD && (xflags & (half ? 4 : 2)), 32 * w, (int)(row1 - c0), l, f);
+                            ADD, 32 * w, (int)(row1 - c0), l, f);
         vec += weighted_sum(own, half ? frs[par] : fdl[par], h);
         vecs[half * D + 32 * w + c] = vec;
         with_planes<LX>(lo_on, [&](auto np) {
@@ -1678,14 +1773,14 @@ __global__ __launch_bounds__(4 * D, 2) void ks_bwd_dkv_wide(
 // ---------------------------------------------------------------------------
 // Backward without the mask: dK_c = b (V_c R^T - 1 u^T), dV_c = a 1 w^T + b K_c R, R, u, w the sums
 // over the whole sequence.
-// LD > D: xflags as above.
+// LD > D: ADD as above.
 // ---------------------------------------------------------------------------
 template <int MODE, int D, int LD, bool ADD>
 __global__ __launch_bounds__(4 * D, 2) void ks_bwd_dkv_read(
     const typename Mode<MODE>::TIO *__restrict__ K, const typename Mode<MODE>::TIO *__restrict__ V,
     typename Mode<MODE>::TIO *__restrict__ dK, typename Mode<MODE>::TIO *__restrict__ dV,
     const float *__restrict__ ws, int N, int nseg, SegMap sm, size_t slot_floats, float a, float b,
-    int xflags, float *__restrict__ Pk, float *__restrict__ Pv)
+    float *__restrict__ Pk, float *__restrict__ Pv, Blocks bl)
 {
     typedef Mode<MODE> MD;
     typedef typename MD::TIO TIO;
@@ -1698,7 +1793,19 @@ __global__ __launch_bounds__(4 * D, 2) void ks_bwd_dkv_read(
     __shared__ __align__(16) float kinv[PROJ ? CR : 4], dots[PROJ ? NW * CR : 4];  // 1 / |k|
     __bf16 *Kt = lds, *Vt = Kt + LQ * PL;  // operand-ordered
 
-    const int bh = blockIdx.x / nseg, seg = blockIdx.x % nseg;
+    int wg = blockIdx.x;
+    const Block at = block_of<(LD > D)>(bl, wg);
+    if constexpr (LD > D) {
+        K += D * at.i;
+        dK += D * at.i;
+        V += D * at.j;
+        dV += D * at.j;
+        ws += at.id * bl.slots;
+        if (at.i) a = 0.f;
+        Pk += at.i * bl.part;
+        Pv += at.j * bl.part;
+    }
+    const int bh = wg / nseg, seg = wg % nseg;
     const size_t base = (size_t)bh * N * LD;
     const TIO *Kp = K + base, *Vp = V + base;
     TIO *dKp = dK + base, *dVp = dV + base;
@@ -1744,8 +1851,8 @@ __global__ __launch_bounds__(4 * D, 2) void ks_bwd_dkv_read(
             for (int m = 0; m < 2; ++m) {
                 const size_t at = (size_t)(c0 + m * 16) * LD, pat = ((size_t)bh * N + c0 + m * 16) * D;
                 const int nrows = (int)(row1 - c0) - m * 16;
-                if (xflags & 2) oldk[m] = load_grad<SWAP, D, LD>(dKp + at, Pk + pat, w, nrows, l);
-                if (xflags & 4) oldv[m] = load_grad<SWAP, D, LD>(dVp + at, Pv + pat, w, nrows, l);
+                oldk[m] = load_grad<SWAP, D, LD>(dKp + at, Pk + pat, w, nrows, l);
+                oldv[m] = load_grad<SWAP, D, LD>(dVp + at, Pv + pat, w, nrows, l);
             }
         }
         cur.k.load(Kp, cn, N);
@@ -1762,7 +1869,7 @@ __global__ __launch_bounds__(4 * D, 2) void ks_bwd_dkv_read(
 #pragma unroll
         for (int m = 0; m < 2; ++m)
             store_grad<SWAP, D, LD>(dKp + (size_t)(c0 + m * 16) * LD,
-                                    Pk + ((size_t)bh * N + c0 + m * 16) * D, ADD && (xflags & 2), w,
+                                    Pk + ((size_t)bh * N + c0 + m * 16) * D, ADD, w,
                                     (int)(row1 - c0) - m * 16, l, x[m], oldk[m]);
         f4v vh[2], vl[2];  // rows n, columns j (SWAP), or rows j, columns n
 #pragma unroll
@@ -1772,7 +1879,7 @@ __global__ __launch_bounds__(4 * D, 2) void ks_bwd_dkv_read(
         for (int m = 0; m < 2; ++m) {
             const f4v f = a * wacc.v + (MD::RN ? b * kinv[m * 16 + c] : b) * (vh[m] + vl[m]);
             store_grad<SWAP, D, LD>(dVp + (size_t)(c0 + m * 16) * LD,
-                                    Pv + ((size_t)bh * N + c0 + m * 16) * D, ADD && (xflags & 4), w,
+                                    Pv + ((size_t)bh * N + c0 + m * 16) * D, ADD, w,
                                     (int)(row1 - c0) - m * 16, l, f, oldv[m]);
         }
     };
@@ -1810,7 +1917,7 @@ bool folds_scan(const Problem &pr, int nseg)
 template <int MODE, int D, int LD>
 la_status run_forward(const Problem &pr, const Plan &pl, const void *Qv, const void *Kv,
                       const void *Vv, void *Ov, float *G, float *ws, float *saved, hipStream_t st,
-                      Tracer &tc, int xflags, const float *Gin, float *Fraw)
+                      Tracer &tc, const BlockScratch &bs)
 {
     typedef typename Mode<MODE>::TIO TIO;
     const TIO *Q = (const TIO *)Qv, *K = (const TIO *)Kv, *V = (const TIO *)Vv;
@@ -1818,32 +1925,51 @@ la_status run_forward(const Problem &pr, const Plan &pl, const void *Qv, const v
     const int nseg = pl.nseg, nrun = pr.causal ? nseg - 1 : nseg;
     const dim3 block(4 * D);
     const bool fold = folds_scan(pr, nseg);
-    if (nrun > 0) {
+    const size_t slots = bs.together ? split_slots(pl, pr.BH) : 0;
+    const auto blocks = [&](int lg, unsigned ids) {
+        return Blocks{lg, ids, slots, pl.saved_bytes / sizeof(float), bs.together ? (size_t)pr.BH * pr.N * D : 0, 0};
+    };
+    const auto sums = [&](const Blocks &bl) {
+        if (nrun == 0) return;
         (pr.causal ? ks_kv_state<MODE, D, false, LD, false> : ks_kv_state<MODE, D, false, LD, true>)<<<
-            dim3(pr.BH * nrun), block, 0, st>>>(
-            K, V, ws, pr.N, nseg, nrun, pl.map, pl.slot_floats, pr.causal ? 1 : 0, nullptr);
+            dim3(pr.BH * nrun << bl.lg), block, 0, st>>>(
+            K, V, ws, pr.N, nseg, nrun, pl.map, pl.slot_floats, pr.causal ? 1 : 0, nullptr, bl);
         tc.mark("fwd_state");
-        if (!fold) {
-            launch_scan_slots(ws, pr.BH, nseg, pl.slot_floats, 0, D * D + 2 * D, pr.causal ? 0 : 2,
-                              pr.causal ? 1 : 0, nseg - 1, st);
-            tc.mark("scan_slots");
+        if (fold) return;
+        launch_scan_slots(ws, pr.BH << bl.lg, nseg, pl.slot_floats, 0, D * D + 2 * D, pr.causal ? 0 : 2,
+                          pr.causal ? 1 : 0, nseg - 1, st);
+        tc.mark("scan_slots");
+    };
+    const auto apply = [&](const Blocks &bl, bool add) {
+        float *g = LD > D && !add ? bs.g : G;
+        if (pr.causal) {
+            auto *kernel = add ? ks_fwd_apply<MODE, D, LD, (LD > D)> : ks_fwd_apply<MODE, D, LD, false>;
+            kernel<<<dim3(pr.BH * nseg << bl.lg), block, 0, st>>>(
+                Q, K, V, O, g, ws, saved, pr.N, nseg, pl.map, pl.slot_floats, fold, pl.saved_floats, pr.a, pr.b, bs.g,
+                bs.f, bl);
+        } else {
+            const int rows_wg = read_rows(pr.BH << bl.lg, pr.N, D), nwg = (pr.N + rows_wg - 1) / rows_wg;
+            auto *kernel = add ? ks_fwd_read<MODE, D, LD, (LD > D)> : ks_fwd_read<MODE, D, LD, false>;
+            kernel<<<dim3(pr.BH * nwg << bl.lg), block, 0, st>>>(
+                Q, O, g, ws, saved, pr.N, nseg, nwg, rows_wg, pl.map.lo_rows, pl.slot_floats, pl.saved_floats, pr.a,
+                pr.b, bs.g, bs.f, bl);
         }
-    }
-    if (pr.causal) {
-        auto *apply = ks_fwd_apply<MODE, D, LD, false>;
-        if (LD > D && (xflags & XF_ACC)) apply = ks_fwd_apply<MODE, D, LD, (LD > D)>;
-        apply<<<dim3(pr.BH * nseg), block, 0, st>>>(
-            Q, K, V, O, G, ws, saved, pr.N, nseg, pl.map, pl.slot_floats, fold, pl.saved_floats, pr.a, pr.b,
-            Gin, Fraw);
+        tc.mark("fwd_apply");
+    };
+    if (LD <= D) {
+        sums(Blocks());
+        apply(Blocks(), false);
+    } else if (bs.together) {
+        sums(blocks(2, 0xe4));          // all four
+        apply(blocks(1, 0x4), false);   // 0 and 1: the shares of the first halves of Q and K
+        apply(blocks(1, 0xe), true);    // 2 and 3
     } else {
-        const int rows_wg = read_rows(pr.BH, pr.N, D), nwg = (pr.N + rows_wg - 1) / rows_wg;
-        auto *read = ks_fwd_read<MODE, D, LD, false>;
-        if (LD > D && (xflags & XF_ACC)) read = ks_fwd_read<MODE, D, LD, (LD > D)>;
-        read<<<dim3(pr.BH * nwg), block, 0, st>>>(
-            Q, O, G, ws, saved, pr.N, nseg, nwg, rows_wg, pl.map.lo_rows, pl.slot_floats,
-            pl.saved_floats, pr.a, pr.b, Gin, Fraw);
+        for (unsigned j = 0; j < 2; ++j)
+            for (unsigned i = 0; i < 2; ++i) {
+                sums(blocks(0, 2 * i + j));
+                apply(blocks(0, 2 * i + j), i == 1);
+            }
     }
-    tc.mark("fwd_apply");
     return launch_status();
 }
 
@@ -1871,7 +1997,7 @@ template <int MODE, int D, int LD>
 la_status run_backward(const Problem &pr, const Plan &pl, const void *Qv, const void *Kv,
                        const void *Vv, const void *Ov, const float *G, const void *dOv, void *dQv,
                        void *dKv, void *dVv, float *ws, const float *saved, hipStream_t st,
-                       Tracer &tc, const BlockPass &bp)
+                       Tracer &tc, const BlockScratch &bs)
 {
     typedef typename Mode<MODE>::TIO TIO;
     typedef BwdSlot<D> SL;
@@ -1879,52 +2005,64 @@ la_status run_backward(const Problem &pr, const Plan &pl, const void *Qv, const 
               *O = (const TIO *)Ov, *dO = (const TIO *)dOv;
     TIO *dQ = (TIO *)dQv, *dK = (TIO *)dKv, *dV = (TIO *)dVv;
     const int nseg = pl.nseg, nrun = pr.causal ? nseg - 1 : nseg;
-    float *dprime = ws + pl.delta_offset_floats;
+    constexpr bool SPLIT = LD > D;
+    float *dprime = SPLIT ? bs.delta : ws + pl.delta_offset_floats;
     const bool fold = folds_scan(pr, nseg);
-    const dim3 grid(pr.BH * nseg), block(4 * D), block2(8 * D);
+    const dim3 block(4 * D), block2(8 * D);
+    const size_t slots = split_slots(pl, pr.BH), T = (size_t)pr.BH * pr.N;
+    const auto blocks = [&](int lg, unsigned ids) {
+        return SPLIT ? Blocks{lg, ids, slots, saved ? pl.saved_bytes / sizeof(float) : slots, T * D, (T + 63) / 64 * 64}
+                     : Blocks();
+    };
+    const int all = SPLIT ? 2 : 0;  // all four block problems
     // forward-running sums before every segment: handed over by the forward pass, or
     // per-segment sums (none needed from a masked pass's last segment) and a scan here
-    if ((!saved || bp.handed) && nrun > 0) {
+    if ((!saved || bs.handed) && nrun > 0) {
         (pr.causal ? ks_kv_state<MODE, D, true, LD, false> : ks_kv_state<MODE, D, true, LD, true>)<<<
-            dim3(pr.BH * nrun), block, 0, st>>>(
-            K, V, ws, pr.N, nseg, nrun, pl.map, pl.slot_floats, pr.causal ? 1 : 0, bp.handed);
+            dim3(pr.BH * nrun << all), block, 0, st>>>(
+            K, V, ws, pr.N, nseg, nrun, pl.map, pl.slot_floats, pr.causal ? 1 : 0, bs.handed, blocks(all, 0xe4));
         tc.mark("bwd_state");
         if (saved || !fold) {
-            launch_scan_slots(ws, pr.BH, nseg, pl.slot_floats, SL::ST, SL::R - SL::ST, pr.causal ? 0 : 2,
-                              pr.causal ? 1 : 0, nseg - 1, st, bp.handed);
+            launch_scan_slots(ws, pr.BH << all, nseg, pl.slot_floats, SL::ST, SL::R - SL::ST, pr.causal ? 0 : 2,
+                              pr.causal ? 1 : 0, nseg - 1, st, bs.handed, pr.BH);
             tc.mark("scan_slots");
         }
     }
     const float *sinit = saved ? saved : ws;
     const size_t sinit_floats = saved ? pl.saved_floats : pl.slot_floats;
-    constexpr bool ADDS = LD > D;  // some launches add to what others left
-    auto *dq = !pr.causal ? ks_bwd_dq<MODE, D, false, LD, false> : ks_bwd_dq_masked<MODE, D, LD, false>();
-    if (ADDS && (bp.xflags & 1))
-        dq = !pr.causal ? ks_bwd_dq<MODE, D, false, LD, ADDS> : ks_bwd_dq_masked<MODE, D, LD, ADDS>();
-    dq<<<grid, pr.causal && D == 32 ? block2 : block, 0, st>>>(
-        Q, K, V, O, G, dO, dQ, ws, sinit, sinit_floats, dprime, pr.N, nseg, pl.map, pl.slot_floats,
-        fold && !saved, pr.b, bp.Pq, bp.handed);
-    tc.mark("bwd_dq");
+    const auto ascend = [&](const Blocks &bl, auto add) {
+        constexpr bool ADD = decltype(add)::value;
+        auto *dq = !pr.causal ? ks_bwd_dq<MODE, D, false, LD, ADD> : ks_bwd_dq_masked<MODE, D, LD, ADD>();
+        dq<<<dim3(pr.BH * nseg << bl.lg), pr.causal && D == 32 ? block2 : block, 0, st>>>(
+            Q, K, V, O, G, dO, dQ, ws, sinit, sinit_floats, dprime, pr.N, nseg, pl.map, pl.slot_floats,
+            fold && !saved, pr.b, bs.q, bs.handed, bl);
+        tc.mark("bwd_dq");
+    };
+    const auto descend = [&](const Blocks &bl, auto add) {
+        constexpr bool ADD = decltype(add)::value;
+        const dim3 grid(pr.BH * nseg << bl.lg);
+        if (pr.causal) {
+            auto *dkv = ks_bwd_dkv_masked<MODE, D, LD, ADD>();
+            dkv<<<grid, MODE == P16 && D == 128 ? block : block2, 0, st>>>(
+                Q, K, V, G, dO, dK, dV, ws, dprime, pr.N, nseg, pl.map, pl.slot_floats, fold, pr.a, pr.b, bs.k, bs.v,
+                bl);
+        } else {
+            ks_bwd_dkv_read<MODE, D, LD, ADD><<<grid, block, 0, st>>>(
+                K, V, dK, dV, ws, pr.N, nseg, pl.map, pl.slot_floats, pr.a, pr.b, bs.k, bs.v, bl);
+        }
+        tc.mark("bwd_dkv");
+    };
+    ascend(blocks(SPLIT, 0x8), std::false_type());  // D = 256: block problems 0 and 2, which begin dQ
+    if constexpr (SPLIT) ascend(blocks(1, 0xd), std::true_type());  // 1 and 3, which add to it
     if (!dK) return launch_status();
     // reverse-running sums left by the ascending sweep
     if (!pr.causal || (nseg > 1 && !fold)) {
-        launch_scan_slots(ws, pr.BH, nseg, pl.slot_floats, SL::R, SL::END - SL::R, pr.causal ? 1 : 2, 0,
+        launch_scan_slots(ws, pr.BH << all, nseg, pl.slot_floats, SL::R, SL::END - SL::R, pr.causal ? 1 : 2, 0,
                           pr.causal ? nseg - 2 : nseg - 1, st);
         tc.mark("scan_slots_rev");
     }
-    if (pr.causal) {
-        auto *dkv = ks_bwd_dkv_masked<MODE, D, LD, false>();
-        if (ADDS && (bp.xflags & 6)) dkv = ks_bwd_dkv_masked<MODE, D, LD, ADDS>();
-        dkv<<<grid, MODE == P16 && D == 128 ? block : block2, 0, st>>>(
-            Q, K, V, G, dO, dK, dV, ws, dprime, pr.N, nseg, pl.map, pl.slot_floats, fold, pr.a, pr.b, bp.xflags,
-            bp.Pk, bp.Pv);
-    } else {
-        auto *dkv = ks_bwd_dkv_read<MODE, D, LD, false>;
-        if (ADDS && (bp.xflags & 6)) dkv = ks_bwd_dkv_read<MODE, D, LD, ADDS>;
-        dkv<<<grid, block, 0, st>>>(K, V, dK, dV, ws, pr.N, nseg, pl.map, pl.slot_floats,
-                                                             pr.a, pr.b, bp.xflags, bp.Pk, bp.Pv);
-    }
-    tc.mark("bwd_dkv");
+    descend(blocks(SPLIT, 0xc), std::false_type());  // 0 and 3, which begin all of dK and dV
+    if constexpr (SPLIT) descend(blocks(1, 0x9), std::true_type());  // 1 and 2, which add to them
     return launch_status();
 }
 
@@ -1933,8 +2071,10 @@ la_status run_totals(const Problem &pr, const Plan &pl, const void *K, const voi
                      hipStream_t st)
 {
     typedef typename Mode<MODE>::TIO TIO;
-    ks_kv_state<MODE, D, false, LD, true><<<dim3(pr.BH * pl.nseg), dim3(4 * D), 0, st>>>(
-        (const TIO *)K, (const TIO *)V, ws, pr.N, pl.nseg, pl.nseg, pl.map, pl.slot_floats, 0, nullptr);
+    const int all = LD > D ? 2 : 0;
+    ks_kv_state<MODE, D, false, LD, true><<<dim3(pr.BH * pl.nseg << all), dim3(4 * D), 0, st>>>(
+        (const TIO *)K, (const TIO *)V, ws, pr.N, pl.nseg, pl.nseg, pl.map, pl.slot_floats, 0, nullptr,
+        Blocks{all, 0xe4, split_slots(pl, pr.BH), 0, 0, 0});
     return launch_status();
 }
 
@@ -1970,20 +2110,20 @@ int mode_of(const Problem &pr)
 
 la_status planes_forward(const Problem &pr, const Plan &pl, int ld, const void *Q, const void *K,
                          const void *V, void *O, float *G, float *ws, float *saved, hipStream_t st,
-                         Tracer &tc, int xflags, const float *Gin, float *Fraw)
+                         Tracer &tc, const BlockScratch &bs)
 {
 #define LA_FORWARD(M, D, LD) \
-    (run_forward<M, D, LD>(pr, pl, Q, K, V, O, G, ws, saved, st, tc, xflags, Gin, Fraw))
+    (run_forward<M, D, LD>(pr, pl, Q, K, V, O, G, ws, saved, st, tc, bs))
     LA_BY_MODE(LA_FORWARD);
 }
 
 la_status planes_backward(const Problem &pr, const Plan &pl, int ld, const void *Q, const void *K,
                           const void *V, const void *O, const float *G, const void *dO, void *dQ,
                           void *dK, void *dV, float *ws, const float *saved, hipStream_t st,
-                          Tracer &tc, const BlockPass &bp)
+                          Tracer &tc, const BlockScratch &bs)
 {
 #define LA_BACKWARD(M, D, LD) \
-    (run_backward<M, D, LD>(pr, pl, Q, K, V, O, G, dO, dQ, dK, dV, ws, saved, st, tc, bp))
+    (run_backward<M, D, LD>(pr, pl, Q, K, V, O, G, dO, dQ, dK, dV, ws, saved, st, tc, bs))
     LA_BY_MODE(LA_BACKWARD);
 }
 

@@ -38,6 +38,26 @@ def test_forward_static_matches_forward(oracle_mod, la):
         assert excess(to_f64(G.reshape(B * H, N)), G_ref, TOL["f32"]) <= 1.0
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("causal", [True, False])
+def test_forward_static_one_block_problem_at_a_time(oracle_mod, la, dtype, causal):
+    """Head size 256 where the states of the four block problems together exceed the scratch: one after another."""
+    la.la_debug_override(0, 0)
+    B, H, N, D = 1, 16, 1400, 256
+    dt = la.LA_F32 if dtype == "f32" else la.LA_BF16
+    assert la.la_workspace_bytes(B, H, N, D, dt, causal, 0) > la.LA_STATIC_SCRATCH_BYTES
+    slices = [0, 7, 15]
+    dev, ref = upload_case(B, H, N, D, dtype, 950, slices)
+    O = torch.full_like(dev["Q"], float("nan"))
+    G = torch.full((B, H, N), float("nan"), device="cuda")
+    la.la_forward_static(dev["Q"], dev["K"], dev["V"], O, G, 1.0, 0.5, causal)
+    torch.cuda.synchronize()
+    assert bool(torch.isfinite(O.float()).all()) and bool(torch.isfinite(G).all())
+    O_ref, G_ref = oracle_mod.forward_rec(ref["Q"], ref["K"], ref["V"], 1.0, 0.5, causal)
+    assert excess(to_f64(O.reshape(B * H, N, D)[slices]), O_ref, TOL[dtype]) <= 1.0
+    assert excess(to_f64(G.reshape(B * H, N)[slices]), G_ref, TOL["f32"]) <= 1.0
+
+
 def test_forward_static_rejects_oversize(la):
     # short forced segments make the per-segment states outgrow the static scratch
     Q = torch.zeros((1, 16, 131072, 128), dtype=torch.bfloat16, device="cuda")
