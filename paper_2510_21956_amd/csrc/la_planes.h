@@ -352,7 +352,8 @@ struct Chunk {
     // Request chunk rows [c0, c0 + 32) of X, the base of a slice of N rows (c0 < N).  The
     // buffer descriptor covers the chunk's valid rows; rows beyond them read as zeros.
     // Nothing looks at the loaded values before the tile is written, so the loads stay in
-    // flight over the chunk before.
+    // flight over the chunk before.  STREAM: with the non-temporal bit.
+    template <bool STREAM = false>
     __device__ __forceinline__ void load(const TIO *X, long c0, int N, int t = threadIdx.x)
     {
         const long rows = (N - c0 < CR) ? N - c0 : CR;
@@ -364,7 +365,7 @@ struct Chunk {
 #pragma unroll
         for (int k = 0; k < NLD; ++k)
             raw[k] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, off + k * 16 * LD * (int)sizeof(TIO),
-                                                           0, 0);
+                                                           0, STREAM ? 2 : 0);
     }
     __device__ __forceinline__ f4v value(int k) const
     {

@@ -45,7 +45,7 @@
 //   bf16, D = 128, 128 slices of 2048            66 / 89 / 112 -> 66 / 88 / 104
 //   bf16, D = 128, 16 slices of 131072           498 / 683 / 918 -> 504 / 690 / 843
 //   bf16 normalised, D = 128, 128 of 2048        106 / 153 / 196 -> 108 / 156 / 194
-//   fp32, D = 16, one slice of 256               12.6 / 14.6 / 17.5 -> 12.5 / 11.4 / 13.0
+//   fp32, D = 16, one slice of 256 in one piece  12.6 / 14.6 / 17.5 -> 12.5 / 11.4 / 13.0
 //   fp32 without the mask, D = 64, 64 of 16384   96 / 242 / 205 -> 96 / 232 / 205
 #include "la_wave32.h"
 
@@ -387,9 +387,9 @@ __device__ __forceinline__ void stage(const CH &ch, __bf16 *tile, float *inv_out
 // Phase 1: per-segment S = sum k v^T, z = sum k, p = sum v (Eq. xy without the factors), to
 // slot `seg + slot_shift` as [S | z | p], or [S^T | z] (TRANSPOSED) for the backward pass.  LONG: z and p
 // with what their additions lose (unmasked passes and prompt states; masked rows see them through
-// plain running sums anyway).
+// plain running sums anyway).  STREAM: K and V by non-temporal loads (kv_state).
 // ---------------------------------------------------------------------------
-template <int MODE, int D, bool TRANSPOSED, int LD, bool LONG>
+template <int MODE, int D, bool TRANSPOSED, int LD, bool LONG, bool STREAM>
 __global__ __launch_bounds__(4 * D, 2) void ks_kv_state(
     const typename Mode<MODE>::TIO *__restrict__ K, const typename Mode<MODE>::TIO *__restrict__ V,
     float *__restrict__ ws, int N, int nseg, int nseg_run, SegMap sm, size_t slot_floats, int slot_shift,
@@ -432,8 +432,8 @@ __global__ __launch_bounds__(4 * D, 2) void ks_kv_state(
     } sets[NT];
     const long c_last = row0 + (row1 - row0 - 1) / CR * CR;
     auto request = [&](long c0, int i) __attribute__((always_inline)) {
-        sets[i].k.load(Kp, min(c0 + i * CR, c_last), N);
-        sets[i].v.load(Vp, min(c0 + i * CR, c_last), N);
+        sets[i].k.template load<STREAM>(Kp, min(c0 + i * CR, c_last), N);
+        sets[i].v.template load<STREAM>(Vp, min(c0 + i * CR, c_last), N);
     };
     auto put = [&](int i) __attribute__((always_inline)) {
         __bf16 *Kt = lds + i * TP, *Vt = Kt + LQ * PL;
@@ -1914,6 +1914,24 @@ bool folds_scan(const Problem &pr, int nseg)
     return pr.causal && nseg <= (pr.D <= 32 ? 9 : pr.D == 64 ? 5 : 1);
 }
 
+// ks_kv_state with non-temporal loads where what it reads is not found in the last-level cache (256 MB) afterwards:
+// K and V (tensors = 2) exceed it, or, where the pass reads them once, all four tensors do.  It then reads 4.8
+// to 6.5 TB/s, and 4.0 to 5.5 with plain loads; where the pass before left that cache full of stores, part of that is
+// their way to memory, left to the next kernel (step without the mask, fp32, D = 64, 64 slices of 16384 rows: sums 137
+// and 112, apply kernel 95 and 117).  Plain / non-temporal, us, 64 slices, K and V of 300 MB: bf16, D = 64, forward
+// 205 / 182, without the mask 154 / 129, prefill and forward 259 / 236, step 601 / 586; fp32, D = 64, 220 / 208,
+// 148 / 133, 289 / 276, 670 / 660; fp32, D = 128, 273 / 268, 182 / 178.  Of 90 and 200 MB, where the apply kernel still
+// finds some of K and V: bf16, D = 64, forward 60.0 / 62.3, 119 / 123, prefill 151 / 160.  Without the mask the line
+// shows at K and V of 128 MB: forward, bf16, D = 64, of 100 MB 42.4 / 42.3, of 135 64.1 / 55.0, of 170 88.3 / 67.9.
+// At head size 256 the block problems of a launch read K and V after one another: plain loads.
+template <int MODE, int D, bool TRANSPOSED, int LD, bool LONG>
+auto kv_state(const Problem &pr, int tensors)
+{
+    const size_t bytes = sizeof(typename Mode<MODE>::TIO) * (size_t)pr.BH * pr.N * LD * tensors;
+    return LD <= D && bytes > (size_t)256 << 20 ? ks_kv_state<MODE, D, TRANSPOSED, LD, LONG, (LD <= D)>
+                                                : ks_kv_state<MODE, D, TRANSPOSED, LD, LONG, false>;
+}
+
 template <int MODE, int D, int LD>
 la_status run_forward(const Problem &pr, const Plan &pl, const void *Qv, const void *Kv,
                       const void *Vv, void *Ov, float *G, float *ws, float *saved, hipStream_t st,
@@ -1931,7 +1949,7 @@ la_status run_forward(const Problem &pr, const Plan &pl, const void *Qv, const v
     };
     const auto sums = [&](const Blocks &bl) {
         if (nrun == 0) return;
-        (pr.causal ? ks_kv_state<MODE, D, false, LD, false> : ks_kv_state<MODE, D, false, LD, true>)<<<
+        (pr.causal ? kv_state<MODE, D, false, LD, false>(pr, 2) : kv_state<MODE, D, false, LD, true>(pr, 4))<<<
             dim3(pr.BH * nrun << bl.lg), block, 0, st>>>(
             K, V, ws, pr.N, nseg, nrun, pl.map, pl.slot_floats, pr.causal ? 1 : 0, nullptr, bl);
         tc.mark("fwd_state");
@@ -1983,8 +2001,9 @@ constexpr auto ks_bwd_dq_masked()
 
 // The descending masked sweep: 32 columns a wave for bf16 at D = 128, whose tiles and states leave room for
 // it (us, 32 columns and 16 with four waves a SIMD, medians of six runs: 128 slices of 2048 rows 109 and 118, 16
-// of 131072 825 and 911, 64 of 500 31.0 and 32.5; a step at head size 256, 64 of 4096, 1596 and 1609).  fp32 at D = 128 is within 2 % either way; at D = 64 the four waves are faster (bf16, 36 slices
-// of 5003 rows 30.0 against 34.2).
+// of 131072 825 and 911, 64 of 500 31.0 and 32.5; a step at head size 256, 64 of 4096, one block problem after
+// another, 1596 and 1609).  fp32 at D = 128 is within 2 % either way; at D = 64 the four waves are faster
+// (bf16, 36 slices of 5003 rows 30.0 against 34.2).
 template <int MODE, int D, int LD, bool ADD>
 constexpr auto ks_bwd_dkv_masked()
 {
@@ -2018,7 +2037,7 @@ la_status run_backward(const Problem &pr, const Plan &pl, const void *Qv, const 
     // forward-running sums before every segment: handed over by the forward pass, or
     // per-segment sums (none needed from a masked pass's last segment) and a scan here
     if ((!saved || bs.handed) && nrun > 0) {
-        (pr.causal ? ks_kv_state<MODE, D, true, LD, false> : ks_kv_state<MODE, D, true, LD, true>)<<<
+        (pr.causal ? kv_state<MODE, D, true, LD, false>(pr, 2) : kv_state<MODE, D, true, LD, true>(pr, 4))<<<
             dim3(pr.BH * nrun << all), block, 0, st>>>(
             K, V, ws, pr.N, nseg, nrun, pl.map, pl.slot_floats, pr.causal ? 1 : 0, bs.handed, blocks(all, 0xe4));
         tc.mark("bwd_state");
@@ -2072,7 +2091,7 @@ la_status run_totals(const Problem &pr, const Plan &pl, const void *K, const voi
 {
     typedef typename Mode<MODE>::TIO TIO;
     const int all = LD > D ? 2 : 0;
-    ks_kv_state<MODE, D, false, LD, true><<<dim3(pr.BH * pl.nseg << all), dim3(4 * D), 0, st>>>(
+    kv_state<MODE, D, false, LD, true>(pr, 2)<<<dim3(pr.BH * pl.nseg << all), dim3(4 * D), 0, st>>>(
         (const TIO *)K, (const TIO *)V, ws, pr.N, pl.nseg, pl.nseg, pl.map, pl.slot_floats, 0, nullptr,
         Blocks{all, 0xe4, split_slots(pl, pr.BH), 0, 0, 0});
     return launch_status();

@@ -472,3 +472,37 @@ def test_unmasked_cuts(la, B, H, N, D, dtype):
     got = gpu_backward_saved(la, dev, O, G, saved, 1.0, 0.5, False)
     for x, y in zip(got, gpu_backward(la, dev, O, G, 1.0, 0.5, False)):
         assert excess(to_f64(x), to_f64(y), TOL[dtype]) <= 1.0
+
+
+# K and V beyond the last-level cache (256 MB): the sums of 32-row chunks, with a ragged last one, in three segments
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("D", [16, 32, 64, 128])
+def test_sums_of_large_tensors(la, D, dtype):
+    """The last slices of a problem whose K and V exceed the last-level cache come out as they do by themselves, bit by
+    bit in segments of the same length: passes with and without the mask, plain and normalising, and prompt states."""
+    N, (td, dt) = 3001, (torch.float32, la.LA_F32) if dtype == "f32" else (torch.bfloat16, la.LA_BF16)
+    H = (256 << 20) // (2 * td.itemsize * N * D) + 1
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(D)
+    big = {n: torch.randn((1, H, N, D), device="cuda", generator=gen).to(td) for n in ("Q", "K", "V", "dO")}
+    for n in "QK":
+        big[n] *= D ** -0.5
+    own = {n: x[:, -2:].contiguous() for n, x in big.items()}
+    la.la_debug_override(1024, 0)
+    try:
+        for causal in (True, False):
+            for fwd, bwd in ((gpu_forward, gpu_backward), (_qknorm_forward, _qknorm_backward)):
+                got, want = fwd(la, big, 1.0, 0.5, causal), fwd(la, own, 1.0, 0.5, causal)
+                got += bwd(la, big, *got, 1.0, 0.5, causal)
+                want += bwd(la, own, *want, 1.0, 0.5, causal)
+                for name, x, y in zip(("O", "G", "dQ", "dK", "dV"), got, want):
+                    assert torch.equal(x[:, -2:], y), (D, dtype, causal, fwd.__name__, name)
+        states = []
+        for x in (big, own):
+            h = x["K"].shape[1]
+            states.append(torch.zeros(la.la_decode_state_bytes(1, h, D) // 4, device="cuda"))  # has padding
+            la.la_decode_prefill(x["K"], x["V"], states[-1], 0,
+                                 scratch(la.la_workspace_bytes(1, h, N, D, dt, 0, 0), "cuda"))
+        assert torch.equal(states[0][-states[1].numel():], states[1])
+    finally:
+        la.la_debug_override(0, 0)
