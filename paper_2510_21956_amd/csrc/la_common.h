@@ -252,7 +252,7 @@ inline SplitScratch split_scratch(const Plan &pl128, int BH, int N, la_dtype dt,
 // blocks, then state_block_from_totals on each.
 la_status split_prefill(const Problem &pr, const Plan &pl, const void *K, const void *V, float *ws,
                         float *state, int accumulate, hipStream_t st);
-// saved (may be null): the hand-over buffers of the four passes one after another, pl.saved_bytes each, and
+// saved (may be null): the hand-over buffers of the four block problems one after another, pl.saved_bytes each, and
 // behind them kWitnessWords words a slice that tell the backward pass whose sums they are.
 constexpr int kWitnessWords = 256;
 // Where more is handed over only as far as it is no larger than a tensor (make_plan).

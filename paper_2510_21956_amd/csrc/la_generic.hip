@@ -237,9 +237,9 @@ __global__ __launch_bounds__(NT) void k_scan_slots(float *__restrict__ ws, int n
     float *p = ws + (size_t)blockIdx.x * nseg * slot_floats + off + e;
     // The slots are read BATCH at a time before anything is added or written back: one memory
     // round trip per BATCH slots instead of one per slot (the sums are formed in the same order
-    // either way).  A step on one slice of 60000 rows (468 slots), bf16, D = 64: 143 us with 8, 133
-    // with 16, 134 with 32; 36 slices of 14 slots: 108.7, 107.8, 110.7.  Up to eight slots take 8
-    // (192 slices of 3: 7.0 us a scan, 7.7 with 16).
+    // either way).  bf16, D = 64, a step on 36 slices of 14 slots: 108.7 us with 8, 107.8 with 16, 110.7 with
+    // 32.  Up to eight slots take 8 (192 slices of 3: 7.0 us a scan, 7.7 with 16), more than sixteen
+    // k_scan_parts (launch_scan_slots).
     float run = 0.f, lost = 0.f;
     const int n = hi - lo + 1;
     for (int i0 = 0; i0 < n; i0 += BATCH) {
