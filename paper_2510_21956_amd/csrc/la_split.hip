@@ -875,8 +875,8 @@ __global__ __launch_bounds__(4 * D, 2) void ks_fwd_read(
 //   R += (Q/g)_c^T dO_c,  u += sum dprime (q/g),  w += sum dO / g
 // The state is held transposed (rows j, columns r): the product contracts over j.
 // LD > D: ADD marks the second of the two launches that build dQ up; handed as in BlockScratch.
-// fp32 at D = 128 without the mask holds S^T, R and two chunks in 256 registers but for 6 to 10, which
-// go to scratch once a chunk (a state in its accumulators less would cost a pass over Q and dO).
+// fp32 at D = 128 holds S^T, R and two chunks in 234 to 256 registers; normalised, with the mask, one more
+// goes to scratch (a state in its accumulators less would cost a pass over Q and dO).
 // ---------------------------------------------------------------------------
 template <int MODE, int D, bool CAUSAL, int LD, bool ADD>
 __global__ __launch_bounds__(4 * D, 2) void ks_bwd_dq(
