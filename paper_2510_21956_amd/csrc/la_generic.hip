@@ -278,7 +278,7 @@ __global__ __launch_bounds__(32 * PARTS) void k_scan_parts(float *__restrict__ w
     const bool on = e < len;
     float *p = ws + (size_t)blockIdx.x * nseg * slot_floats + off + (on ? e : 0);
     const int n = hi - lo + 1;
-    float before = 0.f, lost = 0.f;  // the slots before this round; what mode 2 lost
+    float before = 0.f, lost = 0.f;  // the slots of the batches before; what mode 2 lost
     const auto add = [&](float &run, float &less, float x) __attribute__((always_inline)) {
         const float sum = run + x, y = sum - run;
         less += (run - (sum - y)) + (x - y);
