@@ -274,11 +274,14 @@ struct Attention : torch::autograd::Function<Attention> {
         const size_t ns = saved_state_bytes(B, H, N, D, dt, causal);
         at::Tensor saved;
         if (ns) saved = buffer(ns, Q);
+        // everything that can throw, while the interpreter lock is held
+        void *const q = Q.data_ptr(), *const k = K.data_ptr(), *const v = V.data_ptr(), *const o = O.data_ptr(),
+                   *const w = ws.data_ptr(), *const sv = ns ? saved.data_ptr() : nullptr, *const st = current_stream(Q);
+        float *const g = (float *)G.data_ptr();
+        const size_t wb = bytes(ws), sb = ns ? bytes(saved) : 0;
         int rc;
         Py_BEGIN_ALLOW_THREADS rc = (norm ? fwd_qknorm_save : fwd_save)(
-            Q.data_ptr(), K.data_ptr(), V.data_ptr(), O.data_ptr(), (float *)G.data_ptr(), B, H, N, D, (float)a,
-            (float)b, causal, dt, ws.data_ptr(), bytes(ws), ns ? saved.data_ptr() : nullptr, ns ? bytes(saved) : 0,
-            current_stream(Q), nullptr);
+            q, k, v, o, g, B, H, N, D, (float)a, (float)b, causal, dt, w, wb, sv, sb, st, nullptr);
         Py_END_ALLOW_THREADS
         if (rc != 0) throw Status{rc};
         ctx->save_for_backward({Q, K, V, O, G});
@@ -354,6 +357,7 @@ PyObject *attention(PyObject *, PyObject *const *x, Py_ssize_t n)
         for (int i = 0; i < 3; ++i)
             require(tensor(x[i]).is_cuda() && tensor(x[i]).get_device() == Q.get_device() &&
                     !tensor(x[i])._fw_grad(0).defined());
+        for (int i = 0; i < 3; ++i) tensor(x[i]).const_data_ptr();  // throws where there is no storage
         require(!at::impl::torch_function_mode_enabled() && !c10::impl::TorchDispatchModeTLS::any_modes_set() &&
                 !torch::jit::tracer::isTracing());
         if (const auto &transforms = at::functorch::functorchTLSAccessor())

@@ -410,6 +410,11 @@ def test_autograd_nodes_native_and_python(la, knobs, monkeypatch, norm, D, dtype
         refuse(lambda: torch.autograd.grad(P, (X,), P.detach()))  # its graph is gone
         O2 = la.linear_attention(Q * 1, K, V)
         refuse(lambda: torch.func.grad(lambda q: la.linear_attention(q, K, V).sum())(Q))
+        escaped = []  # a wrapper without storage, kept after its transform has ended
+        torch.func.grad(lambda q: escaped.append(q) or q.sum())(Q)
+        for args in ((escaped[0],) * 3, (Q, escaped[0], V), (Q, K, escaped[0])):
+            E = la.linear_attention(*args, 1.0, 0.5, True, norm)
+            got += [E, *torch.autograd.grad(E.float().sum(), (Q,))]
         with torch.no_grad():
             K.add_(1)
         refuse(lambda: O2.sum().backward())  # K is not what was saved
