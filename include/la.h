@@ -249,15 +249,18 @@ LA_API la_status la_decode_prefill(const void *K, const void *V,
 /*
  * la_forward for callers that cannot allocate or pass a workspace: code under
  * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.
- * Same computation and results as la_forward, with the workspace in a static
+ * Same computation as la_forward, with the workspace in a static
  * device array inside the library (LA_STATIC_SCRATCH_BYTES per GPU, held until
- * the process ends).  The call allocates nothing and frees nothing.  Problems
- * whose la_workspace_bytes(..., 0) exceeds LA_STATIC_SCRATCH_BYTES are
- * rejected with LA_ERR_WORKSPACE (nothing enqueued), but for D = 16, where the
- * call takes kernels with a quarter of that workspace instead and serves up to
- * 26214 slices; the five benchmark configurations fit.  All calls on one GPU share the array: calls that
- * overlap in time on one GPU (different streams, different threads) race, and
- * the caller must order them.  The first call on each GPU resolves the
+ * the process ends).  The call allocates nothing and frees nothing.  Where
+ * la_workspace_bytes(..., 0) fits LA_STATIC_SCRATCH_BYTES (the five benchmark
+ * configurations do) the results are la_forward's, bit for bit.  Where it does
+ * not, the call cuts the sequences into fewer, longer segments, at D = 256 works
+ * on one block of columns after another, and at D = 16 takes kernels with a
+ * quarter of the workspace (up to 26214 slices): the results then differ from
+ * la_forward's by the order of the sums.  What does not fit even so is rejected
+ * with LA_ERR_WORKSPACE (nothing enqueued).  All calls on one GPU share the array:
+ * calls that overlap in time on one GPU (different streams, different threads) race,
+ * and the caller must order them.  The first call on each GPU resolves the
  * array's device address (make it outside graph capture); if that fails the
  * call returns LA_ERR_LAUNCH.
  */

@@ -96,12 +96,13 @@ Plan make_plan(int B, int H, int N, int D, la_dtype dt, int causal, int is_backw
     p.saved_floats = round_up(DD + D, 64);
     p.saved_bytes = (size_t)BH * p.nseg * p.saved_floats * 4;
     // D = 256 runs as passes of the D = 128 kernels (split_forward / split_backward): their
-    // workspace, plus what the forward passes hand to each other
+    // workspace, plus what the passes hand to each other.  The slots above, 264 KB a segment, are those of the
+    // token-serial kernels, which run behind the test hook alone (and la_decode_prefill does not even then).
     if (D == 256) {
         const Plan h = block_plan(B, H, N, dt, causal, is_backward, cut);
         const size_t need =
             split_scratch(h, (int)BH, N, dt, is_backward).total_floats * sizeof(float);
-        if (need > p.total_bytes) p.total_bytes = need;
+        if (need > p.total_bytes || !g_force_generic.load(std::memory_order_relaxed)) p.total_bytes = need;
         // The hand-over, 264 KB a segment, is optional here; its size is that of the cut that is nearest to one
         // workgroup a unit, of 192 rows a segment at least, or of the plan's where that is finer.  The plan itself
         // has half of that where slices are few, as two block problems share a launch.  One segment with the

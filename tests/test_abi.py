@@ -101,7 +101,8 @@ def test_cuts(lib, BH, N, D, e, causal, most):
 
 
 @pytest.mark.parametrize("BH,N,D,dt", [(120, 383, 256, 1), (4, 2000, 256, 0), (190, 4000, 128, 0), (252, 2000, 128, 1),
-                                       (7000, 40, 16, 0), (20000, 40, 16, 0)])
+                                       (7000, 40, 16, 0), (20000, 40, 16, 0), (15, 2000, 256, 0), (8, 3600, 256, 0),
+                                       (2, 15013, 256, 0), (25, 1231, 256, 0), (1, 28490, 256, 0)])
 def test_forward_static_takes_coarser_cuts(lib, BH, N, D, dt):
     """Where the states of the finest cut exceed the scratch, a coarser one is taken: not LA_ERR_WORKSPACE."""
     import torch
