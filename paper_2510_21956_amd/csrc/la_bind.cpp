@@ -75,15 +75,16 @@ la_dtype dtype_code(const at::Tensor &t)
     require(t.scalar_type() == at::kFloat || t.scalar_type() == at::kBFloat16);
     return t.scalar_type() == at::kFloat ? LA_F32 : LA_BF16;
 }
-float number(PyObject *o)
+double real(PyObject *o)
 {
-    if (PyFloat_CheckExact(o)) return (float)PyFloat_AS_DOUBLE(o);
+    if (PyFloat_CheckExact(o)) return PyFloat_AS_DOUBLE(o);
     PyObject *f = PyNumber_Float(o);  // what float(o) gives
     require(f);
     const double x = PyFloat_AS_DOUBLE(f);
     Py_DECREF(f);
-    return (float)x;
+    return x;
 }
+float number(PyObject *o) { return (float)real(o); }
 int truth(PyObject *o)
 {
     const int x = PyObject_IsTrue(o);
@@ -347,6 +348,7 @@ PyObject *attention(PyObject *, PyObject *const *x, Py_ssize_t n)
 {
     HANDLE_TH_ERRORS
     at::Tensor O;
+    double a = 0, b = 0;
     PyObject *declined = guarded(n, 7, [&]() -> PyObject * {
         for (int i = 0; i < 3; ++i)
             if (!plain(x[i])) Py_RETURN_NONE;
@@ -362,12 +364,12 @@ PyObject *attention(PyObject *, PyObject *const *x, Py_ssize_t n)
                 !torch::jit::tracer::isTracing());
         if (const auto &transforms = at::functorch::functorchTLSAccessor())
             transforms->checkSupportsCppAutogradFunction();  // throws inside of vmap, grad and the like
-        number(x[3]), number(x[4]);
+        a = real(x[3]);
+        b = real(x[4]);
         return PyBool_FromLong(1);
     });
     if (declined != Py_True) return declined;
     Py_DECREF(declined);
-    const double a = PyFloat_AsDouble(x[3]), b = PyFloat_AsDouble(x[4]);
     const int causal = PyObject_IsTrue(x[5]), norm = PyObject_IsTrue(x[6]);
     if (PyErr_Occurred()) return nullptr;
     try {

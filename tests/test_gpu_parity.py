@@ -395,6 +395,7 @@ def test_autograd_nodes_native_and_python(la, knobs, monkeypatch, norm, D, dtype
         got = [O, P, *torch.autograd.grad(loss, (Q, K, V, X), retain_graph=True)]
         got += torch.autograd.grad(loss, (Q, K, V, X), create_graph=True)
         got += torch.autograd.grad(P, (X,), torch.ones((), device="cuda", dtype=P.dtype).expand(P.shape))
+        got.append(la.linear_attention(Q, K, V, "1.0", "0.25"))  # whatever float() takes
         with torch.no_grad():
             got.append(la.linear_attention(Q, K, V))
         assert not got[-1].requires_grad and all(not t.requires_grad for t in got[2:6])
