@@ -396,6 +396,9 @@ def test_autograd_nodes_native_and_python(la, knobs, monkeypatch, norm, D, dtype
         got += torch.autograd.grad(loss, (Q, K, V, X), create_graph=True)
         got += torch.autograd.grad(P, (X,), torch.ones((), device="cuda", dtype=P.dtype).expand(P.shape))
         got.append(la.linear_attention(Q, K, V, "1.0", "0.25"))  # whatever float() takes
+        coef = torch.tensor(1.5, requires_grad=True)  # an input without a gradient, which makes O require one
+        got.append(la.linear_attention(Q.detach(), K.detach(), V.detach(), coef, 0.25, True, norm))
+        assert torch.autograd.grad(got[-1].float().sum(), (coef,), allow_unused=True) == (None,)
         with torch.no_grad():
             got.append(la.linear_attention(Q, K, V))
         assert not got[-1].requires_grad and all(not t.requires_grad for t in got[2:6])
