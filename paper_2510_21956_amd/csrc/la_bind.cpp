@@ -14,6 +14,7 @@
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/custom_function.h>
+#include <torch/csrc/autograd/python_cpp_function.h>
 #include <torch/csrc/autograd/python_variable.h>
 #include <torch/csrc/jit/frontend/tracer.h>
 
@@ -342,6 +343,61 @@ struct Attention : torch::autograd::Function<Attention> {
     }
 };
 
+// What grad_fn shows of LinearAttentionFunction's own: saved_tensors, la_args and la_saved.
+using AttentionNode = torch::autograd::CppNode<Attention>;
+AttentionNode &node(PyObject *self)
+{
+    return static_cast<AttentionNode &>(*reinterpret_cast<torch::autograd::THPCppFunction *>(self)->cdata);
+}
+PyObject *saved_tensors(PyObject *self, void *)
+{
+    HANDLE_TH_ERRORS
+    const auto saved = node(self).ctx_.get_saved_variables();
+    PyObject *t = PyTuple_New((Py_ssize_t)saved.size());
+    for (size_t i = 0; t && i < saved.size(); ++i) PyTuple_SET_ITEM(t, (Py_ssize_t)i, THPVariable_Wrap(saved[i]));
+    return t;
+    END_HANDLE_TH_ERRORS
+}
+PyObject *la_args(PyObject *self, void *)
+{
+    HANDLE_TH_ERRORS
+    auto &d = node(self).ctx_.saved_data;
+    return Py_BuildValue("ddNN", d["a"].toDouble(), d["b"].toDouble(), PyBool_FromLong(d["causal"].toBool()),
+                         PyBool_FromLong(d["norm"].toBool()));
+    END_HANDLE_TH_ERRORS
+}
+PyObject *la_saved(PyObject *self, void *)
+{
+    HANDLE_TH_ERRORS
+    const auto &d = node(self).ctx_.saved_data;
+    const auto it = d.find("sums");
+    if (it == d.end()) Py_RETURN_NONE;
+    return THPVariable_Wrap(it->second.toTensor());
+    END_HANDLE_TH_ERRORS
+}
+void show_node()
+{
+    using namespace torch::autograd;
+    static PyTypeObject type;
+    if (type.tp_name) return;
+    static PyMethodDef functions[] = {{"name", THPCppFunction_name, METH_NOARGS, nullptr},
+                                      {"register_hook", THPCppFunction_register_hook, METH_O, nullptr},
+                                      {"register_prehook", THPCppFunction_register_prehook, METH_O, nullptr},
+                                      {"_register_hook_dict", THPCppFunction_register_hook_dict, METH_O, nullptr},
+                                      {"_sequence_nr", THPCppFunction_sequence_nr, METH_NOARGS, nullptr},
+                                      {nullptr}};
+    static PyGetSetDef properties[] = {{"next_functions", THPCppFunction_next_functions, nullptr, nullptr, nullptr},
+                                       {"requires_grad", THPCppFunction_requires_grad, nullptr, nullptr, nullptr},
+                                       {"metadata", THPCppFunction_metadata, nullptr, nullptr, nullptr},
+                                       {"_input_metadata", THPCppFunction_input_metadata, nullptr, nullptr, nullptr},
+                                       {"saved_tensors", saved_tensors, nullptr, nullptr, nullptr},
+                                       {"la_args", la_args, nullptr, nullptr, nullptr},
+                                       {"la_saved", la_saved, nullptr, nullptr, nullptr},
+                                       {nullptr}};
+    registerCppFunction(typeid(AttentionNode),
+                        _initFunctionPyTypeObject(type, "LinearAttention", properties, functions));
+}
+
 // Q, K, V, a, b, causal, normalise -> O, or the library's status.  None: LinearAttentionFunction takes over, which is
 // where modes, transforms and traces that look into Python functions find what they look for.
 PyObject *attention(PyObject *, PyObject *const *x, Py_ssize_t n)
@@ -406,7 +462,10 @@ PyObject *init(PyObject *, PyObject *const *x, Py_ssize_t n)
     Py_XSETREF(python_backward, x[0]);
     Py_INCREF(x[1]);
     Py_XSETREF(raw_stream, x[1]);
+    HANDLE_TH_ERRORS
+    show_node();
     Py_RETURN_NONE;
+    END_HANDLE_TH_ERRORS
 }
 
 PyMethodDef methods[] = {{"init", (PyCFunction)(void (*)())init, METH_FASTCALL, nullptr},

@@ -391,8 +391,11 @@ def test_autograd_nodes_native_and_python(la, knobs, monkeypatch, norm, D, dtype
             O = la.linear_attention(Q, K, V, 1.0, 0.5, True, norm)
             P = la.linear_attention(X.transpose(1, 2), K, V, 1, 0.25, False, norm)
         assert ("LinearAttentionFunction" in O.grad_fn.name()) == (node == "python")
+        shown, sums = O.grad_fn.saved_tensors, O.grad_fn.la_saved
+        assert len(shown) == 5 and O.grad_fn.la_args == (1.0, 0.5, True, norm)
+        assert (sums is None) == (D == 16) and (sums is None or sums.dtype == torch.uint8)
         loss = O.float().sum() + (P.float() ** 2).sum()
-        got = [O, P, *torch.autograd.grad(loss, (Q, K, V, X), retain_graph=True)]
+        got = [*shown, O, P, *torch.autograd.grad(loss, (Q, K, V, X), retain_graph=True)]
         got += torch.autograd.grad(loss, (Q, K, V, X), create_graph=True)
         got += torch.autograd.grad(P, (X,), torch.ones((), device="cuda", dtype=P.dtype).expand(P.shape))
         got.append(la.linear_attention(Q, K, V, "1.0", "0.25"))  # whatever float() takes
@@ -401,7 +404,7 @@ def test_autograd_nodes_native_and_python(la, knobs, monkeypatch, norm, D, dtype
         assert torch.autograd.grad(got[-1].float().sum(), (coef,), allow_unused=True) == (None,)
         with torch.no_grad():
             got.append(la.linear_attention(Q, K, V))
-        assert not got[-1].requires_grad and all(not t.requires_grad for t in got[2:6])
+        assert not got[-1].requires_grad and all(not t.requires_grad for t in got[7:11])
         refused = []
 
         def refuse(f):
