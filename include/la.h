@@ -294,7 +294,7 @@ LA_API void la_debug_override(int seg_len, int force_generic);
  * la_backward_saved, which then skips that recomputation.  This is an
  * addition to the set {Q,K,V,O,g} that Sec. 3.2 keeps: O(B*H*(N/segment)*D^2)
  * floats, small next to the tensors where these are large (8 to 17 MB at D = 64
- * and 128 where the segments just fill the GPU, 68 MB at D = 256), but larger than
+ * and 128 where the segments just fill the GPU, 34 MB at D = 256), but larger than
  * a tensor where sequences are short.
  *
  *   la_saved_state_bytes: size of the `saved` buffer for this problem (0 for

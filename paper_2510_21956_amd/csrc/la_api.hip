@@ -103,17 +103,13 @@ Plan make_plan(int B, int H, int N, int D, la_dtype dt, int causal, int is_backw
         const size_t need =
             split_scratch(h, (int)BH, N, dt, is_backward).total_floats * sizeof(float);
         if (need > p.total_bytes || !g_force_generic.load(std::memory_order_relaxed)) p.total_bytes = need;
-        // The hand-over, 264 KB a segment, is optional here; its size is that of the cut that is nearest to one
-        // workgroup a unit, of 192 rows a segment at least, or of the plan's where that is finer.  The plan itself
-        // has half of that where slices are few, as two block problems share a launch.  One segment with the
-        // mask hands nothing over: 256 bytes that stay unused.  Slices cut into several segments have 340 in all
-        // at most, 90 MB.  What takes more than kSplitSavedMost, hundreds or thousands of short slices, is handed
-        // over only where it is no larger than one of the tensors (8000 slices of 40 rows without the mask, bf16:
-        // 2.1 GB of sums next to tensors of 164 MB).
-        const long nseg = max((long)h.nseg, max(min((256 + BH / 2) / BH, (long)N / 192), 1L));
-        const size_t tensor = (size_t)BH * N * D * (dt == LA_F32 ? 4 : 2);
-        const size_t bytes = split_saved_bytes(h, (int)BH) + 4 * (nseg - h.nseg) * (h.saved_bytes / h.nseg);
-        p.saved_bytes = causal && nseg == 1 ? 256 : bytes <= kSplitSavedMost || bytes <= tensor ? bytes : 0;
+        // The hand-over, 264 KB a segment, is optional here.  One segment with the mask hands nothing over: 256
+        // bytes that stay unused.  Slices cut into several segments have 128 in all at most, 34 MB.  What takes
+        // more than kSplitSavedMost, hundreds or thousands of short slices without the mask, is handed over only
+        // where it is no larger than one of the tensors (8000 slices of 40 rows, bf16: 2.1 GB of sums next to
+        // tensors of 164 MB).
+        const size_t tensor = (size_t)BH * N * D * (dt == LA_F32 ? 4 : 2), bytes = split_saved_bytes(h, (int)BH);
+        p.saved_bytes = causal && h.nseg == 1 ? 256 : bytes <= kSplitSavedMost || bytes <= tensor ? bytes : 0;
     }
     return p;
 }

@@ -77,8 +77,8 @@ def test_workspace_bytes(lib):
 
 
 @pytest.mark.parametrize("B,H,N,e,causal,want", [
-    (4, 16, 4096, 4, 1, "sums"), (1, 8, 8000, 2, 1, "sums"), (1, 1, 200000, 2, 0, "sums"), (10, 17, 400, 2, 1, "sums"),
-    (10, 50, 200, 4, 1, "unused"), (8, 1000, 40, 2, 1, "unused"),  # one segment with the mask
+    (4, 16, 4096, 4, 1, "sums"), (1, 8, 8000, 2, 1, "sums"), (1, 1, 200000, 2, 0, "sums"), (6, 10, 1000, 2, 1, "sums"),
+    (10, 17, 400, 2, 1, "unused"), (1, 65, 1000, 2, 1, "unused"), (10, 10, 1000, 4, 1, "unused"), (10, 50, 200, 4, 1, "unused"), (8, 1000, 40, 2, 1, "unused"),  # one segment with the mask
     (8, 1000, 40, 2, 0, "none"), (10, 50, 200, 4, 0, "none"), (8, 1000, 300, 4, 0, "sums")])
 def test_hand_over_size_at_head_size_256(lib, B, H, N, e, causal, want):
     """Bounded by 96 MiB or one tensor, and no room for sums where none are handed over."""
@@ -86,6 +86,12 @@ def test_hand_over_size_at_head_size_256(lib, B, H, N, e, causal, want):
     n = la.la_saved_state_bytes(B, H, N, 256, la.LA_F32 if e == 4 else la.LA_BF16, causal)
     assert n <= max(96 << 20, B * H * N * 256 * e)
     assert n == {"unused": 256, "none": 0}.get(want, n) and (want != "sums" or n >= 4 * B * H * 128 * 129 * 4)
+    if want == "sums":  # no more than the segments of the sums kernel have: theirs are the workspace's first part
+        slots = 4 * (128 * 128 + 2 * 128)
+        shares = B * H * N * 4 * (1 if e == 4 else 1 + 2 * 128)
+        ws = la.la_workspace_bytes(B, H, N, 256, la.LA_F32 if e == 4 else la.LA_BF16, causal, 0)
+        nseg = (ws - shares) // (4 * slots * B * H)
+        assert n <= 4 * B * H * nseg * 4 * (128 * 128 + 128) + 1024 * B * H
 
 
 @pytest.mark.parametrize("BH,N,D,e,causal,most", [
