@@ -342,7 +342,10 @@ LA_API la_status la_backward_saved(const void *Q, const void *K, const void *V,
  * kernel and events[k] right after their k-th kernel, and fill `names[k-1]`
  * with a static string naming that kernel.  `recorded` receives the number of
  * events recorded (kernels + 1); if `capacity` is too small only the first
- * `capacity` events are recorded.  The caller synchronises and reads the
+ * `capacity` events are recorded.  No call has more than LA_MAX_TRACE entries: at
+ * D = 256 the forward pass that la_backward runs again (O or G NULL) is one entry, and
+ * so are the two kernels that form the sums of slices whose hand-over does not hold.
+ * The caller synchronises and reads the
  * intervals with hipEventElapsedTime.  The library never waits on the events.
  */
 #define LA_MAX_TRACE 8

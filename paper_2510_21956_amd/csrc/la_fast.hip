@@ -100,6 +100,7 @@ la_status split_forward(const Problem &pr, const Plan &pl, const void *Q, const 
     if (s != LA_OK || !saved) return s;
     k_leave_witness<<<dim3(pr.BH), dim3(64), 0, st>>>((const uint32_t *)O, witness(saved, pl), pr.N, row_words(pr.dt),
                                                       problem_key(pr, pl));
+    tc.mark("leave_witness");
     return launch_status();
 }
 
@@ -121,6 +122,7 @@ la_status split_backward(const Problem &pr, const Plan &pl, const void *Q, const
         int *handed = (int *)(ws + sc.flag_off);
         k_check_witness<<<dim3(pr.BH), dim3(64), 0, st>>>((const uint32_t *)O, witness((float *)saved, pl), handed,
                                                           pr.N, row_words(pr.dt), problem_key(pr, pl));
+        tc.mark("check_witness");
         bs.handed = handed;
     }
     return planes_backward(p, pl, 256, Q, K, V, O, G, dO, dQ, dK, dV, ws, saved, st, tc, bs);

@@ -2040,11 +2040,11 @@ la_status run_backward(const Problem &pr, const Plan &pl, const void *Qv, const 
         (pr.causal ? kv_state<MODE, D, true, LD, false>(pr, 2) : kv_state<MODE, D, true, LD, true>(pr, 4))<<<
             dim3(pr.BH * nrun << all), block, 0, st>>>(
             K, V, ws, pr.N, nseg, nrun, pl.map, pl.slot_floats, pr.causal ? 1 : 0, bs.handed, blocks(all, 0xe4));
-        tc.mark("bwd_state");
+        if (!bs.handed) tc.mark("bwd_state");  // one entry with the scan where both return at once (LA_MAX_TRACE)
         if (saved || !fold) {
             launch_scan_slots(ws, pr.BH << all, nseg, pl.slot_floats, SL::ST, SL::R - SL::ST, pr.causal ? 0 : 2,
                               pr.causal ? 1 : 0, nseg - 1, st, bs.handed, pr.BH);
-            tc.mark("scan_slots");
+            tc.mark(bs.handed ? "bwd_state_scan" : "scan_slots");
         }
     }
     const float *sinit = saved ? saved : ws;

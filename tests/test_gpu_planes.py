@@ -1,5 +1,7 @@
 """The plane-split matrix-core kernels at the sizes where they can go wrong: chunk and segment
 edges, every tile form, the padded head size, exact scaling, non-finite inputs."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -170,6 +172,41 @@ def test_sums_at_head_size_256_are_used_only_where_they_were_written(la, dtype, 
     saved[:3 * (128 * 128 + 128) * 4] = 0xFF
     got = gpu_backward_saved(la, dev, O, G, saved, 1.0, 0.5, causal)
     assert torch.isnan(got[0][0, 0].float()).any()
+
+
+@pytest.mark.parametrize("handed", [True, False])
+@pytest.mark.parametrize("causal", [True, False])
+def test_trace_at_head_size_256_reaches_the_last_kernel(la, causal, handed):
+    """Forward, backward and recomputing backward passes: every kernel in an entry, up to the last."""
+    dev, _ = upload_case(1, 2, 700, 256, "f32", 6900, [0])
+    O, G, saved = gpu_forward_save(la, dev, 1.0, 0.5, causal)
+    grads = [torch.empty_like(O) for _ in range(3)]
+
+    def names(call):
+        events = [torch.cuda.Event(enable_timing=True) for _ in range(la.LA_MAX_TRACE + 4)]
+        for e in events:
+            e.record()
+        tr = la.la_trace()
+        tr.events = (ctypes.c_void_p * len(events))(*(e.cuda_event for e in events))
+        tr.capacity = len(events)
+        call(tr)
+        torch.cuda.synchronize()
+        assert tr.recorded - 1 <= la.LA_MAX_TRACE
+        return [tr.names[k].decode() for k in range(tr.recorded - 1)]
+
+    def ws(which):
+        return scratch(la.la_workspace_bytes(1, 2, 700, 256, la.LA_F32, causal, which), "cuda")
+    own = ["bwd_state", "scan_slots"]
+    sums = ["check_witness", "bwd_state_scan"] if handed else own
+    sweeps = ["bwd_dq", "bwd_dq", "scan_slots_rev", "bwd_dkv", "bwd_dkv"]
+    args = dev["Q"], dev["K"], dev["V"]
+    kept = saved if handed else None
+    assert names(lambda tr: la.la_forward_save(*args, O, G, 1.0, 0.5, causal, ws(0), kept, None, tr)) == \
+        ["fwd_state", "scan_slots", "fwd_apply", "fwd_apply"] + ["leave_witness"] * handed
+    for again in (0, 1):
+        og = (None, None) if again else (O, G)
+        assert names(lambda tr: la.la_backward_saved(*args, *og, dev["dO"], *grads, 1.0, 0.5, causal, ws(1 + again), kept,
+                                                     None, tr)) == ["fwd_again"] * again + sums + sweeps
 
 
 @pytest.mark.parametrize("causal", [True, False])
