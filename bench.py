@@ -423,7 +423,7 @@ def measure(cfg, args, steps, warmup, torch, wl, la):
                 kcount[name] = kcount.get(name, 0) + 1
         evf.destroy()
         evb.destroy()
-    kernels_ms = {k: ksum[k] / kcount[k] for k in ksum}
+    kernels_ms = {k: ksum[k] / kcount[k] for k in ksum}  # of one launch (D = 256 has two of a name in a pass)
 
     # Roofline of the dominant kernel (the one with the longest average duration).
     alg_bytes = algorithmic_bytes(D, e, cfg.causal)
@@ -495,8 +495,8 @@ def measure(cfg, args, steps, warmup, torch, wl, la):
                        "mfma_peak_TFLOPs": mfma_peak, "frac_of_mfma_peak": pass_tflops / mfma_peak},
         "kernels_ms": kernels_ms,
         # the two passes separately: sums of the traced kernel intervals
-        "forward_ms_traced": sum(v for k, v in kernels_ms.items() if k.startswith("fwd:")),
-        "backward_ms_traced": sum(v for k, v in kernels_ms.items() if k.startswith("bwd:")),
+        "forward_ms_traced": sum(v / reps for k, v in ksum.items() if k.startswith("fwd:")),
+        "backward_ms_traced": sum(v / reps for k, v in ksum.items() if k.startswith("bwd:")),
         "peak_allocated_device_bytes": int(peak_bytes),
         "workspace_bytes": {"forward": wsf.numel(), "backward": wsb.numel(), "saved": nsv},
         "roofline": roofline,
