@@ -91,10 +91,20 @@ LA_API const char *la_status_string(la_status s);
  * unsupported arguments.  The workspace holds the per-segment running-sum
  * states (S = sum k v^T, z = sum k, p = sum v of Eq. xy; and the reverse sums
  * of Eq. endd for the backward pass) that let segments of one sequence run in
- * parallel; its size is O(B*H*(N/segment)*D^2 + B*H*N).  D = 256 runs as passes over
- * blocks of 128 columns; with bf16 tensors the shares that one pass hands to the next stay
- * in float32 in the workspace: 512 more bytes per token-head for la_forward, 2048 for
+ * parallel; its size is O(B*H*(N/segment)*D^2 + B*H*N).  D = 256 runs on
+ * blocks of 128 columns; with bf16 tensors the shares that one launch hands to the next stay
+ * in float32 in the workspace: 1024 more bytes per token-head for la_forward, 3072 for
  * la_backward.
+ *
+ * The sizes do not grow steadily with N: a sequence is cut into the number of segments that
+ * costs least, and a longer one may be cut into fewer (bf16, D = 32, 156 slices: 8.8 MB at
+ * N = 773, 2.0 MB at 1165).  A caller that keeps one buffer for several lengths takes the
+ * largest of their sizes, or, for every length up to N, this bound (in bytes, plus 1024):
+ *     la_forward   4 M E (E + 2)       + at D = 256 B*H*N * 4, in bf16 * 1028
+ *     la_backward  4 M E (2 E + 4)     + B*H*N * 4, at D = 256 B*H*(N + 1) * 8, in bf16 * 3080
+ *     hand-over    4 M E (E + 2)       + at D = 256 B*H * 1024      (la_saved_state_bytes)
+ * with E = 32, 32, 64, 128, 128 and M = max(B*H, 3072), max(B*H, 3072), max(B*H, 1536),
+ * max(B*H, 768), 4 max(B*H, 128) at D = 16, 32, 64, 128, 256.
  */
 LA_API size_t la_workspace_bytes(int B, int H, int N, int D, la_dtype dt, int causal,
                           int is_backward);
@@ -294,10 +304,12 @@ LA_API void la_debug_override(int seg_len, int force_generic);
  * la_backward_saved, which then skips that recomputation.  This is an
  * addition to the set {Q,K,V,O,g} that Sec. 3.2 keeps: O(B*H*(N/segment)*D^2)
  * floats, small next to the tensors where these are large (8 to 17 MB at D = 64
- * and 128 where the segments just fill the GPU, 34 MB at D = 256), but larger than
+ * and 128 where the segments just fill the GPU, up to three times that where three
+ * rounds of them do; 34 MB at D = 256), but larger than
  * a tensor where sequences are short.
  *
- *   la_saved_state_bytes: size of the `saved` buffer for this problem (0 for
+ *   la_saved_state_bytes: size of the `saved` buffer for this problem (it does not grow
+ *       steadily with N either: see la_workspace_bytes; 0 for
  *       invalid arguments, and 0 when the library would not use one -- D = 16,
  *       and D = 256 where it would exceed both 96 MB and one tensor's bytes;
  *       a zero-size buffer may be NULL).

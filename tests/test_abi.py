@@ -94,6 +94,27 @@ def test_hand_over_size_at_head_size_256(lib, B, H, N, e, causal, want):
         assert n <= 4 * B * H * nseg * 4 * (128 * 128 + 128) + 1024 * B * H
 
 
+@pytest.mark.parametrize("D", [16, 32, 64, 128, 256])
+def test_sizes_stay_below_the_documented_bound(lib, D):
+    """include/la.h: what a buffer for every length up to N takes; sizes themselves may fall as N grows."""
+    import paper_2510_21956_amd as la
+    E = {16: 32, 256: 128}.get(D, D)
+    for BH in (1, 3, 16, 60, 130, 156, 200, 700, 3100):
+        M = 4 * max(BH, 128) if D == 256 else max(BH, {16: 3072, 32: 3072, 64: 1536, 128: 768}[D])
+        for dt, causal in ((la.LA_F32, 0), (la.LA_F32, 1), (la.LA_BF16, 0), (la.LA_BF16, 1)):
+            most = [0, 0, 0]
+            for N in (1, 33, 300, 773, 1165, 3001, 10000, 65537):
+                wide = D == 256 and dt == la.LA_BF16
+                bound = (4 * M * E * (E + 2) + (BH * N * (1028 if wide else 4) if D == 256 else 0),
+                         4 * M * E * (2 * E + 4) + (BH * (N + 1) * (3080 if wide else 8) if D == 256 else BH * N * 4),
+                         4 * M * E * (E + 2) + (BH * 1024 if D == 256 else 0))
+                size = (la.la_workspace_bytes(1, BH, N, D, dt, causal, 0),
+                        la.la_workspace_bytes(1, BH, N, D, dt, causal, 1),
+                        la.la_saved_state_bytes(1, BH, N, D, dt, causal))
+                most = [max(x, y) for x, y in zip(most, size)]
+                assert all(x <= y + 1024 for x, y in zip(most, bound)), (BH, N, dt, causal, most, bound)
+
+
 @pytest.mark.parametrize("BH,N,D,e,causal,most", [
     (4, 500, 128, 4, 1, 64), (4, 500, 128, 2, 1, 32), (1, 256, 16, 4, 1, 8), (1, 30000, 64, 2, 1, 512),
     (60, 4000, 64, 4, 1, 512), (42, 9979, 128, 4, 1, 256), (190, 10000, 128, 2, 1, 768), (64, 100000, 64, 4, 0, 512)])
