@@ -163,53 +163,79 @@ __device__ __forceinline__ void put(float *dst, T x, int accumulate)
     *d = accumulate ? *d + x : x;
 }
 
-// state (+)= the sums of [S | z | p] over the slots of every slice, count (+)= N; W floats a thread.
-// With few slots a slice this is a copy, bound by memory: 16 bytes a thread (1024 slices of 20 rows,
-// D = 128, bf16, with the sums kernel: 37 us; 92 with 4 bytes).  With many, which only few slices
-// have, the round trips along the slots bound it: more threads, 4 bytes each (one slice of 60000
-// rows, 468 slots, D = 64, bf16: 22 us; 31 with 16 bytes).
-constexpr int kManySlots = 32;
+// Few slots a slice: this is a copy, bound by memory, 16 bytes a thread (W = 4; 1024 slices of 20 rows, D = 128, bf16,
+// with the sums kernel: 37 us; 92 with 4 bytes).  Many, which only few slices have: the round trips along the slots
+// bound it, so 16 groups of 32 lanes (W = 1) read a run of them each and add up through LDS.  16 bytes and runs, us, with
+// the sums kernel, fp32, one slice: D = 32, 33 slots 9.9 and 10.0, 96 12.1 and 10.0, 300 27.8 and 10.1; D = 128, 33 11.6 and
+// 10.0, 300 38.6 and 22.3; six slices at D = 128, 33 15.9 and 16.3, 160 43.6 and 39.2.  (One thread a float, one slot after
+// another: one slice of 24342 rows, D = 32, 761 slots, 40.4; runs 10.9.)
+constexpr int kManySlots = 32, kRuns = 16;
 template <int W>
-__global__ __launch_bounds__(256) void k_state_from_totals(const float *__restrict__ ws,
+constexpr int kStateThreads = W == 1 ? 32 * kRuns : 256;
+// Floats that a workgroup makes, and the first one of this thread.
+template <int W>
+constexpr int kStateFloats = W == 1 ? 32 : 4 * 256;
+template <int W>
+__device__ __forceinline__ int state_float()
+{
+    return blockIdx.y * kStateFloats<W> + (W == 1 ? threadIdx.x % 32 : W * threadIdx.x);
+}
+// The sum at e over all slots where `there`; called by every thread.  W = 1: in the first 32 threads.
+template <int W>
+__device__ __forceinline__ auto slot_total(const float *src, int e, bool there, int nseg, size_t slot_floats)
+{
+    if constexpr (W == 4) {
+        return there ? sum_slots<4>(src, e, nseg, slot_floats) : f4{};
+    } else {
+        __shared__ float sums[kRuns][32];
+        const int run = threadIdx.x / 32, n = (nseg + kRuns - 1) / kRuns, first = min(run * n, nseg);
+        sums[run][threadIdx.x % 32] =
+            there ? sum_slots<1>(src + (size_t)first * slot_floats, e, min(n, nseg - first), slot_floats) : 0.f;
+        block_sync();
+        float x = 0.f;
+        for (int r = 0; r < kRuns && run == 0; ++r) x += sums[r][threadIdx.x];
+        return x;
+    }
+}
+
+// state (+)= the sums of [S | z | p] over the slots of every slice, count (+)= N.
+template <int W>
+__global__ __launch_bounds__(kStateThreads<W>) void k_state_from_totals(const float *__restrict__ ws,
                                                            float *__restrict__ state, int D,
                                                            int nseg, size_t slot_floats,
                                                            size_t state_floats, int N,
                                                            int accumulate)
 {
-    const int bh = blockIdx.x, len = D * D + 2 * D, e = W * (blockIdx.y * 256 + threadIdx.x);
+    const int bh = blockIdx.x, len = D * D + 2 * D, e = state_float<W>();
     const float *src = ws + (size_t)bh * nseg * slot_floats;
     float *dst = state + (size_t)bh * state_floats;
-    if (e < len) put(dst + e, sum_slots<W>(src, e, nseg, slot_floats), accumulate);
+    const auto x = slot_total<W>(src, e, e < len, nseg, slot_floats);
+    if (W == 1 && threadIdx.x >= 32) return;
+    if (e < len) put(dst + e, x, accumulate);
     else if (e == len) put(dst + e, (float)N, accumulate);
 }
 
 // The same for D = 256 from the slots of the block problem (k block i, v block j) at D = 128:
 // S block (i, j); z block i (taken when j = 0); p block j (when i = 0); the count once.
 template <int W>
-__global__ __launch_bounds__(256) void k_state_block_from_totals(const float *__restrict__ ws,
+__global__ __launch_bounds__(kStateThreads<W>) void k_state_block_from_totals(const float *__restrict__ ws,
                                                                  float *__restrict__ state,
                                                                  int nseg, size_t slot_floats,
                                                                  size_t state_floats, int bi,
                                                                  int bj, int N, int accumulate)
 {
     constexpr int H = 128, D = 256;
-    const int bh = blockIdx.x, len = H * H + 2 * H, e = W * (blockIdx.y * 256 + threadIdx.x);
+    const int bh = blockIdx.x, len = H * H + 2 * H, e = state_float<W>();
     const float *src = ws + (size_t)bh * nseg * slot_floats;
     float *dst = state + (size_t)bh * state_floats;
-    int to;
-    if (e < H * H) {
-        to = (bi * H + e / H) * D + bj * H + e % H;
-    } else if (e < H * H + H) {
-        if (bj != 0) return;
-        to = D * D + bi * H + (e - H * H);
-    } else if (e < len) {
-        if (bi != 0) return;
-        to = D * D + D + bj * H + (e - H * H - H);
-    } else {
-        if (e == len && bi == 0 && bj == 0) put(dst + D * D + 2 * D, (float)N, accumulate);
-        return;
-    }
-    put(dst + to, sum_slots<W>(src, e, nseg, slot_floats), accumulate);
+    int to = -1;  // nothing to write
+    if (e < H * H) to = (bi * H + e / H) * D + bj * H + e % H;
+    else if (e < H * H + H) to = bj == 0 ? D * D + bi * H + (e - H * H) : -1;
+    else if (e < len) to = bi == 0 ? D * D + D + bj * H + (e - H * H - H) : -1;
+    const auto x = slot_total<W>(src, e, to >= 0, nseg, slot_floats);
+    if (W == 1 && threadIdx.x >= 32) return;
+    if (to >= 0) put(dst + to, x, accumulate);
+    else if (e == len && bi == 0 && bj == 0) put(dst + D * D + 2 * D, (float)N, accumulate);
 }
 
 // Stage 1 of sum(X * Y): workgroup w sums a fixed contiguous share into partials[w].
@@ -339,15 +365,18 @@ la_status decode_step(const void *Q, const void *K, const void *V, void *O, floa
     return decode_by_d<bf16_t>(Q, K, V, O, G, state, BH, Tn, D, sf, a, b, st);
 }
 
-// Thread blocks for len floats and the count, W floats a thread.
-static int state_blocks(int len, int W) { return (len / W + 1 + 255) / 256; }
+// Workgroups for len floats and the count.
+template <int W>
+static int state_blocks(int len) { return (len + 1 + kStateFloats<W> - 1) / kStateFloats<W>; }
 
 la_status state_from_totals(const float *ws, float *state, int BH, int D, int nseg,
                             size_t slot_floats, int N, int accumulate, hipStream_t st)
 {
-    const int W = nseg > kManySlots ? 1 : 4;
-    auto *kernel = W == 4 ? k_state_from_totals<4> : k_state_from_totals<1>;
-    kernel<<<dim3(BH, state_blocks(D * D + 2 * D, W)), dim3(256), 0, st>>>(
+    const int len = D * D + 2 * D;
+    const bool many = nseg > kManySlots;
+    (many ? k_state_from_totals<1> : k_state_from_totals<4>)<<<
+        dim3(BH, many ? state_blocks<1>(len) : state_blocks<4>(len)),
+        dim3(many ? kStateThreads<1> : kStateThreads<4>), 0, st>>>(
         ws, state, D, nseg, slot_floats, decode_state_floats(D), N, accumulate);
     return hipGetLastError() == hipSuccess ? LA_OK : LA_ERR_LAUNCH;
 }
@@ -356,9 +385,11 @@ la_status state_block_from_totals(const float *ws, float *state, int BH, int nse
                                   size_t slot_floats, int bi, int bj, int N, int accumulate,
                                   hipStream_t st)
 {
-    const int W = nseg > kManySlots ? 1 : 4;
-    auto *kernel = W == 4 ? k_state_block_from_totals<4> : k_state_block_from_totals<1>;
-    kernel<<<dim3(BH, state_blocks(128 * 128 + 2 * 128, W)), dim3(256), 0, st>>>(
+    const int len = 128 * 128 + 2 * 128;
+    const bool many = nseg > kManySlots;
+    (many ? k_state_block_from_totals<1> : k_state_block_from_totals<4>)<<<
+        dim3(BH, many ? state_blocks<1>(len) : state_blocks<4>(len)),
+        dim3(many ? kStateThreads<1> : kStateThreads<4>), 0, st>>>(
         ws, state, nseg, slot_floats, decode_state_floats(256), bi, bj, N, accumulate);
     return hipGetLastError() == hipSuccess ? LA_OK : LA_ERR_LAUNCH;
 }
