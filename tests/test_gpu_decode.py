@@ -149,6 +149,20 @@ def test_prefill_adds_any_number_of_slots(la, D, nseg):
     assert np.array_equal(twice, 2.0 * once)
 
 
+# bf16: shorter than a prompt's shortest segments, prompts in one segment and in several of their own, more than a round
+@pytest.mark.parametrize("BH,N,D", [(3, 70, 32), (2, 257, 64), (5, 700, 128), (300, 90, 128), (140, 400, 128)])
+def test_prefill_in_segments_of_its_own(la, BH, N, D):
+    dev, ref = draw(BH, N, D, "bf16", 960 + N)
+    K, V = dev["K"].view(1, BH, N, D), dev["V"].view(1, BH, N, D)
+    state = torch.zeros(la.la_decode_state_bytes(1, BH, D) // 4, device="cuda")
+    ws = scratch(la.la_workspace_bytes(1, BH, N, D, la.LA_BF16, False, 0), "cuda")
+    la.la_decode_prefill(K, V, state, 0, ws)
+    k, v = ref["K"], ref["V"]
+    want = np.concatenate([np.matmul(k.transpose(0, 2, 1), v).reshape(BH, -1), k.sum(1), v.sum(1),
+                           np.full((BH, 1), float(N))], axis=1)
+    assert excess(canonical_state(state, BH, D), want, TOL["f32"]) <= 1.0
+
+
 def _outcome(call):
     try:
         call()
