@@ -117,9 +117,10 @@ def test_sizes_stay_below_the_documented_bound(lib, D):
 
 @pytest.mark.parametrize("BH,N,D,e,causal,most", [
     (4, 500, 128, 4, 1, 64), (4, 500, 128, 2, 1, 32), (1, 256, 16, 4, 1, 8), (1, 30000, 64, 2, 1, 512),
-    (60, 4000, 64, 4, 1, 512), (42, 9979, 128, 4, 1, 256), (190, 10000, 128, 2, 1, 768), (64, 100000, 64, 4, 0, 512)])
+    (60, 4000, 64, 4, 1, 512), (42, 9979, 128, 4, 1, 256), (190, 10000, 128, 2, 1, 768), (64, 100000, 64, 4, 0, 512),
+    (12, 61, 16, 4, 0, 12), (5, 51, 64, 4, 0, 5), (10, 60, 32, 4, 1, 10), (28, 112, 64, 4, 1, 112), (37, 128, 32, 4, 0, 37)])
 def test_cuts(lib, BH, N, D, e, causal, most):
-    """Short sequences are cut into the shortest segments, and no cut leaves a few segments over what the compute
+    """Short sequences are cut into the shortest segments, unless that costs more kernels than it saves, and no cut leaves a few segments over what the compute
     units hold in whole rounds."""
     import paper_2510_21956_amd as la
     S = max(D, 32)
