@@ -98,7 +98,7 @@ LA_API const char *la_status_string(la_status s);
  *
  * The sizes do not grow steadily with N: a sequence is cut into the number of segments that
  * costs least, and a longer one may be cut into fewer (bf16, D = 32, 156 slices: 8.8 MB at
- * N = 773, 2.0 MB at 1165).  A caller that keeps one buffer for several lengths takes the
+ * N = 773, 2.7 MB at 1165).  A caller that keeps one buffer for several lengths takes the
  * largest of their sizes, or, for every length up to N, this bound (in bytes, plus 1024):
  *     la_forward   4 M E (E + 2)       + at D = 256 B*H*N * 4, in bf16 * 1028
  *     la_backward  4 M E (2 E + 4)     + B*H*N * 4, at D = 256 B*H*(N + 1) * 8, in bf16 * 3080
