@@ -165,11 +165,12 @@ __device__ __forceinline__ void put(float *dst, T x, int accumulate)
 
 // Few slots a slice: this is a copy, bound by memory, 16 bytes a thread (W = 4; 1024 slices of 20 rows, D = 128, bf16,
 // with the sums kernel: 37 us; 92 with 4 bytes).  Many, which only few slices have: the round trips along the slots
-// bound it, so 16 groups of 32 lanes (W = 1) read a run of them each and add up through LDS.  16 bytes and runs, us, with
-// the sums kernel, fp32, one slice: D = 32, 33 slots 9.9 and 10.0, 96 12.1 and 10.0, 300 27.8 and 10.1; D = 128, 33 11.6 and
-// 10.0, 300 38.6 and 22.3; six slices at D = 128, 33 15.9 and 16.3, 160 43.6 and 39.2.  (One thread a float, one slot after
-// another: one slice of 24342 rows, D = 32, 761 slots, 40.4; runs 10.9.)
-constexpr int kManySlots = 32, kRuns = 16;
+// bound it, so 8 groups of 32 lanes (W = 1) read a run of them each and add up through LDS.  16 bytes and runs, us, with
+// the sums kernel, fp32, one slice: D = 32, 33 slots 10.6 and 10.8, 96 12.2 and 10.8, 300 27.7 and 10.8; D = 128, 33 11.5 and
+// 10.9, 300 38.5 and 21.7; six slices at D = 128, 33 16.1 and 14.9, 160 42.5 and 39.1.  One thread a float and one slot
+// after another, 700 slots of one slice, D = 32 38.5, D = 128 53.2; runs 12.1 and 31.3 (16 of them 10.7 and 31.8, but
+// 16.3 for the 33 slots of six slices).
+constexpr int kManySlots = 32, kRuns = 8;
 template <int W>
 constexpr int kStateThreads = W == 1 ? 32 * kRuns : 256;
 // Floats that a workgroup makes, and the first one of this thread.

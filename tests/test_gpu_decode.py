@@ -124,7 +124,7 @@ def test_decode_argument_errors(la):
     assert la.la_decode_state_bytes(1, 1, 48) == 0
 
 
-# one slot a slice, a batch of sixteen and one more, either side of the change to runs of slots (3 at 33, the last ones
+# one slot a slice, a batch of sixteen and one more, either side of the change to runs of slots (5 at 33, the last one
 # empty), more than a batch in a run
 @pytest.mark.parametrize("nseg", [1, 16, 17, 32, 33, 50, 259])
 @pytest.mark.parametrize("D", [16, 64, 256])
