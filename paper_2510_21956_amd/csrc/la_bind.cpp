@@ -421,7 +421,8 @@ PyObject *attention(PyObject *, PyObject *const *x, Py_ssize_t n)
         if (const auto &transforms = at::functorch::functorchTLSAccessor())
             transforms->checkSupportsCppAutogradFunction();  // throws inside of vmap, grad and the like
         // a tensor among the coefficients and switches is an input of the Python node: its grad makes O require one
-        for (int i = 3; i < 7; ++i) require(!THPVariable_Check(x[i]));
+        for (int i = 3; i < 7; ++i)
+            require(PyFloat_CheckExact(x[i]) || PyLong_Check(x[i]) || !THPVariable_Check(x[i]));
         a = real(x[3]);
         b = real(x[4]);
         return PyBool_FromLong(1);
