@@ -633,8 +633,10 @@ la_status la_decode_prefill(const void *K, const void *V, float *state, size_t s
     // ones, in two rounds at most (us, the plan's segments and these: D = 128, 12 slices of 1278 rows 14.8 and 11.1,
     // 175 of 2422 59.8 and 49.7, 135 of 3817 68.5 and 53.6; D = 64, 207 of 4339 45.5 and 37.4).  fp32, over 600 shapes
     // at D = 128, takes 7 % longer in them.
-    const la::Plan own = la::make_plan(B, H, N, D, dt, 0, 0, true, la::Cut{128, 2});
-    if (dt == LA_BF16 && la::use_fast(pr) && own.total_bytes < pl.total_bytes) pl = own;
+    if (dt == LA_BF16 && la::use_fast(pr)) {
+        const la::Plan own = la::make_plan(B, H, N, D, dt, 0, 0, true, la::Cut{128, 2});
+        if (own.total_bytes < pl.total_bytes) pl = own;
+    }
     s = la::use_fast(pr) ? la::planes_totals(pr, pl, D, K, V, (float *)workspace, st)
                          : la::generic_kv_totals(pr, pl, K, V, (float *)workspace, st);
     if (s != LA_OK) return s;
