@@ -171,7 +171,7 @@ void launch_scan_slots(float *ws, int BH, int nseg, size_t slot_floats, int off,
 // dK == nullptr: the ascending sweep alone, dQ for the coefficients in pr.
 // planes_totals: the per-segment sums over the whole sequence, S = sum k v^T, z = sum k, p = sum v,
 // in the slots of every slice as [S | z | p] (forward plan without the mask), ld = 256: those of the four block
-// problems one after another; state_from_totals adds the slots up.
+// problems one after another, or of `block` alone (pl.together not set); state_from_totals adds the slots up.
 // `handed` (one int a slice on the device; null: `saved` holds whenever it is given): the slices whose sums
 // in `saved` hold; the sums of the others are formed in the workspace, as without `saved`.
 struct BlockScratch {
@@ -188,7 +188,7 @@ la_status planes_backward(const Problem &pr, const Plan &pl, int ld, const void 
                           void *dK, void *dV, float *ws, const float *saved, hipStream_t st,
                           Tracer &tc, const BlockScratch &bs = BlockScratch());
 la_status planes_totals(const Problem &pr, const Plan &pl, int ld, const void *K, const void *V,
-                        float *ws, hipStream_t st);
+                        float *ws, hipStream_t st, int block = 0);
 
 // sum over all elements of X * Y (n elements of dt) -> out[0] = scale0 * sum, out[1] = scale1 * sum;
 // `partials` is scratch of at least reduce_dot_partials() floats.  Fixed summation order.
@@ -249,7 +249,7 @@ inline SplitScratch split_scratch(const Plan &pl128, int BH, int N, la_dtype dt,
     return s;
 }
 // The decode state of a D = 256 problem (+)= the sums over its N rows of K, V: the D = 128 sums kernel on all four
-// blocks, then state_block_from_totals on each.
+// blocks, then state_block_from_totals on each, or both on one block after another.
 la_status split_prefill(const Problem &pr, const Plan &pl, const void *K, const void *V, float *ws,
                         float *state, int accumulate, hipStream_t st);
 // saved (may be null): the hand-over buffers of the four block problems one after another, pl.saved_bytes each, and

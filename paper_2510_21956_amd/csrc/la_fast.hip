@@ -70,10 +70,26 @@ la_status split_prefill(const Problem &pr, const Plan &pl, const void *K, const 
 {
     Problem p = pr;
     p.D = 128;
-    la_status s = planes_totals(p, pl, 256, K, V, ws, st);
-    for (int b = 0; b < 4 && s == LA_OK; ++b)
-        s = state_block_from_totals(ws + b * split_slots(pl, pr.BH), state, pr.BH, pl.nseg, pl.slot_floats, b / 2,
-                                    b % 2, pr.N, accumulate, st);
+    // fp32: one block after another, each in as many segments as fit the slots of all four, where the shared launch
+    // leaves units idle for more rows than six more launches cost (65 to 85 slices, whose blocks are a round and a little
+    // more; us, shared and one after another: 66 slices of 2000 rows 237 and 189, 76 of 3509 405 and 341, 84 of 6000 718
+    // and 614).  The shared launch reads half of the rows out of the last-level cache: bf16 is faster in it everywhere
+    // (76 of 3509 113 and 128), fp32 where that is all there is to gain (35 of 10000 401 and 413).
+    Plan one = make_plan(1, pr.BH, pr.N, 128, pr.dt, 0, 0, true, kCoarse);
+    one.together = false;
+    const auto rows = [&](long problems, const Plan &x) {
+        return (problems * pr.BH * x.nseg + 255) / 256 * min(x.seg_len, pr.N);
+    };
+    const bool shared = pr.dt != LA_F32 || one.nseg > 4 * pl.nseg || rows(4, pl) <= 5 * rows(1, one) ||
+                        rows(4, pl) <= 4 * rows(1, one) + 600;
+    la_status s = shared ? planes_totals(p, pl, 256, K, V, ws, st) : LA_OK;
+    for (int b = 0; b < 4 && s == LA_OK; ++b) {
+        if (!shared) s = planes_totals(p, one, 256, K, V, ws, st, b);
+        const Plan &x = shared ? pl : one;
+        if (s == LA_OK)
+            s = state_block_from_totals(ws + (shared ? b * split_slots(pl, pr.BH) : 0), state, pr.BH, x.nseg, x.slot_floats,
+                                        b / 2, b % 2, pr.N, accumulate, st);
+    }
     return s;
 }
 

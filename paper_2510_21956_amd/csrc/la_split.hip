@@ -2086,14 +2086,14 @@ la_status run_backward(const Problem &pr, const Plan &pl, const void *Qv, const 
 }
 
 template <int MODE, int D, int LD>
-la_status run_totals(const Problem &pr, const Plan &pl, const void *K, const void *V, float *ws,
+la_status run_totals(const Problem &pr, const Plan &pl, const void *K, const void *V, float *ws, int block,
                      hipStream_t st)
 {
     typedef typename Mode<MODE>::TIO TIO;
-    const int all = LD > D ? 2 : 0;
-    kv_state<MODE, D, false, LD, true>(pr, 2)<<<dim3(pr.BH * pl.nseg << all), dim3(4 * D), 0, st>>>(
-        (const TIO *)K, (const TIO *)V, ws, pr.N, pl.nseg, pl.nseg, pl.map, pl.slot_floats, 0, nullptr,
-        Blocks{all, 0xe4, split_slots(pl, pr.BH), 0, 0, 0});
+    const bool all = LD > D && pl.together;
+    const Blocks bl = all ? Blocks{2, 0xe4, split_slots(pl, pr.BH), 0, 0, 0} : Blocks{0, (unsigned)block, 0, 0, 0, 0};
+    kv_state<MODE, D, false, LD, true>(pr, 2)<<<dim3(pr.BH * pl.nseg << bl.lg), dim3(4 * D), 0, st>>>(
+        (const TIO *)K, (const TIO *)V, ws, pr.N, pl.nseg, pl.nseg, pl.map, pl.slot_floats, 0, nullptr, bl);
     return launch_status();
 }
 
@@ -2147,9 +2147,9 @@ la_status planes_backward(const Problem &pr, const Plan &pl, int ld, const void 
 }
 
 la_status planes_totals(const Problem &pr, const Plan &pl, int ld, const void *K, const void *V,
-                        float *ws, hipStream_t st)
+                        float *ws, hipStream_t st, int block)
 {
-#define LA_TOTALS(M, D, LD) (run_totals<M, D, LD>(pr, pl, K, V, ws, st))
+#define LA_TOTALS(M, D, LD) (run_totals<M, D, LD>(pr, pl, K, V, ws, block, st))
     LA_BY_MODE(LA_TOTALS);
 }
 

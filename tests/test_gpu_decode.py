@@ -163,6 +163,25 @@ def test_prefill_in_segments_of_its_own(la, BH, N, D):
     assert excess(canonical_state(state, BH, D), want, TOL["f32"]) <= 1.0
 
 
+def test_prefill_one_block_after_another(la):
+    """fp32 at head size 256 where the four blocks do not share a launch: set, then added to."""
+    BH, N, D = 66, 1000, 256
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(3)
+    K, V = (torch.randn((1, BH, N, D), device="cuda", generator=gen) for _ in range(2))
+    state = torch.zeros(la.la_decode_state_bytes(1, BH, D) // 4, device="cuda")
+    ws = scratch(la.la_workspace_bytes(1, BH, 4 * N, D, la.LA_F32, False, 0), "cuda")
+    long = [torch.cat([x] * 4, 2) for x in (K, V)]  # 4000 rows: one block after another
+    la.la_decode_prefill(*long, state, 0, ws)
+    once = canonical_state(state, BH, D)
+    la.la_decode_prefill(*long, state, 1, ws)
+    assert np.array_equal(canonical_state(state, BH, D), 2.0 * once)
+    k, v = K[0].double(), V[0].double()
+    want = torch.cat([torch.stack([x.t().contiguous() @ y for x, y in zip(k, v)]).flatten(1), k.sum(1), v.sum(1),
+                      torch.full((BH, 1), float(N), device="cuda", dtype=torch.float64)], 1) * 4
+    assert excess(once, want.cpu().numpy(), TOL["f32"]) <= 1.0
+
+
 def _outcome(call):
     try:
         call()
