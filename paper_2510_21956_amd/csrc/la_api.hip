@@ -26,8 +26,8 @@ static bool supported_d(int D) { return D == 16 || D == 32 || D == 64 || D == 12
 // two at D = 64, four at D <= 32).  Of the cuts that give every unit k segments, k = 1 .. 3 resident, and of no cut
 // at all, the one is taken that costs least in rows:
 //   (segment) x 3/2 ((segments of that unit) + (its rounds)): segments that run together on a unit hide some of each
-//   other's latency; 384 for a round after the first; 2 `kernels` for a cut, whose segments' states have kernels of
-//   their own.
+//   other's latency; `round` for a round after the first, whose segments' states are moved as well; 2 `kernels` for a
+//   cut, whose segments' states have kernels of their own.
 // Short sequences in few slices are cut down to the shortest segments (a step, us, with 192 rows a segment at least,
 // 128 at D <= 64, and now: fp32, D = 128, 4 slices of 500 rows 157 and 48; bf16, D = 64, 1 of 30000 87 and 46; fp32,
 // D = 32, 8 of 300 50 and 27), and a cut never leaves a few workgroups to a round of their own (fp32, D = 64, 60
@@ -37,19 +37,22 @@ static bool supported_d(int D) { return D == 16 || D == 32 || D == 64 || D == 12
 // 128 rows, D = 32 1.09, D = 64 0.91; bf16 is not cut there by its `kernels`).
 // Over 4163 shapes of 1 to 630 slices and 18 to 65000 rows, D = 16 to 128, masked and not, each timed in up to 19 cuts, a
 // step takes 1.011 times the best cut's time on the average (1.22 with segments of 128 or 192 rows at least); with
-// `kernels` halved 1.014, doubled 1.021, with 384 halved 1.011, doubled 1.012, without it 1.023, with 2 (segments) +
-// (rounds) 1.012, without the exception above 1.013.  Forward and backward pass share the cut: a forward pass alone on some
+// `kernels` halved 1.013, doubled 1.021, with `round` halved 1.011, doubled 1.012, 0 1.023, with 2 (segments) + (rounds)
+// 1.012, without the exception above 1.013.  `round` of 384 and 768 differ in larger problems: where they choose
+// differently, 768 is faster by 1.04 in a step, 1.09 in a forward pass alone (bf16, D = 64 and 128, 750 shapes) and by 1.006
+// and 1.05 (fp32, D = 128, masked, 196), and slower by 1.02 in a step without the mask (fp32, D = 128, 138).  Forward and backward pass share the cut: a forward pass alone on some
 // hundred masked rows takes 3 us longer than in one piece, the backward pass 4 to 11 less (D = 64, fp32, 2 slices of 95
 // rows, forward 9.1 and 11.4, backward 20.2 and 16.2).
 static long segment_rows(long BH, int N, int D, la_dtype dt, int causal, Cut cut)
 {
     const long step = dt == LA_F32 ? 32 : 64, resident = D >= 128 ? 1 : D == 64 ? 2 : 4;
     const long kernels = dt == LA_F32 ? (D >= 128 ? 64 : 48) : (D >= 128 || !causal ? 192 : 64);
+    const long round = (D >= 64 && dt == LA_BF16) || (D >= 128 && causal) ? 768 : 384;
     BH *= cut.problems;
     const long most = cut.min_rows ? max(N / cut.min_rows, 1) : (N + step - 1) / step;
     const auto cost = [&](long rows) {
         const long load = (BH * ((N + rows - 1) / rows) + 255) / 256, rounds = (load + resident - 1) / resident;
-        return rows / 2 * 3 * (load + rounds) + 384 * (rounds - 1) + (rows < N ? 2 * kernels : 0);
+        return rows / 2 * 3 * (load + rounds) + round * (rounds - 1) + (rows < N ? 2 * kernels : 0);
     };
     long best_rows = (long)round_up((size_t)N, step), best = cost((long)round_up((size_t)N, 32));
     if (dt == LA_F32 && !causal && D <= 64 && N <= (D == 64 ? 96 : 128)) return best_rows;
