@@ -39,10 +39,11 @@ static bool supported_d(int D) { return D == 16 || D == 32 || D == 64 || D == 12
 // step takes 1.011 times the best cut's time on the average (1.22 with segments of 128 or 192 rows at least); with
 // `kernels` halved 1.013, doubled 1.021, with `round` halved 1.011, doubled 1.012, 0 1.023, with 2 (segments) + (rounds)
 // 1.012, without the exception above 1.013.  `round` of 384 and 768 differ in larger problems: where they choose
-// differently, 768 is faster by 1.04 in a step, 1.09 in a forward pass alone (bf16, D = 64 and 128, 750 shapes) and by 1.006
-// and 1.05 (fp32, D = 128, masked, 196), and slower by 1.02 in a step without the mask (fp32, D = 128, 138).  Forward and backward pass share the cut: a forward pass alone on some
-// hundred masked rows takes 3 us longer than in one piece, the backward pass 4 to 11 less (D = 64, fp32, 2 slices of 95
-// rows, forward 9.1 and 11.4, backward 20.2 and 16.2).
+// differently, 768 is faster by 1.04 in a step, 1.09 in a forward pass alone (bf16, D = 64 and 128, 750 shapes) and by
+// 1.006 and 1.05 (fp32, D = 128, masked, 196), and slower by 1.02 in a step without the mask (fp32, D = 128, 138).
+// Forward and backward pass share the cut: a forward pass alone on some hundred masked rows takes 3 us longer than in
+// one piece, the backward pass 4 to 11 less (D = 64, fp32, 2 slices of 95 rows, forward 9.1 and 11.4, backward 20.2 and
+// 16.2).
 static long segment_rows(long BH, int N, int D, la_dtype dt, int causal, Cut cut)
 {
     const long step = dt == LA_F32 ? 32 : 64, resident = D >= 128 ? 1 : D == 64 ? 2 : 4;
